@@ -11,7 +11,7 @@
 // reads its G weights once, into registers (G fp32 values; lanes of a wavefront hold adjacent
 // columns, so each of the G loads is one coalesced 256-byte read of a row of W and all G are in
 // flight together), and every later step works from there: W is read from HBM exactly once and the
-// kernel is bound by fp64 arithmetic (2^q candidate distances per weight and iteration).  Within
+// kernel is bound by vector instruction issue.  Within
 // a pass a weight's code is chosen and immediately folded into the sums the least-squares step
 // needs -- the integer Gram matrix of [1 b_0 .. b_{q-1}] and the fp64 right-hand side -- so nothing
 // per weight is stored until the last iteration writes the codes.  All arithmetic is fp64: the
@@ -33,24 +33,81 @@
 
 namespace {
 
+// compile-time loop: body(std::integral_constant<int, 0>), ..., body(std::integral_constant<int, N - 1>)
+template <int N, class F>
+__device__ __forceinline__ void unrolled(F &&body)
+{
+    if constexpr (N > 0) {
+        unrolled<N - 1>(body);
+        body(std::integral_constant<int, N - 1>{});
+    }
+}
+
+// ascending odd-even merge sort of NC keys (a power of two), all comparisons at compile-time positions
+template <int NC>
+__device__ __forceinline__ void sort_keys(uint32_t (&key)[NC])
+{
+#pragma unroll
+    for (int p = 1; p < NC; p *= 2)
+#pragma unroll
+        for (int k = p; k >= 1; k /= 2)
+#pragma unroll
+            for (int j = k % p; j + k < NC; j += 2 * k)
+#pragma unroll
+                for (int i = 0; i < k; ++i)
+                    if (i + j + k < NC && (i + j) / (2 * p) == (i + j + k) / (2 * p)) {
+                        const uint32_t a = key[i + j], b = key[i + j + k];
+                        key[i + j] = min(a, b);
+                        key[i + j + k] = max(a, b);
+                    }
+}
+
+// Bit-pattern selection.  The codes are the argmin over 2^q candidate distances, computed in fp64, first minimum in
+// code order; scanning them costs 4 x 2^q vector instructions per weight and round.  With the candidate values sorted,
+// only the two neighbours of a weight compete, and which of them wins is monotone in the weight, so there is an exact
+// fp32 number T at which the choice changes: the smallest fp32 weight for which the upper neighbour wins.  The 2^q - 1
+// thresholds are made once per group and round, and a weight's code is then a binary search: q fp32 comparisons.
+// What makes T exact (tests compare every code with the scan's):
+//   - sorted neighbours at least 2^-40 S apart, S the scale of the group's numbers: all fp64 roundings together stay
+//     below 2^-50 S, so only neighbours compete and the choice between them is monotone;
+//   - with m the midpoint in fp64 (error below 2^-48 S) and t its rounding to fp32: where |t - m| > 2^-45 S the sign of
+//     t - m decides for t, and the next fp32 number on the other side is on the other side of m as well; otherwise
+//     the two distances of t and of that neighbour are compared as the scan compares them.
+// A lane that meets neither (equal candidates of a degenerate group, a midpoint at zero) sends its wavefront through the
+// scan for that round.
+// The first two levels of the search have their thresholds in registers, the others read them from a lane-private LDS
+// column, in ascending order (the number of thresholds passed so far is the address); a second column holds, per sorted position, a word with byte j = 0x3f where the code has bit
+// j: moved to the top of the high half of a double it is 2^-15, the factor with which the weight enters plane j's sum (the
+// sums are kept times 2^-15: every product and rounding is the one without the factor).  Codes are counted in a third.
+// Per weight and round 11 vector instructions at q = 2 and 25 at q = 4, instead of 27 and about 110 for the scan.
+// 4096 x 4096, G = 128, ten rounds: q = 1 / 2 / 3 / 4  84 / 154 / 274 / 493 us with the scan, 67 / 97 / 135 / 185 us now;
+// G = 32, where the work per group and round (sort, thresholds, elimination) is as long as the weights' own:
+// 76 / 154 / 291 / 520 -> 65 / 113 / 177 / 287 us; G = 256, weights from the L2: 171 / 689 / 829 / 950 -> 134 / 163 / 206 / 261 us.
 template <int Q, int G>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256, Q == 4 && G == 32 ? 3 : 2)
 hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_t *__restrict__ codes,
                     uint16_t *__restrict__ scales, uint16_t *__restrict__ zeros, float *__restrict__ group_err)
 {
     constexpr int NC = 1 << Q, P = Q + 1;
+    __shared__ uint32_t lds[4 * 3 * NC * 64];
     const int n = (int)(blockIdx.x * 256 + threadIdx.x);
     const int gi = (int)blockIdx.y;
     if (n >= N) return;
     const int ngroups = K / G;
     const float *w0 = W + (size_t)gi * G * N + n;
     uint8_t *c0 = codes + (size_t)gi * G * N + n;
+    // this lane's columns, one word every 64: thresholds in order | plane words by sorted position | counts.  The
+    // second and third also hold the candidate values (fp64, by code) while the thresholds are made.
+    uint32_t *const tree = lds + (threadIdx.x >> 6) * (3 * NC * 64) + (threadIdx.x & 63);
+    uint32_t *const plane = tree + NC * 64;
+    uint32_t *const count = plane + NC * 64;
 
     // groups of up to 128 weights stay in registers; longer ones are re-read (from L2) every pass
     constexpr bool RESIDENT = G <= 128;
     constexpr int GR = RESIDENT ? G : 1;
     float wv[GR];
     float lof, hif;   // Alg. 1 steps 2-3 (min / max are exact in fp32)
+    double rw = 0.0;  // sum of the weights, in order
     if constexpr (RESIDENT) {
 #pragma unroll
         for (int i = 0; i < G; ++i) wv[i] = w0[(size_t)i * N];
@@ -60,13 +117,17 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
             lof = wv[i] < lof ? wv[i] : lof;
             hif = wv[i] > hif ? wv[i] : hif;
         }
+#pragma unroll
+        for (int i = 0; i < G; ++i) rw += (double)wv[i];
     } else {
         lof = hif = w0[0];
+        rw = (double)lof;
 #pragma unroll 8
         for (int i = 1; i < G; ++i) {
             const float v = w0[(size_t)i * N];
             lof = v < lof ? v : lof;
             hif = v > hif ? v : hif;
+            rw += (double)v;
         }
     }
     auto weight = [&](int i) -> float {
@@ -90,80 +151,248 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
     // the G store addresses are not kept in registers across the other iterations)
     auto iteration = [&](auto last_c) {
         constexpr bool last = decltype(last_c)::value;
-        // candidate values V_c = sum_j s_j bit_j(c)   (step 7)
-        double V[NC];
+        const double z = theta[0];
+        double S = fmax(fabs(lo), fabs(hi)) + fabs(z);
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
+        for (int j = 0; j < Q; ++j) S += fabs(theta[1 + j]);
+        const double gap_min = S * 0x1p-40, band = S * 0x1p-45;
+
+        // candidate values V_c = sum_j s_j bit_j(c)   (step 7), sorted by the leading bits of their fp32 rounding with
+        // the code in the last q bits (an order that is not the fp64 one shows as a gap below gap_min)
+        uint32_t key[NC];
+        unrolled<NC>([&](auto cc) {
+            constexpr int c = decltype(cc)::value;
             double v = 0.0;
 #pragma unroll
             for (int j = 0; j < Q; ++j) v += theta[1 + j] * (double)((c >> j) & 1);
-            V[c] = v;
+            const uint64_t b = __builtin_bit_cast(uint64_t, v);
+            plane[(2 * c) * 64] = (uint32_t)b;
+            plane[(2 * c + 1) * 64] = (uint32_t)(b >> 32);
+            const uint32_t u = __builtin_bit_cast(uint32_t, (float)v);
+            key[c] = ((u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u)) & ~(uint32_t)(NC - 1)) | (uint32_t)c;
+        });
+        sort_keys<NC>(key);
+        auto value_of = [&](uint32_t code) -> double {
+            const uint32_t at = code * 128;
+            return __builtin_bit_cast(double, ((uint64_t)plane[at + 64] << 32) | plane[at]);
+        };
+        bool good = true;
+        float top[3];   // the thresholds at the quarters (q = 1: the only one)
+        double va = value_of(key[0] & (NC - 1));
+        unrolled<NC - 1>([&](auto ii) {
+            constexpr int i = decltype(ii)::value + 1;
+            const uint32_t ca = key[i - 1] & (NC - 1), cb = key[i] & (NC - 1);
+            const double vb = value_of(cb);
+            good = good && vb - va >= gap_min;
+            const double m = 0.5 * (va + vb) + z;
+            const float t = (float)m;
+            const double off = (double)t - m;
+            bool upper = off > 0.0;   // the upper neighbour wins at t
+            const uint32_t tb = __builtin_bit_cast(uint32_t, t);
+            const uint32_t away = (int32_t)tb < 0 ? ~0u : 1u;   // one fp32 step up (away: in bits)
+            const float next = __builtin_bit_cast(float, tb + away);
+            const bool near = fabs(off) <= band;
+            good = good && t != 0.f;
+            if (__any(near)) {
+                const float prev = __builtin_bit_cast(float, tb - away);
+                auto upper_wins = [&](float w) {
+                    const double what = (double)w - z;
+                    const double da = fabs(what - va), db = fabs(what - vb);
+                    return db < da || (db == da && cb < ca);
+                };
+                const bool at_t = upper_wins(t);
+                const bool beside = upper_wins(at_t ? prev : next);
+                good = good && (!near || at_t != beside);
+                upper = near ? at_t : upper;
+            }
+            const float T = upper ? t : next;
+            if constexpr (i % (NC > 2 ? NC / 4 : 1) == 0) top[NC > 2 ? i / (NC / 4) - 1 : 0] = T;
+            else tree[i * 64] = __builtin_bit_cast(uint32_t, T);
+            va = vb;
+        });
+        const bool scan = __any(!good);
+
+        // per sorted position (or per code, for the scan): the plane word; counts start at zero
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            const uint32_t c = scan ? (uint32_t)i : key[i] & (NC - 1);
+            const uint32_t ones = __umul24(c, 0x204081u) & 0x01010101u;   // bit j of the code in byte j
+            plane[i * 64] = (ones << 6) - ones;
+            count[i * 64] = 0u;
         }
-        const double z = theta[0];
-        int nb[Q], nbb[Q][Q];
-        double rb[Q], rw = 0.0;
+        double rb[Q];
+#pragma unroll
+        for (int j = 0; j < Q; ++j) rb[j] = 0.0;
+        // folds weight i, whose plane word has been read, into the sums
+        auto fold = [&](int i, float w, uint32_t word) {
+            const double wd = (double)w;
+#pragma unroll
+            for (int j = 0; j < Q; ++j) {
+                const uint32_t hi32 = __builtin_amdgcn_perm(0u, word, ((uint32_t)j << 24) | 0x0c0c0cu);
+                rb[j] = __builtin_fma(__builtin_bit_cast(double, (uint64_t)hi32 << 32), wd, rb[j]);   // exact product: same rounding as an add
+            }
+            if constexpr (last) {
+                uint32_t c = 0;
+#pragma unroll
+                for (int j = 0; j < Q; ++j) c |= ((word >> (8 * j)) & 1u) << j;
+                c0[(size_t)i * N] = (uint8_t)c;
+            }
+        };
+        if (!scan) {
+            // Eight weights at a time, one level of the search for all of them before the next, and the sums of the
+            // previous eight between the levels: an LDS read is used some thirty instructions after it was issued
+            // (with the weights of a group in registers there are two wavefronts on a SIMD to cover for each other).
+            constexpr int B = 8;
+            // LEN weights from src, the group's weights i0, i0 + 1, ..
+            auto pass = [&](auto &src, auto len_c, int i0) {
+                constexpr int LEN = decltype(len_c)::value;
+                uint32_t word[2][B];
+                uint32_t *at[B];
+                // an opaque copy of the weight, made at its use: otherwise the optimiser converts every weight to fp64 once
+                // and keeps both
+                auto sum_up = [&](int i, uint32_t w) {
+                    asm volatile("" : "+v"(src[i]));
+                    fold(i0 + i, src[i], w);
+                };
+#pragma unroll
+                for (int i = 0; i < LEN; i += B) {
+                    const int par = (i / B) & 1;
+#pragma unroll
+                    for (int u = 0; u < B; ++u) {
+                        const float w = src[i + u];
+                        if constexpr (Q >= 2) {
+                            const bool up = w >= top[1];
+                            const float T = up ? top[2] : top[0];
+                            const uint32_t half = up ? NC / 2 * 64u : 0u;
+                            at[u] = tree + half + (w >= T ? NC / 4 * 64u : 0u);
+                        } else {
+                            at[u] = tree + (w >= top[0] ? 64u : 0u);
+                        }
+                    }
+                    constexpr int levels = Q > 2 ? Q - 1 : 1;             // LDS reads in a row
+                    constexpr int per = (B + levels - 1) / levels;        // previous weights summed up behind each
+#pragma unroll
+                    for (int lv = 0; lv < levels; ++lv) {
+                        float node[B];
+                        const int step = NC >> (lv + 3);                  // positions this level decides between
+#pragma unroll
+                        for (int u = 0; u < B; ++u) {
+                            if (lv + 1 < levels) node[u] = __builtin_bit_cast(float, at[u][step * 64]);
+                            else word[par][u] = at[u][NC * 64];
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (i > 0) {
+#pragma unroll
+                            for (int u = lv * per; u < (lv + 1) * per && u < B; ++u) sum_up(i - B + u, word[par ^ 1][u]);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (lv + 1 < levels) {
+#pragma unroll
+                            for (int u = 0; u < B; ++u) at[u] += src[i + u] >= node[u] ? step * 64u : 0u;
+                        }
+                    }
+#pragma unroll
+                    for (int u = 0; u < B; ++u) __hip_atomic_fetch_add(at[u] + 2 * NC * 64, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                }
+#pragma unroll
+                for (int u = 0; u < B; ++u) sum_up(LEN - B + u, word[(LEN / B - 1) & 1][u]);
+            };
+            if constexpr (RESIDENT) {
+                pass(wv, std::integral_constant<int, G>{}, 0);
+            } else {
+                // weights come from the L2: the next 32 are requested while 32 are worked on
+                constexpr int AHEAD = 32;
+                float nx[AHEAD];
+#pragma unroll
+                for (int u = 0; u < AHEAD; ++u) nx[u] = w0[(size_t)u * N];
+#pragma unroll 1
+                for (int i = 0; i < G; i += AHEAD) {
+                    float cur[AHEAD];
+#pragma unroll
+                    for (int u = 0; u < AHEAD; ++u) cur[u] = nx[u];
+#pragma unroll
+                    for (int u = 0; u < AHEAD; ++u) nx[u] = w0[(size_t)min(i + AHEAD + u, G - 1) * N];
+                    pass(cur, std::integral_constant<int, AHEAD>{}, i);
+                }
+            }
+        } else {
+            // the scan of all candidates, weights re-read (rare)
+            double V[NC];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                double v = 0.0;
+#pragma unroll
+                for (int j = 0; j < Q; ++j) v += theta[1 + j] * (double)((c >> j) & 1);
+                V[c] = v;
+            }
+#pragma unroll 1
+            for (int i = 0; i < G; ++i) {
+                const float w = w0[(size_t)i * N];
+                const double what = (double)w - z;
+                uint32_t best = 0;
+                double bd = fabs(what - V[0]);
+#pragma unroll
+                for (int c = 1; c < NC; ++c) {   // first minimum wins ties
+                    const double d = fabs(what - V[c]);
+                    best = d < bd ? (uint32_t)c : best;
+                    bd = __builtin_fmin(bd, d);
+                }
+                fold(i, w, plane[best * 64]);
+                __hip_atomic_fetch_add(&count[best * 64], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < Q; ++j) rb[j] *= 0x1p15;
+
+        // counts by code, from counts by sorted position
+        int cnt[NC];
+#pragma unroll
+        for (int i = 0; i < NC; ++i) cnt[i] = (int)count[i * 64];
+        if (!scan) {
+#pragma unroll
+            for (int i = 0; i < NC; ++i) plane[(key[i] & (NC - 1)) * 64] = (uint32_t)cnt[i];
+#pragma unroll
+            for (int i = 0; i < NC; ++i) cnt[i] = (int)plane[i * 64];
+        }
         unsigned present = 0u;
+        int nb[Q], nbb[Q][Q];
 #pragma unroll
         for (int j = 0; j < Q; ++j) {
             nb[j] = 0;
-            rb[j] = 0.0;
 #pragma unroll
             for (int k = 0; k < Q; ++k) nbb[j][k] = 0;
         }
-#pragma unroll(RESIDENT ? G : 8)
-        for (int i = 0; i < G; ++i) {
-            const double w = (double)weight(i);
-            const double what = w - z;
-            int best = 0;
-            double bd = fabs(what - V[0]);
 #pragma unroll
-            for (int c = 1; c < NC; ++c) {   // first minimum wins ties
-                const double d = fabs(what - V[c]);
-                best = d < bd ? c : best;
-                bd = __builtin_fmin(bd, d);
-            }
-            present |= 1u << best;
-            rw += w;
+        for (int c = 0; c < NC; ++c) {
+            present |= cnt[c] ? 1u << c : 0u;
 #pragma unroll
             for (int j = 0; j < Q; ++j) {
-                const int bj = (best >> j) & 1;
-                nb[j] += bj;
-                rb[j] = __builtin_fma((double)bj, w, rb[j]);   // bj * w is exact: same rounding as an add
+                if (!((c >> j) & 1)) continue;
+                nb[j] += cnt[c];
 #pragma unroll
-                for (int k = j + 1; k < Q; ++k) nbb[j][k] += bj & (best >> k);
+                for (int k = j + 1; k < Q; ++k)
+                    if ((c >> k) & 1) nbb[j][k] += cnt[c];
             }
-            if constexpr (last) c0[(size_t)i * N] = (uint8_t)best;
-            // keep the instruction scheduler from converting many weights ahead (register pressure)
-            if (RESIDENT && (i & 3) == 3) __builtin_amdgcn_sched_barrier(0);
         }
-
-        // the sums are complete here; without this the optimiser postpones them past the branches
-        // below and keeps every weight's code in a register until then
-#pragma unroll
-        for (int j = 0; j < Q; ++j) {
-            asm volatile("" : "+v"(rb[j]), "+v"(nb[j]));
-#pragma unroll
-            for (int k = j + 1; k < Q; ++k) asm volatile("" : "+v"(nbb[j][k]));
-        }
-        asm volatile("" : "+v"(rw), "+v"(present));
 
         // ---- which columns of [1 b_0 .. b_{Q-1}] are independent ---------------------------------------------
         // Fraction-free elimination on the Gram matrix of the distinct rows present.  Every
         // intermediate is a minor of that matrix: a sum over at most C(16,5) row subsets of squared
         // determinants of 0/1 matrices of order <= 5 (each <= 5), so below 2^17; products and their
-        // differences stay below 2^35 and the divisions are exact, hence fp64 computes them exactly.
+        // differences stay below 2^35 and the divisions are exact, hence fp64 computes them exactly (a
+        // quotient as product with the reciprocal, rounded to the nearest integer).
         double gm[P][P];
 #pragma unroll
         for (int a = 0; a < P; ++a)
 #pragma unroll
-            for (int b = 0; b < P; ++b) {
-                int cnt = 0;
+            for (int b = a; b < P; ++b) {
+                unsigned both = 0u;   // codes whose row has a one in columns a and b
 #pragma unroll
                 for (int c = 0; c < NC; ++c) {
                     const int ra = a == 0 ? 1 : (c >> (a - 1)) & 1, rc = b == 0 ? 1 : (c >> (b - 1)) & 1;
-                    if (ra & rc) cnt += (int)((present >> c) & 1u);
+                    if (ra & rc) both |= 1u << c;
                 }
-                gm[a][b] = (double)cnt;
+                gm[a][b] = (double)__builtin_popcount(present & both);
             }
         bool is_act[P];
         double prev = 1.0;
@@ -172,10 +401,12 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
             const double pv = gm[k][k];
             is_act[k] = pv != 0.0;
             if (is_act[k]) {
+                const double inv_prev = 1.0 / prev;
 #pragma unroll
                 for (int i = k + 1; i < P; ++i)
 #pragma unroll
-                    for (int j = k + 1; j < P; ++j) gm[i][j] = (gm[i][j] * pv - gm[i][k] * gm[k][j]) / prev;
+                    for (int j = i; j < P; ++j)   // symmetric
+                        gm[i][j] = __builtin_rint((gm[i][j] * pv - gm[k][i] * gm[k][j]) * inv_prev);
                 prev = pv;
             }
         }
@@ -193,19 +424,24 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
 #pragma unroll
             for (int k = j + 1; k < Q; ++k) A[1 + j][1 + k] = A[1 + k][1 + j] = (double)nbb[j][k];
         }
+        bool full = true;
 #pragma unroll
-        for (int a = 0; a < P; ++a) {
-            double v = r[a];
+        for (int k = 0; k < P; ++k) full = full && is_act[k];
+        if (!__all(full)) {
 #pragma unroll
-            for (int col = 0; col < P; ++col)
-                if (col != a && !is_act[col]) v -= A[a][col] * theta[col];
-            r[a] = is_act[a] ? v : theta[a];
+            for (int a = 0; a < P; ++a) {
+                double v = r[a];
+#pragma unroll
+                for (int col = 0; col < P; ++col)
+                    if (col != a && !is_act[col]) v -= A[a][col] * theta[col];
+                r[a] = is_act[a] ? v : theta[a];
+            }
+#pragma unroll
+            for (int a = 0; a < P; ++a)
+#pragma unroll
+                for (int b = 0; b < P; ++b)
+                    if (!is_act[a] || !is_act[b]) A[a][b] = a == b ? 1.0 : 0.0;
         }
-#pragma unroll
-        for (int a = 0; a < P; ++a)
-#pragma unroll
-            for (int b = 0; b < P; ++b)
-                if (!is_act[a] || !is_act[b]) A[a][b] = a == b ? 1.0 : 0.0;
         // elimination without pivoting: the matrix is symmetric positive definite
 #pragma unroll
         for (int k = 0; k < P; ++k) {
