@@ -506,6 +506,148 @@ void plan_mx_problem(const HlqDims &dm, int W, int cpw, GemvProb &p)
     p.nslices = (dm.nchunks + p.cps - 1) / p.cps;
 }
 
+// Work split of a launch of the one-row matrix-core kernel (hlq_gemv_cols.hip).  A step is 16 columns x 4 chunks of one
+// wavefront.
+struct ColsSplit {
+    int kw, cps;       // wavefronts per column block, chunks per K slice
+    int ntg;           // workgroups per K slice
+    bool pairs;        // two slices that meet in slots of the counter block (8 bytes a column)
+};
+
+int cols_blocks(const HlqDims &dm) { return (dm.N + 15) / 16; }
+
+// wavefronts on one column block: as many as there are windows to hand out
+int cols_kw(int W, int nchunks)
+{
+    int kw = 1;
+    while (kw * 2 <= W && kw < (nchunks + 3) / 4) kw *= 2;
+    return kw;
+}
+
+// Which launches of one activation row go there instead of to the 64-column kernel (hlq_gemv_mx.hip).  It wins wherever a
+// launch is short of wavefronts, and with groups of 128 and more on every size measured (microseconds, 64-column kernel
+// against this one): q = 2, G = 128  4096 x 1024 4.95 / 3.17, 4096 x 4096 5.42 / 3.53, 14336 x 4096 7.95 / 6.0, 8B layer
+// (27648 chunk-tiles) 13.8 / 13.2, 70B layer (104448) 42.1 / 41.1.  Its four column blocks of a tile fetch the lines of the
+// tile's scales one after the other, which costs it the long launches with narrow groups: G = 32  4096 x 28672
+// (14336) 12.1 / 13.3, 70B layer 70.7 / 72.3 (q = 4: 126 / 135);  G = 64, q = 2  70B layer 48.0 / 49.7, LM head (256512)
+// 56.5 / 57.9 (q = 4: 94.8 / 90.5).  With one plane a step is too short for its fixed part on launches of one round:
+// q = 1, G = 256  8B layer 9.4 / 10.1, but 70B layer 28.8 / 25.8.
+bool cols_wins(long units, int q, int G)
+{
+    if (G == 32) return units < 12000;
+    if (q == 1) return units < 20000 || units >= 60000;
+    if (G == 64 && q <= 3) return units < 60000;
+    return true;
+}
+
+// cpw: forced chunks per wavefront (0: automatic); forced_w likewise.  Returns the wavefronts per workgroup.
+int plan_cols(int count, const HlqDims *dms, int forced_w, int cpw, ColsSplit *out)
+{
+    const int q = dms[0].q, G = dms[0].G, maxw = hlq_gemv_cols_max_waves(q, G);
+    long blocks = 0;
+    for (int i = 0; i < count; ++i) blocks += cols_blocks(dms[i]);
+    // K slices.  One up to sixteen windows (K = 8192: a window per wavefront).  Two up to 32 windows, in which case the sides
+    // meet in one exchange per column: 14336 x 1024 5.5 us in one slice, 4.5 in two; 14336 x 512 5.4 / 4.4; 11008 x 5000,
+    // q = 3, G = 64 10.1 / 9.3; where the columns alone give every compute unit its workgroup it costs a little instead,
+    // 14336 x 4096 6.0 / 6.5, 11008 x 4096 5.5 / 5.8.  Longer K over few columns: one slice per sixteen windows,
+    // partial sums and arrival counters: 28672 x 1024 8.5 / 6.5, 28672 x 512 8.3 / 5.8; over more columns one slice,
+    // 28672 x 8192 13.5.
+    int most_wins = 1;
+    long slots = 0;   // of the counter block, of which half is left to arrival counters
+    for (int i = 0; i < count; ++i) {
+        const int n = dms[i].nchunks, wins = (n + 3) / 4;
+        const bool two = wins > 16 && wins <= 32 && 2L * dms[i].N <= HLQ_WS_ARRIVAL_COUNTERS / 2;
+        const int per = two ? (wins + 1) / 2 : blocks <= 128 && wins > 32 ? 16 : wins;
+        const int slices = (wins + per - 1) / per;
+        int cps = (n + slices - 1) / slices;
+        if (cpw) cps = (forced_w ? forced_w : 8) * (cpw < HLQ_MAX_K / HLQ_CHUNK_K ? cpw : HLQ_MAX_K / HLQ_CHUNK_K);
+        cps = (cps + 1) & ~1;   // slices of more than one chunk pair: windows start even
+        if (cps < 4) cps = 4;
+        out[i].cps = cps < n ? cps : n;
+        const int w = (out[i].cps + 3) / 4;
+        if (w > most_wins) most_wins = w;
+        out[i].pairs = out[i].cps < n && 2 * out[i].cps >= n && slots + 2L * dms[i].N <= HLQ_WS_ARRIVAL_COUNTERS / 2;
+        if (out[i].pairs) slots += 2L * dms[i].N;
+    }
+    // wavefronts per workgroup: as many as windows, eight or sixteen
+    int W = forced_w ? forced_w : most_wins > 8 ? 16 : 8;
+    if (W > maxw) W = maxw;
+    while (W & (W - 1)) W &= W - 1;
+
+    // Workgroups: one step per wavefront if all of those are resident at once (the kernel's one-step form: 59 registers at
+    // q <= 2, up to 75 otherwise), else as few steps per wavefront as one generation of workgroups (16 wavefronts a
+    // compute unit) needs: a second generation of a few costs as much as a full one (8B layer 20 us instead of 13).
+    long one_step = 0, cost[HLQ_MAX_BATCH];
+    bool one_round = true;
+    for (int i = 0; i < count; ++i) {
+        out[i].kw = cols_kw(W, out[i].cps);
+        const int rounds = ((out[i].cps + 3) / 4 + out[i].kw - 1) / out[i].kw, streams = W / out[i].kw;
+        const int slices = (dms[i].nchunks + out[i].cps - 1) / out[i].cps;
+        cost[i] = (long)cols_blocks(dms[i]) * rounds * slices / streams;
+        one_step += (long)((cols_blocks(dms[i]) + streams - 1) / streams) * slices;
+        one_round = one_round && rounds == 1;
+    }
+    const int per_cu = (q <= 2 && G >= 64 ? 32 : 24) / W;
+    const bool single = one_round && one_step <= 256L * (per_cu > 0 ? per_cu : 1);
+    long steps = 1;
+    if (!single)
+        for (;; ++steps) {
+            long wgs = 0;
+            for (int i = 0; i < count; ++i) wgs += (cost[i] + steps - 1) / steps;
+            if (wgs <= 4096 / W || steps >= 40) break;
+        }
+    for (int i = 0; i < count; ++i) {
+        const int nb = cols_blocks(dms[i]), streams = W / out[i].kw, slices = (dms[i].nchunks + out[i].cps - 1) / out[i].cps;
+        long ntg = single ? (nb + streams - 1) / streams : ((cost[i] + steps - 1) / steps + slices - 1) / slices;
+        const int cap = slices > 1 && !out[i].pairs ? 4 : HLQ_COLS_MAX_SLOTS / out[i].kw;   // column blocks a workgroup can hold
+        if (ntg < (nb + cap - 1) / cap) ntg = (nb + cap - 1) / cap;
+        if (ntg > nb) ntg = nb;
+        out[i].ntg = (int)(ntg < 1 ? 1 : ntg);
+    }
+    return W;
+}
+
+void plan_cols_problem(const HlqDims &dm, const ColsSplit &sp, GemvProb &p)
+{
+    p.kw = sp.kw;
+    p.cps = sp.cps;
+    p.nslices = (dm.nchunks + sp.cps - 1) / sp.cps;
+    p.ntg = sp.ntg;
+}
+
+// the kernel's own record, from the planned and placed problem
+ColsProb cols_record(const GemvProb &p, int W, bool pairs)
+{
+    ColsProb r;
+    const int nb = (p.N + 15) / 16;
+    r.packed = p.packed;
+    r.x = p.x;
+    r.y = p.y;
+    r.part = p.part;
+    r.cnt = p.cnt;
+    r.tile_bytes = (unsigned)(HLQ_TILE_N * p.col_bytes);   // below 2^27: K <= 2^21 and at most 0.8 bytes a weight
+    r.N = p.N;
+    r.nchunks = p.nchunks;
+    r.cps = p.cps;
+    r.nslices = p.nslices;
+    r.slice_magic = p.slice_magic;
+    r.ntg = p.ntg;
+    r.blk_begin = p.blk_begin;
+    r.cb_base = nb / p.ntg;
+    r.cb_rem = nb % p.ntg;
+    const int full = ((p.cps < p.nchunks ? p.cps : p.nchunks) + 3) / 4, last = (p.nchunks - (p.nslices - 1) * p.cps + 3) / 4;
+    r.wbase = (uint16_t)(full / p.kw);   // windows of K = 2^21: 4096
+    r.wrem = (uint16_t)(full % p.kw);
+    r.wbase_l = (uint16_t)(last / p.kw);
+    r.wrem_l = (uint16_t)(last % p.kw);
+    r.kw_shift = (uint8_t)p.kw_shift;
+    r.st_shift = 0;
+    while ((p.kw << r.st_shift) < W) ++r.st_shift;
+    r.swz_shift = r.cb_rem ? 0 : r.cb_base == 1 ? 2 : r.cb_base == 2 ? 1 : 0;
+    r.pairs = pairs;
+    return r;
+}
+
 } // namespace
 
 hlq_status hlq_gemv_path_override(int path)
@@ -545,6 +687,7 @@ hlq_status hlq_launch_ws_init(void *ws, size_t bytes, hipStream_t st)
 // plan can also be inspected without a GPU (hlq_gemv_plan_query).
 struct GemvLaunchShape {
     bool mx;
+    bool cols;        // the one-row kernel with 16 columns per wavefront (hlq_gemv_cols.hip)
     bool rowsk;       // the many-rows kernel (hlq_gemm_rows.hip) instead of the few-rows instantiation of the GEMV kernel
     int W, TN, rows;
     long nblocks;
@@ -563,6 +706,7 @@ static hlq_status plan_gemv_batch(int count, const HlqGemvItem *items, hlq_out_d
         if (items[i].M != rows) return HLQ_ERR_UNSUPPORTED;
     if (rows < 1 || rows > hlq_gemm_mx_rows_per_pass(items[0].dm.G)) return HLQ_ERR_UNSUPPORTED;
     const bool mx = use_mx() || rows > 1;   // several activation rows exist in the matrix-core kernels only
+    const bool cols = mx && rows == 1 && cols_wins(units, items[0].dm.q, items[0].dm.G);
     // more rows than one operand of the GEMV kernel holds: the many-rows kernel (terms chained through the
     // accumulator, activations converted once per workgroup), where it exists for this group size
     bool rowsk = rows > hlq_gemv_mx_rows_per_set(items[0].dm.G) && rows <= hlq_gemm_rows_max(items[0].dm.G) &&
@@ -578,6 +722,10 @@ static hlq_status plan_gemv_batch(int count, const HlqGemvItem *items, hlq_out_d
         // traffic, short enough that the launch has several workgroups per compute unit
         pl.cpw = units < 12000 ? 4 : 16;   // measured on the 8B layer at q = 4: 16 beats 8 (one round of workgroups instead of two)
         if (const int v = g_plan_cpw.load(std::memory_order_relaxed)) pl.cpw = v < 4 ? 4 : v;
+    } else if (cols) {
+        pl.W = pl.cpw = 0;   // plan_cols chooses
+        if (const int v = g_plan_w.load(std::memory_order_relaxed)) pl.W = v;
+        if (const int v = g_plan_cpw.load(std::memory_order_relaxed)) pl.cpw = v;
     } else if (rows > 1) {
         // measured (8B shapes, q = 4, M = 2..8): short runs on few wavefronts per workgroup for narrow
         // launches, longer runs and eight wavefronts once there are enough tiles
@@ -589,7 +737,7 @@ static hlq_status plan_gemv_batch(int count, const HlqGemvItem *items, hlq_out_d
     {
         const int q0 = items[0].dm.q, G0 = items[0].dm.G;
         if (mx || !gemv_two_tiles_ok(q0, G0) || table_variant() >= 0) pl.TN = 1;
-        const int maxw = mx ? hlq_gemv_mx_max_waves(q0, G0) : gemv_max_threads(q0, G0, pl.TN) / 64;
+        const int maxw = cols ? 16 : mx ? hlq_gemv_mx_max_waves(q0, G0) : gemv_max_threads(q0, G0, pl.TN) / 64;
         if (pl.W > maxw) pl.W = maxw;
         if (!mx && table_variant() >= 0 && pl.W > 8) pl.W = 8;   // the plain variant kernels: up to 512 lanes
         if (rowsk) {
@@ -599,10 +747,17 @@ static hlq_status plan_gemv_batch(int count, const HlqGemvItem *items, hlq_out_d
         if (mx)   // a power of two
             while (pl.W & (pl.W - 1)) pl.W &= pl.W - 1;
     }
-    if (pl.W < 1 || pl.W > 16 || (pl.TN != 1 && pl.TN != 2) || pl.cpw < 1) return HLQ_ERR_UNSUPPORTED;
+    if (!cols && (pl.W < 1 || pl.W > 16 || (pl.TN != 1 && pl.TN != 2) || pl.cpw < 1)) return HLQ_ERR_UNSUPPORTED;
     // chunks per K slice of the lookup kernel: each of its W wavefronts takes cpw chunks of one tile
-    int cps = slice_chunks(pl);
+    int cps = cols ? 4 : slice_chunks(pl);
     if (cps < 4) cps = 4;
+
+    ColsSplit split[HLQ_MAX_BATCH];
+    if (cols) {
+        HlqDims dms[HLQ_MAX_BATCH];
+        for (int i = 0; i < count; ++i) dms[i] = items[i].dm;
+        pl.W = plan_cols(count, dms, pl.W, pl.cpw, split);
+    }
 
     b.count = count;
     b.out_f32 = out == HLQ_OUT_F32;
@@ -634,7 +789,9 @@ static hlq_status plan_gemv_batch(int count, const HlqGemvItem *items, hlq_out_d
         p.M = rows;
         p.ldx = items[order[i]].ldx;
         p.ldy = items[order[i]].ldy;
-        if (rowsk) {
+        if (cols) {
+            plan_cols_problem(dm, split[order[i]], p);
+        } else if (rowsk) {
             plan_mx_problem(dm, pl.W, pl.cpw, p);
         } else if (mx) {
             plan_mx_problem(dm, pl.W, pl.cpw, p);
@@ -656,8 +813,10 @@ static hlq_status plan_gemv_batch(int count, const HlqGemvItem *items, hlq_out_d
         p.cnt = cnt + cnt_used;
         p.part = part;
         blk += (long)p.ntg * p.nslices;
-        if (p.nslices > 1) {
-            cnt_used += mx ? dm.ntiles : p.ntg;
+        if (cols && split[order[i]].pairs) {
+            cnt_used += 2L * dm.N;   // N is a multiple of 8: the slots stay 8-byte aligned
+        } else if (p.nslices > 1) {
+            cnt_used += mx && !cols ? dm.ntiles : p.ntg;
             part += (size_t)p.nslices * dm.N * rows;
         }
     }
@@ -677,12 +836,16 @@ static hlq_status plan_gemv_batch(int count, const HlqGemvItem *items, hlq_out_d
             b.p[i].xexp = nullptr;
         }
     }
+    if (cols)
+        for (int i = 0; i < count; ++i) b.cp[i] = cols_record(b.p[i], pl.W, split[order[i]].pairs);
     for (int i = count; i < HLQ_MAX_BATCH; ++i) {
         b.p[i] = b.p[0];
+        if (cols) b.cp[i] = b.cp[0];
         b.blk_begin[i] = 0x7fffffff;
     }
     if (cnt_used > HLQ_WS_ARRIVAL_COUNTERS || blk > 0x7fffffffL) return HLQ_ERR_UNSUPPORTED;
     ls.mx = mx;
+    ls.cols = cols;
     ls.rowsk = rowsk;
     ls.W = pl.W;
     ls.TN = pl.TN;
@@ -705,6 +868,11 @@ hlq_status hlq_launch_gemv_batch(int count, const HlqGemvItem *items, hlq_out_dt
     const unsigned blk = (unsigned)ls.nblocks;
     if (ls.rowsk) {
         s = hlq_launch_gemm_rows(b, blk, ls.W, ls.rows, q, G, st);
+        if (s != HLQ_OK) return s;
+        return hlq_hip_status(hipGetLastError());
+    }
+    if (ls.cols) {
+        s = hlq_launch_gemv_cols(b, blk, ls.W, q, G, st);
         if (s != HLQ_OK) return s;
         return hlq_hip_status(hipGetLastError());
     }

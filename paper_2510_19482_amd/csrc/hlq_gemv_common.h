@@ -23,12 +23,33 @@ struct GemvProb {
     int *xexp;         //                   and the exponent of every row's scale [16]
 };
 
+// A problem of the one-row matrix-core kernel (hlq_gemv_cols.hip): what its head needs, in as few words as it takes -- a
+// launch of a small matrix lasts three microseconds, and a workgroup's first load waits for these.
+struct ColsProb {
+    const char *packed;
+    const uint16_t *x;
+    void *y;
+    float *part;       // [nslices][N] partial sums (nslices > 1)
+    int *cnt;          // [ntg] arrival counters, or 64-bit slots per column (pairs); zero between launches
+    unsigned tile_bytes;   // 64 columns
+    int N, nchunks, cps, nslices;
+    unsigned slice_magic;  // as in GemvProb
+    int ntg, blk_begin;
+    int cb_base, cb_rem;   // column blocks of 16 per workgroup: cb_base, the first cb_rem workgroups one more
+    uint16_t wbase, wrem, wbase_l, wrem_l;   // windows of four chunks per wavefront likewise; _l: in the last K slice
+    uint8_t kw_shift;  // log2 of the wavefronts on one column block
+    uint8_t st_shift;  // log2 of the streams: groups of these wavefronts with consecutive shares of the column blocks
+    uint8_t swz_shift; // log2 of the workgroups that share a 64-column tile
+    uint8_t pairs;     // two K slices that meet in 64-bit slots at cnt, one per column
+};
+
 // Host-side description of a launch.
 struct GemvBatch {
     int blk_begin[HLQ_MAX_BATCH];   // first block of every problem, ascending; unused entries INT_MAX
     int count;
     int out_f32;
     GemvProb p[HLQ_MAX_BATCH];
+    ColsProb cp[HLQ_MAX_BATCH];     // one-row matrix-core kernel
 };
 
 // What the kernels take: the first blocks of the problems and the flag as leading scalar arguments --
@@ -83,6 +104,12 @@ __device__ __forceinline__ void store_out(void *y, size_t idx, float v, int out_
 // per tile: ntg = ceil(ntiles / (W / kw)) tile groups, one arrival counter per TILE
 hlq_status hlq_launch_gemv_mx(const GemvBatch &b, unsigned nblocks, int W, int nsets, int rows, int q, int G, hipStream_t st);
 int hlq_gemv_mx_max_waves(int q, int G);
+
+// one activation row (hlq_gemv_cols.hip): W (1..16) wavefronts, kw of them (a power of two) on each column block, at most
+// four column blocks per workgroup where K is split across workgroups, one arrival counter per workgroup column
+#define HLQ_COLS_MAX_SLOTS 640   // (column blocks of a workgroup) x kw: 64 bytes of LDS each
+int hlq_gemv_cols_max_waves(int q, int G);
+hlq_status hlq_launch_gemv_cols(const GemvBatch &b, unsigned nblocks, int W, int q, int G, hipStream_t st);
 
 // many-rows kernel (hlq_gemm_rows.hip): W = 2, 4 or 8 wavefronts, one tile each, all on the workgroup's K slice
 hlq_status hlq_launch_gemm_rows(const GemvBatch &b, unsigned nblocks, int W, int rows, int q, int G, hipStream_t st);
