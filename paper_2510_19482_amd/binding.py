@@ -41,7 +41,8 @@ def _load() -> ctypes.CDLL:
     # loaded first: libhlq then binds to that copy, and both sides share one runtime, one device
     # context and the same stream handles.  Loaded the other way round the process ends up with
     # two runtimes and launches fail with "no ROCm-capable device".
-    import torch  # noqa: F401
+    global torch
+    import torch
     lib = ctypes.CDLL(LIB_PATH)
     vp, sz, i64, u32 = ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int64, ctypes.c_uint32
     dp = ctypes.POINTER(HlqDesc)
@@ -159,18 +160,21 @@ def workspace_bytes(desc: HlqDesc, M: int) -> int:
 
 # ---- torch-facing helpers (device tensors in, device tensors out) -------------------------
 def _stream_ptr(stream=None) -> int:
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return int(s.cuda_stream)
+    if stream is not None:
+        return int(stream.cuda_stream)
+    if not torch.cuda.is_initialized():
+        return int(torch.cuda.current_stream().cuda_stream)
+    # the handle of the calling thread's current stream on its current device, without the Stream object around it:
+    # a one-row call of a small matrix spends 3 us on the GPU, and building that object took 1.5 us of the host's time
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _ptr(t) -> int:
-    return 0 if t is None else int(t.data_ptr())
+    return 0 if t is None else t.data_ptr()
 
 
 def hlq_pack(desc: HlqDesc, codes, scales, zeros, packed=None, stream=None):
     """codes u8 [K,N], scales fp16 [q,K/G,N], zeros fp16 [K/G,N] (cuda tensors) -> packed u8 blob."""
-    import torch
     total, _, _ = packed_bytes(desc)
     if packed is None:
         packed = torch.empty(total, dtype=torch.uint8, device=codes.device)
@@ -180,7 +184,6 @@ def hlq_pack(desc: HlqDesc, codes, scales, zeros, packed=None, stream=None):
 
 
 def hlq_unpack(desc: HlqDesc, packed, stream=None):
-    import torch
     K, N, q, G = desc.K, desc.N, desc.q, desc.G
     codes = torch.empty((K, N), dtype=torch.uint8, device=packed.device)
     scales = torch.empty((q, K // G, N), dtype=torch.float16, device=packed.device)
@@ -198,7 +201,6 @@ def batch_workspace_bytes(descs) -> int:
 
 
 def _new_workspace(nbytes: int, device, stream=None):
-    import torch
     ws = torch.empty(nbytes, dtype=torch.uint8, device=device)
     _check("hlq_workspace_init", lib.hlq_workspace_init(_ptr(ws), ws.numel(), _stream_ptr(stream)))
     return ws
@@ -216,7 +218,6 @@ def alloc_batch_workspace(descs, device="cuda", stream=None):
 def hlq_quantize(desc: HlqDesc, W, t_max: int = 10, with_err: bool = False, stream=None):
     """Alg. 1 on W fp32 cuda [K, N] -> codes u8 [K, N], scales fp16 [q, K/G, N], zeros fp16 [K/G, N]
     (and the per-group squared error fp32 [K/G, N] with with_err=True)."""
-    import torch
     assert W.dtype == torch.float32 and W.is_contiguous() and tuple(W.shape) == (desc.K, desc.N)
     dev = W.device
     codes = torch.empty((desc.K, desc.N), dtype=torch.uint8, device=dev)
@@ -302,14 +303,14 @@ class GemmBatch:
 
 def hlq_lut_gemv(desc: HlqDesc, packed, x, y=None, out_f32: bool = False, ws=None, stream=None):
     """y[N] = x[K] @ W^ ; x fp16 cuda tensor."""
-    import torch
     if y is None:
         y = torch.empty(desc.N, dtype=torch.float32 if out_f32 else torch.float16, device=x.device)
     if ws is None:
         ws = alloc_workspace(desc, 1, x.device)
-    _check("hlq_lut_gemv", lib.hlq_lut_gemv(ctypes.byref(desc), _ptr(packed), _ptr(x), _ptr(y),
-                                            HLQ_OUT_F32 if out_f32 else HLQ_OUT_F16, _ptr(ws), ws.numel(),
-                                            _stream_ptr(stream)))
+    status = lib.hlq_lut_gemv(desc, _ptr(packed), _ptr(x), _ptr(y), HLQ_OUT_F32 if out_f32 else HLQ_OUT_F16, _ptr(ws), ws.numel(),
+                              _stream_ptr(stream))
+    if status != HLQ_OK:
+        raise HlqError("hlq_lut_gemv", status)
     return y
 
 
@@ -326,7 +327,6 @@ def hlq_lut_gemv_static(desc: HlqDesc, packed, x, y, out_f32: bool = False, stre
 
 def hlq_lut_gemm(desc: HlqDesc, packed, X, Y=None, out_f32: bool = False, ws=None, stream=None):
     """Y[M,N] = X[M,K] @ W^ ; X fp16 cuda tensor, row-major (stride(1) == 1)."""
-    import torch
     M = X.shape[0]
     if Y is None:
         Y = torch.empty((M, desc.N), dtype=torch.float32 if out_f32 else torch.float16, device=X.device)
