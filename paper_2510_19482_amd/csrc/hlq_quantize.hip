@@ -80,16 +80,20 @@ __device__ __forceinline__ void sort_keys(uint32_t (&key)[NC])
 // j: moved to the top of the high half of a double it is 2^-15, the factor with which the weight enters plane j's sum (the
 // sums are kept times 2^-15: every product and rounding is the one without the factor).  Codes are counted in a third.
 // Per weight and round 11 vector instructions at q = 2 and 25 at q = 4, instead of 27 and about 110 for the scan.
-// 4096 x 4096, G = 128, ten rounds: q = 1 / 2 / 3 / 4  84 / 154 / 274 / 493 us with the scan, 67 / 97 / 135 / 185 us now;
+// 4096 x 4096, G = 128, ten rounds: q = 1 / 2 / 3 / 4  84 / 154 / 274 / 493 us with the scan, 54 / 97 / 133 / 185 us now;
 // G = 32, where the work per group and round (sort, thresholds, elimination) is as long as the weights' own:
-// 76 / 154 / 291 / 520 -> 65 / 113 / 177 / 287 us; G = 256, weights from the L2: 171 / 689 / 829 / 950 -> 134 / 163 / 206 / 261 us.
+// 76 / 154 / 291 / 520 -> 60 / 124 / 177 / 290 us; G = 256, weights from the L2: 171 / 689 / 829 / 950 -> 128 / 161 / 206 / 261 us.
+// Of launches too small to fill the chip only q = 2, G = 32 does not gain: 512 x 512 22.0 us with the scan, 23.1 now.
 template <int Q, int G>
 __global__ void __launch_bounds__(256, Q == 4 && G == 32 ? 3 : 2)
 hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_t *__restrict__ codes,
                     uint16_t *__restrict__ scales, uint16_t *__restrict__ zeros, float *__restrict__ group_err)
 {
     constexpr int NC = 1 << Q, P = Q + 1;
-    __shared__ uint32_t lds[4 * 3 * NC * 64];
+    // few candidates: everything in registers.  At q = 2 the tables in LDS are 5 % faster on large matrices (G = 128 97 us
+    // against 100), but with groups of 32 a small launch waits for them in every round (512 x 512: 25.6 us against 23.1)
+    constexpr bool SMALL = Q == 1 || (Q == 2 && G == 32);
+    __shared__ uint32_t lds[SMALL ? 1 : 4 * 3 * NC * 64];
     const int n = (int)(blockIdx.x * 256 + threadIdx.x);
     const int gi = (int)blockIdx.y;
     if (n >= N) return;
@@ -98,7 +102,7 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
     uint8_t *c0 = codes + (size_t)gi * G * N + n;
     // this lane's columns, one word every 64: thresholds in order | plane words by sorted position | counts.  The
     // second and third also hold the candidate values (fp64, by code) while the thresholds are made.
-    uint32_t *const tree = lds + (threadIdx.x >> 6) * (3 * NC * 64) + (threadIdx.x & 63);
+    uint32_t *const tree = lds + (SMALL ? 0 : (threadIdx.x >> 6) * (3 * NC * 64) + (threadIdx.x & 63));
     uint32_t *const plane = tree + NC * 64;
     uint32_t *const count = plane + NC * 64;
 
@@ -160,29 +164,60 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
         // candidate values V_c = sum_j s_j bit_j(c)   (step 7), sorted by the leading bits of their fp32 rounding with
         // the code in the last q bits (an order that is not the fp64 one shows as a gap below gap_min)
         uint32_t key[NC];
+        double sorted[SMALL ? NC : 1];   // SMALL: sorted as they are, with their codes as keys
         unrolled<NC>([&](auto cc) {
             constexpr int c = decltype(cc)::value;
             double v = 0.0;
 #pragma unroll
             for (int j = 0; j < Q; ++j) v += theta[1 + j] * (double)((c >> j) & 1);
-            const uint64_t b = __builtin_bit_cast(uint64_t, v);
-            plane[(2 * c) * 64] = (uint32_t)b;
-            plane[(2 * c + 1) * 64] = (uint32_t)(b >> 32);
-            const uint32_t u = __builtin_bit_cast(uint32_t, (float)v);
-            key[c] = ((u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u)) & ~(uint32_t)(NC - 1)) | (uint32_t)c;
+            if constexpr (SMALL) {
+                sorted[c] = v;
+                key[c] = (uint32_t)c;
+            } else {
+                const uint64_t b = __builtin_bit_cast(uint64_t, v);
+                plane[(2 * c) * 64] = (uint32_t)b;
+                plane[(2 * c + 1) * 64] = (uint32_t)(b >> 32);
+                const uint32_t u = __builtin_bit_cast(uint32_t, (float)v);
+                key[c] = ((u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u)) & ~(uint32_t)(NC - 1)) | (uint32_t)c;
+            }
         });
-        sort_keys<NC>(key);
-        auto value_of = [&](uint32_t code) -> double {
-            const uint32_t at = code * 128;
-            return __builtin_bit_cast(double, ((uint64_t)plane[at + 64] << 32) | plane[at]);
+        if constexpr (SMALL) {
+            auto order = [&](int a, int b) {
+                const bool swap = sorted[b] < sorted[a];
+                const double va = sorted[a], vb = sorted[b];
+                const uint32_t ca = key[a], cb = key[b];
+                sorted[a] = swap ? vb : va;
+                sorted[b] = swap ? va : vb;
+                key[a] = swap ? cb : ca;
+                key[b] = swap ? ca : cb;
+            };
+            if constexpr (NC == 2) {
+                order(0, 1);
+            } else {
+                order(0, 1);
+                order(2, 3);
+                order(0, 2);
+                order(1, 3);
+                order(1, 2);
+            }
+        } else {
+            sort_keys<NC>(key);
+        }
+        auto value_at = [&](int i) -> double {   // of sorted position i
+            if constexpr (SMALL) {
+                return sorted[i];
+            } else {
+                const uint32_t at = (key[i] & (NC - 1)) * 128;
+                return __builtin_bit_cast(double, ((uint64_t)plane[at + 64] << 32) | plane[at]);
+            }
         };
         bool good = true;
         float top[3];   // the thresholds at the quarters (q = 1: the only one)
-        double va = value_of(key[0] & (NC - 1));
+        double va = value_at(0);
         unrolled<NC - 1>([&](auto ii) {
             constexpr int i = decltype(ii)::value + 1;
             const uint32_t ca = key[i - 1] & (NC - 1), cb = key[i] & (NC - 1);
-            const double vb = value_of(cb);
+            const double vb = value_at(i);
             good = good && vb - va >= gap_min;
             const double m = 0.5 * (va + vb) + z;
             const float t = (float)m;
@@ -193,7 +228,7 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
             const float next = __builtin_bit_cast(float, tb + away);
             const bool near = fabs(off) <= band;
             good = good && t != 0.f;
-            if (__any(near)) {
+            if (__any(near)) {   // in the first round mostly: the middle of the grid is an fp32 number
                 const float prev = __builtin_bit_cast(float, tb - away);
                 auto upper_wins = [&](float w) {
                     const double what = (double)w - z;
@@ -213,13 +248,21 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
         const bool scan = __any(!good);
 
         // per sorted position (or per code, for the scan): the plane word; counts start at zero
+        uint32_t words[SMALL ? NC : 1];
 #pragma unroll
         for (int i = 0; i < NC; ++i) {
             const uint32_t c = scan ? (uint32_t)i : key[i] & (NC - 1);
             const uint32_t ones = __umul24(c, 0x204081u) & 0x01010101u;   // bit j of the code in byte j
-            plane[i * 64] = (ones << 6) - ones;
-            count[i * 64] = 0u;
+            if constexpr (SMALL) {
+                words[i] = (ones << 6) - ones;
+            } else {
+                plane[i * 64] = (ones << 6) - ones;
+                count[i * 64] = 0u;
+            }
         }
+        int cnt[NC];   // SMALL, until the pass is over: weights at or above threshold i (position i and higher)
+#pragma unroll
+        for (int i = 0; i < NC; ++i) cnt[i] = 0;
         double rb[Q];
 #pragma unroll
         for (int j = 0; j < Q; ++j) rb[j] = 0.0;
@@ -238,7 +281,42 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
                 c0[(size_t)i * N] = (uint8_t)c;
             }
         };
-        if (!scan) {
+        if (!scan && SMALL) {
+            // a comparison per threshold; its outcome picks the plane word and is counted
+            auto take = [&](int i, float w) {
+                uint32_t word = words[0];
+#pragma unroll
+                for (int k = 1; k < NC; ++k) {
+                    const bool up = w >= top[k - 1];
+                    word = up ? words[k] : word;
+                    cnt[k] += up ? 1 : 0;
+                }
+                fold(i, w, word);
+            };
+            if constexpr (RESIDENT) {
+#pragma unroll
+                for (int i = 0; i < G; ++i) {
+                    take(i, weight(i));
+                    if ((i & 7) == 7) __builtin_amdgcn_sched_barrier(0);
+                }
+            } else {
+                constexpr int AHEAD = 32;   // weights come from the L2: the next 32 are requested while 32 are worked on
+                float nx[AHEAD];
+#pragma unroll
+                for (int u = 0; u < AHEAD; ++u) nx[u] = w0[(size_t)u * N];
+#pragma unroll 1
+                for (int i = 0; i < G; i += AHEAD) {
+                    float cur[AHEAD];
+#pragma unroll
+                    for (int u = 0; u < AHEAD; ++u) cur[u] = nx[u];
+#pragma unroll
+                    for (int u = 0; u < AHEAD; ++u) nx[u] = w0[(size_t)min(i + AHEAD + u, G - 1) * N];
+#pragma unroll
+                    for (int u = 0; u < AHEAD; ++u) take(i + u, cur[u]);
+                }
+            }
+        } else if (!scan) {
+            if constexpr (!SMALL) {
             // Eight weights at a time, one level of the search for all of them before the next, and the sums of the
             // previous eight between the levels: an LDS read is used some thirty instructions after it was issued
             // (with the weights of a group in registers there are two wavefronts on a SIMD to cover for each other).
@@ -315,6 +393,7 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
                     pass(cur, std::integral_constant<int, AHEAD>{}, i);
                 }
             }
+            }
         } else {
             // the scan of all candidates, weights re-read (rare)
             double V[NC];
@@ -337,22 +416,47 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
                     best = d < bd ? (uint32_t)c : best;
                     bd = __builtin_fmin(bd, d);
                 }
-                fold(i, w, plane[best * 64]);
-                __hip_atomic_fetch_add(&count[best * 64], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                if constexpr (SMALL) {
+                    uint32_t word = words[0];
+#pragma unroll
+                    for (int c = 1; c < NC; ++c) word = best == (uint32_t)c ? words[c] : word;
+                    fold(i, w, word);
+#pragma unroll
+                    for (int c = 0; c < NC; ++c) cnt[c] += best == (uint32_t)c ? 1 : 0;
+                } else {
+                    fold(i, w, plane[best * 64]);
+                    __hip_atomic_fetch_add(&count[best * 64], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                }
             }
         }
 #pragma unroll
         for (int j = 0; j < Q; ++j) rb[j] *= 0x1p15;
 
         // counts by code, from counts by sorted position
-        int cnt[NC];
+        if constexpr (SMALL) {
+            if (!scan) {
+                int at[NC], by_code[NC];
+                cnt[0] = G;
 #pragma unroll
-        for (int i = 0; i < NC; ++i) cnt[i] = (int)count[i * 64];
-        if (!scan) {
+                for (int i = 0; i < NC; ++i) at[i] = cnt[i] - (i + 1 < NC ? cnt[i + 1] : 0);
 #pragma unroll
-            for (int i = 0; i < NC; ++i) plane[(key[i] & (NC - 1)) * 64] = (uint32_t)cnt[i];
+                for (int c = 0; c < NC; ++c) {
+                    by_code[c] = 0;
 #pragma unroll
-            for (int i = 0; i < NC; ++i) cnt[i] = (int)plane[i * 64];
+                    for (int i = 0; i < NC; ++i) by_code[c] += key[i] == (uint32_t)c ? at[i] : 0;
+                }
+#pragma unroll
+                for (int c = 0; c < NC; ++c) cnt[c] = by_code[c];
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < NC; ++i) cnt[i] = (int)count[i * 64];
+            if (!scan) {
+#pragma unroll
+                for (int i = 0; i < NC; ++i) plane[(key[i] & (NC - 1)) * 64] = (uint32_t)cnt[i];
+#pragma unroll
+                for (int i = 0; i < NC; ++i) cnt[i] = (int)plane[i * 64];
+            }
         }
         unsigned present = 0u;
         int nb[Q], nbb[Q][Q];
