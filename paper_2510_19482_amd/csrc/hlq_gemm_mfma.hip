@@ -36,6 +36,7 @@
 // 8..15 in lanes 32..63 for the SAME 32 columns; one v_permlane32_swap per register hands the
 // upper k-slots of columns 0..31 to lanes 32..63 and the lower k-slots of columns 32..63 to
 // lanes 0..31, giving the B operands of both 32-column halves of the tile.
+#include "hlq_gemm_safe.h"
 #include "hlq_mfma_common.h"
 
 namespace {
@@ -340,43 +341,72 @@ hlq_gemm_mfma_group_kernel(const int4v bb_lo, const int4v bb_hi, const int M, co
                               P.cps, P.nslices, out_f32, cg, sl, rb, range_flag);
 }
 
-// adds the partial sums of all problems of a grouped launch whose K was split; 256 outputs per block
+// Adds the partial sums of the problems of a launch whose K was split, four outputs per lane (N is a multiple of 8), or,
+// if the tiled kernel met parameters outside its range, computes the call again: one launch behind the tiled kernel instead
+// of two.  A dependent launch costs 1.7 us even when it only looks at the flag; the sums are latency-bound themselves
+// (one 4-byte load per lane and slice and a 64-bit division per output before).
 struct GemmRedProb {
     const float *part;
     void *Y;
     long ldy;
     int N, nslices, blk_begin;
+    int wide;   // Y's rows are aligned to four elements: one store per lane
 };
 struct GemmRedProbs {
     GemmRedProb p[HLQ_MAX_BATCH];
 };
+constexpr int RED_LANES = 256, RED_OUT = 4 * RED_LANES;   // outputs per block
 
-__global__ void __launch_bounds__(256)
-hlq_gemm_mfma_group_reduce_kernel(const int4v bb_lo, const int4v bb_hi, const int M, const int out_f32,
-                                  const GemmRedProbs probs)
+__global__ void __launch_bounds__(RED_LANES)
+hlq_gemm_mfma_group_reduce_kernel(const int4v bb_lo, const int4v bb_hi, const int M, const int out_f32, int *flag,
+                                  const GemmRedProbs probs, const HlqSafeProbs again)
 {
+    const int redo = *(const int *)flag;   // written by the launch before this one
     const int blk = (int)blockIdx.x;
     const GemmRedProb P = probs.p[group_problem_of(bb_lo, bb_hi, blk)];
-    const size_t i = (size_t)(blk - P.blk_begin) * 256 + threadIdx.x;
+    const size_t i = ((size_t)(blk - P.blk_begin) * RED_LANES + threadIdx.x) * 4;
     const size_t total = (size_t)M * P.N;
-    if (i >= total) return;
-    float a = 0.f;
-    for (int s = 0; s < P.nslices; ++s) a += P.part[(size_t)s * total + i];
-    const size_t m = i / P.N, n = i % P.N;
-    store_out(P.Y, m * P.ldy + n, a, out_f32);
+    if (redo == 0) {
+        if (i >= total) return;
+        float4v a = {0.f, 0.f, 0.f, 0.f};
+        const float *src = P.part + i;
+        int s = 0;
+        for (; s + 4 <= P.nslices; s += 4) {   // four slices in flight, added in slice order
+            const float4v v0 = *(const float4v *)(src + (size_t)(s + 0) * total), v1 = *(const float4v *)(src + (size_t)(s + 1) * total);
+            const float4v v2 = *(const float4v *)(src + (size_t)(s + 2) * total), v3 = *(const float4v *)(src + (size_t)(s + 3) * total);
+            a = (((a + v0) + v1) + v2) + v3;
+        }
+        for (; s < P.nslices; ++s) a += *(const float4v *)(src + (size_t)s * total);
+        const size_t m = total <= 0xffffffffu ? (unsigned)i / (unsigned)P.N : i / (unsigned)P.N;
+        const size_t at = m * P.ldy + (i - m * P.N);
+        typedef _Float16 half4v __attribute__((ext_vector_type(4)));
+        if (P.wide && out_f32) {
+            *(float4v *)((float *)P.Y + at) = a;
+        } else if (P.wide) {
+            *(half4v *)((_Float16 *)P.Y + at) = (half4v){(_Float16)a.x, (_Float16)a.y, (_Float16)a.z, (_Float16)a.w};
+        } else {
+            store_out(P.Y, at + 0, a.x, out_f32);
+            store_out(P.Y, at + 1, a.y, out_f32);
+            store_out(P.Y, at + 2, a.z, out_f32);
+            store_out(P.Y, at + 3, a.w, out_f32);
+        }
+        return;
+    }
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    hlq_safe_recompute(again, M, out_f32, flag, flag + 1, (long)blk * (RED_LANES / 64) + wave, (long)gridDim.x * (RED_LANES / 64));
 }
 
-__global__ void __launch_bounds__(256)
-hlq_gemm_mfma_reduce_kernel(const float *__restrict__ ws, void *__restrict__ Y, long ldy, int M, int N,
-                            int nslices, int out_f32)
+// one problem of that launch; returns its blocks
+static long reduce_problem(GemmRedProb &r, const float *part, void *Y, long ldy, int N, int nslices, int64_t M, int out_f32, long blk)
 {
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    const size_t total = (size_t)M * N;
-    if (i >= total) return;
-    float a = 0.f;
-    for (int s = 0; s < nslices; ++s) a += ws[(size_t)s * total + i];
-    const size_t m = i / N, n = i % N;
-    store_out(Y, m * ldy + n, a, out_f32);
+    r.part = part;
+    r.Y = Y;
+    r.ldy = ldy;
+    r.N = N;
+    r.nslices = nslices;
+    r.blk_begin = (int)blk;
+    r.wide = (((uintptr_t)Y | ((uintptr_t)ldy * (out_f32 ? 4u : 2u))) & (out_f32 ? 15u : 7u)) == 0;
+    return (long)(((size_t)M * N + RED_OUT - 1) / RED_OUT);
 }
 
 struct MfmaPlan {
@@ -504,12 +534,6 @@ hlq_status hlq_launch_gemm_mfma(const HlqDims &dm, const void *packed, const uin
     default: return HLQ_ERR_UNSUPPORTED;
     }
     if (s != HLQ_OK) return s;
-    if (p.nslices > 1) {
-        const size_t total = (size_t)M * dm.N;
-        hlq_gemm_mfma_reduce_kernel<<<(unsigned)((total + 255) / 256), 256, 0, st>>>(part, Y, (long)ldy, (int)M, dm.N,
-                                                                                    p.nslices, out_f32);
-    }
-    // behind it, the fp32 fallback for weights outside the range of the fp16 rebuild (a no-op unless the flag went up)
     HlqGemvItem it;
     it.dm = dm;
     it.packed = packed;
@@ -517,6 +541,20 @@ hlq_status hlq_launch_gemm_mfma(const HlqDims &dm, const void *packed, const uin
     it.y = Y;
     it.ldx = (long)ldx;
     it.ldy = (long)ldy;
+    if (p.nslices > 1) {
+        GemmRedProbs rp;
+        HlqSafeProbs again;
+        s = hlq_safe_problems(1, &it, M, again);
+        if (s != HLQ_OK) return s;
+        const long blocks = reduce_problem(rp.p[0], part, Y, (long)ldy, dm.N, p.nslices, M, out_f32, 0);
+        if (blocks > 0x7fffffffL / (RED_LANES / 64)) return HLQ_ERR_UNSUPPORTED;
+        for (int i = 1; i < HLQ_MAX_BATCH; ++i) rp.p[i] = rp.p[0];
+        const int none = 0x7fffffff;
+        hlq_gemm_mfma_group_reduce_kernel<<<(unsigned)blocks, RED_LANES, 0, st>>>((int4v){0, none, none, none}, (int4v){none, none, none, none},
+                                                                                 (int)M, out_f32, hlq_ws_range_flag(ws), rp, again);
+        return hlq_hip_status(hipGetLastError());
+    }
+    // behind it, the fp32 fallback for weights outside the range of the fp16 rebuild (a no-op unless the flag went up)
     s = hlq_launch_gemm_safe(1, &it, M, out, ws, st);
     if (s != HLQ_OK) return s;
     return hlq_hip_status(hipGetLastError());
@@ -615,16 +653,9 @@ hlq_status hlq_launch_gemm_mfma_batch(int count, const HlqGemvItem *items, int64
         blk += (long)blocks;
         if (blk > 0x7fffffffL) return HLQ_ERR_UNSUPPORTED;
         if (p.nslices > 1) {
-            GemmRedProb &r = rp.p[nred];
-            r.part = part;
-            r.Y = it.y;
-            r.ldy = it.ldy;
-            r.N = it.dm.N;
-            r.nslices = p.nslices;
-            r.blk_begin = (int)rblk;
-            rbegin[nred++] = (int)rblk;
-            rblk += (long)(((size_t)M * it.dm.N + 255) / 256);
-            if (rblk > 0x7fffffffL) return HLQ_ERR_UNSUPPORTED;
+            rbegin[nred] = (int)rblk;
+            rblk += reduce_problem(rp.p[nred++], part, it.y, it.ldy, it.dm.N, p.nslices, M, out == HLQ_OUT_F32, rblk);
+            if (rblk > 0x7fffffffL / (RED_LANES / 64)) return HLQ_ERR_UNSUPPORTED;
             part += (size_t)p.nslices * (size_t)M * (size_t)it.dm.N;
         }
     }
@@ -649,7 +680,11 @@ hlq_status hlq_launch_gemm_mfma_batch(int count, const HlqGemvItem *items, int64
             rbegin[i] = 0x7fffffff;
         }
         const int4v rlo = {rbegin[0], rbegin[1], rbegin[2], rbegin[3]}, rhi = {rbegin[4], rbegin[5], rbegin[6], rbegin[7]};
-        hlq_gemm_mfma_group_reduce_kernel<<<(unsigned)rblk, 256, 0, st>>>(rlo, rhi, (int)M, out_f32, rp);
+        HlqSafeProbs again;
+        s = hlq_safe_problems(count, items, M, again);
+        if (s != HLQ_OK) return s;
+        hlq_gemm_mfma_group_reduce_kernel<<<(unsigned)rblk, RED_LANES, 0, st>>>(rlo, rhi, (int)M, out_f32, hlq_ws_range_flag(ws), rp, again);
+        return hlq_hip_status(hipGetLastError());
     }
     s = hlq_launch_gemm_safe(count, items, M, out, ws, st);
     if (s != HLQ_OK) return s;
