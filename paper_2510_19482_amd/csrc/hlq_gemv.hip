@@ -643,7 +643,7 @@ ColsProb cols_record(const GemvProb &p, int W, bool pairs)
     r.kw_shift = (uint8_t)p.kw_shift;
     r.st_shift = 0;
     while ((p.kw << r.st_shift) < W) ++r.st_shift;
-    r.swz_shift = r.cb_rem ? 0 : r.cb_base == 1 ? 2 : r.cb_base == 2 ? 1 : 0;
+    r.unused = 0;
     r.pairs = pairs;
     return r;
 }

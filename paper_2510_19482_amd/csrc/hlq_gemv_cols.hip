@@ -34,8 +34,8 @@
 // Work split.  A workgroup of W wavefronts owns adjacent column blocks and one K slice; the windows of the slice are
 // dealt out to the wavefronts, whose results meet in LDS.  K slices of different workgroups meet in the workspace: two
 // in an exchange per column, more as in the other GEMV kernels (partial sums, an arrival counter per workgroup column, the
-// last one adds in slice order).  Column blocks of one 64-column tile share the cache lines of its scales: where they go
-// to different workgroups, the block order puts these on one XCD (workgroups go to the eight XCDs in turn).
+// last one adds in slice order).  Column blocks of one 64-column tile share the cache lines of its scales: neighbouring
+// workgroups run on one XCD (they go to the eight XCDs in turn, so the block order is dealt out to match).
 #include "hlq_gemv_common.h"
 
 namespace {
@@ -98,9 +98,9 @@ hlq_gemv_cols_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32, co
     const int local = (int)blockIdx.x - P.blk_begin;
     int tg = P.nslices > 1 ? (int)__umulhi((unsigned)local, P.slice_magic) : local;
     const int slice = local - tg * P.nslices;
-    {   // neighbours that share a tile (2^swz_shift workgroups): 8 workgroups apart, i.e. on one XCD
-        const int span = 8 << P.swz_shift, r = tg & (span - 1), at = tg - r;
-        if (at + span <= P.ntg) tg = at + ((r & 7) << P.swz_shift) + (r >> 3);
+    {   // neighbours share a tile's cache lines: each XCD (workgroups go to the eight in turn) takes consecutive ones
+        const int xcd = tg & 7, each = P.ntg >> 3;
+        tg = xcd * each + min(xcd, P.ntg & 7) + (tg >> 3);
     }
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;

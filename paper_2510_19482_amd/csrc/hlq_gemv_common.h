@@ -39,8 +39,8 @@ struct ColsProb {
     uint16_t wbase, wrem, wbase_l, wrem_l;   // windows of four chunks per wavefront likewise; _l: in the last K slice
     uint8_t kw_shift;  // log2 of the wavefronts on one column block
     uint8_t st_shift;  // log2 of the streams: groups of these wavefronts with consecutive shares of the column blocks
-    uint8_t swz_shift; // log2 of the workgroups that share a 64-column tile
     uint8_t pairs;     // two K slices that meet in 64-bit slots at cnt, one per column
+    uint8_t unused;
 };
 
 // Host-side description of a launch.
