@@ -810,11 +810,12 @@ static hlq_status plan_gemv_batch(int count, const HlqGemvItem *items, hlq_out_d
         if ((unsigned long long)p.ntg * p.nslices * p.nslices >= 0x100000000ULL) return HLQ_ERR_UNSUPPORTED;
         p.blk_begin = (int)blk;
         b.blk_begin[i] = (int)blk;
+        if (cols && split[order[i]].pairs) cnt_used = (cnt_used + 1) & ~1L;   // 64-bit slots, behind any number of 32-bit counters
         p.cnt = cnt + cnt_used;
         p.part = part;
         blk += (long)p.ntg * p.nslices;
         if (cols && split[order[i]].pairs) {
-            cnt_used += 2L * dm.N;   // N is a multiple of 8: the slots stay 8-byte aligned
+            cnt_used += 2L * dm.N;
         } else if (p.nslices > 1) {
             cnt_used += mx && !cols ? dm.ntiles : p.ntg;
             part += (size_t)p.nslices * dm.N * rows;

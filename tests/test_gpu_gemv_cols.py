@@ -83,6 +83,24 @@ def test_two_slices_of_several_problems_share_one_counter_block():
     assert int(batch.ws[:131072].count_nonzero()) == 0
 
 
+def test_counters_and_slots_side_by_side():
+    # three slices with an odd number of arrival counters in front of two slices with 64-bit slots
+    q, G = 2, 128
+    shapes = [(16896, 72), (14336, 40), (12288, 24)]
+    cases = [case(K, N, q, G, "mixed") for K, N in shapes]
+    ys = [torch.empty(N, dtype=torch.float32, device="cuda") for _, N in shapes]
+    infos = B.gemv_plan_query([c[0] for c in cases], 1)
+    assert [i.slices for i in infos] == [3, 2, 2] and infos[0].tile_groups % 2 == 1
+    batch = B.GemvBatch([c[0] for c in cases], [c[1] for c in cases], [c[2] for c in cases], ys, out_f32=True)
+    for _ in range(3):
+        for y in ys:
+            y.fill_(7.0)
+        batch.launch()
+        for c, y in zip(cases, ys):
+            check(y, c[3])
+    assert int(batch.ws[:131072].count_nonzero()) == 0
+
+
 @pytest.mark.parametrize("q,G,N", [(2, 32, 23040), (1, 64, 40000), (2, 64, 122880)])
 def test_either_side_of_the_size_rule(q, G, N):
     # K = 4096: 32 chunk-tiles per 64 columns; the named N is the first or close to the first that the 64-column kernel takes
