@@ -548,7 +548,7 @@ int plan_cols(int count, const HlqDims *dms, int forced_w, int cpw, ColsSplit *o
     for (int i = 0; i < count; ++i) blocks += cols_blocks(dms[i]);
     // K slices.  One up to sixteen windows (K = 8192: a window per wavefront).  Two up to 32 windows, in which case the sides
     // meet in one exchange per column: 14336 x 1024 5.5 us in one slice, 4.5 in two; 14336 x 512 5.4 / 4.4; 11008 x 5000,
-    // q = 3, G = 64 10.1 / 9.3; where the columns alone give every compute unit its workgroup it costs a little instead,
+    // q = 3, G = 64 10.1 / 8.4; where the columns alone give every compute unit its workgroup it costs a little instead,
     // 14336 x 4096 6.0 / 6.5, 11008 x 4096 5.5 / 5.8.  Longer K over few columns: one slice per sixteen windows,
     // partial sums and arrival counters: 28672 x 1024 8.5 / 6.5, 28672 x 512 8.3 / 5.8; over more columns one slice,
     // 28672 x 8192 13.5.
