@@ -25,7 +25,8 @@
 // decided exactly on the small integer Gram matrix of the distinct rows [1 bits(c)] (entries <= 16):
 // fraction-free elimination in column order, in which a zero pivot (the Gram determinant of the
 // independent columns so far plus this one) marks a dependent column, which is then skipped.
-// Every loop below has compile-time bounds and indices, so all of this lives in registers.
+// Every loop below has compile-time bounds and indices, so all of this lives in registers (and the tables of the search in
+// LDS); none of it in scratch memory.
 #include "hlq_internal.h"
 #include <type_traits>
 
@@ -62,6 +63,12 @@ __device__ __forceinline__ void sort_keys(uint32_t (&key)[NC])
                     }
 }
 
+// wavefronts on a SIMD that the registers have to leave room for (the weights of a group take G of them)
+constexpr int quantize_waves(int q, int G)
+{
+    return G == 32 ? (q == 1 ? 7 : q == 2 ? 5 : q == 3 ? 4 : 3) : G == 128 ? (q == 1 ? 3 : 2) : q <= 2 ? 4 : 3;
+}
+
 // Bit-pattern selection.  The codes are the argmin over 2^q candidate distances, computed in fp64, first minimum in
 // code order; scanning them costs 4 x 2^q vector instructions per weight and round.  With the candidate values sorted,
 // only the two neighbours of a weight compete, and which of them wins is monotone in the weight, so there is an exact
@@ -72,34 +79,50 @@ __device__ __forceinline__ void sort_keys(uint32_t (&key)[NC])
 //     below 2^-50 S, so only neighbours compete and the choice between them is monotone;
 //   - with m the midpoint in fp64 (error below 2^-48 S) and t its rounding to fp32: where |t - m| > 2^-45 S the sign of
 //     t - m decides for t, and the next fp32 number on the other side is on the other side of m as well; otherwise
-//     the two distances of t and of that neighbour are compared as the scan compares them.
-// A lane that meets neither (equal candidates of a degenerate group, a midpoint at zero) sends its wavefront through the
-// scan for that round.
+//     the two distances of t and of that neighbour are compared as the scan compares them;
+//   - where both of them fall on one side (a midpoint at or near zero: every group with min = -max, i.e. 0.9 % of the groups
+//     and 43 % of the wavefronts for N(0, s) weights in bf16) T is found by bisection over the fp32 numbers.
+// A lane that meets none of this (equal candidates of a degenerate group) sends its
+// wavefront through the scan for that round.
 // The first two levels of the search have their thresholds in registers, the others read them from a lane-private LDS
-// column, in ascending order (the number of thresholds passed so far is the address); a second column holds, per sorted position, a word with byte j = 0x3f where the code has bit
-// j: moved to the top of the high half of a double it is 2^-15, the factor with which the weight enters plane j's sum (the
-// sums are kept times 2^-15: every product and rounding is the one without the factor).  Codes are counted in a third.
-// Per weight and round 11 vector instructions at q = 2 and 25 at q = 4, instead of 27 and about 110 for the scan.
-// 4096 x 4096, G = 128, ten rounds: q = 1 / 2 / 3 / 4  84 / 154 / 274 / 493 us with the scan, 54 / 97 / 133 / 185 us now;
-// G = 32, where the work per group and round (sort, thresholds, elimination) is as long as the weights' own:
-// 76 / 154 / 291 / 520 -> 60 / 124 / 177 / 290 us; G = 256, weights from the L2: 171 / 689 / 829 / 950 -> 128 / 161 / 206 / 261 us.
-// Of launches too small to fill the chip only q = 2, G = 32 does not gain: 512 x 512 22.0 us with the scan, 23.1 now.
+// column, in ascending order (the number of thresholds passed so far is the address); a second column holds, per sorted
+// position, a word with byte j = 0x3f where the code has bit j: moved to the top of the high half of a double it is 2^-15,
+// the factor with which the weight enters plane j's sum (the sums are kept times 2^-15: every product and rounding is the
+// one without the factor).  Codes are counted in a third.
+// Per weight and round 11 vector instructions at q = 2 and 25 at q = 4, instead of 27 and about 110 for a scan with counts.
+// 4096 x 4096, ten rounds, q = 1 / 2 / 3 / 4, us, all rounds by scan -> search, by the weights' distribution:
+//   G = 128  fp32 normals         77 / 146 / 266 / 491 -> 50 / 89 / 129 / 181
+//            rounded to bf16      77 / 146 / 266 / 491 -> 52 / 91 / 131 / 182
+//   G = 32   fp32 normals         73 / 142 / 270 / 491 -> 50 / 106 / 163 / 272
+//   G = 256  (from the L2)       166 / 686 / 829 / 949 -> 127 / 155 / 201 / 255
 template <int Q, int G>
-__global__ void __launch_bounds__(256, Q == 4 && G == 32 ? 3 : 2)
+__global__ void __launch_bounds__(256, quantize_waves(Q, G))
 hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_t *__restrict__ codes,
                     uint16_t *__restrict__ scales, uint16_t *__restrict__ zeros, float *__restrict__ group_err)
 {
-    constexpr int NC = 1 << Q, P = Q + 1;
+    constexpr int NC = 1 << Q, P = Q + 1, QUARTER = NC > 2 ? NC / 4 : 1;
     // few candidates: everything in registers.  At q = 2 the tables in LDS are 5 % faster on large matrices (G = 128 97 us
     // against 100), but with groups of 32 a small launch waits for them in every round (512 x 512: 25.6 us against 23.1)
     constexpr bool SMALL = Q == 1 || (Q == 2 && G == 32);
     __shared__ uint32_t lds[SMALL ? 1 : 4 * 3 * NC * 64];
-    const int n = (int)(blockIdx.x * 256 + threadIdx.x);
+    const unsigned n = blockIdx.x * 256 + threadIdx.x;
     const int gi = (int)blockIdx.y;
-    if (n >= N) return;
+    if (n >= (unsigned)N) return;
     const int ngroups = K / G;
-    const float *w0 = W + (size_t)gi * G * N + n;
-    uint8_t *c0 = codes + (size_t)gi * G * N + n;
+    // the group's rows (at most 2^30 bytes: N <= 2^20) through descriptors: row i is a scalar offset and the lane's column a
+    // vector one that never changes, where 64-bit addresses would take two vector registers per access in flight
+    const __amdgpu_buffer_rsrc_t w_rows = __builtin_amdgcn_make_buffer_rsrc((void *)(W + (size_t)gi * G * N), 0, G * N * 4, 0x00020000);
+    const __amdgpu_buffer_rsrc_t c_rows = __builtin_amdgcn_make_buffer_rsrc(codes + (size_t)gi * G * N, 0, G * N, 0x00020000);
+    auto load_row = [&](int offset) -> float { return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(w_rows, (int)(n * 4), offset, 0)); };
+    // as many rows as dst takes from row i on; the offset is a running sum (one scalar instruction a row)
+    auto load_rows = [&](auto &dst, int i, int stride) {
+        int offset = i * stride * 4;
+#pragma unroll
+        for (int u = 0; u < (int)(sizeof(dst) / sizeof(dst[0])); ++u) {
+            dst[u] = load_row(offset);
+            offset += stride * 4;
+        }
+    };
     // this lane's columns, one word every 64: thresholds in order | plane words by sorted position | counts.  The
     // second and third also hold the candidate values (fp64, by code) while the thresholds are made.
     uint32_t *const tree = lds + (SMALL ? 0 : (threadIdx.x >> 6) * (3 * NC * 64) + (threadIdx.x & 63));
@@ -113,8 +136,7 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
     float lof, hif;   // Alg. 1 steps 2-3 (min / max are exact in fp32)
     double rw = 0.0;  // sum of the weights, in order
     if constexpr (RESIDENT) {
-#pragma unroll
-        for (int i = 0; i < G; ++i) wv[i] = w0[(size_t)i * N];
+        load_rows(wv, 0, N);
         lof = hif = wv[0];
 #pragma unroll
         for (int i = 1; i < G; ++i) {
@@ -124,11 +146,11 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
 #pragma unroll
         for (int i = 0; i < G; ++i) rw += (double)wv[i];
     } else {
-        lof = hif = w0[0];
+        lof = hif = load_row(0);
         rw = (double)lof;
 #pragma unroll 8
         for (int i = 1; i < G; ++i) {
-            const float v = w0[(size_t)i * N];
+            const float v = load_row(i * N * 4);
             lof = v < lof ? v : lof;
             hif = v > hif ? v : hif;
             rw += (double)v;
@@ -141,111 +163,193 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
             asm volatile("" : "+v"(wv[i]));
             return wv[i];
         } else {
-            return w0[(size_t)i * N];
+            return load_row(i * N * 4);
         }
     };
     const double lo = (double)lof, hi = (double)hif;
     const double delta = (hi - lo) / (double)(NC - 1);
+    const float largest = fmaxf(fabsf(lof), fabsf(hif));
     double theta[P];   // theta[0] = z, theta[1 + j] = s_j
     theta[0] = lo;
 #pragma unroll
     for (int j = 0; j < Q; ++j) theta[1 + j] = delta * (double)(1 << j);
 
-    // one iteration of Alg. 1; the last one also stores the codes (a separate instantiation, so that
-    // the G store addresses are not kept in registers across the other iterations)
+    // one iteration of Alg. 1; the last one also stores the codes (a separate instantiation: a test per weight costs more)
     auto iteration = [&](auto last_c) {
         constexpr bool last = decltype(last_c)::value;
+        int stride = N;   // of rows; an opaque copy: the multiples of N that the first loads took are not kept for later
+        asm volatile("" : "+s"(stride));
         const double z = theta[0];
-        double S = fmax(fabs(lo), fabs(hi)) + fabs(z);
+        double S = (double)largest + fabs(z);
 #pragma unroll
         for (int j = 0; j < Q; ++j) S += fabs(theta[1 + j]);
-        const double gap_min = S * 0x1p-40, band = S * 0x1p-45;
+        const double gap_min = S > 0.0 ? S * 0x1p-40 : 1.0, band = fmax(S * 0x1p-45, 0x1p-149);   // (all zero: equal candidates)
 
-        // candidate values V_c = sum_j s_j bit_j(c)   (step 7), sorted by the leading bits of their fp32 rounding with
-        // the code in the last q bits (an order that is not the fp64 one shows as a gap below gap_min)
         uint32_t key[NC];
-        double sorted[SMALL ? NC : 1];   // SMALL: sorted as they are, with their codes as keys
-        unrolled<NC>([&](auto cc) {
-            constexpr int c = decltype(cc)::value;
-            double v = 0.0;
+        float top[3];   // the thresholds at the quarters (q = 1: the only one); the others are in LDS
+        bool scan;
+        {
+            // candidate values V_c = sum_j s_j bit_j(c)   (step 7), sorted by the leading bits of their fp32 rounding with
+            // the code in the last q bits (an order that is not the fp64 one shows as a gap below gap_min)
+            double sorted[SMALL ? NC : 1];   // SMALL: sorted as they are, with their codes as keys
+            unrolled<NC>([&](auto cc) {
+                constexpr int c = decltype(cc)::value;
+                double v = 0.0;
 #pragma unroll
-            for (int j = 0; j < Q; ++j) v += theta[1 + j] * (double)((c >> j) & 1);
+                for (int j = 0; j < Q; ++j) v += theta[1 + j] * (double)((c >> j) & 1);
+                if constexpr (SMALL) {
+                    sorted[c] = v;
+                    key[c] = (uint32_t)c;
+                } else {
+                    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+                    plane[(2 * c) * 64] = (uint32_t)b;
+                    plane[(2 * c + 1) * 64] = (uint32_t)(b >> 32);
+                    const uint32_t u = __builtin_bit_cast(uint32_t, (float)v);
+                    key[c] = ((u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u)) & ~(uint32_t)(NC - 1)) | (uint32_t)c;
+                }
+            });
             if constexpr (SMALL) {
-                sorted[c] = v;
-                key[c] = (uint32_t)c;
+                auto order = [&](int a, int b) {
+                    const bool swap = sorted[b] < sorted[a];
+                    const double va = sorted[a], vb = sorted[b];
+                    const uint32_t ca = key[a], cb = key[b];
+                    sorted[a] = swap ? vb : va;
+                    sorted[b] = swap ? va : vb;
+                    key[a] = swap ? cb : ca;
+                    key[b] = swap ? ca : cb;
+                };
+                if constexpr (NC == 2) {
+                    order(0, 1);
+                } else {
+                    order(0, 1);
+                    order(2, 3);
+                    order(0, 2);
+                    order(1, 3);
+                    order(1, 2);
+                }
             } else {
-                const uint64_t b = __builtin_bit_cast(uint64_t, v);
-                plane[(2 * c) * 64] = (uint32_t)b;
-                plane[(2 * c + 1) * 64] = (uint32_t)(b >> 32);
-                const uint32_t u = __builtin_bit_cast(uint32_t, (float)v);
-                key[c] = ((u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u)) & ~(uint32_t)(NC - 1)) | (uint32_t)c;
+                sort_keys<NC>(key);
             }
-        });
-        if constexpr (SMALL) {
-            auto order = [&](int a, int b) {
-                const bool swap = sorted[b] < sorted[a];
-                const double va = sorted[a], vb = sorted[b];
-                const uint32_t ca = key[a], cb = key[b];
-                sorted[a] = swap ? vb : va;
-                sorted[b] = swap ? va : vb;
-                key[a] = swap ? cb : ca;
-                key[b] = swap ? ca : cb;
+            auto value_of = [&](uint32_t at) -> double { return __builtin_bit_cast(double, ((uint64_t)plane[at + 64] << 32) | plane[at]); };
+            auto value_at = [&](int i) -> double {   // of sorted position i
+                if constexpr (SMALL) return sorted[i];
+                else return value_of((key[i] & (NC - 1)) * 128);
             };
-            if constexpr (NC == 2) {
-                order(0, 1);
-            } else {
-                order(0, 1);
-                order(2, 3);
-                order(0, 2);
-                order(1, 3);
-                order(1, 2);
-            }
-        } else {
-            sort_keys<NC>(key);
-        }
-        auto value_at = [&](int i) -> double {   // of sorted position i
-            if constexpr (SMALL) {
-                return sorted[i];
-            } else {
-                const uint32_t at = (key[i] & (NC - 1)) * 128;
-                return __builtin_bit_cast(double, ((uint64_t)plane[at + 64] << 32) | plane[at]);
-            }
-        };
-        bool good = true;
-        float top[3];   // the thresholds at the quarters (q = 1: the only one)
-        double va = value_at(0);
-        unrolled<NC - 1>([&](auto ii) {
-            constexpr int i = decltype(ii)::value + 1;
-            const uint32_t ca = key[i - 1] & (NC - 1), cb = key[i] & (NC - 1);
-            const double vb = value_at(i);
-            good = good && vb - va >= gap_min;
-            const double m = 0.5 * (va + vb) + z;
-            const float t = (float)m;
-            const double off = (double)t - m;
-            bool upper = off > 0.0;   // the upper neighbour wins at t
-            const uint32_t tb = __builtin_bit_cast(uint32_t, t);
-            const uint32_t away = (int32_t)tb < 0 ? ~0u : 1u;   // one fp32 step up (away: in bits)
-            const float next = __builtin_bit_cast(float, tb + away);
-            const bool near = fabs(off) <= band;
-            good = good && t != 0.f;
-            if (__any(near)) {   // in the first round mostly: the middle of the grid is an fp32 number
-                const float prev = __builtin_bit_cast(float, tb - away);
+            // The threshold between two neighbours (candidate values below and above; tie: the upper one's code is the smaller)
+            // whose midpoint is so close to zero that fp32 numbers are denser there than the distances are exact.  Whether
+            // the upper one wins, as the scan decides it, is still monotone in the weight, so the smallest fp32 number for
+            // which it does is found by bisection.  The decision changes at multiples of half an fp64 unit of the numbers
+            // involved: the midpoint plus small multiples of 2^-57 S are tried first, then the fp32 numbers beside the two
+            // that remain, and what is still open after that is halved to the end.  open: the lane has such a threshold.
+            auto bisect = [&](double below, double above, bool tie, bool open) -> float {
                 auto upper_wins = [&](float w) {
                     const double what = (double)w - z;
-                    const double da = fabs(what - va), db = fabs(what - vb);
-                    return db < da || (db == da && cb < ca);
+                    const double da = fabs(what - below), db = fabs(what - above);
+                    return db < da || (db == da && tie);
                 };
-                const bool at_t = upper_wins(t);
-                const bool beside = upper_wins(at_t ? prev : next);
-                good = good && (!near || at_t != beside);
-                upper = near ? at_t : upper;
+                auto to_key = [](float f) -> int32_t {   // fp32 numbers in ascending order
+                    const int32_t b = __builtin_bit_cast(int32_t, f);
+                    return b ^ (b >> 31 & 0x7fffffff);
+                };
+                auto at_key = [](int32_t k) -> float { return __builtin_bit_cast(float, k ^ (k >> 31 & 0x7fffffff)); };
+                const double mid = (double)(float)(0.5 * (below + above) + z);
+                const double unit = __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, S) & 0x7ff0000000000000u) * 0x1p-57;
+                auto multiple = [&](int k) -> float { return (float)(mid + (double)k * unit); };
+                int kl = -256, kh = 256;
+                const bool inside = !upper_wins(multiple(kl)) && upper_wins(multiple(kh));
+#pragma unroll 1
+                for (int s = 0; s < 9; ++s) {
+                    const int k = (kl + kh) >> 1;
+                    const bool up = upper_wins(multiple(k));
+                    kl = up ? kl : k;
+                    kh = up ? k : kh;
+                }
+                // (no such multiple: all numbers up to S, beyond which no weight lies)
+                int32_t below_k = to_key(inside ? multiple(kl) : -(float)S), above_k = to_key(inside ? multiple(kh) : (float)S);
+                above_k = above_k == 0 ? -1 : above_k;   // both zeros are the same weight
+                const bool first = upper_wins(at_key(below_k + 1)), second = upper_wins(at_key(above_k - 1));
+                const int32_t lower = below_k + 1;
+                below_k = first ? below_k : second ? lower : above_k - 1;
+                above_k = first ? lower : second ? above_k - 1 : above_k;
+#pragma unroll 1
+                for (int s = 0; s < 32 && __any(open && (uint32_t)above_k - (uint32_t)below_k > 1u); ++s) {
+                    const int32_t half = (below_k & above_k) + ((below_k ^ above_k) >> 1);
+                    const bool up = upper_wins(at_key(half));
+                    below_k = up ? below_k : half;
+                    above_k = up ? half : above_k;
+                }
+                return at_key(above_k);
+            };
+            bool good = true;
+            uint32_t hard = 0u;   // the threshold that is left to the bisection below: position, codes of the two sides
+            double va = value_at(0);
+            unrolled<NC - 1>([&](auto ii) {
+                constexpr int i = decltype(ii)::value + 1;
+                const uint32_t ca = key[i - 1] & (NC - 1), cb = key[i] & (NC - 1);
+                const double vb = value_at(i);
+                good = good && vb - va >= gap_min;
+                const double m = 0.5 * (va + vb) + z;
+                const float t = (float)m;
+                const double off = (double)t - m;
+                bool upper = off > 0.0;   // the upper neighbour wins at t
+                const uint32_t tb = __builtin_bit_cast(uint32_t, t);
+                const uint32_t away = (int32_t)tb < 0 ? ~0u : 1u;   // one fp32 step up (away: in bits)
+                const float next = __builtin_bit_cast(float, tb + away);
+                const bool near = fabs(off) <= band;
+                bool found = false;
+                float bisected = 0.f;
+                if (__any(near)) {   // in the first round mostly: the middle of the grid is an fp32 number
+                    const float prev = __builtin_bit_cast(float, tb - away);
+                    auto upper_wins = [&](float w) {
+                        const double what = (double)w - z;
+                        const double da = fabs(what - va), db = fabs(what - vb);
+                        return db < da || (db == da && cb < ca);
+                    };
+                    const bool at_t = upper_wins(t);
+                    const bool beside = upper_wins(at_t ? prev : next);
+                    upper = near ? at_t : upper;
+                    const bool open = near && (t == 0.f || at_t == beside);
+                    if (__builtin_expect(__any(open), 0)) {
+                        if constexpr (Q == 1) {
+                            bisected = bisect(va, vb, cb < ca, open);
+                            found = open;
+                        } else {
+                            good = good && !(open && hard);   // a second one
+                            hard = open ? (uint32_t)i | ca << 8 | cb << 16 : hard;
+                        }
+                    }
+                }
+                float T = upper ? t : next;
+                if constexpr (Q == 1) T = found ? bisected : T;
+                if constexpr (i % QUARTER == 0) top[i / QUARTER - 1] = T;
+                else tree[i * 64] = __builtin_bit_cast(uint32_t, T);
+                va = vb;
+            });
+            if constexpr (Q > 1) {
+                if (__builtin_expect(__any(hard != 0u), 0)) {
+                    const uint32_t at = hard & 0xffu, code_below = hard >> 8 & 0xffu, code_above = hard >> 16;
+                    double below, above;
+                    if constexpr (SMALL) {
+                        below = sorted[0];
+                        above = sorted[1];
+#pragma unroll
+                        for (int i = 2; i < NC; ++i) {
+                            below = at == (uint32_t)i ? sorted[i - 1] : below;
+                            above = at == (uint32_t)i ? sorted[i] : above;
+                        }
+                    } else {
+                        below = value_of(code_below * 128);
+                        above = value_of(code_above * 128);
+                    }
+                    const float T = bisect(below, above, code_above < code_below, hard != 0u);
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) top[k] = at == (uint32_t)((k + 1) * QUARTER) ? T : top[k];
+                    if constexpr (NC > 4)
+                        if (at) tree[at * 64] = __builtin_bit_cast(uint32_t, T);
+                }
             }
-            const float T = upper ? t : next;
-            if constexpr (i % (NC > 2 ? NC / 4 : 1) == 0) top[NC > 2 ? i / (NC / 4) - 1 : 0] = T;
-            else tree[i * 64] = __builtin_bit_cast(uint32_t, T);
-            va = vb;
-        });
-        const bool scan = __any(!good);
+            scan = __any(!good);
+        }
 
         // per sorted position (or per code, for the scan): the plane word; counts start at zero
         uint32_t words[SMALL ? NC : 1];
@@ -278,7 +382,7 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
                 uint32_t c = 0;
 #pragma unroll
                 for (int j = 0; j < Q; ++j) c |= ((word >> (8 * j)) & 1u) << j;
-                c0[(size_t)i * N] = (uint8_t)c;
+                __builtin_amdgcn_raw_buffer_store_b8((uint8_t)c, c_rows, (int)n, i * stride, 0);
             }
         };
         if (!scan && SMALL) {
@@ -302,15 +406,14 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
             } else {
                 constexpr int AHEAD = 32;   // weights come from the L2: the next 32 are requested while 32 are worked on
                 float nx[AHEAD];
-#pragma unroll
-                for (int u = 0; u < AHEAD; ++u) nx[u] = w0[(size_t)u * N];
+                load_rows(nx, 0, stride);
 #pragma unroll 1
                 for (int i = 0; i < G; i += AHEAD) {
                     float cur[AHEAD];
 #pragma unroll
                     for (int u = 0; u < AHEAD; ++u) cur[u] = nx[u];
-#pragma unroll
-                    for (int u = 0; u < AHEAD; ++u) nx[u] = w0[(size_t)min(i + AHEAD + u, G - 1) * N];
+                    if (i + AHEAD < G) load_rows(nx, i + AHEAD, stride);
+                    __builtin_amdgcn_sched_barrier(0);   // the loads go out first
 #pragma unroll
                     for (int u = 0; u < AHEAD; ++u) take(i + u, cur[u]);
                 }
@@ -319,7 +422,7 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
             if constexpr (!SMALL) {
             // Eight weights at a time, one level of the search for all of them before the next, and the sums of the
             // previous eight between the levels: an LDS read is used some thirty instructions after it was issued
-            // (with the weights of a group in registers there are two wavefronts on a SIMD to cover for each other).
+            // (with the weights of a group in registers there are two to five wavefronts on a SIMD to cover for each other).
             constexpr int B = 8;
             // LEN weights from src, the group's weights i0, i0 + 1, ..
             auto pass = [&](auto &src, auto len_c, int i0) {
@@ -338,14 +441,10 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
 #pragma unroll
                     for (int u = 0; u < B; ++u) {
                         const float w = src[i + u];
-                        if constexpr (Q >= 2) {
-                            const bool up = w >= top[1];
-                            const float T = up ? top[2] : top[0];
-                            const uint32_t half = up ? NC / 2 * 64u : 0u;
-                            at[u] = tree + half + (w >= T ? NC / 4 * 64u : 0u);
-                        } else {
-                            at[u] = tree + (w >= top[0] ? 64u : 0u);
-                        }
+                        const bool up = w >= top[1];
+                        const float T = up ? top[2] : top[0];
+                        const uint32_t half = up ? NC / 2 * 64u : 0u;
+                        at[u] = tree + half + (w >= T ? NC / 4 * 64u : 0u);
                     }
                     constexpr int levels = Q > 2 ? Q - 1 : 1;             // LDS reads in a row
                     constexpr int per = (B + levels - 1) / levels;        // previous weights summed up behind each
@@ -381,15 +480,14 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
                 // weights come from the L2: the next 32 are requested while 32 are worked on
                 constexpr int AHEAD = 32;
                 float nx[AHEAD];
-#pragma unroll
-                for (int u = 0; u < AHEAD; ++u) nx[u] = w0[(size_t)u * N];
+                load_rows(nx, 0, stride);
 #pragma unroll 1
                 for (int i = 0; i < G; i += AHEAD) {
                     float cur[AHEAD];
 #pragma unroll
                     for (int u = 0; u < AHEAD; ++u) cur[u] = nx[u];
-#pragma unroll
-                    for (int u = 0; u < AHEAD; ++u) nx[u] = w0[(size_t)min(i + AHEAD + u, G - 1) * N];
+                    if (i + AHEAD < G) load_rows(nx, i + AHEAD, stride);
+                    __builtin_amdgcn_sched_barrier(0);   // the loads go out first
                     pass(cur, std::integral_constant<int, AHEAD>{}, i);
                 }
             }
@@ -406,7 +504,7 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
             }
 #pragma unroll 1
             for (int i = 0; i < G; ++i) {
-                const float w = w0[(size_t)i * N];
+                const float w = load_row(i * stride * 4);
                 const double what = (double)w - z;
                 uint32_t best = 0;
                 double bd = fabs(what - V[0]);
@@ -577,7 +675,7 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
         double e = 0.0;
 #pragma unroll(RESIDENT ? G : 8)
         for (int i = 0; i < G; ++i) {
-            const int c = c0[(size_t)i * N];
+            const int c = __builtin_amdgcn_raw_buffer_load_b8(c_rows, (int)n, i * N, 0);
             double v = theta[0];
 #pragma unroll
             for (int j = 0; j < Q; ++j) v += theta[1 + j] * (double)((c >> j) & 1);
