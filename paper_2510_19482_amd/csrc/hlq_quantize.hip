@@ -82,7 +82,8 @@ constexpr int quantize_waves(int q, int G)
 //     the two distances of t and of that neighbour are compared as the scan compares them;
 //   - where both of them fall on one side (a midpoint at or near zero: every group with min = -max, i.e. 0.9 % of the groups
 //     and 43 % of the wavefronts for N(0, s) weights in bf16) T is found by bisection over the fp32 numbers.
-// A lane that meets none of this (equal candidates of a degenerate group) sends its
+// A group whose weights are all equal (padded or pruned columns) has equal candidates in every round; it takes code 0.
+// A lane that meets none of this (candidates that coincide up to rounding: groups of few distinct values) sends its
 // wavefront through the scan for that round.
 // The first two levels of the search have their thresholds in registers, the others read them from a lane-private LDS
 // column, in ascending order (the number of thresholds passed so far is the address); a second column holds, per sorted
@@ -93,6 +94,7 @@ constexpr int quantize_waves(int q, int G)
 // 4096 x 4096, ten rounds, q = 1 / 2 / 3 / 4, us, all rounds by scan -> search, by the weights' distribution:
 //   G = 128  fp32 normals         77 / 146 / 266 / 491 -> 50 / 89 / 129 / 181
 //            rounded to bf16      77 / 146 / 266 / 491 -> 52 / 91 / 131 / 182
+//            a zero column in 64  77 / 146 / 267 / 490 -> 51 / 90 / 131 / 184
 //   G = 32   fp32 normals         73 / 142 / 270 / 491 -> 50 / 106 / 163 / 272
 //   G = 256  (from the L2)       166 / 686 / 829 / 949 -> 127 / 155 / 201 / 255
 template <int Q, int G>
@@ -168,6 +170,7 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
     };
     const double lo = (double)lof, hi = (double)hif;
     const double delta = (hi - lo) / (double)(NC - 1);
+    const bool constant = lof == hif && rw - rw == 0.0;   // all weights equal (and no NaN among them)
     const float largest = fmaxf(fabsf(lof), fabsf(hif));
     double theta[P];   // theta[0] = z, theta[1 + j] = s_j
     theta[0] = lo;
@@ -183,7 +186,9 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
         double S = (double)largest + fabs(z);
 #pragma unroll
         for (int j = 0; j < Q; ++j) S += fabs(theta[1 + j]);
-        const double gap_min = S > 0.0 ? S * 0x1p-40 : 1.0, band = fmax(S * 0x1p-45, 0x1p-149);   // (all zero: equal candidates)
+        // a group whose weights are all equal has equal candidates in every round and takes code 0: its thresholds are NaN
+        const double gap_min = constant ? -1.0 : S * 0x1p-40, band = fmax(S * 0x1p-45, 0x1p-149);
+        const double zt = constant ? (double)__builtin_inff() : z;
 
         uint32_t key[NC];
         float top[3];   // the thresholds at the quarters (q = 1: the only one); the others are in LDS
@@ -288,7 +293,7 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
                 const uint32_t ca = key[i - 1] & (NC - 1), cb = key[i] & (NC - 1);
                 const double vb = value_at(i);
                 good = good && vb - va >= gap_min;
-                const double m = 0.5 * (va + vb) + z;
+                const double m = 0.5 * (va + vb) + zt;
                 const float t = (float)m;
                 const double off = (double)t - m;
                 bool upper = off > 0.0;   // the upper neighbour wins at t
