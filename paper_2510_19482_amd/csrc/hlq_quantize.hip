@@ -84,7 +84,7 @@ constexpr int quantize_waves(int q, int G)
 //     and 43 % of the wavefronts for N(0, s) weights in bf16) T is found by bisection over the fp32 numbers.
 // A group whose weights are all equal (padded or pruned columns) has equal candidates in every round; it takes code 0.
 // A lane that meets none of this (candidates that coincide up to rounding: groups of few distinct values) sends its
-// wavefront through the scan for that round.
+// wavefront through the scan for that round, and for the ones after it.
 // The first two levels of the search have their thresholds in registers, the others read them from a lane-private LDS
 // column, in ascending order (the number of thresholds passed so far is the address); a second column holds, per sorted
 // position, a word with byte j = 0x3f where the code has bit j: moved to the top of the high half of a double it is 2^-15,
@@ -95,7 +95,8 @@ constexpr int quantize_waves(int q, int G)
 //   G = 128  fp32 normals         77 / 146 / 266 / 491 -> 50 / 89 / 129 / 181
 //            rounded to bf16      77 / 146 / 266 / 491 -> 52 / 91 / 131 / 182
 //            a zero column in 64  77 / 146 / 267 / 490 -> 51 / 90 / 131 / 184
-//   G = 32   fp32 normals         73 / 142 / 270 / 491 -> 50 / 106 / 163 / 272
+//            -1, 0, 1 times 0.03  77 / 146 / 266 / 488 -> 52 / 132 / 220 / 383 (scan from the second or third round on)
+//   G = 32   fp32 normals         73 / 142 / 270 / 491 -> 50 / 106 / 163 / 272;  -1, 0, 1: 67 / 142 / 268 / 481 -> 58 / 149 / 233 / 435
 //   G = 256  (from the L2)       166 / 686 / 829 / 949 -> 127 / 155 / 201 / 255
 template <int Q, int G>
 __global__ void __launch_bounds__(256, quantize_waves(Q, G))
@@ -177,6 +178,11 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
 #pragma unroll
     for (int j = 0; j < Q; ++j) theta[1 + j] = delta * (double)(1 << j);
 
+    // Rounds in a row that needed the scan: a wavefront stays with it after STAY of them (data of few distinct values needs
+    // it in every round: without this -1, 0, 1 at q = 2, G = 32 takes 226 us and not 149).  At q = 4 a single one can
+    // be a coincidence, candidates closer than the keys' 19 bits tell apart.
+    constexpr int STAY = Q == 4 ? 2 : 1;
+    int scans = 0;
     // one iteration of Alg. 1; the last one also stores the codes (a separate instantiation: a test per weight costs more)
     auto iteration = [&](auto last_c) {
         constexpr bool last = decltype(last_c)::value;
@@ -192,8 +198,11 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
 
         uint32_t key[NC];
         float top[3];   // the thresholds at the quarters (q = 1: the only one); the others are in LDS
-        bool scan;
-        {
+        // through readfirstlane, here and below: the optimiser takes the choice for a scalar one (otherwise it keeps the
+        // registers of both ways at once) and makes no copy of the round for each value
+        scans = __builtin_amdgcn_readfirstlane(scans);
+        int chosen = scans >= STAY;
+        if (chosen == 0) {
             // candidate values V_c = sum_j s_j bit_j(c)   (step 7), sorted by the leading bits of their fp32 rounding with
             // the code in the last q bits (an order that is not the fp64 one shows as a gap below gap_min)
             double sorted[SMALL ? NC : 1];   // SMALL: sorted as they are, with their codes as keys
@@ -353,14 +362,20 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
                         if (at) tree[at * 64] = __builtin_bit_cast(uint32_t, T);
                 }
             }
-            scan = __any(!good);
+            chosen = __any(!good) ? 1 : 0;
+        } else {
+#pragma unroll
+            for (int i = 0; i < NC; ++i) key[i] = (uint32_t)i;   // (not used)
         }
+        chosen = __builtin_amdgcn_readfirstlane(chosen);
+        const bool scan = chosen != 0;
+        scans = scan ? scans + 1 : 0;
 
-        // per sorted position (or per code, for the scan): the plane word; counts start at zero
+        // per sorted position: the plane word; counts start at zero
         uint32_t words[SMALL ? NC : 1];
 #pragma unroll
         for (int i = 0; i < NC; ++i) {
-            const uint32_t c = scan ? (uint32_t)i : key[i] & (NC - 1);
+            const uint32_t c = key[i] & (NC - 1);
             const uint32_t ones = __umul24(c, 0x204081u) & 0x01010101u;   // bit j of the code in byte j
             if constexpr (SMALL) {
                 words[i] = (ones << 6) - ones;
@@ -390,7 +405,7 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
                 __builtin_amdgcn_raw_buffer_store_b8((uint8_t)c, c_rows, (int)n, i * stride, 0);
             }
         };
-        if (!scan && SMALL) {
+        if (__builtin_expect(!scan, 1) && SMALL) {
             // a comparison per threshold; its outcome picks the plane word and is counted
             auto take = [&](int i, float w) {
                 uint32_t word = words[0];
@@ -423,7 +438,7 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
                     for (int u = 0; u < AHEAD; ++u) take(i + u, cur[u]);
                 }
             }
-        } else if (!scan) {
+        } else if (__builtin_expect(!scan, 1)) {
             if constexpr (!SMALL) {
             // Eight weights at a time, one level of the search for all of them before the next, and the sums of the
             // previous eight between the levels: an LDS read is used some thirty instructions after it was issued
@@ -498,7 +513,8 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
             }
             }
         } else {
-            // the scan of all candidates, weights re-read (rare)
+            // the scan of all candidates
+            uint32_t counted = 0u;
             double V[NC];
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
@@ -507,9 +523,7 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
                 for (int j = 0; j < Q; ++j) v += theta[1 + j] * (double)((c >> j) & 1);
                 V[c] = v;
             }
-#pragma unroll 1
-            for (int i = 0; i < G; ++i) {
-                const float w = load_row(i * stride * 4);
+            auto take = [&](int i, float w) {
                 const double what = (double)w - z;
                 uint32_t best = 0;
                 double bd = fabs(what - V[0]);
@@ -519,17 +533,45 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
                     best = d < bd ? (uint32_t)c : best;
                     bd = __builtin_fmin(bd, d);
                 }
+                const uint32_t ones = __umul24(best, 0x204081u) & 0x01010101u;
+                fold(i, w, (ones << 6) - ones);
                 if constexpr (SMALL) {
-                    uint32_t word = words[0];
-#pragma unroll
-                    for (int c = 1; c < NC; ++c) word = best == (uint32_t)c ? words[c] : word;
-                    fold(i, w, word);
-#pragma unroll
-                    for (int c = 0; c < NC; ++c) cnt[c] += best == (uint32_t)c ? 1 : 0;
+                    counted += Q == 1 ? best : 1u << 8 * best;   // q = 2: four counts of at most 32
                 } else {
-                    fold(i, w, plane[best * 64]);
                     __hip_atomic_fetch_add(&count[best * 64], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
                 }
+            };
+            // from the registers; at q = 4, G = 128 that would be 9000 instructions a round, and the weights come from memory,
+            // requested eight ahead
+            if constexpr (RESIDENT && G * NC <= 1024) {
+#pragma unroll
+                for (int i = 0; i < G; ++i) {
+                    float w;   // a copy: the register itself is the same one whichever way the round went
+                    asm volatile("" : "=v"(w) : "0"(wv[i]));
+                    take(i, w);
+                    if ((i & 3) == 3) __builtin_amdgcn_sched_barrier(0);   // not many weights converted ahead (registers)
+                }
+            } else {
+                constexpr int AHEAD = RESIDENT ? 8 : 32;
+                float nx[AHEAD];
+                load_rows(nx, 0, stride);
+#pragma unroll 1
+                for (int i = 0; i < G; i += AHEAD) {
+                    float cur[AHEAD];
+#pragma unroll
+                    for (int u = 0; u < AHEAD; ++u) cur[u] = nx[u];
+                    if (i + AHEAD < G) load_rows(nx, i + AHEAD, stride);
+                    __builtin_amdgcn_sched_barrier(0);   // the loads go out first
+#pragma unroll
+                    for (int u = 0; u < AHEAD; ++u) {
+                        take(i + u, cur[u]);
+                        if ((u & 3) == 3) __builtin_amdgcn_sched_barrier(0);   // not many weights converted ahead (registers)
+                    }
+                }
+            }
+            if constexpr (SMALL) {
+#pragma unroll
+                for (int c = 0; c < NC; ++c) cnt[c] = Q == 1 ? (c ? (int)counted : G - (int)counted) : (int)(counted >> 8 * c & 0xffu);
             }
         }
 #pragma unroll

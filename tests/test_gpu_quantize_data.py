@@ -22,6 +22,10 @@ def weights(kind, K, N):
     if kind == "dead":
         W[:, 7::64] = 0.0
         W[:, 9::64] = 0.013
+    if kind == "ternary":
+        W = (rng.integers(-1, 2, (K, N)) * 0.03).astype(np.float32)
+    if kind == "steps":
+        W = (rng.integers(-8, 8, (K, N)) * 0.003).astype(np.float32)
     return W
 
 
@@ -40,7 +44,7 @@ def microseconds(q, G, W):
 
 
 # every format once; 1 round (the starting parameters are the same numbers on both sides, so are exact ties), then 10
-@pytest.mark.parametrize("kind,rounds", [("bf16", 1), ("bf16", 10), ("dead", 1), ("dead", 10)])
+@pytest.mark.parametrize("kind,rounds", [("bf16", 1), ("bf16", 10), ("dead", 1), ("dead", 10), ("ternary", 1), ("steps", 1)])
 @pytest.mark.parametrize("q", [1, 2, 3, 4])
 @pytest.mark.parametrize("G", [32, 64, 128, 256])
 def test_codes(kind, rounds, q, G):
@@ -50,9 +54,10 @@ def test_codes(kind, rounds, q, G):
 
 
 # bound: what was measured, and a quarter more; with a scan of all candidates from memory for these the ratios were
-# 1.7, 1.3, 1.4, 5.5 and 2.2
+# 1.7, 1.3, 1.4, 5.5, 2.2, 5.5 and 3.8
 @pytest.mark.parametrize("kind,q,G,bound", [("bf16", 1, 128, 1.3), ("bf16", 2, 64, 1.3), ("bf16", 1, 256, 1.25),
-                                           ("dead", 2, 128, 1.25), ("dead", 4, 32, 1.25)])
+                                           ("dead", 2, 128, 1.25), ("dead", 4, 32, 1.25), ("ternary", 2, 128, 2.0),
+                                           ("ternary", 4, 128, 2.6)])
 def test_time_does_not_depend_on_the_data(kind, q, G, bound):
     plain, special = (microseconds(q, G, dev(weights(k, 4096, 4096))) for k in ("plain", kind))
     print(kind, q, G, f"{special:.1f} us, fp32 normals {plain:.1f} us", flush=True)
