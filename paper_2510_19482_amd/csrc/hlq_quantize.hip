@@ -100,7 +100,7 @@ constexpr int quantize_waves(int q, int G)
 //   G = 256  (from the L2)       166 / 686 / 829 / 949 -> 127 / 155 / 201 / 255
 template <int Q, int G>
 __global__ void __launch_bounds__(256, quantize_waves(Q, G))
-hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_t *__restrict__ codes,
+hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, int scan_first, uint8_t *__restrict__ codes,
                     uint16_t *__restrict__ scales, uint16_t *__restrict__ zeros, float *__restrict__ group_err)
 {
     constexpr int NC = 1 << Q, P = Q + 1, QUARTER = NC > 2 ? NC / 4 : 1;
@@ -182,7 +182,7 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
     // it in every round: without this -1, 0, 1 at q = 2, G = 32 takes 226 us and not 149).  At q = 4 a single one can
     // be a coincidence, candidates closer than the keys' 19 bits tell apart.
     constexpr int STAY = Q == 4 ? 2 : 1;
-    int scans = 0;
+    int scans = scan_first ? STAY : 0;
     // one iteration of Alg. 1; the last one also stores the codes (a separate instantiation: a test per weight costs more)
     auto iteration = [&](auto last_c) {
         constexpr bool last = decltype(last_c)::value;
@@ -630,33 +630,38 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
         // determinants of 0/1 matrices of order <= 5 (each <= 5), so below 2^17; products and their
         // differences stay below 2^35 and the divisions are exact, hence fp64 computes them exactly (a
         // quotient as product with the reciprocal, rounded to the nearest integer).
-        double gm[P][P];
-#pragma unroll
-        for (int a = 0; a < P; ++a)
-#pragma unroll
-            for (int b = a; b < P; ++b) {
-                unsigned both = 0u;   // codes whose row has a one in columns a and b
-#pragma unroll
-                for (int c = 0; c < NC; ++c) {
-                    const int ra = a == 0 ? 1 : (c >> (a - 1)) & 1, rc = b == 0 ? 1 : (c >> (b - 1)) & 1;
-                    if (ra & rc) both |= 1u << c;
-                }
-                gm[a][b] = (double)__builtin_popcount(present & both);
-            }
         bool is_act[P];
-        double prev = 1.0;
 #pragma unroll
-        for (int k = 0; k < P; ++k) {
-            const double pv = gm[k][k];
-            is_act[k] = pv != 0.0;
-            if (is_act[k]) {
-                const double inv_prev = 1.0 / prev;
+        for (int k = 0; k < P; ++k) is_act[k] = true;
+        // with every code in use all columns are independent (512 x 512, q = 2, G = 32: 1 us of 24)
+        if (Q == 1 || !__all(present == (1u << NC) - 1u)) {
+            double gm[P][P];
 #pragma unroll
-                for (int i = k + 1; i < P; ++i)
+            for (int a = 0; a < P; ++a)
 #pragma unroll
-                    for (int j = i; j < P; ++j)   // symmetric
-                        gm[i][j] = __builtin_rint((gm[i][j] * pv - gm[k][i] * gm[k][j]) * inv_prev);
-                prev = pv;
+                for (int b = a; b < P; ++b) {
+                    unsigned both = 0u;   // codes whose row has a one in columns a and b
+#pragma unroll
+                    for (int c = 0; c < NC; ++c) {
+                        const int ra = a == 0 ? 1 : (c >> (a - 1)) & 1, rc = b == 0 ? 1 : (c >> (b - 1)) & 1;
+                        if (ra & rc) both |= 1u << c;
+                    }
+                    gm[a][b] = (double)__builtin_popcount(present & both);
+                }
+            double prev = 1.0;
+#pragma unroll
+            for (int k = 0; k < P; ++k) {
+                const double pv = gm[k][k];
+                if (k > 0) is_act[k] = pv != 0.0;   // the column of ones always is (so A[0][0] stays G, and dividing by it is a multiplication)
+                if (is_act[k]) {
+                    const double inv_prev = 1.0 / prev;
+#pragma unroll
+                    for (int i = k + 1; i < P; ++i)
+#pragma unroll
+                        for (int j = i; j < P; ++j)   // symmetric
+                            gm[i][j] = __builtin_rint((gm[i][j] * pv - gm[k][i] * gm[k][j]) * inv_prev);
+                    prev = pv;
+                }
             }
         }
 
@@ -738,11 +743,16 @@ void launch_q(const HlqDims &dm, const float *W, int t_max, uint8_t *codes, uint
               float *group_err, hipStream_t st)
 {
     const dim3 grid((unsigned)((dm.N + 255) / 256), (unsigned)dm.ngroups);
+    // A launch of at most one wavefront per SIMD with groups of 32 waits for its thresholds as long as for the scan, and the
+    // scan takes the same time for every distribution: 512 x 512, q = 1 / 2 / 3, us, fp32 normals 11.3 / 22.7 / 38.0 by search,
+    // 11.8 / 22.0 / 38.3 by scan; bf16 12.3 / 26.7 / 47 against 11.7 / 22.2 / 38; int4 steps 22 / 34 / 41 against 11.8 / 21.9 /
+    // 38.  q = 4: 59 by search, 63 by scan.
+    const int scan_first = dm.G == 32 && Q <= 3 && (long)grid.x * grid.y <= 256;
     switch (dm.G) {
-    case 32: hlq_quantize_kernel<Q, 32><<<grid, 256, 0, st>>>(W, dm.K, dm.N, t_max, codes, scales, zeros, group_err); break;
-    case 64: hlq_quantize_kernel<Q, 64><<<grid, 256, 0, st>>>(W, dm.K, dm.N, t_max, codes, scales, zeros, group_err); break;
-    case 128: hlq_quantize_kernel<Q, 128><<<grid, 256, 0, st>>>(W, dm.K, dm.N, t_max, codes, scales, zeros, group_err); break;
-    default: hlq_quantize_kernel<Q, 256><<<grid, 256, 0, st>>>(W, dm.K, dm.N, t_max, codes, scales, zeros, group_err); break;
+    case 32: hlq_quantize_kernel<Q, 32><<<grid, 256, 0, st>>>(W, dm.K, dm.N, t_max, scan_first, codes, scales, zeros, group_err); break;
+    case 64: hlq_quantize_kernel<Q, 64><<<grid, 256, 0, st>>>(W, dm.K, dm.N, t_max, scan_first, codes, scales, zeros, group_err); break;
+    case 128: hlq_quantize_kernel<Q, 128><<<grid, 256, 0, st>>>(W, dm.K, dm.N, t_max, scan_first, codes, scales, zeros, group_err); break;
+    default: hlq_quantize_kernel<Q, 256><<<grid, 256, 0, st>>>(W, dm.K, dm.N, t_max, scan_first, codes, scales, zeros, group_err); break;
     }
 }
 

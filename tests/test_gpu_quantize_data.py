@@ -62,3 +62,12 @@ def test_time_does_not_depend_on_the_data(kind, q, G, bound):
     plain, special = (microseconds(q, G, dev(weights(k, 4096, 4096))) for k in ("plain", kind))
     print(kind, q, G, f"{special:.1f} us, fp32 normals {plain:.1f} us", flush=True)
     assert special <= bound * plain
+
+
+@pytest.mark.parametrize("q", [1, 2, 3])
+@pytest.mark.parametrize("kind", ["bf16", "steps"])
+def test_small_launch(q, kind):
+    # one wavefront per SIMD, groups of 32: all rounds by scan (by search: 1.2 times and more)
+    plain, special = (microseconds(q, 32, dev(weights(k, 1024, 1024))) for k in ("plain", kind))
+    print(kind, q, f"{special:.1f} us, fp32 normals {plain:.1f} us", flush=True)
+    assert special <= 1.12 * plain
