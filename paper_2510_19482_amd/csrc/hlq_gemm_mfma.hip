@@ -409,6 +409,15 @@ static long reduce_problem(GemmRedProb &r, const float *part, void *Y, long ldy,
     return (long)(((size_t)M * N + RED_OUT - 1) / RED_OUT);
 }
 
+// Workgroups of that launch: those of the sums, and enough that the call is computed again by as many wavefronts as behind
+// a tiled launch without split K (a group may split nothing but a narrow problem).  The surplus ones look at the flag and leave.
+static unsigned reduce_blocks(long sums, const HlqSafeProbs &again)
+{
+    const long redo = (again.items_total + RED_LANES / 64 - 1) / (RED_LANES / 64), most = HLQ_SAFE_WAVES / (RED_LANES / 64);
+    const long want = redo < most ? redo : most;
+    return (unsigned)(sums > want ? sums : want);
+}
+
 struct MfmaPlan {
     int MW, cps, nslices, rowblocks;
 };
@@ -550,7 +559,7 @@ hlq_status hlq_launch_gemm_mfma(const HlqDims &dm, const void *packed, const uin
         if (blocks > 0x7fffffffL / (RED_LANES / 64)) return HLQ_ERR_UNSUPPORTED;
         for (int i = 1; i < HLQ_MAX_BATCH; ++i) rp.p[i] = rp.p[0];
         const int none = 0x7fffffff;
-        hlq_gemm_mfma_group_reduce_kernel<<<(unsigned)blocks, RED_LANES, 0, st>>>((int4v){0, none, none, none}, (int4v){none, none, none, none},
+        hlq_gemm_mfma_group_reduce_kernel<<<reduce_blocks(blocks, again), RED_LANES, 0, st>>>((int4v){0, none, none, none}, (int4v){none, none, none, none},
                                                                                  (int)M, out_f32, hlq_ws_range_flag(ws), rp, again);
         return hlq_hip_status(hipGetLastError());
     }
@@ -683,7 +692,7 @@ hlq_status hlq_launch_gemm_mfma_batch(int count, const HlqGemvItem *items, int64
         HlqSafeProbs again;
         s = hlq_safe_problems(count, items, M, again);
         if (s != HLQ_OK) return s;
-        hlq_gemm_mfma_group_reduce_kernel<<<(unsigned)rblk, RED_LANES, 0, st>>>(rlo, rhi, (int)M, out_f32, hlq_ws_range_flag(ws), rp, again);
+        hlq_gemm_mfma_group_reduce_kernel<<<reduce_blocks(rblk, again), RED_LANES, 0, st>>>(rlo, rhi, (int)M, out_f32, hlq_ws_range_flag(ws), rp, again);
         return hlq_hip_status(hipGetLastError());
     }
     s = hlq_launch_gemm_safe(count, items, M, out, ws, st);

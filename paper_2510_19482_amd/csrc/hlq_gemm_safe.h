@@ -5,6 +5,7 @@
 #include "hlq_internal.h"
 
 constexpr int SAFE_ROWS = 8;   // activation rows per work item
+#define HLQ_SAFE_WAVES 512      // wavefronts of a launch that does nothing else: each of them costs the normal case a look at the flag
 
 __device__ __forceinline__ float half_bits_to_float(uint16_t h) { return (float)__builtin_bit_cast(_Float16, h); }
 

@@ -29,7 +29,7 @@ hlq_status hlq_launch_gemm_safe(int count, const HlqGemvItem *items, int64_t M, 
     const hlq_status s = hlq_safe_problems(count, items, M, pr);
     if (s != HLQ_OK) return s;
     // few workgroups: in the normal case all of them only look at the flag and leave, and that costs per workgroup
-    const unsigned grid = (unsigned)(pr.items_total < 512 ? pr.items_total : 512);
+    const unsigned grid = (unsigned)(pr.items_total < HLQ_SAFE_WAVES ? pr.items_total : HLQ_SAFE_WAVES);
     hlq_gemm_safe_kernel<<<grid, 64, 0, st>>>(pr, (int)M, out == HLQ_OUT_F32, hlq_ws_range_flag(ws), hlq_ws_range_flag(ws) + 1);
     return HLQ_OK;
 }
