@@ -31,25 +31,30 @@ __device__ __forceinline__ void hlq_safe_recompute(const HlqSafeProbs &pr, const
         for (int r = 0; r < SAFE_ROWS; ++r) acc[r] = 0.f;
         for (int c = 0; c < P.nchunks; ++c) {
             const char *rec = tile_base + hlq_rec_in_tile(tw, c, q, G);
-            uint32_t w[4][4];
-            for (int j = 0; j < q; ++j) {
-                const uint4 v = ((const uint4 *)rec)[j * tw + lane_c];
-                w[j][0] = v.x; w[j][1] = v.y; w[j][2] = v.z; w[j][3] = v.w;
-            }
             // scales of the chunk's quant segments; a 256-wide group keeps them in the record of its even chunk
             const int cm = G > 128 ? (c & ~1) : c;
             const uint16_t *mp = (const uint16_t *)(tile_base + hlq_rec_in_tile(tw, cm, q, G) + (size_t)tw * q * 16);
-            const int gs = G < 128 ? G : 128;
-            for (int sg = 0; sg < 128 / gs; ++sg) {
-                float s[4] = {0.f, 0.f, 0.f, 0.f};
-                for (int j = 0; j < q; ++j) s[j] = half_bits_to_float(mp[(sg * (q + 1) + j) * tw + lane_c]);
-                const float z = half_bits_to_float(mp[(sg * (q + 1) + q) * tw + lane_c]);
-                for (int k0 = sg * gs; k0 < (sg + 1) * gs; ++k0) {
-                    const int bit = hlq_bit_pos(k0 & 31), d = k0 >> 5;
+            float s[4] = {0.f, 0.f, 0.f, 0.f}, z = 0.f;
+            // word by word (32 k), all indices known at compile time: nothing of this is in scratch memory, which the launch
+            // that also adds the partial sums would have to set aside in every call
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                uint32_t w[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) w[j] = j < q ? ((const uint32_t *)rec)[(j * tw + lane_c) * 4 + d] : 0u;
+                if (d == 0 || G == 32 || (G == 64 && d == 2)) {   // a quant group begins
+                    const int sg = G >= 128 ? 0 : 32 * d / G;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) s[j] = j < q ? half_bits_to_float(mp[(sg * (q + 1) + j) * tw + lane_c]) : 0.f;
+                    z = half_bits_to_float(mp[(sg * (q + 1) + q) * tw + lane_c]);
+                }
+                for (int b = 0; b < 32; ++b) {
+                    const int bit = hlq_bit_pos(b);
                     float wv = z;
-                    for (int j = 0; j < q; ++j)
-                        if ((w[j][d] >> bit) & 1u) wv += s[j];
-                    const size_t k = (size_t)c * 128 + k0;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        if ((w[j] >> bit) & 1u) wv += s[j];
+                    const size_t k = (size_t)c * 128 + 32 * d + b;
 #pragma unroll
                     for (int r = 0; r < SAFE_ROWS; ++r) {
                         const int m = min(m0 + r, M - 1);   // rows past M repeat the last one and are dropped

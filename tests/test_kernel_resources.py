@@ -20,7 +20,7 @@ def kernels():
     return found
 
 
-@pytest.mark.parametrize("part", ["hlq_quantize_kernel"])
+@pytest.mark.parametrize("part", ["hlq_quantize_kernel", "hlq_gemm_mfma_group_reduce_kernel", "hlq_gemm_safe_kernel"])
 def test_no_scratch_memory(part):
     # scratch is memory that the runtime sets aside per wavefront, and a spilled register is a trip to it in the inner loop
     mine = {n: k for n, k in kernels().items() if part in n}
