@@ -44,6 +44,13 @@ def check(batch, ys, refs):
         assert int(batch.ws[:COUNTER_BYTES].count_nonzero()) == 0
 
 
+@pytest.mark.parametrize("M", [17, 40, 70])
+def test_calls_that_split_nothing(M):
+    # K of two chunks cannot be split: the recomputation has a launch of its own
+    check(*group([(256, 328)], M))
+    check(*group([(256, 200), (256, 1096), (128, 72)], M, big=1))
+
+
 def microseconds(batch):
     best = float("inf")
     for _ in range(4):
