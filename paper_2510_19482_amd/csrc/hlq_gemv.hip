@@ -432,6 +432,7 @@ struct GemvPlan {
     int TN;    // column tiles per wavefront (1 or 2)
     int W;     // wavefronts per workgroup (K ranges added through LDS)
     int cpw;   // target chunks per wavefront; a slice is W * cpw chunks (rounded to even)
+    int forced_w, forced_cpw;   // of these, what hlq_set_gemv_plan or the environment asks for (0: nothing)
 };
 
 // process-wide overrides set by hlq_set_gemv_plan (0 = automatic).  Atomic, so that a launch on one
@@ -475,11 +476,13 @@ GemvPlan plan_gemv(long units)
         pl.cpw = units < 12000 ? 4 : 7;
     }
     if (env_tn) pl.TN = env_tn;
-    if (env_w) pl.W = env_w;
-    if (env_cpw) pl.cpw = env_cpw;
     if (const int v = g_plan_tn.load(std::memory_order_relaxed)) pl.TN = v;
-    if (const int v = g_plan_w.load(std::memory_order_relaxed)) pl.W = v;
-    if (const int v = g_plan_cpw.load(std::memory_order_relaxed)) pl.cpw = v;
+    pl.forced_w = env_w;
+    pl.forced_cpw = env_cpw;
+    if (const int v = g_plan_w.load(std::memory_order_relaxed)) pl.forced_w = v;
+    if (const int v = g_plan_cpw.load(std::memory_order_relaxed)) pl.forced_cpw = v;
+    if (pl.forced_w) pl.W = pl.forced_w;
+    if (pl.forced_cpw) pl.cpw = pl.forced_cpw;
     return pl;
 }
 
@@ -723,9 +726,9 @@ static hlq_status plan_gemv_batch(int count, const HlqGemvItem *items, hlq_out_d
         pl.cpw = units < 12000 ? 4 : 16;   // measured on the 8B layer at q = 4: 16 beats 8 (one round of workgroups instead of two)
         if (const int v = g_plan_cpw.load(std::memory_order_relaxed)) pl.cpw = v < 4 ? 4 : v;
     } else if (cols) {
-        pl.W = pl.cpw = 0;   // plan_cols chooses
-        if (const int v = g_plan_w.load(std::memory_order_relaxed)) pl.W = v;
-        if (const int v = g_plan_cpw.load(std::memory_order_relaxed)) pl.cpw = v;
+        pl.W = pl.forced_w;   // 0: plan_cols chooses
+        pl.cpw = pl.forced_cpw;
+        if (pl.W < 0 || pl.cpw < 0) return HLQ_ERR_UNSUPPORTED;   // (of the environment)
     } else if (rows > 1) {
         // measured (8B shapes, q = 4, M = 2..8): short runs on few wavefronts per workgroup for narrow
         // launches, longer runs and eight wavefronts once there are enough tiles
