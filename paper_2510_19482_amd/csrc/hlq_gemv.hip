@@ -537,10 +537,10 @@ int cols_kw(int W, int nchunks)
 // q = 1, G = 256  8B layer 9.4 / 10.1, but 70B layer 28.8 / 25.8.
 bool cols_wins(long units, int q, int G)
 {
+    if (hlq_cols_always(q, G)) return true;
     if (G == 32) return units < 12000;
     if (q == 1) return units < 20000 || units >= 60000;
-    if (G == 64 && q <= 3) return units < 60000;
-    return true;
+    return units < 60000;   // G = 64, q = 2, 3
 }
 
 // cpw: forced chunks per wavefront (0: automatic); forced_w likewise.  Returns the wavefronts per workgroup.

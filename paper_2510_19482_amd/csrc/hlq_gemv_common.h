@@ -105,6 +105,10 @@ __device__ __forceinline__ void store_out(void *y, size_t idx, float v, int out_
 hlq_status hlq_launch_gemv_mx(const GemvBatch &b, unsigned nblocks, int W, int nsets, int rows, int q, int G, hipStream_t st);
 int hlq_gemv_mx_max_waves(int q, int G);
 
+// formats whose launches of one activation row all go to hlq_gemv_cols.hip (cols_wins has the measurements): the 64-column
+// kernel is not instantiated for them
+constexpr bool hlq_cols_always(int q, int G) { return q >= 2 && (G >= 128 || (G == 64 && q == 4)); }
+
 // one activation row (hlq_gemv_cols.hip): W (1..16) wavefronts, kw of them (a power of two) on each column block, at most
 // four column blocks per workgroup where K is split across workgroups, one arrival counter per workgroup column
 #define HLQ_COLS_MAX_SLOTS 640   // (column blocks of a workgroup) x kw: 64 bytes of LDS each

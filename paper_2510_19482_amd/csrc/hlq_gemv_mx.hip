@@ -112,11 +112,11 @@ constexpr int mx_rows(int G, int NS, bool batched) { return batched ? NS * (4 / 
 constexpr int mx_xt_bytes(int nrow) { return nrow * 512 + 64; }
 constexpr int mx_wave_lds(int Q, int G, int nrow) { return mx_xt_bytes(nrow) + 64 * mx_meta_stride(Q, G) + nrow * 4 * 64 * 4; }
 // Instantiations whose chunk loop ends in steps without reloads (several copies of the step: they cost
-// registers).  The plain GEMV at one or two planes stays within 128 registers, i.e. two workgroups of
+// registers).  The plain GEMV at one plane stays within 128 registers, i.e. two workgroups of
 // eight wavefronts per CU; the others would lose a resident workgroup or spill, so they drop the loads
 // past the end of a run through the range check of a buffer descriptor instead (measured a few per
 // cent slower than the peeled loop where both are possible: a dropped load still takes its issue slot).
-constexpr bool mx_peeled_tail(int Q, int G, int NR) { return NR == 0 && G >= 128 && Q <= 2; }
+constexpr bool mx_peeled_tail(int Q, int G, int NR) { return NR == 0 && G >= 128 && Q == 1; }
 // Register sets of chunk loads per wavefront (chunks in flight + 1).  Two: launches of this kernel
 // have thousands of wavefronts, which together keep far more than the bandwidth-delay product in
 // flight; deeper prefetch only costs registers, i.e. resident wavefronts (measured: 2 beats 3, 4, 6, 8).
@@ -553,7 +553,7 @@ void launch_qg(const GemvBatch &b, unsigned nblocks, int W, int nsets, int rows,
     hlq_gemv_mx_kernel<Q, G, NS_, NR_><<<nblocks, blk, (size_t)W * mx_wave_lds(Q, G, (NR_) > 0 ? (NR_) : 1), st>>>(a.lo, a.hi, a.out_f32, a.probs)
     // the smallest instantiation that holds `rows` (rows <= nsets * RPS is checked by the caller)
     if (nsets == 0) {
-        HLQ_MX_LAUNCH(1, 0);
+        if constexpr (!hlq_cols_always(Q, G)) HLQ_MX_LAUNCH(1, 0);
     } else if (nsets == 1) {
         switch (rows < RPS ? rows : RPS) {
         case 1: HLQ_MX_LAUNCH(1, 1); break;
@@ -589,11 +589,12 @@ hlq_status launch_q(int G, const GemvBatch &b, unsigned nblocks, int W, int nset
 int hlq_gemv_mx_max_waves(int, int) { return 8; }
 int hlq_gemv_mx_rows_per_set(int G) { return mx_rows(G, 1, true); }
 
-// nsets: 0 = GEMV (one activation row per problem), 1 / 2 = batched rows with that many row sets
+// nsets: 0 = GEMV (one activation row per problem, formats without hlq_cols_always), 1 / 2 = batched rows with that many row sets
 // (every problem's M must fit nsets * hlq_gemv_mx_rows_per_set(G)).
 hlq_status hlq_launch_gemv_mx(const GemvBatch &b, unsigned nblocks, int W, int nsets, int rows, int q, int G, hipStream_t st)
 {
     if (W < 1 || W > 8 || (W & (W - 1)) || nsets < 0 || nsets > 2) return HLQ_ERR_UNSUPPORTED;
+    if (nsets == 0 && hlq_cols_always(q, G)) return HLQ_ERR_UNSUPPORTED;
     if (rows < 1 || rows > (nsets ? nsets : 1) * hlq_gemv_mx_rows_per_set(G)) return HLQ_ERR_UNSUPPORTED;
     switch (q) {
     case 1: return launch_q<1>(G, b, nblocks, W, nsets, rows, st);
