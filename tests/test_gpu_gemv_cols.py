@@ -101,9 +101,21 @@ def test_counters_and_slots_side_by_side():
     assert int(batch.ws[:131072].count_nonzero()) == 0
 
 
-@pytest.mark.parametrize("q,G,N", [(2, 32, 23040), (1, 64, 40000), (2, 64, 122880)])
-def test_either_side_of_the_size_rule(q, G, N):
-    # K = 4096: 32 chunk-tiles per 64 columns; the named N is the first or close to the first that the 64-column kernel takes
-    for n in (N - 264, N + 200):
+def is_cols(d):
+    """Whether a one-row launch goes to the 16-column kernel: with K = 4096 its plan has eight wavefronts on a column block,
+    and a workgroup per share of ceil(N / 16) blocks; the 64-column kernel has one per W / kw tiles."""
+    i = B.gemv_plan_query([d], 1)[0]
+    tiles, per = -(-d.N // 64), i.waves_per_workgroup // i.waves_per_tile
+    return i.tile_groups != -(-tiles // per)
+
+
+# K = 4096: 32 chunk-tiles per 64 columns.  first: the first N (a multiple of 64) whose launch is at or past the named
+# number of chunk-tiles
+@pytest.mark.parametrize("q,G,units,below", [(2, 32, 12000, True), (4, 32, 12000, True), (2, 64, 60000, True), (3, 64, 60000, True),
+                                             (1, 64, 20000, True), (1, 128, 20000, True), (1, 128, 60000, False)])
+def test_either_side_of_the_size_rule(q, G, units, below):
+    first = -(-units // 32) * 64
+    for n, cols in ((first - 64, below), (first - 40, not below)):      # 40 columns of one more tile
         d, packed, x, ref = case(4096, n, q, G, "rule")
+        assert is_cols(d) == cols, n
         check(B.hlq_lut_gemv(d, packed, x, out_f32=True), ref)

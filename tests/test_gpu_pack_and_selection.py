@@ -52,7 +52,7 @@ def test_selection_on_ties(q, G):
     rng = np.random.default_rng(7 * q + G)
     W = (rng.integers(-12, 13, (K, N)) / 8.0).astype(np.float32)
     W[0::G], W[1::G] = 1.5, -1.5                     # the grid's midpoint is exactly zero
-    W[:, 40:] *= np.float32(2.0 ** -120)             # and in the subnormal range of fp32
+    W[:, 40:] *= np.float32(2.0 ** -140)             # and in the subnormal range of fp32 (multiples of 2^-143)
     W[:, 64:] = rng.integers(0, 2, (K, 8)).astype(np.float32)   # all candidates but two unused
     W[:, 70] = 0.25                                  # equal candidates
     codes_ref, _, _ = QO.quantize(W.astype(np.float64), q, G, t_max=1)
