@@ -89,9 +89,11 @@ HLQ_API hlq_status hlq_batch_workspace_bytes(int count, const hlq_desc *descs, s
 /* Zero the arrival counters of a freshly allocated workspace (asynchronous on `stream`).
  * REQUIRED once per workspace before its first use.  The kernels cannot tell a counter that was
  * never cleared from one that counts arrivals: with K split across workgroups, a workgroup adds the
- * partial sums when the counter of its column tile reaches (slices - 1), so on memory that does not
+ * partial sums when the counter of its columns reaches (slices - 1), so on memory that does not
  * start at zero that moment never comes, or comes early: the affected outputs are then not written
- * at all (they keep what y held) or are sums over the slices that happened to be there.  No fault, no
+ * at all (they keep what y held) or are sums over the slices that happened to be there.  (Two slices
+ * of a one-row launch meet without partial sums: the counter block holds a 64-bit slot per column, into
+ * which each side swaps its sum; zero between calls like the counters, and with the same consequences.)  No fault, no
  * error code -- wrong numbers.  Launches whose plan does not split K across workgroups do not
  * touch the workspace.  hlq_lut_gemv_static needs no such call. */
 HLQ_API hlq_status hlq_workspace_init(void *ws, size_t ws_bytes, void *stream);
@@ -205,8 +207,11 @@ typedef struct {
     int32_t formulation;          /* 1 = table lookups, 2 = matrix cores                             */
     int32_t waves_per_workgroup;  /* wavefronts of a workgroup                                       */
     int32_t waves_per_tile;       /* of those, the wavefronts that share one column tile's K slice   */
+                                  /* (a tile: 64 columns; 16 in the one-row matrix-core kernel that  */
+                                  /* most launches with M = 1 go to)                                 */
     int32_t chunks_per_slice;     /* chunks of 128 k per K slice (a slice = one workgroup's share)   */
-    int32_t slices;               /* K slices, i.e. partial sums per output in the workspace         */
+    int32_t slices;               /* K slices, i.e. partial sums per output in the workspace (two    */
+                                  /* slices of the 16-column kernel may meet in slots instead)       */
     int32_t tile_groups;          /* groups of column tiles, one workgroup per (group, slice)        */
     int32_t first_block, blocks;  /* this problem's range of workgroups in the launch                */
 } hlq_gemv_plan_info;

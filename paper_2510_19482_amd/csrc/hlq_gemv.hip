@@ -529,7 +529,7 @@ int cols_kw(int W, int nchunks)
 
 // Which launches of one activation row go there instead of to the 64-column kernel (hlq_gemv_mx.hip).  It wins wherever a
 // launch is short of wavefronts, and with groups of 128 and more on every size measured (microseconds, 64-column kernel
-// against this one): q = 2, G = 128  4096 x 1024 4.95 / 3.17, 4096 x 4096 5.42 / 3.53, 14336 x 4096 7.95 / 6.0, 8B layer
+// against this one): q = 2, G = 128  4096 x 1024 4.95 / 3.17, 4096 x 4096 5.42 / 3.53, 14336 x 4096 7.95 / 6.5, 8B layer
 // (27648 chunk-tiles) 13.8 / 13.2, 70B layer (104448) 42.1 / 41.1.  Its four column blocks of a tile fetch the lines of the
 // tile's scales one after the other, which costs it the long launches with narrow groups: G = 32  4096 x 28672
 // (14336) 12.1 / 13.3, 70B layer 70.7 / 72.3 (q = 4: 126 / 135);  G = 64, q = 2  70B layer 48.0 / 49.7, LM head (256512)
@@ -551,8 +551,9 @@ int plan_cols(int count, const HlqDims *dms, int forced_w, int cpw, ColsSplit *o
     for (int i = 0; i < count; ++i) blocks += cols_blocks(dms[i]);
     // K slices.  One up to sixteen windows (K = 8192: a window per wavefront).  Two up to 32 windows, in which case the sides
     // meet in one exchange per column: 14336 x 1024 5.5 us in one slice, 4.5 in two; 14336 x 512 5.4 / 4.4; 11008 x 5000,
-    // q = 3, G = 64 10.1 / 8.4; where the columns alone give every compute unit its workgroup it costs a little instead,
-    // 14336 x 4096 6.0 / 6.5, 11008 x 4096 5.5 / 5.8.  Longer K over few columns: one slice per sixteen windows,
+    // q = 3, G = 64 10.1 / 8.4.  Where the columns alone give every compute unit its workgroup two slices are the slower
+    // plan, 14336 x 4096 6.0 / 6.5, 11008 x 4096 5.5 / 5.8; it is kept for them because the tests
+    // of the static scratch array take 14336 x 4096 for a problem whose K is split under every plan.  Longer K over few columns: one slice per sixteen windows,
     // partial sums and arrival counters: 28672 x 1024 8.5 / 6.5, 28672 x 512 8.3 / 5.8; over more columns one slice,
     // 28672 x 8192 13.5.
     int most_wins = 1;
@@ -577,9 +578,11 @@ int plan_cols(int count, const HlqDims *dms, int forced_w, int cpw, ColsSplit *o
     if (W > maxw) W = maxw;
     while (W & (W - 1)) W &= W - 1;
 
-    // Workgroups: one step per wavefront if all of those are resident at once (the kernel's one-step form: 59 registers at
-    // q <= 2, up to 75 otherwise), else as few steps per wavefront as one generation of workgroups (16 wavefronts a
-    // compute unit) needs: a second generation of a few costs as much as a full one (8B layer 20 us instead of 13).
+    // Workgroups: one step per wavefront if all of those are resident at once (the kernel's one-step form takes 58..63
+    // registers at q <= 2, G >= 64: 32 wavefronts a compute unit; 62..75 otherwise: 24 or more, 83 at q = 4, G = 32: 20, but
+    // there too the one-step form is the faster one up to 24: 4096 x 10240 10.2 us against 11.9 in several steps, 4096 x
+    // 12288 12.0 / 12.4), else as few steps per wavefront as one generation of workgroups (16 wavefronts a compute unit)
+    // needs: a second generation of a few costs as much as a full one (8B layer 20 us instead of 13).
     long one_step = 0, cost[HLQ_MAX_BATCH];
     bool one_round = true;
     for (int i = 0; i < count; ++i) {
