@@ -29,3 +29,20 @@ def test_counter_summaries_bench_reads():
     assert os.path.exists(os.path.join(ROOT, q["source"]))
     v = json.load(open(os.path.join(prof, "gemv_8b_layer_q2_table_variants_counters.json")))
     assert os.path.exists(os.path.join(ROOT, v["source"]))
+
+
+def test_line_on_stdout_is_short_and_whole():
+    sys.path.insert(0, ROOT)
+    import bench
+    head = {"metric": "m", "value": 4752.523688104141, "unit": "GB/s", "n_gpus": 1, "steps": 20, "warmup": 5, "ms_per_step": 0.0136,
+            "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "f32", "data": "synthetic",
+            "config": {"workload": "w", "launch": "one"}, "roofline": {"kernel": "k", "bound": "hbm", "frac": 0.59123456, "peak": 8000.0, "unit": "GB/s"}}
+    point = {"M": 1, "us_per_launch": 17.8261234567, "value": 5352.9123456, "packed_bytes": 10**8, "note": "n" * 300,
+             "roofline": {"kernel": "k" * 60, "bound": "hbm", "frac": 0.6702612345, "peak": 8000.0, "note": "n" * 200}}
+    out = dict(head, plain_read={"sweep_us": [{"workgroups": 256, "us": 12.3456789}] * 70, "one": point}, broken={"error": "E: no"},
+               **{f"config{i}": {"a": point, "b": point} for i in range(12)})
+    b = bench.brief(out)
+    assert {k: b[k] for k in head} == head                    # the contract's keys and the headline's roofline as they are
+    assert b["broken"] == {"error": "E: no"}
+    assert b["config3"]["a"]["us_per_launch"] == 17.826 and b["config3"]["a"]["roofline"] == {"bound": "hbm", "frac": 0.67026}
+    assert len(json.dumps(b)) < 5000 < 20000 < len(json.dumps(out))
