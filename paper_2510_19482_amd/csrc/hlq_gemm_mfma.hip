@@ -426,7 +426,8 @@ struct MfmaPlan {
 // a second kernel adds.  The choice minimises a small cost model fitted to measurements on MI355X
 // (M = 16 .. 2048, the 8B layer shapes): a chunk costs a workgroup t1 when it has its CU to itself
 // and t2 = 1.65 t1 when two workgroups share the CU (two per CU is the occupancy limit), workgroups
-// run in rounds of 512, and the reduction costs a launch plus reading the partials back.
+// run in rounds of 512, and the reduction costs a launch plus reading the partials back (fitted when the sums and the
+// range fallback were two launches, 5 us; they are one now, and the split has not been fitted again).
 MfmaPlan plan_mfma(const HlqDims &dm, int64_t M)
 {
     MfmaPlan p;
