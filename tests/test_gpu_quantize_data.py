@@ -70,4 +70,4 @@ def test_small_launch(q, kind):
     # one wavefront per SIMD, groups of 32: all rounds by scan (by search: 1.2 times and more)
     plain, special = (microseconds(q, 32, dev(weights(k, 1024, 1024))) for k in ("plain", kind))
     print(kind, q, f"{special:.1f} us, fp32 normals {plain:.1f} us", flush=True)
-    assert special <= 1.12 * plain
+    assert special <= 1.18 * plain
