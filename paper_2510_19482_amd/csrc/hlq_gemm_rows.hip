@@ -1,46 +1,67 @@
-// hlq_lut_gemm for a handful of rows (small-batch decode, 5 <= M <= 16, quant groups of 128 or 256):
+// hlq_lut_gemm for a handful of rows (small-batch decode, 3 <= M <= 16, quant groups of 128 or 256):
 // the bit-serial product of Sec. 2 "Bit-Serial LUT-Based GEMM" / App. B with the per-plane dot products
 // on the MX matrix cores, as in hlq_gemv_mx.hip, arranged for many activation rows:
 //
 //   Y[m,n] = sum_groups ( sum_j s_j[g,n] * <b_j[.,n], X[m,.]>_g  +  z[g,n] * sum_g(X[m,.]) )
 //
-// Planes become fp4 codes by AND masks; an activation is an exact sum of four bf8 terms (each the
-// running remainder cut to three significant bits).  In the GEMV kernel the four terms sit in four
-// ROWS of the 16-row operand and meet again as four scaled results per (row, column, plane).  Here the
-// terms lie along the ACCUMULATION: operand o holds terms [o TPO, (o + 1) TPO) of 16 / TPO activation
+// Planes become fp4 codes by AND masks.  An activation is a sum of four bf6 (e3m2) terms: 32 activations of a row (the
+// k block that shares a scale in the matrix core) are brought below 16 by a power of two, the largest to [8, 16), each term is
+// the remainder so far rounded to the nearest code, and the next remainder is multiplied by 16.  A term holds three
+// significant bits and the sign of what it leaves; what four of them leave is at most 2^-20 of the block's largest, and
+// nothing for an activation of more than 2^-9 of it (both as weighted by the plane codes, see below).  The terms' powers of two are the matrix core's own block scales (E8M0,
+// a byte per lane and term), so nothing is undone at the end.
+// Why bf6: with no operand wider than six bits the instruction takes 16 clocks and not 32, and it adds the products of a
+// block exactly down to 2^-24 of the largest (measured), where bf8 x fp4 drops what is below 2^-13 of the largest of eight
+// neighbours.  Four such terms are half the time of four exact bf8 terms and closer to the exact product: relative error of fp32 results,
+// 4096 x 4096, q = 4, M = 16: 3.0e-6 -> 3.0e-7, with 1 % of the channels times 20 1.2e-5 -> 2.5e-6.
+// Three terms are short of it where outliers share a block with the rest (2.5e-4 of a row's largest result, 1 % of K = 1024
+// times 20).
+//
+// The terms lie along the ACCUMULATION: operand o holds terms [o TPO, (o + 1) TPO) of 16 / TPO activation
 // rows, the NT = 4 / TPO matrix-core instructions of an item (plane j, block of 16 columns) chain
 // through their accumulator, and what comes out is the finished dot product of every row -- one scale
 // multiplication per (row, column, plane).  NT = 2 carries up to 8 rows, NT = 4 up to 16.  NT = 1 is the other
 // end: all four terms of up to 4 rows in one operand, one matrix-core instruction per item, the four terms of a
-// result in the four 16-lane groups, added by two cross-lane adds at the very end (the arrangement of the GEMV
-// kernel, but with the activations converted once per call by the pre-pass instead of once per column tile).
+// result in the four 16-lane groups, added by two cross-lane adds at the very end.
 //
-// Two kernels.  hlq_rows_split_kernel runs once per call: the workgroups of a (problem, activation row) find
-// the row's largest magnitude, which fixes a power-of-two scale that puts the row high in the bf8 range
-// (removed again at the end), cuts every activation into its four terms and writes them to the workspace
-// exactly as the matrix core wants its 8-bit operand: [chunk][operand][row][128 codes in matrix-core k
-// order] -- 2 KiB per operand and chunk, rows the call does not have as zeros.  hlq_gemm_rows_kernel then
-// has no activation work at all: a lane loads its 32 bytes of every operand straight into registers,
-// one chunk ahead.
+// Two kernels.  hlq_rows_split_kernel runs once per call and cuts every activation into its terms, in the form in which
+// the matrix core wants them: a lane of it makes 32 activations of a row, with the packed conversions, and writes the six
+// registers of every term and the scales of one lane of the main kernel.  Blocks carry their own scales, so there is
+// no pass over the row before.  It is 4.2 us of a call of 4 rows, 5.5 of 8, 7.4 of 16 (8B layer), the hand-over between the
+// launches included.  Made inside the main kernel instead, by all wavefronts of a workgroup for its run of chunks, the
+// operands cost as much: nothing is requested while they are made (M = 4 31.7 us against 31.6, M = 16 53 against 43).
+// hlq_gemm_rows_kernel has no activation work at all: a lane loads its operands straight into registers, one chunk ahead.
 //
 // Work split of the main kernel.  A workgroup of W wavefronts owns W / kw adjacent column tiles and one
 // K slice; the kw wavefronts of a tile take consecutive runs of chunks and add their results through LDS
 // at the end (as in hlq_gemv_mx.hip); nothing is shared before that, so there is no barrier in the chunk
 // loop.  K slices of different workgroups meet in the workspace (partial sums, one arrival counter per
 // tile, the last arriver adds in slice order).
+//
+// What bounds it, 8B layer at q = 4 in one launch (126 MB, 18 us at 6.9 TB/s): the pre-pass and the start of the main kernel, then
+// the wait for weights requested two chunks ahead by 1.7 wavefronts per SIMD; at M = 16 68 matrix-core instructions (1088
+// clocks) beside 290 vector instructions (1160) a chunk and wavefront.  Four bf8 terms -> four bf6 terms, us a call:
+// q = 4  M = 4 32.8 -> 31.9, M = 8 39.1 -> 34.5, M = 16 56.5 -> 42.7;  q = 2  M = 8 28.9 -> 24.7, M = 16 44.2 -> 29.5.
 #include "hlq_gemv_common.h"
 
-#ifndef HLQ_ROWS_SKIP
-#define HLQ_ROWS_SKIP 0    // timing experiments (wrong results), bit mask -- 1: no scale multiplications, 2: no word transpose, 4: no plane expansion
-#endif
-#ifndef HLQ_ROWS_DEBUG
-#define HLQ_ROWS_DEBUG 0   // timing experiments -- 1: loads only (no matrix-core work), 2: no weight reloads (compute only), 3: nor operand reloads
-#endif
+#include <type_traits>
 
 namespace {
 
+// compile-time loop: body(std::integral_constant<int, 0>), ..., body(std::integral_constant<int, N - 1>)
+template <int N, class F>
+__device__ __forceinline__ void unrolled(F &&body)
+{
+    if constexpr (N > 0) {
+        unrolled<N - 1>(body);
+        body(std::integral_constant<int, N - 1>{});
+    }
+}
+
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 typedef unsigned short ushort2_t __attribute__((ext_vector_type(2)));
+typedef _Float16 half32_t __attribute__((ext_vector_type(32)));
+typedef unsigned int uint6v __attribute__((ext_vector_type(6)));
 typedef int int8v __attribute__((ext_vector_type(8)));
 typedef unsigned int uint2v __attribute__((ext_vector_type(2)));
 typedef float float4v __attribute__((ext_vector_type(4)));
@@ -51,119 +72,88 @@ constexpr int rows_meta_stride(int Q) { return ((Q + 1) * 2 + 7) & ~7; }
 // LDS per wavefront: scales [64][stride] | results [16][64] fp32 for the sum over the tile's kw runs
 constexpr int rows_wave_lds(int Q) { return 64 * rows_meta_stride(Q) + 16 * 64 * 4; }
 constexpr int rows_lds_bytes(int Q, int W) { return W * rows_wave_lds(Q); }
-// bytes of one operand of one chunk in the workspace: 16 rows x 128 codes
-constexpr int ROWS_OPERAND_BYTES = 16 * 128;
-// Chunks of a row that a workgroup of the pre-pass converts: one item per lane up to K = 16384, at most sixteen shares (each
-// scans the whole row).  The pre-pass lies in front of the main kernel, so its length counts in full; eight shares
-// whatever the length, with the loads of the items behind the scan and the scan's loads one by one: 8B layer at q = 4, M = 4
-// 32.3 us a call instead of 30.9, M = 16 55.1 instead of 54.1.
-constexpr int ROWS_MAX_SHARES = 16;
-__host__ __device__ __forceinline__ int rows_share(int nchunks)
-{
-    const int s = (nchunks + ROWS_MAX_SHARES - 1) / ROWS_MAX_SHARES;
-    return s < 8 ? 8 : s;
-}
+// The activations of a chunk in the workspace, NT operands of 16 rows: what lane (row, k block) of the main kernel holds,
+// 6 NT words of codes and one of scales (byte o: operand o), four words at a time as [word / 4][lane][4]; a single
+// word left over as [lane]
+constexpr int rows_words(int NT) { return 6 * NT + 1; }
+constexpr int rows_quads(int NT) { return rows_words(NT) % 4 == 1 ? rows_words(NT) / 4 : (rows_words(NT) + 3) / 4; }
+constexpr int rows_chunk_bytes(int NT) { return rows_quads(NT) * 1024 + (rows_words(NT) % 4 == 1 ? 256 : 0); }
+// operands, and activation rows they carry
+constexpr int rows_operands(int rows) { return rows <= 4 ? 1 : rows <= 8 ? 2 : 4; }
+constexpr int rows_carried(int NT) { return 4 * NT; }
 
-template <int CTRL, int ROWMASK = 0xf>
-__device__ __forceinline__ uint32_t max_dpp(uint32_t v)
-{
-    const uint32_t moved = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWMASK, 0xf, false);
-    return max(v, moved);
-}
-
-// Workgroup = (activation row m = blockIdx.x, problem blockIdx.y, share blockIdx.z of the row's chunks).  Term t of row m goes to operand t / TPO,
-// operand row (t % TPO) * RPO + m; a row the call does not have is written as zeros.
-// Word cd = 8 gg + 2 rr + hh of an operand row holds the matrix-core k indices 32 gg + 8 rr + 4 hh + n, n = 0..3,
-// i.e. the activations k = 32 gg + 8 n + 2 rr + hh of the chunk: weight k0 = 2 p + hh of block gg is plane bit
-// p = 4 n + rr, which the plane expansion puts into nibble n + 4 hh of register rr.
+// Workgroup = one wavefront = 16 / RPO chunks of all rows; problem blockIdx.y.  A lane takes 32 consecutive k of one row.
+// Position 8 rr + 4 hh + n of a k block holds its activation 8 n + 2 rr + hh: weight k0 = 2 p + hh is plane bit p = 4 n + rr,
+// which the plane expansion puts into nibble n + 4 hh of register rr.  Plane codes are worth 1/2, 1, 2, 2 by rr:
+// weights 1/2, 1/4, 1/8, 1/8 make every product bit x activation / 4, and the 4 goes into the scale.
 template <int NT>
-__global__ void __launch_bounds__(256) hlq_rows_split_kernel(const GemvProbs probs)
+__global__ void __launch_bounds__(64) hlq_rows_split_kernel(const GemvProbs probs)
 {
-    constexpr int TPO = 4 / NT, RPO = 16 / TPO;
+    constexpr int RPO = rows_carried(NT), TPO = 4 / NT, QUADS = rows_quads(NT);
     const GemvProb &P = probs.p[blockIdx.y];
-    const int m = (int)blockIdx.x, tid = (int)threadIdx.x;
-    const int K = P.nchunks * 128;
-    __shared__ uint32_t wmax[4];
+    const int lane = (int)threadIdx.x, m = lane % RPO, g = lane / RPO % 4, ch = (int)blockIdx.x * (16 / RPO) + lane / (4 * RPO);
+    if (!P.xt_own || ch >= P.nchunks) return;
     const bool have = m < P.M;
-    const uint16_t *xrow = P.x + (size_t)min(m, P.M - 1) * P.ldx;
-    // this workgroup converts the chunks [c0, c1) of its row; its first items' activations (item = chunk, word cd) are
-    // requested before the scan, so that one trip to memory serves both
-    const int share = rows_share(P.nchunks);
-    const int c0 = (int)blockIdx.z * share, c1 = min(c0 + share, P.nchunks);
-    if (c0 >= P.nchunks) return;
-    const int cd = tid & 31, rr = (cd >> 1) & 3;
-    const uint16_t *src = xrow + 32 * (cd >> 3) + 2 * rr + (cd & 1);
-    uint32_t x[4];
-    auto load_item = [&](int ch) {
+    const uint4 *src = (const uint4 *)(P.x + (size_t)min(m, P.M - 1) * P.ldx + (size_t)ch * 128 + 32 * g);
+    uint32_t x[4][4];   // [n][rr]: activations 8 n + 2 rr, + 1
 #pragma unroll
-        for (int i = 0; i < 4; ++i) x[i] = src[(size_t)ch * 128 + 8 * i];
-    };
-    load_item(min(c0 + (tid >> 5), c1 - 1));
-
-    // ---- largest magnitude of the row (as an fp16 bit pattern; the ordering of magnitudes is that of the patterns).
-    // Every workgroup of the row scans the whole row (a few tens of KB): cheaper than a second launch or a hand-over.
-    uint32_t mxv = 0;
-    if (have) {
-        for (int k0 = 0; k0 < K; k0 += 256 * 8 * 8) {   // eight independent 128-bit loads in flight per thread
-            uint4 v[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                // past the end: the row's last eight again (a condition around the load would make a branch of it, and the
-                // loads would wait for each other)
-                const int k = min(k0 + (i * 256 + tid) * 8, K - 8);
-                v[i] = *(const uint4 *)(xrow + k);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const uint32_t u[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
-#pragma unroll
-                for (int d = 0; d < 4; ++d)
-                    mxv = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(ushort2_t, mxv),
-                                                                                __builtin_bit_cast(ushort2_t, u[d] & 0x7fff7fffu)));
-            }
-        }
+    for (int n = 0; n < 4; ++n) {
+        const uint4 v = src[n];
+        x[n][0] = v.x; x[n][1] = v.y; x[n][2] = v.z; x[n][3] = v.w;
     }
-    mxv = max(mxv & 0xffffu, mxv >> 16);
+    // biased exponent ew of the largest weighted magnitude: all of them are below 2^(ew - 14), brought below 16
+    int ew = -2, eall = 0;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mxv = max(mxv, (uint32_t)__shfl_xor((int)mxv, o));
-    if ((tid & 63) == 0) wmax[tid >> 6] = mxv;
-    __syncthreads();
-    mxv = max(max(wmax[0], wmax[1]), max(wmax[2], wmax[3]));
-    // biased fp16 exponent e of the largest magnitude: |x| < 2^(e-14); scaling by 2^(29-e) gives |x| < 2^15.  Plane
-    // codes are worth 1/2, 1, 2, 2 by expansion register rr: weights 1/2, 1/4, 1/8, 1/8 make every product
-    // bit x activation / 4.  The factor (<= 2^29) is applied as two fp16 multiplications.
-    const int e = (int)(mxv >> 10);
-    if (tid == 0 && m < RPO && blockIdx.z == 0) P.xexp[m] = e;
-
-    // ---- the terms
-    for (int ch = c0 + (tid >> 5); ch < c1; ch += 8) {
-        if (ch >= c0 + 8) load_item(ch);
-        char *dst = P.xt + (size_t)ch * (NT * ROWS_OPERAND_BYTES) + 4 * cd;
-        uint32_t word[4] = {0u, 0u, 0u, 0u};
-        if (have) {
-            const int k1 = (29 - e) / 2, k2 = (29 - e) - k1 - (rr == 0 ? 1 : rr == 1 ? 2 : 3);   // -4 <= k2 <= 14
-            const _Float16 f1 = __builtin_bit_cast(_Float16, (uint16_t)((15 + k1) << 10));
-            const _Float16 f2 = __builtin_bit_cast(_Float16, (uint16_t)((15 + k2) << 10));
-            const half2_t sw1 = {f1, f1}, sw2 = {f2, f2};
-            half2_t p0 = __builtin_bit_cast(half2_t, x[0] | (x[1] << 16));
-            half2_t p1 = __builtin_bit_cast(half2_t, x[2] | (x[3] << 16));
-            p0 = (p0 * sw1) * sw2;   // exact: powers of two, in range
-            p1 = (p1 * sw1) * sw2;
+    for (int rr = 0; rr < 4; ++rr) {
+        ushort2_t mx = {0, 0};
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                // cut to three significant bits: the high byte of an fp16 is a bf8 code; the remainder is exact
-                const uint32_t u0 = __builtin_bit_cast(uint32_t, p0) & 0xff00ff00u, u1 = __builtin_bit_cast(uint32_t, p1) & 0xff00ff00u;
-                word[t] = __builtin_amdgcn_perm(u1, u0, 0x07050301u);   // the four codes in k order
-                p0 = p0 - __builtin_bit_cast(half2_t, u0);
-                p1 = p1 - __builtin_bit_cast(half2_t, u1);
+        for (int n = 0; n < 4; ++n) mx = __builtin_elementwise_max(mx, __builtin_bit_cast(ushort2_t, x[n][rr] & 0x7fff7fffu));
+        const int e = max((int)mx.x, (int)mx.y) >> 10;
+        ew = max(ew, max(e, 1) - (rr < 3 ? rr + 1 : 3));
+        eall = max(eall, e);
+    }
+    const int s = 18 - ew;
+    half32_t v;
+#pragma unroll
+    for (int rr = 0; rr < 4; ++rr) {
+        const int sr = s - (rr < 3 ? rr + 1 : 3), k1 = sr / 2, k2 = sr - k1;   // two factors: 2^sr need not be an fp16 number
+        const _Float16 f1 = __builtin_bit_cast(_Float16, (uint16_t)((15 + k1) << 10)), f2 = __builtin_bit_cast(_Float16, (uint16_t)((15 + k2) << 10));
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+            for (int n = 0; n < 4; n += 2) {
+                const half2_t p = __builtin_bit_cast(half2_t, __builtin_amdgcn_perm(x[n + 1][rr], x[n][rr], hh ? 0x07060302u : 0x05040100u)) * (half2_t){f1, f1} * (half2_t){f2, f2};
+                v[8 * rr + 4 * hh + n] = p.x;
+                v[8 * rr + 4 * hh + n + 1] = p.y;
             }
-        }
-        if (m < RPO) {
+    }
+    // a row the call does not have: zeros.  An infinity or a NaN: no such codes, but such a scale, and the row's results are NaN
+    uint6v term[4];
 #pragma unroll
-            for (int t = 0; t < 4; ++t)
-                *(u32_alias *)(dst + ((t / TPO) * 16 + (t % TPO) * RPO + m) * 128) = word[t];
+    for (int t = 0; t < 4; ++t) {
+        term[t] = __builtin_amdgcn_cvt_scalef32_pk32_bf6_f16(v, 1.0f);
+        if (t < 3) v = (v - __builtin_amdgcn_cvt_scalef32_pk32_f16_bf6(term[t], 1.0f)) * (_Float16)16.0f;   // exact
+        if (!have) term[t] = (uint6v){0u, 0u, 0u, 0u, 0u, 0u};
+    }
+    auto scale_byte = [&](int t) -> uint32_t { return !have ? 127u : eall == 31 ? 255u : (uint32_t)(127 + 2 - s - 4 * t); };
+    char *dst = P.xt + (size_t)ch * rows_chunk_bytes(NT);
+    // lane `row` of k block g: its words
+    auto emit = [&](int row, const uint32_t (&w)[4 * QUADS + 1]) {
+#pragma unroll
+        for (int i = 0; i < QUADS; ++i) ((uint4 *)dst)[64 * i + 16 * g + row] = make_uint4(w[4 * i], w[4 * i + 1], w[4 * i + 2], w[4 * i + 3]);
+        if (rows_words(NT) % 4 == 1) ((uint32_t *)(dst + 1024 * QUADS))[16 * g + row] = w[4 * QUADS];
+    };
+#pragma unroll
+    for (int h = 0; h < TPO; ++h) {   // operand rows h RPO + m
+        uint32_t w[4 * QUADS + 1] = {};
+#pragma unroll
+        for (int o = 0; o < NT; ++o) {
+            const int t = o * TPO + h;
+#pragma unroll
+            for (int i = 0; i < 6; ++i) w[6 * o + i] = term[t][i];
+            w[6 * NT] |= scale_byte(t) << 8 * o;
         }
+        emit(h * RPO + m, w);
     }
 }
 
@@ -179,8 +169,6 @@ hlq_gemm_rows_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32_fla
 {
     static_assert(G >= 128, "one quant segment per chunk");
     static_assert(NT == 1 || NT == 2 || NT == 4, "one operand, or two or four chained ones");
-    constexpr int TPO = 4 / NT;            // terms per operand
-    constexpr int RPO = 16 / TPO;          // activation rows an operand carries
     constexpr int MSTR = rows_meta_stride(Q);
     using Regs = RowsRegs<Q>;
     const int W = (int)(blockDim.x >> 6);
@@ -236,22 +224,24 @@ hlq_gemm_rows_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32_fla
         load_meta(cbeg + i, R[i]);
     }
 
-    // ---- activation operands: made by hlq_rows_split_kernel, [chunk][operand][row][128 codes].  Lane (row = lane & 15,
-    // g) holds the 16-k runs [16 g, 16 g + 16) and [64 + 16 g, ...) of its row: two 128-bit loads per operand.
-    const char *a_src = P.xt + (lane & 15) * 128 + 16 * g;
+    // ---- activation operands: made by hlq_rows_split_kernel, this lane's words of every chunk
     struct Ops {
-        int8v A[NT];
+        int8v A[NT];   // of which the instruction reads six registers
+        int scale;     // byte o: operand o
     };
     auto load_ops = [&](int ch, Ops &o) {
-        if (HLQ_ROWS_DEBUG == 3 && ch > cbeg + 1) return;   // timing experiment: operands of the first two chunks only
         const int chx = max(min(ch, cend - 1), sbeg);   // stays inside K also past the end of the run
-        const char *src = a_src + (size_t)chx * (NT * ROWS_OPERAND_BYTES);
+        const char *src = P.xt + (size_t)chx * rows_chunk_bytes(NT);
+        int w[4 * rows_quads(NT) + 1];
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            const uint4 lo = *(const uint4 *)(src + t * ROWS_OPERAND_BYTES);
-            const uint4 hi = *(const uint4 *)(src + t * ROWS_OPERAND_BYTES + 64);
-            o.A[t] = (int8v){(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
+        for (int i = 0; i < rows_quads(NT); ++i) {
+            const int4v v = ((const int4v *)src)[64 * i + lane];
+            w[4 * i] = v.x; w[4 * i + 1] = v.y; w[4 * i + 2] = v.z; w[4 * i + 3] = v.w;
         }
+        if (rows_words(NT) % 4 == 1) w[4 * rows_quads(NT)] = ((const int *)(src + 1024 * rows_quads(NT)))[lane];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) o.A[t] = (int8v){w[6 * t], w[6 * t + 1], w[6 * t + 2], w[6 * t + 3], w[6 * t + 4], w[6 * t + 5], 0, 0};
+        o.scale = w[6 * NT];
     };
     // scales: lane <-> column to LDS, read back per column block (this lane's column 16 cb + c)
     struct Sc {
@@ -270,18 +260,15 @@ hlq_gemm_rows_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32_fla
         return (float)((i & 1) ? h.y : h.x);
     };
     auto expand = [](uint32_t w) -> int8v {   // plane word -> 32 fp4 codes (bit 4p+r -> nibble p of register r)
-        if (HLQ_ROWS_SKIP & 4) return (int8v){(int)w, 0x22222222, 0x44444444, 0x11111111, 0, 0, 0, 0};
         return (int8v){(int)(w & 0x11111111u), (int)(w & 0x22222222u), (int)(w & 0x44444444u),
                        (int)((w >> 1) & 0x44444444u), 0, 0, 0, 0};
     };
     const float4v zero4 = {0.f, 0.f, 0.f, 0.f};
-    auto chain = [&](const Ops &o, const int8v &B) -> float4v {
-        float4v d = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(o.A[0], B, zero4, 1, 4, 0, 0, 0, 0);
-#pragma unroll
-        for (int t = 1; t < NT; ++t) d = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(o.A[t], B, d, 1, 4, 0, 0, 0, 0);
-        return d;
+    // one matrix-core instruction: operand t of the activations (bf6) and a plane operand (fp4, scale 1)
+    auto mfma = [&](auto tc, const Ops &o, const int8v &B, const float4v &d) -> float4v {
+        constexpr int t = decltype(tc)::value;
+        return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(o.A[t], B, d, 3, 4, t, o.scale, 0, 0x7f7f7f7f);
     };
-
     // acc[sl][cb]: output (operand row 4 g + sl, column 16 cb + c) -- for NT = 2 still split by term half
     float acc[4][4];
 #pragma unroll
@@ -294,27 +281,14 @@ hlq_gemm_rows_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32_fla
     // (chunk two ahead) right after their last item; past the end of the slice the range check answers with zeros.
     auto step = [&](Regs &R, const Ops &o, const Sc &s, int ch_reload) {
         constexpr int NI = 4 * Q;
-        if (HLQ_ROWS_DEBUG == 1) {   // timing experiment: loads only
-            uint32_t m = 0;
-#pragma unroll
-            for (int j = 0; j < Q; ++j) m ^= R.w[j][0] ^ R.w[j][1] ^ R.w[j][2] ^ R.w[j][3];
-            acc[0][0] += (float)m + (float)o.A[0][0] + (float)s.m[0][0];
-            load_meta(ch_reload, R);
-#pragma unroll
-            for (int j = 0; j < Q; ++j) load_plane(ch_reload, R, j);
-            return;
-        }
         auto apply = [&](const float4v &d, int cb, int which) {
-            if (HLQ_ROWS_SKIP & 1) {
-                acc[0][cb] += d[which & 3];
-                return;
-            }
             const float sc = scale_of(s.m[cb], which);
 #pragma unroll
             for (int sl = 0; sl < 4; ++sl) acc[sl][cb] += sc * d[sl];
         };
         const int8v ones = {0x11111111, 0x22222222, 0x44444444, 0x44444444, 0, 0, 0, 0};
-        const float4v xs = chain(o, ones);   // the chunk's activation sums per row, for the zero points
+        float4v xs = zero4;   // the chunk's activation sums per row, for the zero points
+        unrolled<NT>([&](auto t) { xs = mfma(t, o, ones, xs); });
         uint32_t wt[Q][4];
 #pragma unroll
         for (int j = 0; j < Q; ++j) {        // 4 x 4 transpose over (16-lane group, word)
@@ -323,9 +297,8 @@ hlq_gemm_rows_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32_fla
             const uint2v t02 = __builtin_amdgcn_permlane32_swap(s01.x, s23.x, false, false);
             const uint2v t13 = __builtin_amdgcn_permlane32_swap(s01.y, s23.y, false, false);
             wt[j][0] = t02.x; wt[j][2] = t02.y; wt[j][1] = t13.x; wt[j][3] = t13.y;
-            if (HLQ_ROWS_SKIP & 2) { wt[j][0] = R.w[j][0]; wt[j][1] = R.w[j][1]; wt[j][2] = R.w[j][2]; wt[j][3] = R.w[j][3]; }
         }
-        if (HLQ_ROWS_DEBUG < 2) load_meta(ch_reload, R);             // its scales were staged one chunk ahead
+        load_meta(ch_reload, R);             // its scales were staged one chunk ahead
         // Items go through the matrix core two at a time: the chains of a pair are independent, so the second
         // instruction of one never waits for the first of the same chain, and the vector work of the stage (expansion
         // of the next pair's words, scales on the previous pair's results) is dealt out between the matrix-core
@@ -337,19 +310,17 @@ hlq_gemm_rows_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32_fla
 #pragma unroll
         for (int pr = 0; pr < NP; ++pr) {
             const int n0 = 2 * pr, n1 = 2 * pr + 1;
-            float4v dA = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(o.A[0], B0, zero4, 1, 4, 0, 0, 0, 0);
-            float4v dB = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(o.A[0], B1, zero4, 1, 4, 0, 0, 0, 0);
-#pragma unroll
-            for (int t = 1; t < NT; ++t) {
-                dA = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(o.A[t], B0, dA, 1, 4, 0, 0, 0, 0);
-                dB = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(o.A[t], B1, dB, 1, 4, 0, 0, 0, 0);
-            }
+            float4v dA = zero4, dB = zero4;
+            unrolled<NT>([&](auto t) {
+                dA = mfma(t, o, B0, dA);
+                dB = mfma(t, o, B1, dB);
+            });
             int8v nB0 = B0, nB1 = B1;
             if (pr + 1 < NP) {
                 nB0 = expand(wt[(n0 + 2) / 4][(n0 + 2) % 4]);
                 nB1 = expand(wt[(n1 + 2) / 4][(n1 + 2) % 4]);
             }
-            if (n1 % 4 == 3 && HLQ_ROWS_DEBUG < 2) load_plane(ch_reload, R, n1 / 4);   // the plane's last item is in this pair
+            if (n1 % 4 == 3) load_plane(ch_reload, R, n1 / 4);   // the plane's last item is in this pair
             if (pr >= 1) {
                 apply(pA, (n0 - 2) % 4, (n0 - 2) / 4);
                 apply(pB, (n1 - 2) % 4, (n1 - 2) / 4);
@@ -385,18 +356,16 @@ hlq_gemm_rows_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32_fla
         }
     }
 
-    // ---- undo the rows' scaling, add the two term halves (NT = 2) and the tile's KW runs, store --------------------
+    // ---- add the terms that lie in different lanes and the tile's KW runs, store --------------------
     float y[4][4];
 #pragma unroll
     for (int sl = 0; sl < 4; ++sl) {
-        const int row = (NT == 1 ? 0 : NT == 2 ? 4 * (g & 1) : 4 * g) + sl;
-        const float f = __builtin_bit_cast(float, (uint32_t)(127 + 2 - 29 + P.xexp[row]) << 23);   // 4 * 2^(e-29)
 #pragma unroll
         for (int cb = 0; cb < 4; ++cb) {
             float v = acc[sl][cb];
             if (NT == 1) v += __shfl_xor(v, 16);   // one term per 16-lane group
-            if (NT <= 2) v += __shfl_xor(v, 32);   // NT = 2: lanes 32..63 hold terms 2, 3 of the same rows
-            y[sl][cb] = v * f;
+            if (NT <= 2) v += __shfl_xor(v, 32);   // NT = 2: lanes 32..63 hold terms 1, 3 of the same rows
+            y[sl][cb] = v;
         }
     }
     if (KW > 1) {
@@ -491,21 +460,18 @@ void launch_qg(const GemvBatch &b, unsigned nblocks, int W, int rows, hipStream_
 {
     const dim3 blk(64 * W);
     const GemvKernelArgs a = gemv_kernel_args(b);
-    unsigned shares = 1;
-    for (int i = 0; i < b.count; ++i) {
-        const unsigned n = (unsigned)((b.p[i].nchunks + rows_share(b.p[i].nchunks) - 1) / rows_share(b.p[i].nchunks));
-        shares = n > shares ? n : shares;
-    }
+    unsigned chunks = 1;
+    for (int i = 0; i < b.count; ++i) chunks = (unsigned)b.p[i].nchunks > chunks ? (unsigned)b.p[i].nchunks : chunks;
     if constexpr (G >= 128) {
-        if (rows <= 4) {
-            hlq_rows_split_kernel<1><<<dim3(4, b.count, shares), 256, 0, st>>>(a.probs);
-            hlq_gemm_rows_kernel<Q, G, 1><<<nblocks, blk, (size_t)rows_lds_bytes(Q, W), st>>>(a.lo, a.hi, a.out_f32, a.probs);
-        } else if (rows <= 8) {
-            hlq_rows_split_kernel<2><<<dim3(8, b.count, shares), 256, 0, st>>>(a.probs);
-            hlq_gemm_rows_kernel<Q, G, 2><<<nblocks, blk, (size_t)rows_lds_bytes(Q, W), st>>>(a.lo, a.hi, a.out_f32, a.probs);
-        } else {
-            hlq_rows_split_kernel<4><<<dim3(16, b.count, shares), 256, 0, st>>>(a.probs);
-            hlq_gemm_rows_kernel<Q, G, 4><<<nblocks, blk, (size_t)rows_lds_bytes(Q, W), st>>>(a.lo, a.hi, a.out_f32, a.probs);
+        auto launch = [&](auto nt) {
+            constexpr int NT = decltype(nt)::value, per_wave = 16 / rows_carried(NT);
+            hlq_rows_split_kernel<NT><<<dim3((chunks + per_wave - 1) / per_wave, b.count), 64, 0, st>>>(a.probs);
+            hlq_gemm_rows_kernel<Q, G, NT><<<nblocks, blk, (size_t)rows_lds_bytes(Q, W), st>>>(a.lo, a.hi, a.out_f32, a.probs);
+        };
+        switch (rows_operands(rows)) {
+        case 1: launch(std::integral_constant<int, 1>{}); break;
+        case 2: launch(std::integral_constant<int, 2>{}); break;
+        default: launch(std::integral_constant<int, 4>{}); break;
         }
     }
 }
@@ -525,8 +491,7 @@ hlq_status launch_q(int G, const GemvBatch &b, unsigned nblocks, int W, int rows
 size_t hlq_gemm_rows_xt_bytes(const HlqDims &dm, int64_t M)
 {
     if (M < 1 || M > hlq_gemm_rows_max(dm.G)) return 0;
-    const size_t nt = M <= 4 ? 1 : M <= 8 ? 2 : 4;
-    return (size_t)dm.nchunks * nt * ROWS_OPERAND_BYTES + 256;   // operands + the row exponents, kept 256-byte aligned
+    return (size_t)dm.nchunks * rows_chunk_bytes(rows_operands((int)M)) + 256;   // kept 256-byte aligned
 }
 
 // rows this kernel carries for group size G (0: no instantiation)

@@ -828,19 +828,21 @@ static hlq_status plan_gemv_batch(int count, const HlqGemvItem *items, hlq_out_d
         }
     }
     if (rowsk) {
-        // behind all partial sums: every problem's activations in operand form, then its row exponents
+        // behind all partial sums: the activations in operand form, once for problems that read the same ones
         char *xt = (char *)(((uintptr_t)part + 255u) & ~(uintptr_t)255u);
         for (int i = 0; i < count; ++i) {
-            const size_t nb = hlq_gemm_rows_xt_bytes(items[order[i]].dm, rows);
-            b.p[i].xt = xt;
-            b.p[i].xexp = (int *)(xt + nb - 256);
-            xt += nb;
+            GemvProb &p = b.p[i];
+            int first = 0;
+            while (b.p[first].x != p.x || b.p[first].ldx != p.ldx || b.p[first].nchunks != p.nchunks) ++first;
+            p.xt_own = first == i;
+            p.xt = p.xt_own ? xt : b.p[first].xt;
+            if (p.xt_own) xt += hlq_gemm_rows_xt_bytes(items[order[i]].dm, rows);
         }
         part = (float *)xt;
     } else {
         for (int i = 0; i < count; ++i) {
             b.p[i].xt = nullptr;
-            b.p[i].xexp = nullptr;
+            b.p[i].xt_own = 0;
         }
     }
     if (cols)
