@@ -17,13 +17,10 @@
 // 128-bit fragment read touches per cycle over all banks.  Each lane picks the global address
 // whose data belongs at its LDS position, so one instruction still reads four whole 256-byte rows.
 //
-// Rebuilding weights.  A lane holds, per plane, the 128 bits of its column for the chunk; in a
-// 32-bit plane word bits p and p+16 are the adjacent weights k0 = 2p, 2p+1 of the word's 32-k
-// block.  (w << t) & 0x20002000 isolates such a pair at bit 13 of the two 16-bit halves: read as
-// packed fp16 that is (2^-7 * b[2p], 2^-7 * b[2p+1]); with mask 0x40004000 (bit 14) it is
-// (2 * b, 2 * b).  One v_pk_fma_f16 per plane with the pre-scaled scale (s * 2^7 or s / 2) adds
-// s_j * b_j for two weights; the chain starts from (z, z).  Cost: 8 shifts + 16 ANDs per word and
-// plane, 16*q packed FMAs per word: about 2.3 VALU lane-ops per weight at q = 2.
+// Rebuilding weights.  A lane holds, per plane, the 128 bits of its column for the chunk and turns them into packed fp16
+// pairs of adjacent k (hlq_mfma_common.h): two and three planes by look-up of four weights at a time among the four or
+// eight that a quant group has, one plane (and the fourth of four) by a mask that leaves the bits in the exponent fields of
+// a pair and a packed FMA with the pre-scaled scale.
 // Range of this path: |s_j| < 512 (pre-scaling by 2^7 must stay finite in fp16) -- HLQ scales are
 // weight magnitudes, orders of magnitude below that.  The kernel checks every scale and zero it
 // loads; if one is outside, it raises a flag and the fp32 fallback launched behind it
@@ -154,7 +151,7 @@ __device__ __forceinline__ void gemm_mfma_block(const char *__restrict__ packed,
     // MFMAs as side work of a step,
     // one stage ahead of its use (scheduling barriers keep the stages apart):
     //   - the A fragment of step s + 1 (one 128-bit LDS read) is requested before the MFMAs of step s;
-    //   - the 16 weight pairs of word d + 1 are rebuilt 16 / (2 MW) per step during word d;
+    //   - the 16 weight pairs of word d + 1 are rebuilt 8 / MW per step during word d;
     //   - the four lane exchanges that form the B operands of the next k-step are spread over the MW
     //     steps of the current one.
     // largest magnitude (as an fp16 bit pattern) among the scales and zeros this lane has used: the rebuild below is
@@ -166,18 +163,16 @@ __device__ __forceinline__ void gemm_mfma_block(const char *__restrict__ packed,
 #pragma unroll
             for (int r = 0; r <= Q; ++r) meta_max = max(meta_max, R.mt[sg][r] & 0x7fffu);
         const size_t xb = (size_t)buf * ROWS * XROW;
-        constexpr int STEPS = 8 * MW, SPW = 2 * MW, PPS = 16 / SPW, XPS = (4 + MW - 1) / MW;
+        constexpr int STEPS = 8 * MW, SPW = 2 * MW, PPS = 8 / SPW, XPS = (4 + MW - 1) / MW;
         auto frag = [&](int s) -> half8v {
             const int mb = s % MW, ks = (s / MW) & 1, d = s / SPW;
             return *(const half8v *)(xrow[(d & 1) * 2 + ks] + xb + (size_t)mb * 32 * XROW + (d >> 1) * 64);
         };
         uint32_t wp[2][16];   // rebuilt pairs of the current / next word: wp[d & 1][p] = k 32d + 2p, 2p + 1
-        HlqSegScales<Q> sc;
-        uint32_t wd[Q];
+        HlqRebuild<Q> rb;
         auto word_setup = [&](int d) {
-            sc.set(R.mt[(d * 32) / GS]);
-#pragma unroll
-            for (int j = 0; j < Q; ++j) wd[j] = R.w[j][d];
+            if (d * 32 % GS == 0) rb.segment(R.mt[(d * 32) / GS]);
+            rb.word(R.w, d);
         };
         // B operands of a k-step: after the exchange lo = columns 0..31 of the tile (lanes 0..31 hold
         // k-slots 0..7, lanes 32..63 slots 8..15), hi = columns 32..63
@@ -190,7 +185,7 @@ __device__ __forceinline__ void gemm_mfma_block(const char *__restrict__ packed,
         // prologue: word 0 in full, operands of its first k-step, first fragment
         word_setup(0);
 #pragma unroll
-        for (int p = 0; p < 16; ++p) wp[0][p] = hlq_rebuild_pair<Q>(wd, sc, p);
+        for (int p = 0; p < 8; ++p) rb.pairs(p, wp[0][p], wp[0][p + 8]);
 #pragma unroll
         for (int v = 0; v < 4; ++v) exchange(0, 0, v, lo_c, hi_c);
         half8v a_cur = frag(0);
@@ -206,7 +201,7 @@ __device__ __forceinline__ void gemm_mfma_block(const char *__restrict__ packed,
             __builtin_amdgcn_sched_barrier(0);
             if (d < 3) {
 #pragma unroll
-                for (int p = i * PPS; p < (i + 1) * PPS; ++p) wp[(d + 1) & 1][p] = hlq_rebuild_pair<Q>(wd, sc, p);
+                for (int p = i * PPS; p < (i + 1) * PPS; ++p) rb.pairs(p, wp[(d + 1) & 1][p], wp[(d + 1) & 1][p + 8]);
             }
             // operands of the next k-step: (d, 1) during (d, 0), (d + 1, 0) during (d, 1)
             const int nd = ks == 0 ? d : d + 1, nks = ks ^ 1;
