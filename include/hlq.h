@@ -176,9 +176,9 @@ HLQ_API hlq_status hlq_lut_gemv_batch(int count, const hlq_desc *descs, const vo
  * kernel takes all problems up to 4 rows at G >= 128 (4 at G = 64, 2 at G = 32: two row sets);
  * 5..16 rows at G >= 128 go to the many-rows kernel (a small pre-pass that writes the activations in
  * matrix-core operand form into the workspace, then one launch) when the launch is large enough
- * for it to win, see hlq_set_gemm_path; everything else to one launch of the tiled matrix-core
- * kernel (plus one that adds the partial sums when K is cut: the seven GEMMs of an 8B layer run
- * 1.3x faster than as seven calls at M = 2048).  If the
+ * for it to win, see hlq_set_gemm_path; everything else to one launch of a matrix-core kernel that
+ * rebuilds W^ (one for up to 32 rows, a tiled one for more and for the largest launches, plus one that adds
+ * the partial sums when K is cut: the seven GEMMs of an 8B layer run 1.3x faster than as seven calls at M = 2048).  If the
  * lookup formulation is forced the problems run one after the other on the stream.  M = 0 is a
  * no-op.
  *   ws / ws_bytes: workspace of at least hlq_gemm_batch_workspace_bytes(count, descs, M). */
@@ -238,17 +238,18 @@ HLQ_API hlq_status hlq_set_gemv_path(int path);
  * 1 = table lookups always,
  * 2 = matrix cores always: for a few rows (M <= 4 at G >= 128, <= 2 at G = 64, 1 at G = 32) the
  *     GEMV kernel of hlq_set_gemv_path(2) with several activation rows per operand, for 5..16 rows on large
- *     problems (G >= 128) the many-rows kernel, otherwise the tiled kernel that rebuilds W^ in fp16 registers
+ *     problems (G >= 128) the many-rows kernel, otherwise kernels that rebuild W^ in fp16 registers: up to 32 rows
+ *     (below 80000 chunk-tiles) the short-M kernel, which cuts K inside a workgroup, else the tiled kernel
  *     (hlq_lut_gemm_batch keeps up to twice as many rows on the GEMV kernel at G <= 64),
- * 3 = as 2 but never the few-rows GEMV kernel,
+ * 3 = the tiled kernel always,
  * 4 = as 2, and 3..16 rows (G >= 128) always go to the many-rows kernel (by default only when the call or grouped
  *     launch is large enough for it to win: from 4096 chunk-tiles of 64 columns x 128 k at q >= 3 and 12000 at
- *     q <= 2 for 5..8 rows, from 2400 resp. 20000 for 9..16 rows, smaller ones going to the tiled kernel; 3 and 4
+ *     q <= 2 for 5..8 rows, from 2400 resp. 14000 for 9..16 rows, smaller ones going to the short-M kernel; 3 and 4
  *     rows from 20000 chunk-tiles at q = 4, 4 rows from 40000 at q = 3 and 60000 at q <= 2, otherwise they stay
  *     on the few-rows GEMV kernel).
- * Other values: HLQ_ERR_UNSUPPORTED.  The fp16-rebuild kernel represents scales up to |s_j| < 512 (and
- * zeros of that size); it checks what it loads, and a call whose weights lie outside is computed again
- * by an fp32 kernel launched behind it (slow, but right for every finite fp16 parameter). */
+ * Other values: HLQ_ERR_UNSUPPORTED.  The fp16-rebuild kernels represent scales up to |s_j| < 512 (and
+ * zeros of that size); they check what they load, and what depends on weights that lie outside is computed again
+ * in fp32 (slow, but right for every finite fp16 parameter). */
 HLQ_API hlq_status hlq_set_gemm_path(int path);
 
 /* Y[M, N] = X[M, K] @ W^  (same procedure with one table set per row, the decoded

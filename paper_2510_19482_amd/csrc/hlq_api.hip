@@ -99,7 +99,9 @@ hlq_status hlq_batch_workspace_bytes(int count, const hlq_desc *descs, size_t *b
 
 static size_t batch_partial_bytes(int count, const HlqDims *dms, int64_t M)
 {
-    return M > 1 ? hlq_gemm_mfma_batch_partial_bytes(count, dms, M) : 0;
+    if (M <= 1) return 0;
+    const size_t tiled = hlq_gemm_mfma_batch_partial_bytes(count, dms, M), few = hlq_gemm_short_partial_bytes(count, dms, M);
+    return few > tiled ? few : tiled;
 }
 
 hlq_status hlq_gemm_batch_workspace_bytes(int count, const hlq_desc *descs, int64_t M, size_t *bytes)
@@ -273,6 +275,12 @@ hlq_status hlq_lut_gemm_batch(int count, const hlq_desc *descs, const void *cons
     // more rows on the matrix cores: one launch of the tiled kernel over all problems (and one for the partial
     // sums where K is split)
     if (count > 1 && hlq_gemm_uses_matrix_cores(M)) {
+        HlqDims dms[HLQ_MAX_BATCH];
+        for (int i = 0; i < count; ++i) dms[i] = items[i].dm;
+        if (!hlq_gemm_tiled_only() && hlq_gemm_short_wins(count, dms, M)) {
+            const hlq_status s = hlq_launch_gemm_short(count, items, M, out, ws, (hipStream_t)stream);
+            if (s != HLQ_ERR_UNSUPPORTED) return s;
+        }
         const hlq_status s = hlq_launch_gemm_mfma_batch(count, items, M, out, ws, (hipStream_t)stream);
         if (s != HLQ_ERR_UNSUPPORTED) return s;
     }

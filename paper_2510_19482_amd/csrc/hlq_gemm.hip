@@ -273,6 +273,9 @@ static bool use_mfma(int64_t M)
 // true if hlq_launch_gemm sends M rows (that fit one pass) to the few-rows matrix-core GEMV kernel
 bool hlq_gemm_uses_mx_rows(int64_t M) { return use_mfma(M) && g_gemm_path.load(std::memory_order_relaxed) != 3; }
 
+// true if nothing but the tiled kernel is wanted (hlq_set_gemm_path(3))
+bool hlq_gemm_tiled_only() { return g_gemm_path.load(std::memory_order_relaxed) == 3; }
+
 // true if the many-rows kernel is to take all the rows it can carry (hlq_set_gemm_path(4))
 bool hlq_gemm_rows_all() { return g_gemm_path.load(std::memory_order_relaxed) == 4; }
 
@@ -283,9 +286,10 @@ size_t hlq_gemm_partial_bytes(const HlqDims &dm, int64_t M)
 {
     size_t a = hlq_gemm_lut_partial_bytes(dm, M);
     const size_t b = hlq_gemm_mfma_partial_bytes(dm, M);
-    const size_t e = hlq_gemm_mx_partial_bytes(dm, M);
+    const size_t e = hlq_gemm_mx_partial_bytes(dm, M), f = hlq_gemm_short_partial_bytes(1, &dm, M);
     if (b > a) a = b;
     if (e > a) a = e;
+    if (f > a) a = f;
     return a;
 }
 
@@ -302,6 +306,16 @@ hlq_status hlq_launch_gemm(const HlqDims &dm, const void *packed, const uint16_t
         if (g_gemm_path.load(std::memory_order_relaxed) != 3 && M <= hlq_gemm_rows_max(dm.G) &&
             (hlq_gemm_rows_all() || hlq_gemm_rows_wins((long)dm.ntiles * dm.nchunks, dm.q, M)))
             return hlq_launch_gemm_mx_rows(dm, packed, X, M, ldx, Y, ldy, out, ws, st);
+        if (!hlq_gemm_tiled_only() && hlq_gemm_short_wins(1, &dm, M)) {
+            HlqGemvItem it;
+            it.dm = dm;
+            it.packed = packed;
+            it.x = X;
+            it.y = Y;
+            it.ldx = (long)ldx;
+            it.ldy = (long)ldy;
+            return hlq_launch_gemm_short(1, &it, M, out, ws, st);
+        }
         return hlq_launch_gemm_mfma(dm, packed, X, M, ldx, Y, ldy, out, ws, st);
     }
     return hlq_launch_gemm_lut(dm, packed, X, M, ldx, Y, ldy, out, ws, st);

@@ -33,29 +33,12 @@
 // 8..15 in lanes 32..63 for the SAME 32 columns; one v_permlane32_swap per register hands the
 // upper k-slots of columns 0..31 to lanes 32..63 and the lower k-slots of columns 32..63 to
 // lanes 0..31, giving the B operands of both 32-column halves of the tile.
-#include "hlq_gemm_safe.h"
+#include "hlq_gemm_reduce.h"
 #include "hlq_mfma_common.h"
 
 namespace {
 
-__device__ __forceinline__ void store_out(void *y, size_t idx, float v, int out_f32)
-{
-    if (out_f32) ((float *)y)[idx] = v;
-    else ((_Float16 *)y)[idx] = (_Float16)v;   // round-to-nearest-even
-}
-
 constexpr int XROW = 128;   // halfs per staged X row: the 128 k of a chunk as 16 swizzled 16-byte units
-
-// vmcnt(0) with the other counters left alone (expcnt 7, lgkmcnt 15)
-constexpr int WAIT_VM0 = (7 << 4) | (15 << 8);
-
-// 16 bytes per lane from global memory straight into LDS at lds_base + 16 * lane.  Issued as inline
-// assembly so that the compiler's wait-count bookkeeping does not tie later LDS reads (of the other
-// buffer) to it; completion is awaited explicitly (vmcnt) before the barrier that publishes the tile.
-__device__ __forceinline__ void dma_16B_per_lane(const void *gptr, uint32_t lds_base)
-{
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gptr), "s"(lds_base) : "memory", "m0");
-}
 
 template <int Q, int G>
 struct WRegs {
@@ -226,11 +209,11 @@ __device__ __forceinline__ void gemm_mfma_block(const char *__restrict__ packed,
         load_w(min(cbeg + 1, cend - 1), RB);
         dma_x(cbeg, 0);
         if (cbeg + 1 < cend) dma_x(cbeg + 1, 1);
-        __builtin_amdgcn_s_waitcnt(WAIT_VM0);
+        __builtin_amdgcn_s_waitcnt(HLQ_WAIT_VM0);
         __syncthreads();
         for (int c = cbeg; c < cend; c += 2) {
             compute(RA, 0);
-            __builtin_amdgcn_s_waitcnt(WAIT_VM0);   // own share of chunk c + 1 has landed
+            __builtin_amdgcn_s_waitcnt(HLQ_WAIT_VM0);   // own share of chunk c + 1 has landed
             __syncthreads();                        // everyone's has; buffer 0 is free
             if (c + 2 < cend) {
                 load_w(c + 2, RA);
@@ -238,7 +221,7 @@ __device__ __forceinline__ void gemm_mfma_block(const char *__restrict__ packed,
             }
             if (c + 1 < cend) {
                 compute(RB, 1);
-                __builtin_amdgcn_s_waitcnt(WAIT_VM0);
+                __builtin_amdgcn_s_waitcnt(HLQ_WAIT_VM0);
                 __syncthreads();
                 if (c + 3 < cend) {
                     load_w(c + 3, RB);
@@ -334,83 +317,6 @@ hlq_gemm_mfma_group_kernel(const int4v bb_lo, const int4v bb_hi, const int M, co
     const int sl = t - rb * P.nslices;
     gemm_mfma_block<Q, G, MW>(P.packed, P.col_bytes, P.X, P.ldx, M, P.Y, P.ldy, P.part, P.N, P.ntiles, P.nchunks,
                               P.cps, P.nslices, out_f32, cg, sl, rb, range_flag);
-}
-
-// Adds the partial sums of the problems of a launch whose K was split, four outputs per lane (N is a multiple of 8), or,
-// if the tiled kernel met parameters outside its range, computes the call again: one launch behind the tiled kernel instead
-// of two.  A dependent launch costs 1.7 us even when it only looks at the flag; the sums are latency-bound themselves
-// (one 4-byte load per lane and slice and a 64-bit division per output before).
-struct GemmRedProb {
-    const float *part;
-    void *Y;
-    long ldy;
-    int N, nslices, blk_begin;
-    int wide;   // Y's rows are aligned to four elements: one store per lane
-};
-struct GemmRedProbs {
-    GemmRedProb p[HLQ_MAX_BATCH];
-};
-constexpr int RED_LANES = 256, RED_OUT = 4 * RED_LANES;   // outputs per block
-
-__global__ void __launch_bounds__(RED_LANES)
-hlq_gemm_mfma_group_reduce_kernel(const int4v bb_lo, const int4v bb_hi, const int M, const int out_f32, int *flag,
-                                  const GemmRedProbs probs, const HlqSafeProbs again)
-{
-    const int redo = *(const int *)flag;   // written by the launch before this one
-    const int blk = (int)blockIdx.x;
-    const GemmRedProb P = probs.p[group_problem_of(bb_lo, bb_hi, blk)];
-    const size_t i = ((size_t)(blk - P.blk_begin) * RED_LANES + threadIdx.x) * 4;
-    const size_t total = (size_t)M * P.N;
-    if (redo == 0) {
-        if (i >= total) return;
-        float4v a = {0.f, 0.f, 0.f, 0.f};
-        const float *src = P.part + i;
-        int s = 0;
-        for (; s + 4 <= P.nslices; s += 4) {   // four slices in flight, added in slice order
-            const float4v v0 = *(const float4v *)(src + (size_t)(s + 0) * total), v1 = *(const float4v *)(src + (size_t)(s + 1) * total);
-            const float4v v2 = *(const float4v *)(src + (size_t)(s + 2) * total), v3 = *(const float4v *)(src + (size_t)(s + 3) * total);
-            a = (((a + v0) + v1) + v2) + v3;
-        }
-        for (; s < P.nslices; ++s) a += *(const float4v *)(src + (size_t)s * total);
-        const size_t m = total <= 0xffffffffu ? (unsigned)i / (unsigned)P.N : i / (unsigned)P.N;
-        const size_t at = m * P.ldy + (i - m * P.N);
-        typedef _Float16 half4v __attribute__((ext_vector_type(4)));
-        if (P.wide && out_f32) {
-            *(float4v *)((float *)P.Y + at) = a;
-        } else if (P.wide) {
-            *(half4v *)((_Float16 *)P.Y + at) = (half4v){(_Float16)a.x, (_Float16)a.y, (_Float16)a.z, (_Float16)a.w};
-        } else {
-            store_out(P.Y, at + 0, a.x, out_f32);
-            store_out(P.Y, at + 1, a.y, out_f32);
-            store_out(P.Y, at + 2, a.z, out_f32);
-            store_out(P.Y, at + 3, a.w, out_f32);
-        }
-        return;
-    }
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    hlq_safe_recompute(again, M, out_f32, flag, flag + 1, (long)blk * (RED_LANES / 64) + wave, (long)gridDim.x * (RED_LANES / 64));
-}
-
-// one problem of that launch; returns its blocks
-static long reduce_problem(GemmRedProb &r, const float *part, void *Y, long ldy, int N, int nslices, int64_t M, int out_f32, long blk)
-{
-    r.part = part;
-    r.Y = Y;
-    r.ldy = ldy;
-    r.N = N;
-    r.nslices = nslices;
-    r.blk_begin = (int)blk;
-    r.wide = (((uintptr_t)Y | ((uintptr_t)ldy * (out_f32 ? 4u : 2u))) & (out_f32 ? 15u : 7u)) == 0;
-    return (long)(((size_t)M * N + RED_OUT - 1) / RED_OUT);
-}
-
-// Workgroups of that launch: those of the sums, and enough that the call is computed again by as many wavefronts as behind
-// a tiled launch without split K (a group may split nothing but a narrow problem).  The surplus ones look at the flag and leave.
-static unsigned reduce_blocks(long sums, const HlqSafeProbs &again)
-{
-    const long redo = (again.items_total + RED_LANES / 64 - 1) / (RED_LANES / 64), most = HLQ_SAFE_WAVES / (RED_LANES / 64);
-    const long want = redo < most ? redo : most;
-    return (unsigned)(sums > want ? sums : want);
 }
 
 struct MfmaPlan {
@@ -547,17 +453,9 @@ hlq_status hlq_launch_gemm_mfma(const HlqDims &dm, const void *packed, const uin
     it.ldx = (long)ldx;
     it.ldy = (long)ldy;
     if (p.nslices > 1) {
-        GemmRedProbs rp;
-        HlqSafeProbs again;
-        s = hlq_safe_problems(1, &it, M, again);
-        if (s != HLQ_OK) return s;
-        const long blocks = reduce_problem(rp.p[0], part, Y, (long)ldy, dm.N, p.nslices, M, out_f32, 0);
-        if (blocks > 0x7fffffffL / (RED_LANES / 64)) return HLQ_ERR_UNSUPPORTED;
-        for (int i = 1; i < HLQ_MAX_BATCH; ++i) rp.p[i] = rp.p[0];
-        const int none = 0x7fffffff;
-        hlq_gemm_mfma_group_reduce_kernel<<<reduce_blocks(blocks, again), RED_LANES, 0, st>>>((int4v){0, none, none, none}, (int4v){none, none, none, none},
-                                                                                 (int)M, out_f32, hlq_ws_range_flag(ws), rp, again);
-        return hlq_hip_status(hipGetLastError());
+        HlqReduce red(M, out_f32);
+        if (!red.add(part, Y, (long)ldy, dm.N, p.nslices)) return HLQ_ERR_UNSUPPORTED;
+        return hlq_launch_gemm_reduce(red, 1, &it, ws, st);
     }
     // behind it, the fp32 fallback for weights outside the range of the fp16 rebuild (a no-op unless the flag went up)
     s = hlq_launch_gemm_safe(1, &it, M, out, ws, st);
@@ -625,10 +523,9 @@ hlq_status hlq_launch_gemm_mfma_batch(int count, const HlqGemvItem *items, int64
     for (int i = 0; i < count; ++i) dms[i] = items[order[i]].dm;
     const GroupPlan g = plan_group(count, dms, M);
     GemmProbs pr;
-    GemmRedProbs rp;
-    int begin[HLQ_MAX_BATCH], rbegin[HLQ_MAX_BATCH];
-    long blk = 0, rblk = 0;
-    int nred = 0;
+    HlqReduce red(M, out == HLQ_OUT_F32);
+    int begin[HLQ_MAX_BATCH];
+    long blk = 0;
     float *part = (float *)((char *)ws + HLQ_WS_COUNTER_BYTES);
     auto magic = [](int d) { return d > 1 ? (unsigned)((0x100000000ULL + (unsigned)d - 1) / (unsigned)d) : 0u; };
     for (int i = 0; i < count; ++i) {
@@ -658,9 +555,7 @@ hlq_status hlq_launch_gemm_mfma_batch(int count, const HlqGemvItem *items, int64
         blk += (long)blocks;
         if (blk > 0x7fffffffL) return HLQ_ERR_UNSUPPORTED;
         if (p.nslices > 1) {
-            rbegin[nred] = (int)rblk;
-            rblk += reduce_problem(rp.p[nred++], part, it.y, it.ldy, it.dm.N, p.nslices, M, out == HLQ_OUT_F32, rblk);
-            if (rblk > 0x7fffffffL / (RED_LANES / 64)) return HLQ_ERR_UNSUPPORTED;
+            if (!red.add(part, it.y, it.ldy, it.dm.N, p.nslices)) return HLQ_ERR_UNSUPPORTED;
             part += (size_t)p.nslices * (size_t)M * (size_t)it.dm.N;
         }
     }
@@ -679,18 +574,7 @@ hlq_status hlq_launch_gemm_mfma_batch(int count, const HlqGemvItem *items, int64
     default: return HLQ_ERR_UNSUPPORTED;
     }
     if (s != HLQ_OK) return s;
-    if (nred > 0) {
-        for (int i = nred; i < HLQ_MAX_BATCH; ++i) {
-            rp.p[i] = rp.p[0];
-            rbegin[i] = 0x7fffffff;
-        }
-        const int4v rlo = {rbegin[0], rbegin[1], rbegin[2], rbegin[3]}, rhi = {rbegin[4], rbegin[5], rbegin[6], rbegin[7]};
-        HlqSafeProbs again;
-        s = hlq_safe_problems(count, items, M, again);
-        if (s != HLQ_OK) return s;
-        hlq_gemm_mfma_group_reduce_kernel<<<reduce_blocks(rblk, again), RED_LANES, 0, st>>>(rlo, rhi, (int)M, out_f32, hlq_ws_range_flag(ws), rp, again);
-        return hlq_hip_status(hipGetLastError());
-    }
+    if (red.count > 0) return hlq_launch_gemm_reduce(red, count, items, ws, st);
     s = hlq_launch_gemm_safe(count, items, M, out, ws, st);
     if (s != HLQ_OK) return s;
     return hlq_hip_status(hipGetLastError());

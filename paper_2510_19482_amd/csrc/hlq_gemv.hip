@@ -971,15 +971,14 @@ int hlq_gemm_mx_rows_per_pass(int G)
     return many > two_sets ? many : two_sets;
 }
 
-// Many-rows kernel or tiled kernel for 5..16 rows (G >= 128)?  Measured on 8B / 70B layer shapes, single calls and
-// grouped launches, in microseconds (many-rows against tiled).  The many-rows kernel pays per MFMA (q planes x four
-// activation terms per row, twice the instructions from 9 rows on) and needs a launch large enough to spread its
-// wavefronts; the tiled kernel pays for rebuilding the weights, whatever M.
-//   q = 4, up to 8 rows:  2048 chunk-tiles 15.1 / 12.3,  7168: 19.3 / 23.6 and 21.6 / 27.6,  28672: 41 / 64, 8B layer 40 / 68
-//   q = 4, 9..16 rows:    2048: 17.1 / 12.6,  2560 (two matrices) 18.1 / 19.6,  7168: 24.2 / 23.8 and 26.5 / 28.2,  8B layer 60 / 69
-//   q = 2, up to 8 rows:  2048: 13.9 / 10.5,  7168: 16.6 / 16.4 and 19.3 / 17.9,  28672: 29 / 41
-//   q = 2, 9..16 rows:    7168: 20.8 / 16.8 and 23.2 / 18.3,  28672: 43.4 / 42.5,  8B layer 47 / 49
-// The same question for 3 or 4 rows, where the alternative is the few-rows instantiation of the GEMV kernel
+// Many-rows kernel or, with weights rebuilt in fp16, the short-M kernel (hlq_gemm_short.hip) for 5..16 rows (G >= 128)?  The
+// many-rows kernel keeps scales in fp32: a call that it has been taking stays with it although the other one is faster
+// below some 14000 chunk-tiles.  Single calls and grouped launches, us (many-rows / short-M):
+//   q = 4, up to 8 rows:  2048 chunk-tiles 14.8 / 9.3,  7168: 19.4 / 14.8,  14336: 25.7 / 28.5,  20480: 35.8 / 44.8,  8B layer 35.4 / 48.2
+//   q = 4, 9..16 rows:    2048: 15.5 / 9.6,  7168: 21.0 / 13.8,  14336: 28.1 / 28.5,  20480: 42.2 / 44.9,  8B layer 44.2 / 48.4
+//   q = 2, up to 8 rows:  2048: 13.2 / 7.8,  7168: 15.0 / 9.5,  14336: 18.5 / 19.7,  20480: 23.8 / 30.5,  8B layer 24.6 / 32.4
+//   q = 2, 9..16 rows:    7168: 16.7 / 9.9,  14336: 20.3 / 20.0,  28672: 31.3 / 33.4,  8B layer 29.8 / 33.0
+// For 3 or 4 rows the alternative is the few-rows instantiation of the GEMV kernel
 // (which converts the activations in every wavefront and needs no pre-pass).  Measured, many-rows against few-rows:
 //   8B layer (27648 chunk-tiles)  q = 4: 33.3 / 36.4 (3 rows), 33.2 / 39.5 (4 rows);  q = 3: 28.8 / 27.0, 28.7 / 30.1;
 //                                 q = 2: 25.6 / 22.5, 26.0 / 26.0
@@ -994,7 +993,7 @@ bool hlq_gemm_rows_wins_few(long units, int q, int rows)
 bool hlq_gemm_rows_wins(long units, int q, int64_t M)
 {
     if (M <= 8) return units >= (q >= 3 ? 4096 : 12000);
-    return units >= (q >= 3 ? 2400 : 20000);
+    return units >= (q >= 3 ? 2400 : 14000);
 }
 
 // Whether a grouped launch of M rows goes to the matrix-core GEMV-shaped kernels (few-rows / many-rows) rather

@@ -156,6 +156,12 @@ hlq_status hlq_launch_gemm_mfma_batch(int count, const HlqGemvItem *items, int64
                                       hipStream_t st);
 size_t hlq_gemm_mfma_batch_partial_bytes(int count, const HlqDims *dms, int64_t M);
 hlq_status hlq_launch_gemm_safe(int count, const HlqGemvItem *items, int64_t M, hlq_out_dtype out, void *ws, hipStream_t st);
+// up to 32 rows, K cut inside a workgroup (hlq_gemm_short.hip)
+#define HLQ_SHORT_ROWS 32
+size_t hlq_gemm_short_partial_bytes(int count, const HlqDims *dms, int64_t M);
+bool hlq_gemm_short_wins(int count, const HlqDims *dms, int64_t M);
+bool hlq_gemm_tiled_only();
+hlq_status hlq_launch_gemm_short(int count, const HlqGemvItem *items, int64_t M, hlq_out_dtype out, void *ws, hipStream_t st);
 int hlq_gemv_mx_rows_per_set(int G);
 int hlq_gemm_mx_rows_per_pass(int G);
 bool hlq_gemm_batch_on_mx(int count, const HlqGemvItem *items, int64_t M);

@@ -10,6 +10,17 @@ typedef float float16v __attribute__((ext_vector_type(16)));
 typedef unsigned uint2v __attribute__((ext_vector_type(2)));
 typedef unsigned uint4v __attribute__((ext_vector_type(4)));
 
+// vmcnt(0) with the other counters left alone (expcnt 7, lgkmcnt 15)
+constexpr int HLQ_WAIT_VM0 = (7 << 4) | (15 << 8);
+
+// 16 bytes per lane from global memory straight into LDS at lds_base + 16 * lane.  Issued as inline
+// assembly so that the compiler's wait-count bookkeeping does not tie later LDS reads (of the other
+// buffer) to it; completion is awaited explicitly (vmcnt) before the barrier that publishes the tile.
+__device__ __forceinline__ void dma_16B_per_lane(const void *gptr, uint32_t lds_base)
+{
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gptr), "s"(lds_base) : "memory", "m0");
+}
+
 // In a plane word, bits p and p+16 are the adjacent weights k0 = 2p, 2p+1 of the word's 32-k block.
 // (w << t) & 0x20002000 isolates pair p at bit 13 of both 16-bit halves: as packed fp16 that is
 // (2^-7 b[2p], 2^-7 b[2p+1]); with 0x40004000 (bit 14) it is (2 b, 2 b).  Position (13 or 14) and
