@@ -236,8 +236,9 @@ HLQ_API hlq_status hlq_set_gemv_path(int path);
  *     tables shared per workgroup, two barriers per step -- and is kept as the method's own formulation
  *     for reference, not as a tuned competitor),
  * 1 = table lookups always,
- * 2 = matrix cores always: for a few rows (M <= 4 at G >= 128, <= 2 at G = 64, 1 at G = 32) the
- *     GEMV kernel of hlq_set_gemv_path(2) with several activation rows per operand, for 5..16 rows on large
+ * 2 = matrix cores always: for a few rows (M <= 4 at G >= 128, <= 2 at G = 64, 1 at G = 32; up to 4 at any G on
+ *     launches of 256 .. 4096 chunk-tiles with K <= 8192 and, at G <= 64, from 14000 on) the
+ *     GEMV kernels of hlq_set_gemv_path(2) with several activation rows, for 5..16 rows on large
  *     problems (G >= 128) the many-rows kernel, otherwise kernels that rebuild W^ in fp16 registers: up to 32 rows
  *     (below 80000 chunk-tiles) the short-M kernel, which cuts K inside a workgroup, else the tiled kernel
  *     (hlq_lut_gemm_batch keeps up to twice as many rows on the GEMV kernel at G <= 64),

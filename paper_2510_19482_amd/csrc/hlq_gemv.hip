@@ -544,9 +544,9 @@ bool cols_wins(long units, int q, int G)
 }
 
 // cpw: forced chunks per wavefront (0: automatic); forced_w likewise.  Returns the wavefronts per workgroup.
-int plan_cols(int count, const HlqDims *dms, int forced_w, int cpw, ColsSplit *out)
+int plan_cols(int count, const HlqDims *dms, int rows, int forced_w, int cpw, ColsSplit *out)
 {
-    const int q = dms[0].q, G = dms[0].G, maxw = hlq_gemv_cols_max_waves(q, G);
+    const int q = dms[0].q, G = dms[0].G, maxw = hlq_gemv_cols_max_waves(q, G, rows);
     long blocks = 0;
     for (int i = 0; i < count; ++i) blocks += cols_blocks(dms[i]);
     // K slices.  One up to sixteen windows (K = 8192: a window per wavefront).  Two up to 32 windows, in which case the sides
@@ -560,7 +560,7 @@ int plan_cols(int count, const HlqDims *dms, int forced_w, int cpw, ColsSplit *o
     long slots = 0;   // of the counter block, of which half is left to arrival counters
     for (int i = 0; i < count; ++i) {
         const int n = dms[i].nchunks, wins = (n + 3) / 4;
-        const bool two = wins > 16 && wins <= 32 && 2L * dms[i].N <= HLQ_WS_ARRIVAL_COUNTERS / 2;
+        const bool two = rows == 1 && wins > 16 && wins <= 32 && 2L * dms[i].N <= HLQ_WS_ARRIVAL_COUNTERS / 2;
         const int per = two ? (wins + 1) / 2 : blocks <= 128 && wins > 32 ? 16 : wins;
         const int slices = (wins + per - 1) / per;
         int cps = (n + slices - 1) / slices;
@@ -570,7 +570,7 @@ int plan_cols(int count, const HlqDims *dms, int forced_w, int cpw, ColsSplit *o
         out[i].cps = cps < n ? cps : n;
         const int w = (out[i].cps + 3) / 4;
         if (w > most_wins) most_wins = w;
-        out[i].pairs = out[i].cps < n && 2 * out[i].cps >= n && slots + 2L * dms[i].N <= HLQ_WS_ARRIVAL_COUNTERS / 2;
+        out[i].pairs = rows == 1 && out[i].cps < n && 2 * out[i].cps >= n && slots + 2L * dms[i].N <= HLQ_WS_ARRIVAL_COUNTERS / 2;
         if (out[i].pairs) slots += 2L * dms[i].N;
     }
     // wavefronts per workgroup: as many as windows, eight or sixteen
@@ -593,14 +593,16 @@ int plan_cols(int count, const HlqDims *dms, int forced_w, int cpw, ColsSplit *o
         one_step += (long)((cols_blocks(dms[i]) + streams - 1) / streams) * slices;
         one_round = one_round && rounds == 1;
     }
-    const int per_cu = (q <= 2 && G >= 64 ? 32 : 24) / W;
+    // several rows (operands of 24 registers a row and more): what is resident is one generation of 16 or 8 wavefronts
+    const int resident = rows == 1 ? 16 : rows == 2 ? 16 : 8;
+    const int per_cu = (rows > 1 ? resident : q <= 2 && G >= 64 ? 32 : 24) / W;
     const bool single = one_round && one_step <= 256L * (per_cu > 0 ? per_cu : 1);
     long steps = 1;
     if (!single)
         for (;; ++steps) {
             long wgs = 0;
             for (int i = 0; i < count; ++i) wgs += (cost[i] + steps - 1) / steps;
-            if (wgs <= 4096 / W || steps >= 40) break;
+            if (wgs <= 256L * resident / W || steps >= 40) break;
         }
     for (int i = 0; i < count; ++i) {
         const int nb = cols_blocks(dms[i]), streams = W / out[i].kw, slices = (dms[i].nchunks + out[i].cps - 1) / out[i].cps;
@@ -700,6 +702,13 @@ struct GemvLaunchShape {
     size_t ws_used;   // bytes of the workspace this plan touches: the counter block and its partial sums
 };
 
+static bool few_rows_win(int count, const HlqGemvItem *items, int64_t rows)
+{
+    HlqDims dms[HLQ_MAX_BATCH];
+    for (int i = 0; i < count; ++i) dms[i] = items[i].dm;
+    return hlq_gemm_few_wins(count, dms, rows);
+}
+
 static hlq_status plan_gemv_batch(int count, const HlqGemvItem *items, hlq_out_dtype out, void *ws, GemvBatch &b,
                                   GemvLaunchShape &ls)
 {
@@ -710,16 +719,16 @@ static hlq_status plan_gemv_batch(int count, const HlqGemvItem *items, hlq_out_d
     const int rows = items[0].M;
     for (int i = 1; i < count; ++i)
         if (items[i].M != rows) return HLQ_ERR_UNSUPPORTED;
-    if (rows < 1 || rows > hlq_gemm_mx_rows_per_pass(items[0].dm.G)) return HLQ_ERR_UNSUPPORTED;
+    if (rows < 1 || (rows > HLQ_COLS_ROWS && rows > hlq_gemm_mx_rows_per_pass(items[0].dm.G))) return HLQ_ERR_UNSUPPORTED;
     const bool mx = use_mx() || rows > 1;   // several activation rows exist in the matrix-core kernels only
-    const bool cols = mx && rows == 1 && cols_wins(units, items[0].dm.q, items[0].dm.G);
+    const bool cols = mx && (rows == 1 ? cols_wins(units, items[0].dm.q, items[0].dm.G) : few_rows_win(count, items, rows));
     // more rows than one operand of the GEMV kernel holds: the many-rows kernel (terms chained through the
     // accumulator, activations converted once per workgroup), where it exists for this group size
-    bool rowsk = rows > hlq_gemv_mx_rows_per_set(items[0].dm.G) && rows <= hlq_gemm_rows_max(items[0].dm.G) &&
+    bool rowsk = !cols && rows > hlq_gemv_mx_rows_per_set(items[0].dm.G) && rows <= hlq_gemm_rows_max(items[0].dm.G) &&
                  rows <= hlq_gemm_mx_rows_per_pass(items[0].dm.G);
     // three or four rows (which the GEMV kernel's one row set also holds): the one-operand instantiation of the
     // many-rows kernel where its pre-pass pays
-    if (!rowsk && rows >= 3 && rows <= hlq_gemm_rows_max(items[0].dm.G) &&
+    if (!cols && !rowsk && rows >= 3 && rows <= hlq_gemm_rows_max(items[0].dm.G) &&
         (hlq_gemm_rows_all() || hlq_gemm_rows_wins_few(units, items[0].dm.q, rows)))
         rowsk = true;
     if (rowsk) {
@@ -762,7 +771,7 @@ static hlq_status plan_gemv_batch(int count, const HlqGemvItem *items, hlq_out_d
     if (cols) {
         HlqDims dms[HLQ_MAX_BATCH];
         for (int i = 0; i < count; ++i) dms[i] = items[i].dm;
-        pl.W = plan_cols(count, dms, pl.W, pl.cpw, split);
+        pl.W = plan_cols(count, dms, rows, pl.W, pl.cpw, split);
     }
 
     b.count = count;
@@ -881,7 +890,7 @@ hlq_status hlq_launch_gemv_batch(int count, const HlqGemvItem *items, hlq_out_dt
         return hlq_hip_status(hipGetLastError());
     }
     if (ls.cols) {
-        s = hlq_launch_gemv_cols(b, blk, ls.W, q, G, st);
+        s = hlq_launch_gemv_cols(b, blk, ls.W, ls.rows, q, G, st);
         if (s != HLQ_OK) return s;
         return hlq_hip_status(hipGetLastError());
     }
@@ -971,6 +980,29 @@ int hlq_gemm_mx_rows_per_pass(int G)
     return many > two_sets ? many : two_sets;
 }
 
+// Two to four rows on the kernel of one row (hlq_gemv_cols.hip) instead of the few-rows instantiation of the 64-column one, the
+// many-rows or the short-M kernel.  Its operands take 24 registers a row, which leaves eight wavefronts on a compute unit: the
+// better one where a launch is one step or two of all its wavefronts, and where the alternative is weights rebuilt in
+// fp16 or two row sets (G <= 64).  us, alternative / this one:
+//   G >= 128, 2 rows:   4096 x 1024 (512 chunk-tiles) q = 2 6.7 / 5.2,  4096 x 4096 7.4 / 5.5, q = 4 8.4 / 6.1,  4096 x 8192 7.5 / 7.5, q = 4
+//                       10.0 / 8.5,  4096 x 14336 7.8 / 11.5
+//             4 rows:   4096 x 1024 q = 4 9.8 / 7.8,  4096 x 4096 q = 2 9.7 / 7.5,  8192 x 4096 13.4 / 11.3,  4096 x 14336, q = 4 13.3 / 13.6
+//   short or deep:      1024 x 512, q = 2, 2 rows 4.3 / 4.7;  14336 x 1024 10.8 / 11.5
+//   G = 64, 4 rows:     8B layer q = 2 33 / 28, q = 4 50 / 43;  8192 x 57344, q = 2 66 / 47;  4096 x 14336, q = 2 10.0 / 11.6
+//   G = 32:             8192 x 57344, q = 4, 2 rows 109 / 79;  8B layer, q = 2, 4 rows 41 / 36
+bool hlq_gemm_few_wins(int count, const HlqDims *dms, int64_t rows)
+{
+    if (rows < 2 || rows > HLQ_COLS_ROWS || (rows > 2 && hlq_gemm_rows_all())) return false;
+    long units = 0;
+    int deepest = 0;
+    for (int i = 0; i < count; ++i) {
+        units += (long)dms[i].ntiles * dms[i].nchunks;
+        deepest = dms[i].nchunks > deepest ? dms[i].nchunks : deepest;
+    }
+    if (rows > hlq_gemv_mx_rows_per_set(dms[0].G) && units >= 14000) return true;
+    return units >= 256 && units <= 4096 && deepest <= 64;
+}
+
 // Many-rows kernel or, with weights rebuilt in fp16, the short-M kernel (hlq_gemm_short.hip) for 5..16 rows (G >= 128)?  The
 // many-rows kernel keeps scales in fp32: a call that it has been taking stays with it although the other one is faster
 // below some 14000 chunk-tiles.  Single calls and grouped launches, us (many-rows / short-M):
@@ -1004,6 +1036,7 @@ bool hlq_gemm_batch_on_mx(int count, const HlqGemvItem *items, int64_t M)
 {
     if (count < 1 || M < 1) return false;
     const int G = items[0].dm.G;
+    if (few_rows_win(count, items, M)) return true;
     if (M > hlq_gemm_mx_rows_per_pass(G)) return false;
     if (M <= hlq_gemv_mx_rows_per_set(G) || hlq_gemm_rows_max(G) == 0 || hlq_gemm_rows_all()) return true;
     long units = 0;
@@ -1013,7 +1046,7 @@ bool hlq_gemm_batch_on_mx(int count, const HlqGemvItem *items, int64_t M)
 
 size_t hlq_gemm_mx_partial_bytes(const HlqDims &dm, int64_t M)
 {
-    const int cap = hlq_gemm_mx_rows_per_pass(dm.G);
+    const int pass = hlq_gemm_mx_rows_per_pass(dm.G), cap = pass > HLQ_COLS_ROWS ? pass : HLQ_COLS_ROWS;
     const int64_t rows = M < cap ? M : cap;
     // slices are never shorter than 4 chunks here either; the many-rows kernel adds the operand form of the activations
     return (size_t)rows * hlq_gemv_partial_bytes(dm) + hlq_gemm_rows_xt_bytes(dm, 16) + 256;
@@ -1023,7 +1056,7 @@ size_t hlq_gemm_mx_partial_bytes(const HlqDims &dm, int64_t M)
 hlq_status hlq_launch_gemm_mx_rows(const HlqDims &dm, const void *packed, const uint16_t *X, int64_t M, int64_t ldx,
                                    void *Y, int64_t ldy, hlq_out_dtype out, void *ws, hipStream_t st)
 {
-    if (M < 1 || M > hlq_gemm_mx_rows_per_pass(dm.G)) return HLQ_ERR_UNSUPPORTED;
+    if (M < 1) return HLQ_ERR_UNSUPPORTED;
     HlqGemvItem it;
     it.dm = dm;
     it.packed = packed;

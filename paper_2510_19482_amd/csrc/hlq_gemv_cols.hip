@@ -1,4 +1,4 @@
-// hlq_lut_gemv / hlq_lut_gemv_batch, matrix-core formulation for one activation row (Sec. 2, paragraph
+// hlq_lut_gemv / hlq_lut_gemv_batch, matrix-core formulation for one activation row, and for two to four (Sec. 2, paragraph
 // "Bit-Serial LUT-Based GEMM", and App. B; weights in the format of Eq. 3):
 //
 //   y[n] = sum_groups ( sum_j s_j[g,n] * <b_j[.,n], x>_g  +  z[g,n] * sum_g(x) )
@@ -31,6 +31,12 @@
 // four wavefronts at a time instead of one after the other: no gain on long launches; 80 registers (six wavefronts on a
 // SIMD): spills, 10-20 % slower.
 //
+// Two and four rows (small launches, see hlq_gemm_few_wins): every row has four operands of its own, which share the expanded
+// plane words.  They are bf6 terms as in hlq_gemm_rows.hip -- 24 registers a row and not 32, 16 clocks an instruction and not
+// 32 -- with the matrix core's own scale per word, so the window's largest magnitude is not needed; made of the same
+// eight activations per lane, through the packed conversions (at one row their latency, 72 clocks a conversion, is longer than
+// what bf8 terms take).  Relative error of fp32 results at 4096 x 4096, q = 4, 4 rows, 1 % outliers: 1.6e-5 -> 4e-6.
+//
 // Work split.  A workgroup of W wavefronts owns adjacent column blocks and one K slice; the windows of the slice are
 // dealt out to the wavefronts, whose results meet in LDS.  K slices of different workgroups meet in the workspace: two
 // in an exchange per column, more as in the other GEMV kernels (partial sums, an arrival counter per workgroup column, the
@@ -38,21 +44,38 @@
 // workgroups run on one XCD (they go to the eight XCDs in turn, so the block order is dealt out to match).
 #include "hlq_gemv_common.h"
 
+#include <type_traits>
+
 namespace {
 
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 typedef unsigned short ushort2_t __attribute__((ext_vector_type(2)));
+typedef _Float16 half32_t __attribute__((ext_vector_type(32)));
+typedef unsigned int uint6v __attribute__((ext_vector_type(6)));
 typedef int int8v __attribute__((ext_vector_type(8)));
 typedef unsigned int uint2v __attribute__((ext_vector_type(2)));
 typedef float float4v __attribute__((ext_vector_type(4)));
 // the activation codes are written as 64-bit words and read back as 128-bit ones
 typedef unsigned int uint2a __attribute__((ext_vector_type(2), may_alias));
 typedef uint16_t __attribute__((may_alias)) u16_alias;
+typedef uint32_t __attribute__((may_alias)) u32_alias;
 typedef int int4a __attribute__((ext_vector_type(4), may_alias));
 
+// NR: activation rows carried (1, 2 or 4)
+template <int NR>
 struct ColsProbs {
-    ColsProb p[HLQ_MAX_BATCH];
+    std::conditional_t<NR == 1, ColsProb, ColsRowsProb> p[HLQ_MAX_BATCH];
 };
+
+// compile-time loop: body(std::integral_constant<int, 0>), ..., body(std::integral_constant<int, N - 1>)
+template <int N, class F>
+__device__ __forceinline__ void unrolled(F &&body)
+{
+    if constexpr (N > 0) {
+        unrolled<N - 1>(body);
+        body(std::integral_constant<int, N - 1>{});
+    }
+}
 
 template <int CTRL, int ROWMASK = 0xf>
 __device__ __forceinline__ uint32_t max_dpp(uint32_t v)
@@ -74,26 +97,32 @@ struct ColsRegs {
 
 // LDS per wavefront: activation codes [term][chunk][word][32], the terms 16 bytes apart from a multiple of the bank
 // count -- the same bytes hold a step's scales while no operands are being made -- then 128 zero bytes
-constexpr int COLS_TERM = 4 * 128 + 16;
-template <int Q, int G>
-constexpr int cols_zero_at() { return 4 * COLS_TERM > 1024 * ColsRegs<Q, G>::NM ? 4 * COLS_TERM : 1024 * ColsRegs<Q, G>::NM; }
-template <int Q, int G>
-constexpr int cols_wave_lds() { return cols_zero_at<Q, G>() + 128 + 64; }
+// (two and four rows: [row][term][chunk][word][24 bytes], and behind the zeros the scales [row][chunk][word])
+constexpr int COLS_TERM = 4 * 128 + 16, COLS_CODES = 96;
+template <int Q, int G, int NR>
+constexpr int cols_zero_at()
+{
+    constexpr int codes = NR == 1 ? 4 * COLS_TERM : NR * 16 * COLS_CODES, scales = 1024 * ColsRegs<Q, G>::NM;
+    return codes > scales ? codes : scales;
+}
+template <int Q, int G, int NR>
+constexpr int cols_wave_lds() { return cols_zero_at<Q, G, NR>() + 128 + 64; }
 
-// wavefronts per workgroup: sixteen, i.e. at most 128 registers; q = 4 with groups of 32 would spill at that
-constexpr int cols_max_waves(int q, int G) { return q == 4 && G == 32 ? 8 : 16; }
+// wavefronts per workgroup: sixteen, i.e. at most 128 registers; q = 4 with groups of 32 would spill at that, and so would
+// the operands of two and four rows
+constexpr int cols_max_waves(int q, int G, int NR) { return NR > 1 || (q == 4 && G == 32) ? 8 : 16; }
 
 // ONE: no wavefront of the launch has more than one step (nothing is loaded ahead)
-template <int Q, int G, bool ONE>
-__global__ void __launch_bounds__(64 * cols_max_waves(Q, G))
-hlq_gemv_cols_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32, const ColsProbs probs)
+template <int Q, int G, bool ONE, int NR>
+__global__ void __launch_bounds__(64 * cols_max_waves(Q, G, NR))
+hlq_gemv_cols_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32, const ColsProbs<NR> probs)
 {
     using Regs = ColsRegs<Q, G>;
-    constexpr int WAVE_LDS = cols_wave_lds<Q, G>(), ZERO_AT = cols_zero_at<Q, G>();
+    constexpr int WAVE_LDS = cols_wave_lds<Q, G, NR>(), ZERO_AT = cols_zero_at<Q, G, NR>();
     constexpr int SEG = Regs::SEG, CHAIN = 4 / SEG;   // words (matrix-core instructions) per quant group of a chunk
     extern __shared__ __attribute__((aligned(256))) char lds[];
 
-    ColsProb P = probs.p[gemv_problem_of(bb_lo, bb_hi, (int)blockIdx.x)];
+    auto P = probs.p[gemv_problem_of(bb_lo, bb_hi, (int)blockIdx.x)];
     asm volatile("" : "+s"(P.slice_magic), "+s"(P.cb_rem));   // with the others, in one burst: not loaded where first used
     const int local = (int)blockIdx.x - P.blk_begin;
     int tg = P.nslices > 1 ? (int)__umulhi((unsigned)local, P.slice_magic) : local;
@@ -122,7 +151,7 @@ hlq_gemv_cols_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32, co
     const int full_cbs = (P.N & 63) ? P.N >> 6 << 2 : 0x7fffffff;   // column blocks in tiles of full width
 
     char *xt = lds + wave * WAVE_LDS;
-    float *red = (float *)(lds + W * WAVE_LDS);             // [column block][part][16]
+    float *red = (float *)(lds + W * WAVE_LDS);             // [column block][part][row][16]
 
     // ---- loads -----------------------------------------------------------------------------------------------
     // A step's loads go through descriptors that start at the window's first record, at the column block, and end with the
@@ -185,12 +214,17 @@ hlq_gemv_cols_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32, co
     // activations of a window: lane (chunk g, word i, register r) takes the pairs 32 i + 2 r + 8 m, m = 0..3, which are
     // the eight codes of expansion register r (weight k0 = 8 (n & 3) + 2 r + (n >> 2) is nibble n)
     const int xi = (lane >> 2) & 3, xr = lane & 3;
-    uint32_t xw[4];
+    uint32_t xw[NR][4];
     auto load_x = [&](int win) {
         const int cw = sbeg + 4 * win;
-        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(P.x + (size_t)cw * 128), 0, (send - cw) * 256, 0x00020000);
 #pragma unroll
-        for (int m = 0; m < 4; ++m) xw[m] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, g * 256 + xi * 64 + xr * 4 + 16 * m, 0, 0);
+        for (int row = 0; row < NR; ++row) {
+            const uint16_t *x = P.x + (size_t)cw * 128;
+            if constexpr (NR > 1) x += (size_t)min(row, P.M - 1) * P.ldx;   // (a row more than the call has: dropped at the end)
+            const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)x, 0, (send - cw) * 256, 0x00020000);
+#pragma unroll
+            for (int m = 0; m < 4; ++m) xw[row][m] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, g * 256 + xi * 64 + xr * 4 + 16 * m, 0, 0);
+        }
     };
 
         Regs R;
@@ -212,13 +246,97 @@ hlq_gemv_cols_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32, co
     const char *a_zero = xt + ZERO_AT, *a_data = xt + a_t * COLS_TERM + a_sg * 128 + 16 * (g & 1);
     const char *a_lo = a_on && a_sg < 2 ? a_data : a_zero, *a_hi = a_on && a_sg >= 2 ? a_data : a_zero;
     if (lane < 8) ((int4a *)(xt + ZERO_AT))[lane] = (int4a){0, 0, 0, 0};
+    // several rows: row (lane & 15) = 4 sg + t holds the codes of chunk sg, which are k block sg: in lane group g == sg
+    const char *r_data = g == a_sg ? xt + (a_t * 4 + a_sg) * COLS_CODES : xt + ZERO_AT;
     auto expand = [](uint32_t w) -> int8v {   // plane word -> 32 fp4 codes (bit 4p+r -> nibble p of register r)
         return (int8v){(int)(w & 0x11111111u), (int)(w & 0x22222222u), (int)(w & 0x44444444u),
                        (int)((w >> 1) & 0x44444444u), 0, 0, 0, 0};
     };
     const float4v zero4 = {0.f, 0.f, 0.f, 0.f};
-    int8v A[4];
-    float xs[SEG], yscale = 0.f;
+    int8v A[NR][4];       // several rows: six registers of each are used
+    int ascale[NR];       // several rows: byte i: the scale of word i
+    float xs[NR][SEG], yscale = 0.f;
+    // one matrix-core instruction: word i of the activations of a row and a plane operand
+    auto mfma = [&](auto ic, int row, const int8v &B, const float4v &d) -> float4v {
+        constexpr int i = decltype(ic)::value;
+        if constexpr (NR == 1) return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(A[0][i], B, d, 1, 4, 0, 0, 0, 0);
+        else return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(A[row][i], B, d, 3, 4, i, ascale[row], 0, 0x7f7f7f7f);
+    };
+    auto sum_groups = [&]() {
+        const int8v ones = {0x11111111, 0x22222222, 0x44444444, 0x44444444, 0, 0, 0, 0};
+#pragma unroll
+        for (int row = 0; row < NR; ++row)
+            unrolled<SEG>([&](auto sg) {   // activation sums of the quant groups, for the zero points
+                float4v d = zero4;
+                unrolled<CHAIN>([&](auto i) { d = mfma(std::integral_constant<int, decltype(sg)::value * CHAIN + decltype(i)::value>{}, row, ones, d); });
+                xs[row][sg] = (d[0] + d[1]) + (d[2] + d[3]);
+            });
+    };
+    // Several rows: the terms of the many-rows kernel (hlq_gemm_rows.hip), four bf6 codes per activation with one power of two
+    // per 32 activations, i.e. per word; a lane makes the eight codes of one expansion register for every row.
+    auto make_rows = [&]() {
+        half32_t v;
+        const int weight = xr < 3 ? xr + 1 : 3;
+        char *scales = xt + ZERO_AT + 128;
+#pragma unroll
+        for (int row = 0; row < NR; ++row) {
+            uint32_t mx = 0;
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+                mx = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(ushort2_t, mx), __builtin_bit_cast(ushort2_t, xw[row][m] & 0x7fff7fffu)));
+            const uint32_t e = max(mx & 0xffffu, mx >> 16) >> 10;
+            // biased exponent of the word's largest weighted magnitude, plus four; an infinity or a NaN beyond all of them
+            uint32_t ew = max(e, 1u) - (uint32_t)weight + 4u + (e == 31u ? 256u : 0u);
+            ew = max_dpp<0xB1>(ew);          // quad_perm [1,0,3,2]
+            ew = max_dpp<0x4E>(ew);          // quad_perm [2,3,0,1]
+            const int s = 18 + 4 - (int)(ew & 0xffu), sr = s - weight, k1 = sr / 2, k2 = sr - k1;
+            const _Float16 f1 = __builtin_bit_cast(_Float16, (uint16_t)((15 + k1) << 10)), f2 = __builtin_bit_cast(_Float16, (uint16_t)((15 + k2) << 10));
+#pragma unroll
+            for (int n = 0; n < 4; ++n) {   // codes 2 n, 2 n + 1: the even activations of the dwords, then the odd ones
+                const uint32_t a = xw[row][2 * (n & 1)], b = xw[row][2 * (n & 1) + 1];
+                const half2_t p = __builtin_bit_cast(half2_t, __builtin_amdgcn_perm(b, a, n < 2 ? 0x05040100u : 0x07060302u)) * (half2_t){f1, f1} * (half2_t){f2, f2};
+                v[8 * row + 2 * n] = p.x;
+                v[8 * row + 2 * n + 1] = p.y;
+                if constexpr (NR == 2) {   // the conversions take 32
+                    v[16 + 8 * row + 2 * n] = (_Float16)0.0f;
+                    v[16 + 8 * row + 2 * n + 1] = (_Float16)0.0f;
+                }
+            }
+            if (xr == 0) ((uint8_t *)scales)[(row * 4 + g) * 4 + xi] = (uint8_t)(ew >= 256u ? 255 : 127 + 2 - s);
+        }
+        // 48 bits a row and term at byte 6 xr of the word's 24: a 32-bit and a 16-bit store, in this order or the other
+        const bool odd = xr & 1;
+        char *dst = xt + g * COLS_CODES + xi * 24 + 6 * xr;
+        char *dst32 = dst + (odd ? 2 : 0), *dst16 = dst + (odd ? 0 : 4);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const uint6v c = __builtin_amdgcn_cvt_scalef32_pk32_bf6_f16(v, 1.0f);
+            if (t < 3) v = (v - __builtin_amdgcn_cvt_scalef32_pk32_f16_bf6(c, 1.0f)) * (_Float16)16.0f;   // exact
+#pragma unroll
+            for (int row = 0; row < NR; ++row) {
+                const uint32_t w0 = c[3 * row / 2], w1 = c[3 * row / 2 + 1];
+                const uint32_t low = row & 1 ? __builtin_amdgcn_alignbit(w1, w0, 16) : w0, high = row & 1 ? w1 >> 16 : w1 & 0xffffu;
+                const int at = (row * 4 + t) * 4 * COLS_CODES;
+                *(u32_alias *)(dst32 + at) = __builtin_amdgcn_alignbit(high, low, odd ? 16 : 0);
+                *(u16_alias *)(dst16 + at) = (uint16_t)(odd ? low : high);
+            }
+        }
+#pragma unroll
+        for (int row = 0; row < NR; ++row) {
+            int4a q[6];
+#pragma unroll
+            for (int n = 0; n < 6; ++n) q[n] = *(const int4a *)(r_data + (g == a_sg ? row * 16 * COLS_CODES : 0) + 16 * n);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+#pragma unroll
+                for (int k = 0; k < 6; ++k) A[row][i][k] = q[(6 * i + k) / 4][(6 * i + k) % 4];
+                A[row][i][6] = A[row][i][7] = 0;
+            }
+            // term t is 4 t binary places further down (a NaN scale stays one in term 0); where there are no codes any scale will do
+            ascale[row] = g == a_sg ? (int)(((const u32_alias *)scales)[row * 4 + a_sg] - 0x04040404u * a_t) : 0x7f7f7f7f;
+        }
+        sum_groups();
+    };
     auto make_operands = [&]() {
         // largest magnitude of the window -> power-of-two scale (biased fp16 exponent e: |x| < 2^(e-14), scaled by 2^(29-e)
         // below 2^15).  Plane codes are worth 1/2, 1, 2, 2 by register: weights 1/2, 1/4, 1/8, 1/8 make every product
@@ -226,7 +344,7 @@ hlq_gemv_cols_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32, co
         uint32_t mx = 0;
 #pragma unroll
         for (int m = 0; m < 4; ++m)
-            mx = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(ushort2_t, mx), __builtin_bit_cast(ushort2_t, xw[m] & 0x7fff7fffu)));
+            mx = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(ushort2_t, mx), __builtin_bit_cast(ushort2_t, xw[0][m] & 0x7fff7fffu)));
         mx = max(mx & 0xffffu, mx >> 16);
         mx = max_dpp<0xB1>(mx);          // quad_perm [1,0,3,2]
         mx = max_dpp<0x4E>(mx);          // quad_perm [2,3,0,1]
@@ -241,7 +359,7 @@ hlq_gemv_cols_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32, co
         yscale = __builtin_bit_cast(float, (uint32_t)(127 + 2 - 29 + e) << 23);   // 4 * 2^(e-29)
         half2_t p[4];
 #pragma unroll
-        for (int m = 0; m < 4; ++m) p[m] = (__builtin_bit_cast(half2_t, xw[m]) * (half2_t){f1, f1}) * (half2_t){f2, f2};   // exact
+        for (int m = 0; m < 4; ++m) p[m] = (__builtin_bit_cast(half2_t, xw[0][m]) * (half2_t){f1, f1}) * (half2_t){f2, f2};   // exact
         char *dst = xt + g * 128 + xi * 32 + xr * 8;
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
@@ -260,16 +378,9 @@ hlq_gemv_cols_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32, co
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int4a lo = *(const int4a *)(a_lo + 32 * i), hi = *(const int4a *)(a_hi + 32 * i);
-            A[i] = (int8v){lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+            A[0][i] = (int8v){lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
         }
-        const int8v ones = {0x11111111, 0x22222222, 0x44444444, 0x44444444, 0, 0, 0, 0};
-#pragma unroll
-        for (int sg = 0; sg < SEG; ++sg) {   // activation sums of the quant groups, for the zero points
-            float4v d = zero4;
-#pragma unroll
-            for (int i = 0; i < CHAIN; ++i) d = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(A[sg * CHAIN + i], ones, d, 1, 4, 0, 0, 0, 0);
-            xs[sg] = (d[0] + d[1]) + (d[2] + d[3]);
-        }
+        sum_groups();
     };
 
     // ---- steps ---------------------------------------------------------------------------------------------------
@@ -277,11 +388,14 @@ hlq_gemv_cols_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32, co
     int win = wbeg, cb = s0;
     auto step = [&]() {
         if (cb == s0) {
-            make_operands();
+            if constexpr (NR == 1) make_operands();
+            else make_rows();
             if (win + 1 < wend) load_x(win + 1);
         }
         __builtin_amdgcn_sched_barrier(0);   // the operands are made before anything waits for the weights
-        float y = 0.f;
+        float y[NR];
+#pragma unroll
+        for (int row = 0; row < NR; ++row) y[row] = 0.f;
         uint16_t mt[SEG][Q + 1];
 #pragma unroll
         for (int i = 0; i < Regs::NM; ++i) ((int4a *)xt)[64 * i + lane] = R.mt[i];
@@ -290,48 +404,63 @@ hlq_gemv_cols_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32, co
         for (int sg = 0; sg < SEG; ++sg) {
 #pragma unroll
             for (int r = 0; r <= Q; ++r) mt[sg][r] = ((const u16_alias *)xt)[(g * Regs::ROWS + sg * (Q + 1) + r) * 16 + c];
-            y += scale(mt[sg][Q]) * xs[sg];
+#pragma unroll
+            for (int row = 0; row < NR; ++row) y[row] += scale(mt[sg][Q]) * xs[row][sg];
         }
         constexpr int NI = 4 * Q;   // item n: plane n / 4, word n % 4
         int8v B = expand(R.w[0][0]);
-        float4v d[2];
+        float4v d[2][NR];
         __builtin_amdgcn_sched_barrier(0);
+        auto apply = [&](int done) {
+            const float sc = scale(mt[done % SEG][done / SEG]);
 #pragma unroll
-        for (int n = 0; n < NI; ++n) {
-            const int chain = n / CHAIN;   // (plane, segment)
-            d[chain & 1] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(A[n % 4], B, n % CHAIN ? d[chain & 1] : zero4, 1, 4, 0, 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
+            for (int row = 0; row < NR; ++row) {
+                const float4v &f = d[done & 1][row];
+                y[row] += sc * ((f[0] + f[1]) + (f[2] + f[3]));
+            }
+        };
+        unrolled<NI>([&](auto nc) {
+            constexpr int n = decltype(nc)::value, chain = n / CHAIN;   // (plane, segment)
+#pragma unroll
+            for (int row = 0; row < NR; ++row) d[chain & 1][row] = mfma(std::integral_constant<int, n % 4>{}, row, B, n % CHAIN ? d[chain & 1][row] : zero4);
+            if constexpr (NR == 1) __builtin_amdgcn_sched_barrier(0);
             if (n + 1 < NI) {
                 uint32_t &w = R.w[(n + 1) / 4][(n + 1) % 4];
                 asm volatile("" : "+v"(w));   // expanded here and not earlier, where it would hold four more registers
                 B = expand(w);
             }
             if (!ONE && n % 4 == 2) load_plane(R, n / 4);   // the plane's last word has been expanded: the next step's
-            if (n >= CHAIN && n % CHAIN == (CHAIN > 1 ? 1 : 0)) {
-                const int done = chain - 1;
-                const float4v &f = d[done & 1];
-                y += scale(mt[done % SEG][done / SEG]) * ((f[0] + f[1]) + (f[2] + f[3]));
-            }
+            if (n >= CHAIN && n % CHAIN == (CHAIN > 1 ? 1 : 0)) apply(chain - 1);
             __builtin_amdgcn_sched_barrier(0);
-        }
-        {
-            constexpr int done = NI / CHAIN - 1;
-            const float4v &f = d[done & 1];
-            y += scale(mt[done % SEG][done / SEG]) * ((f[0] + f[1]) + (f[2] + f[3]));
-        }
+        });
+        apply(NI / CHAIN - 1);
         // the window's four chunks (lane groups)
         auto fold = [](const uint2v &v) -> float {
             const uint32_t own = v.x, other = v.y;
             return __builtin_bit_cast(float, own) + __builtin_bit_cast(float, other);
         };
-        const uint32_t y1 = __builtin_bit_cast(uint32_t, y);
-        y = fold(__builtin_amdgcn_permlane32_swap(y1, y1, false, false));
-        const uint32_t y2 = __builtin_bit_cast(uint32_t, y);
-        y = fold(__builtin_amdgcn_permlane16_swap(y2, y2, false, false)) * yscale;
-        float *slot = red + ((cb - cb0) * KW + part) * 16 + c;
-        if (lane < 16) {
-            if (win > wbeg) y += *slot;
-            *slot = y;
+#pragma unroll
+        for (int row = 0; row < NR; ++row) {
+            const uint32_t y1 = __builtin_bit_cast(uint32_t, y[row]);
+            y[row] = fold(__builtin_amdgcn_permlane32_swap(y1, y1, false, false));
+            const uint32_t y2 = __builtin_bit_cast(uint32_t, y[row]);
+            y[row] = fold(__builtin_amdgcn_permlane16_swap(y2, y2, false, false));
+        }
+        if constexpr (NR == 1) {
+            y[0] *= yscale;
+            float *slot = red + ((cb - cb0) * KW + part) * 16 + c;
+            if (lane < 16) {
+                if (win > wbeg) y[0] += *slot;
+                *slot = y[0];
+            }
+        } else {   // lane group g stores row g
+            float v = g & 1 ? y[1] : y[0];
+            if constexpr (NR == 4) v = g & 2 ? (g & 1 ? y[3] : y[2]) : v;
+            float *slot = red + (((cb - cb0) * KW + part) * NR + (g & (NR - 1))) * 16 + c;
+            if (g < NR) {
+                if (win > wbeg) v += *slot;
+                *slot = v;
+            }
         }
         if (!ONE) advance();
         if (++cb == s1) {
@@ -342,18 +471,47 @@ hlq_gemv_cols_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32, co
     if (steps > 0) {
         for (int s = 0; s < (ONE ? 1 : steps); ++s) step();
     } else if (wend == wbeg) {   // no window: nothing to add
-        for (int i = lane; i < (s1 - s0) * 16; i += 64) red[((s0 - cb0 + (i >> 4)) * KW + part) * 16 + (i & 15)] = 0.f;
+        for (int i = lane; i < (s1 - s0) * 16 * NR; i += 64) red[((s0 - cb0 + i / (16 * NR)) * KW + part) * 16 * NR + i % (16 * NR)] = 0.f;
     }
     __syncthreads();
 
     // ---- add the wavefronts' windows, store ---------------------------------------------------------------------
     const int cols = min(16 * (cb1 - cb0), P.N - 16 * cb0);
-    if (P.nslices == 1) {
-        for (int i = tid; i < cols; i += 64 * W) {
-            float v = 0.f;
-            for (int w2 = 0; w2 < KW; ++w2) v += red[((i >> 4) * KW + w2) * 16 + (i & 15)];
-            store_out(P.y, (size_t)16 * cb0 + i, v, out_f32);
+    // sum of the wavefronts' windows: column i of the workgroup's, one of the rows
+    auto total = [&](int i, int row) -> float {
+        float v = 0.f;
+        for (int w2 = 0; w2 < KW; ++w2) v += red[(((i >> 4) * KW + w2) * NR + row) * 16 + (i & 15)];
+        return v;
+    };
+    if constexpr (NR > 1) {
+        if (P.nslices == 1) {
+            for (int row = 0; row < P.M; ++row)
+                for (int i = tid; i < cols; i += 64 * W) store_out(P.y, (size_t)row * P.ldy + (size_t)16 * cb0 + i, total(i, row), out_f32);
+            return;
         }
+        // as for one row below, with a row of partial sums for every row
+        if (wave != 0) return;
+        const size_t n = (size_t)16 * cb0 + lane;
+        if (lane < cols)
+            for (int row = 0; row < P.M; ++row)
+                __hip_atomic_store(&P.part[((size_t)slice * P.M + row) * P.N + n], total(lane, row), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        int old = 0;
+        if (lane == 0) old = __hip_atomic_fetch_add(&P.cnt[tg], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        old = __builtin_amdgcn_readfirstlane(old);
+        if (old != P.nslices - 1) return;
+        if (lane < cols)
+            for (int row = 0; row < P.M; ++row) {
+                float a = 0.f;
+                for (int sl = 0; sl < P.nslices; ++sl)
+                    a += __hip_atomic_load(&P.part[((size_t)sl * P.M + row) * P.N + n], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                store_out(P.y, (size_t)row * P.ldy + n, a, out_f32);
+            }
+        if (lane == 0) __hip_atomic_store(&P.cnt[tg], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return;
+    } else {
+    if (P.nslices == 1) {
+        for (int i = tid; i < cols; i += 64 * W) store_out(P.y, (size_t)16 * cb0 + i, total(i, 0), out_f32);
         return;
     }
     // K in two slices: every column has a 64-bit slot that is zero between launches.  Each side swaps its sum in, marked in
@@ -361,8 +519,7 @@ hlq_gemv_cols_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32, co
     // trip to device memory, where partial sums and a counter take three.
     if (P.pairs) {
         for (int i = tid; i < cols; i += 64 * W) {
-            float v = 0.f;
-            for (int w2 = 0; w2 < KW; ++w2) v += red[((i >> 4) * KW + w2) * 16 + (i & 15)];
+            const float v = total(i, 0);
             unsigned long long *slot = (unsigned long long *)P.cnt + 16 * cb0 + i;
             const unsigned long long mine = 1ull << 32 | __builtin_bit_cast(uint32_t, v);
             const unsigned long long met = __hip_atomic_exchange(slot, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -379,9 +536,7 @@ hlq_gemv_cols_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32, co
     const bool col_ok = lane < cols;
     const size_t n = (size_t)16 * cb0 + lane;
     if (col_ok) {
-        float v = 0.f;
-        for (int w2 = 0; w2 < KW; ++w2) v += red[((lane >> 4) * KW + w2) * 16 + (lane & 15)];
-        __hip_atomic_store(&P.part[(size_t)slice * P.N + n], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&P.part[(size_t)slice * P.N + n], total(lane, 0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     int old = 0;
@@ -403,39 +558,55 @@ hlq_gemv_cols_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32, co
         store_out(P.y, n, a, out_f32);
     }
     if (lane == 0) __hip_atomic_store(&P.cnt[tg], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+template <int Q, int G, int NR>
+void launch_rows(const GemvBatch &b, unsigned nblocks, int W, bool one, int slots, hipStream_t st)
+{
+    const size_t lds = (size_t)W * cols_wave_lds<Q, G, NR>() + (size_t)slots * 64 * NR;
+    const int4v lo = {b.blk_begin[0], b.blk_begin[1], b.blk_begin[2], b.blk_begin[3]};
+    const int4v hi = {b.blk_begin[4], b.blk_begin[5], b.blk_begin[6], b.blk_begin[7]};
+    ColsProbs<NR> probs;
+    for (int i = 0; i < HLQ_MAX_BATCH; ++i) {
+        (ColsProb &)probs.p[i] = b.cp[i];
+        if constexpr (NR > 1) {
+            probs.p[i].M = b.p[i].M;
+            probs.p[i].ldx = b.p[i].ldx;
+            probs.p[i].ldy = b.p[i].ldy;
+        }
+    }
+    if (one) hlq_gemv_cols_kernel<Q, G, true, NR><<<nblocks, 64 * W, lds, st>>>(lo, hi, b.out_f32, probs);
+    else hlq_gemv_cols_kernel<Q, G, false, NR><<<nblocks, 64 * W, lds, st>>>(lo, hi, b.out_f32, probs);
 }
 
 template <int Q, int G>
-void launch_qg(const GemvBatch &b, unsigned nblocks, int W, bool one, int slots, hipStream_t st)
+void launch_qg(const GemvBatch &b, unsigned nblocks, int W, int rows, bool one, int slots, hipStream_t st)
 {
-    const size_t lds = (size_t)W * cols_wave_lds<Q, G>() + (size_t)slots * 64;
-    const int4v lo = {b.blk_begin[0], b.blk_begin[1], b.blk_begin[2], b.blk_begin[3]};
-    const int4v hi = {b.blk_begin[4], b.blk_begin[5], b.blk_begin[6], b.blk_begin[7]};
-    ColsProbs probs;
-    for (int i = 0; i < HLQ_MAX_BATCH; ++i) probs.p[i] = b.cp[i];
-    if (one) hlq_gemv_cols_kernel<Q, G, true><<<nblocks, 64 * W, lds, st>>>(lo, hi, b.out_f32, probs);
-    else hlq_gemv_cols_kernel<Q, G, false><<<nblocks, 64 * W, lds, st>>>(lo, hi, b.out_f32, probs);
+    if (rows == 1) launch_rows<Q, G, 1>(b, nblocks, W, one, slots, st);
+    else if (rows == 2) launch_rows<Q, G, 2>(b, nblocks, W, one, slots, st);
+    else launch_rows<Q, G, 4>(b, nblocks, W, one, slots, st);
 }
 
 template <int Q>
-hlq_status launch_q(int G, const GemvBatch &b, unsigned nblocks, int W, bool one, int slots, hipStream_t st)
+hlq_status launch_q(int G, const GemvBatch &b, unsigned nblocks, int W, int rows, bool one, int slots, hipStream_t st)
 {
     switch (G) {
-    case 32: launch_qg<Q, 32>(b, nblocks, W, one, slots, st); return HLQ_OK;
-    case 64: launch_qg<Q, 64>(b, nblocks, W, one, slots, st); return HLQ_OK;
-    case 128: launch_qg<Q, 128>(b, nblocks, W, one, slots, st); return HLQ_OK;
-    case 256: launch_qg<Q, 256>(b, nblocks, W, one, slots, st); return HLQ_OK;
+    case 32: launch_qg<Q, 32>(b, nblocks, W, rows, one, slots, st); return HLQ_OK;
+    case 64: launch_qg<Q, 64>(b, nblocks, W, rows, one, slots, st); return HLQ_OK;
+    case 128: launch_qg<Q, 128>(b, nblocks, W, rows, one, slots, st); return HLQ_OK;
+    case 256: launch_qg<Q, 256>(b, nblocks, W, rows, one, slots, st); return HLQ_OK;
     }
     return HLQ_ERR_UNSUPPORTED;
 }
 
 } // namespace
 
-int hlq_gemv_cols_max_waves(int q, int G) { return cols_max_waves(q, G); }
+int hlq_gemv_cols_max_waves(int q, int G, int rows) { return cols_max_waves(q, G, rows); }
 
-hlq_status hlq_launch_gemv_cols(const GemvBatch &b, unsigned nblocks, int W, int q, int G, hipStream_t st)
+hlq_status hlq_launch_gemv_cols(const GemvBatch &b, unsigned nblocks, int W, int rows, int q, int G, hipStream_t st)
 {
-    if (W < 1 || W > cols_max_waves(q, G)) return HLQ_ERR_UNSUPPORTED;
+    if (rows < 1 || rows > HLQ_COLS_ROWS || W < 1 || W > cols_max_waves(q, G, rows)) return HLQ_ERR_UNSUPPORTED;
     bool one = true;
     int slots = 1;   // (column block, part) pairs a workgroup keeps results of
     for (int i = 0; i < b.count; ++i) {
@@ -446,10 +617,10 @@ hlq_status hlq_launch_gemv_cols(const GemvBatch &b, unsigned nblocks, int W, int
     }
     if (slots > HLQ_COLS_MAX_SLOTS) return HLQ_ERR_UNSUPPORTED;
     switch (q) {
-    case 1: return launch_q<1>(G, b, nblocks, W, one, slots, st);
-    case 2: return launch_q<2>(G, b, nblocks, W, one, slots, st);
-    case 3: return launch_q<3>(G, b, nblocks, W, one, slots, st);
-    case 4: return launch_q<4>(G, b, nblocks, W, one, slots, st);
+    case 1: return launch_q<1>(G, b, nblocks, W, rows, one, slots, st);
+    case 2: return launch_q<2>(G, b, nblocks, W, rows, one, slots, st);
+    case 3: return launch_q<3>(G, b, nblocks, W, rows, one, slots, st);
+    case 4: return launch_q<4>(G, b, nblocks, W, rows, one, slots, st);
     }
     return HLQ_ERR_UNSUPPORTED;
 }

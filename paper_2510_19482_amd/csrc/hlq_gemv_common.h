@@ -43,6 +43,12 @@ struct ColsProb {
     uint8_t unused;
 };
 
+// the same with several activation rows
+struct ColsRowsProb : ColsProb {
+    int M;
+    long ldx, ldy;     // row strides in elements
+};
+
 // Host-side description of a launch.
 struct GemvBatch {
     int blk_begin[HLQ_MAX_BATCH];   // first block of every problem, ascending; unused entries INT_MAX
@@ -112,8 +118,9 @@ constexpr bool hlq_cols_always(int q, int G) { return q >= 2 && (G >= 128 || (G 
 // one activation row (hlq_gemv_cols.hip): W (1..16) wavefronts, kw of them (a power of two) on each column block, at most
 // four column blocks per workgroup where K is split across workgroups, one arrival counter per workgroup column
 #define HLQ_COLS_MAX_SLOTS 640   // (column blocks of a workgroup) x kw: 64 bytes of LDS each
-int hlq_gemv_cols_max_waves(int q, int G);
-hlq_status hlq_launch_gemv_cols(const GemvBatch &b, unsigned nblocks, int W, int q, int G, hipStream_t st);
+#define HLQ_COLS_ROWS 4          // activation rows it carries
+int hlq_gemv_cols_max_waves(int q, int G, int rows);
+hlq_status hlq_launch_gemv_cols(const GemvBatch &b, unsigned nblocks, int W, int rows, int q, int G, hipStream_t st);
 
 // many-rows kernel (hlq_gemm_rows.hip): W = 2, 4 or 8 wavefronts, one tile each, all on the workgroup's K slice
 hlq_status hlq_launch_gemm_rows(const GemvBatch &b, unsigned nblocks, int W, int rows, int q, int G, hipStream_t st);
