@@ -7,9 +7,12 @@
 //     bit-pattern selection   code = argmin_c | (w - z) - sum_j s_j bit_j(c) |      (Bit-Pattern Selection)
 //     linear reconstruction   (s, z) = least squares of w ~ sum_j s_j b_j + z        (Linear Reconstruction, LSE)
 //
-// Groups are independent (App. C), so the unit of work is one lane = one (group, column).  The lane
-// reads its G weights once, into registers (G fp32 values; lanes of a wavefront hold adjacent
-// columns, so each of the G loads is one coalesced 256-byte read of a row of W and all G are in
+// Groups are independent (App. C), so the unit of work is one lane = one (group, column), or two or four neighbouring lanes
+// that take consecutive parts of the group: as many as a launch needs to have a wavefront on every SIMD, and at
+// least two for groups of 256, whose weights would not fit one lane's registers.  The lanes of a group add their counts and sums
+// and make the same thresholds and parameters.  A lane
+// reads its weights once, into registers (G / L fp32 values; lanes of a wavefront hold adjacent
+// columns, so each load is a coalesced read of a row of W (of L rows) and all are in
 // flight together), and every later step works from there: W is read from HBM exactly once and the
 // kernel is bound by vector instruction issue.  Within
 // a pass a weight's code is chosen and immediately folded into the sums the least-squares step
@@ -63,7 +66,7 @@ __device__ __forceinline__ void sort_keys(uint32_t (&key)[NC])
                     }
 }
 
-// wavefronts on a SIMD that the registers have to leave room for (the weights of a group take G of them)
+// wavefronts on a SIMD that the registers have to leave room for (a lane keeps G weights)
 constexpr int quantize_waves(int q, int G)
 {
     return G == 32 ? (q == 1 ? 7 : q == 2 ? 5 : q == 3 ? 4 : 3) : G == 128 ? (q == 1 ? 3 : 2) : q <= 2 ? 4 : 3;
@@ -97,18 +100,19 @@ constexpr int quantize_waves(int q, int G)
 //            a zero column in 64  77 / 146 / 267 / 490 -> 51 / 90 / 131 / 184
 //            -1, 0, 1 times 0.03  77 / 146 / 266 / 488 -> 52 / 132 / 220 / 383 (scan from the second or third round on)
 //   G = 32   fp32 normals         73 / 142 / 270 / 491 -> 50 / 106 / 163 / 272;  -1, 0, 1: 67 / 142 / 268 / 481 -> 58 / 149 / 233 / 435
-//   G = 256  (from the L2)       166 / 686 / 829 / 949 -> 127 / 155 / 201 / 255
-template <int Q, int G>
-__global__ void __launch_bounds__(256, quantize_waves(Q, G))
+//   G = 256                      166 / 686 / 829 / 949 -> 49 / 87 / 124 / 175 (by one lane a group, from the L2 every round, 127 / 155 / 201 / 255)
+template <int Q, int G, int L>
+__global__ void __launch_bounds__(256, quantize_waves(Q, G / L))
 hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, int scan_first, uint8_t *__restrict__ codes,
                     uint16_t *__restrict__ scales, uint16_t *__restrict__ zeros, float *__restrict__ group_err)
 {
+    constexpr int GL = G / L;   // weights of a lane
     constexpr int NC = 1 << Q, P = Q + 1, QUARTER = NC > 2 ? NC / 4 : 1;
     // few candidates: everything in registers.  At q = 2 the tables in LDS are 5 % faster on large matrices (G = 128 97 us
     // against 100), but with groups of 32 a small launch waits for them in every round (512 x 512: 25.6 us against 23.1)
     constexpr bool SMALL = Q == 1 || (Q == 2 && G == 32);
     __shared__ uint32_t lds[SMALL ? 1 : 4 * 3 * NC * 64];
-    const unsigned n = blockIdx.x * 256 + threadIdx.x;
+    const unsigned n = (blockIdx.x * 256 + threadIdx.x) / L, part = threadIdx.x % L;   // column, and part of its group
     const int gi = (int)blockIdx.y;
     if (n >= (unsigned)N) return;
     const int ngroups = K / G;
@@ -116,7 +120,8 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, int sc
     // vector one that never changes, where 64-bit addresses would take two vector registers per access in flight
     const __amdgpu_buffer_rsrc_t w_rows = __builtin_amdgcn_make_buffer_rsrc((void *)(W + (size_t)gi * G * N), 0, G * N * 4, 0x00020000);
     const __amdgpu_buffer_rsrc_t c_rows = __builtin_amdgcn_make_buffer_rsrc(codes + (size_t)gi * G * N, 0, G * N, 0x00020000);
-    auto load_row = [&](int offset) -> float { return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(w_rows, (int)(n * 4), offset, 0)); };
+    const int first_row = (int)(part * GL) * N;
+    auto load_row = [&](int offset) -> float { return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(w_rows, (int)(n * 4) + first_row * 4, offset, 0)); };
     // as many rows as dst takes from row i on; the offset is a running sum (one scalar instruction a row)
     auto load_rows = [&](auto &dst, int i, int stride) {
         int offset = i * stride * 4;
@@ -132,42 +137,42 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, int sc
     uint32_t *const plane = tree + NC * 64;
     uint32_t *const count = plane + NC * 64;
 
-    // groups of up to 128 weights stay in registers; longer ones are re-read (from L2) every pass
-    constexpr bool RESIDENT = G <= 128;
-    constexpr int GR = RESIDENT ? G : 1;
-    float wv[GR];
+    float wv[GL];
     float lof, hif;   // Alg. 1 steps 2-3 (min / max are exact in fp32)
     double rw = 0.0;  // sum of the weights, in order
-    if constexpr (RESIDENT) {
-        load_rows(wv, 0, N);
-        lof = hif = wv[0];
+    load_rows(wv, 0, N);
+    lof = hif = wv[0];
 #pragma unroll
-        for (int i = 1; i < G; ++i) {
-            lof = wv[i] < lof ? wv[i] : lof;
-            hif = wv[i] > hif ? wv[i] : hif;
-        }
+    for (int i = 1; i < GL; ++i) {
+        lof = wv[i] < lof ? wv[i] : lof;
+        hif = wv[i] > hif ? wv[i] : hif;
+    }
 #pragma unroll
-        for (int i = 0; i < G; ++i) rw += (double)wv[i];
-    } else {
-        lof = hif = load_row(0);
-        rw = (double)lof;
-#pragma unroll 8
-        for (int i = 1; i < G; ++i) {
-            const float v = load_row(i * N * 4);
-            lof = v < lof ? v : lof;
-            hif = v > hif ? v : hif;
-            rw += (double)v;
-        }
+    for (int i = 0; i < GL; ++i) rw += (double)wv[i];
+    // the lanes of a group are neighbours: l apart is a permutation of four
+    auto across = [](uint32_t v, auto l) -> uint32_t { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(l)::value == 1 ? 0xB1 : 0x4E, 0xf, 0xf, false); };
+    auto add_parts = [&](double v) -> double {
+        unrolled<(L == 4 ? 2 : L == 2 ? 1 : 0)>([&](auto k) {
+            const std::integral_constant<int, 1 + decltype(k)::value> l;
+            const uint64_t b = __builtin_bit_cast(uint64_t, v);
+            v += __builtin_bit_cast(double, (uint64_t)across((uint32_t)(b >> 32), l) << 32 | across((uint32_t)b, l));
+        });
+        return v;
+    };
+    if constexpr (L > 1) {
+        unrolled<(L == 4 ? 2 : 1)>([&](auto k) {
+            const std::integral_constant<int, 1 + decltype(k)::value> l;
+            const float lo2 = __builtin_bit_cast(float, across(__builtin_bit_cast(uint32_t, lof), l)), hi2 = __builtin_bit_cast(float, across(__builtin_bit_cast(uint32_t, hif), l));
+            lof = lo2 < lof ? lo2 : lof;
+            hif = hi2 > hif ? hi2 : hif;
+        });
+        rw = add_parts(rw);
     }
     auto weight = [&](int i) -> float {
-        if constexpr (RESIDENT) {
-            // opaque to the optimiser, so the fp64 copies are made per use instead of being kept
-            // for the whole kernel (which would double the registers held)
-            asm volatile("" : "+v"(wv[i]));
-            return wv[i];
-        } else {
-            return load_row(i * N * 4);
-        }
+        // opaque to the optimiser, so the fp64 copies are made per use instead of being kept
+        // for the whole kernel (which would double the registers held)
+        asm volatile("" : "+v"(wv[i]));
+        return wv[i];
     };
     const double lo = (double)lof, hi = (double)hif;
     const double delta = (hi - lo) / (double)(NC - 1);
@@ -402,7 +407,7 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, int sc
                 uint32_t c = 0;
 #pragma unroll
                 for (int j = 0; j < Q; ++j) c |= ((word >> (8 * j)) & 1u) << j;
-                __builtin_amdgcn_raw_buffer_store_b8((uint8_t)c, c_rows, (int)n, i * stride, 0);
+                __builtin_amdgcn_raw_buffer_store_b8((uint8_t)c, c_rows, (int)n + first_row, i * stride, 0);
             }
         };
         if (__builtin_expect(!scan, 1) && SMALL) {
@@ -417,32 +422,16 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, int sc
                 }
                 fold(i, w, word);
             };
-            if constexpr (RESIDENT) {
 #pragma unroll
-                for (int i = 0; i < G; ++i) {
-                    take(i, weight(i));
-                    if ((i & 7) == 7) __builtin_amdgcn_sched_barrier(0);
-                }
-            } else {
-                constexpr int AHEAD = 32;   // weights come from the L2: the next 32 are requested while 32 are worked on
-                float nx[AHEAD];
-                load_rows(nx, 0, stride);
-#pragma unroll 1
-                for (int i = 0; i < G; i += AHEAD) {
-                    float cur[AHEAD];
-#pragma unroll
-                    for (int u = 0; u < AHEAD; ++u) cur[u] = nx[u];
-                    if (i + AHEAD < G) load_rows(nx, i + AHEAD, stride);
-                    __builtin_amdgcn_sched_barrier(0);   // the loads go out first
-#pragma unroll
-                    for (int u = 0; u < AHEAD; ++u) take(i + u, cur[u]);
-                }
+            for (int i = 0; i < GL; ++i) {
+                take(i, weight(i));
+                if ((i & 7) == 7) __builtin_amdgcn_sched_barrier(0);
             }
         } else if (__builtin_expect(!scan, 1)) {
             if constexpr (!SMALL) {
             // Eight weights at a time, one level of the search for all of them before the next, and the sums of the
             // previous eight between the levels: an LDS read is used some thirty instructions after it was issued
-            // (with the weights of a group in registers there are two to five wavefronts on a SIMD to cover for each other).
+            // (with the weights in registers there are two to five wavefronts on a SIMD to cover for each other).
             constexpr int B = 8;
             // LEN weights from src, the group's weights i0, i0 + 1, ..
             auto pass = [&](auto &src, auto len_c, int i0) {
@@ -458,13 +447,31 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, int sc
 #pragma unroll
                 for (int i = 0; i < LEN; i += B) {
                     const int par = (i / B) & 1;
+                    {
+                        // All comparisons of a level before what they choose: a comparison's outcome can be read two
+                        // instructions later, and the compiler would wait those out eight times a level (4096 x 1024, G = 64,
+                        // q = 4 80.5 -> 75.7 us, q = 3 54.5 -> 50.7).  Two planes in registers have other work to fill that with
+                        // and lose the shorter encoding (4096 x 1024, G = 128 56 -> 59).
+                        auto apart = [] {
+                            if constexpr (Q > 2) __builtin_amdgcn_sched_barrier(0);
+                        };
+                        bool up[B], quarter[B];
+                        float T[B];
+                        uint32_t half[B];
 #pragma unroll
-                    for (int u = 0; u < B; ++u) {
-                        const float w = src[i + u];
-                        const bool up = w >= top[1];
-                        const float T = up ? top[2] : top[0];
-                        const uint32_t half = up ? NC / 2 * 64u : 0u;
-                        at[u] = tree + half + (w >= T ? NC / 4 * 64u : 0u);
+                        for (int u = 0; u < B; ++u) up[u] = src[i + u] >= top[1];
+                        apart();
+#pragma unroll
+                        for (int u = 0; u < B; ++u) {
+                            T[u] = up[u] ? top[2] : top[0];
+                            half[u] = up[u] ? NC / 2 * 64u : 0u;
+                        }
+                        apart();
+#pragma unroll
+                        for (int u = 0; u < B; ++u) quarter[u] = src[i + u] >= T[u];
+                        apart();
+#pragma unroll
+                        for (int u = 0; u < B; ++u) at[u] = tree + half[u] + (quarter[u] ? NC / 4 * 64u : 0u);
                     }
                     constexpr int levels = Q > 2 ? Q - 1 : 1;             // LDS reads in a row
                     constexpr int per = (B + levels - 1) / levels;        // previous weights summed up behind each
@@ -484,8 +491,12 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, int sc
                         }
                         __builtin_amdgcn_sched_barrier(0);
                         if (lv + 1 < levels) {
+                            bool up[B];
 #pragma unroll
-                            for (int u = 0; u < B; ++u) at[u] += src[i + u] >= node[u] ? step * 64u : 0u;
+                            for (int u = 0; u < B; ++u) up[u] = src[i + u] >= node[u];
+                            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                            for (int u = 0; u < B; ++u) at[u] += up[u] ? step * 64u : 0u;
                         }
                     }
 #pragma unroll
@@ -494,23 +505,7 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, int sc
 #pragma unroll
                 for (int u = 0; u < B; ++u) sum_up(LEN - B + u, word[(LEN / B - 1) & 1][u]);
             };
-            if constexpr (RESIDENT) {
-                pass(wv, std::integral_constant<int, G>{}, 0);
-            } else {
-                // weights come from the L2: the next 32 are requested while 32 are worked on
-                constexpr int AHEAD = 32;
-                float nx[AHEAD];
-                load_rows(nx, 0, stride);
-#pragma unroll 1
-                for (int i = 0; i < G; i += AHEAD) {
-                    float cur[AHEAD];
-#pragma unroll
-                    for (int u = 0; u < AHEAD; ++u) cur[u] = nx[u];
-                    if (i + AHEAD < G) load_rows(nx, i + AHEAD, stride);
-                    __builtin_amdgcn_sched_barrier(0);   // the loads go out first
-                    pass(cur, std::integral_constant<int, AHEAD>{}, i);
-                }
-            }
+            pass(wv, std::integral_constant<int, GL>{}, 0);
             }
         } else {
             // the scan of all candidates
@@ -543,24 +538,24 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, int sc
             };
             // from the registers; at q = 4, G = 128 that would be 9000 instructions a round, and the weights come from memory,
             // requested eight ahead
-            if constexpr (RESIDENT && G * NC <= 1024) {
+            if constexpr (GL * NC <= 1024) {
 #pragma unroll
-                for (int i = 0; i < G; ++i) {
+                for (int i = 0; i < GL; ++i) {
                     float w;   // a copy: the register itself is the same one whichever way the round went
                     asm volatile("" : "=v"(w) : "0"(wv[i]));
                     take(i, w);
                     if ((i & 3) == 3) __builtin_amdgcn_sched_barrier(0);   // not many weights converted ahead (registers)
                 }
             } else {
-                constexpr int AHEAD = RESIDENT ? 8 : 32;
+                constexpr int AHEAD = 8;
                 float nx[AHEAD];
                 load_rows(nx, 0, stride);
 #pragma unroll 1
-                for (int i = 0; i < G; i += AHEAD) {
+                for (int i = 0; i < GL; i += AHEAD) {
                     float cur[AHEAD];
 #pragma unroll
                     for (int u = 0; u < AHEAD; ++u) cur[u] = nx[u];
-                    if (i + AHEAD < G) load_rows(nx, i + AHEAD, stride);
+                    if (i + AHEAD < GL) load_rows(nx, i + AHEAD, stride);
                     __builtin_amdgcn_sched_barrier(0);   // the loads go out first
 #pragma unroll
                     for (int u = 0; u < AHEAD; ++u) {
@@ -571,17 +566,17 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, int sc
             }
             if constexpr (SMALL) {
 #pragma unroll
-                for (int c = 0; c < NC; ++c) cnt[c] = Q == 1 ? (c ? (int)counted : G - (int)counted) : (int)(counted >> 8 * c & 0xffu);
+                for (int c = 0; c < NC; ++c) cnt[c] = Q == 1 ? (c ? (int)counted : GL - (int)counted) : (int)(counted >> 8 * c & 0xffu);
             }
         }
 #pragma unroll
-        for (int j = 0; j < Q; ++j) rb[j] *= 0x1p15;
+        for (int j = 0; j < Q; ++j) rb[j] = add_parts(rb[j] * 0x1p15);
 
         // counts by code, from counts by sorted position
         if constexpr (SMALL) {
             if (!scan) {
                 int at[NC], by_code[NC];
-                cnt[0] = G;
+                cnt[0] = GL;
 #pragma unroll
                 for (int i = 0; i < NC; ++i) at[i] = cnt[i] - (i + 1 < NC ? cnt[i + 1] : 0);
 #pragma unroll
@@ -602,6 +597,11 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, int sc
 #pragma unroll
                 for (int i = 0; i < NC; ++i) cnt[i] = (int)plane[i * 64];
             }
+        }
+        if constexpr (L > 1) {
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+                unrolled<(L == 4 ? 2 : 1)>([&](auto k) { cnt[c] += (int)across((uint32_t)cnt[c], std::integral_constant<int, 1 + decltype(k)::value>{}); });
         }
         unsigned present = 0u;
         int nb[Q], nbb[Q][Q];
@@ -720,21 +720,24 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, int sc
     iteration(std::true_type{});
 
     // ---- outputs: parameters rounded to fp16 (nearest even); error with the unrounded ones ---------------
-    zeros[(size_t)gi * N + n] = __builtin_bit_cast(uint16_t, (_Float16)theta[0]);
+    if (part == 0) {
+        zeros[(size_t)gi * N + n] = __builtin_bit_cast(uint16_t, (_Float16)theta[0]);
 #pragma unroll
-    for (int j = 0; j < Q; ++j) scales[((size_t)j * ngroups + gi) * N + n] = __builtin_bit_cast(uint16_t, (_Float16)theta[1 + j]);
+        for (int j = 0; j < Q; ++j) scales[((size_t)j * ngroups + gi) * N + n] = __builtin_bit_cast(uint16_t, (_Float16)theta[1 + j]);
+    }
     if (group_err) {
         double e = 0.0;
-#pragma unroll(RESIDENT ? G : 8)
-        for (int i = 0; i < G; ++i) {
-            const int c = __builtin_amdgcn_raw_buffer_load_b8(c_rows, (int)n, i * N, 0);
+#pragma unroll
+        for (int i = 0; i < GL; ++i) {
+            const int c = __builtin_amdgcn_raw_buffer_load_b8(c_rows, (int)n + first_row, i * N, 0);
             double v = theta[0];
 #pragma unroll
             for (int j = 0; j < Q; ++j) v += theta[1 + j] * (double)((c >> j) & 1);
             const double dlt = (double)weight(i) - v;
             e += dlt * dlt;
         }
-        group_err[(size_t)gi * N + n] = (float)e;
+        e = add_parts(e);
+        if (part == 0) group_err[(size_t)gi * N + n] = (float)e;
     }
 }
 
@@ -742,17 +745,43 @@ template <int Q>
 void launch_q(const HlqDims &dm, const float *W, int t_max, uint8_t *codes, uint16_t *scales, uint16_t *zeros,
               float *group_err, hipStream_t st)
 {
-    const dim3 grid((unsigned)((dm.N + 255) / 256), (unsigned)dm.ngroups);
     // A launch of at most one wavefront per SIMD with groups of 32 waits for its thresholds as long as for the scan, and the
     // scan takes the same time for every distribution: 512 x 512, q = 1 / 2 / 3, us, fp32 normals 11.3 / 22.7 / 38.0 by search,
     // 11.8 / 22.0 / 38.3 by scan; bf16 12.3 / 26.7 / 47 against 11.7 / 22.2 / 38; int4 steps 22 / 34 / 41 against 11.8 / 21.9 /
     // 38.  q = 4: 59 by search, 63 by scan.
-    const int scan_first = dm.G == 32 && Q <= 3 && (long)grid.x * grid.y <= 256;
+    auto launch = [&](auto g, auto l) {
+        constexpr int G = decltype(g)::value, L = decltype(l)::value;
+        const dim3 grid((unsigned)(((long)dm.N * L + 255) / 256), (unsigned)dm.ngroups);
+        const int scan_first = G == 32 && Q <= 3 && (long)grid.x * grid.y <= 256;
+        hlq_quantize_kernel<Q, G, L><<<grid, 256, 0, st>>>(W, dm.K, dm.N, t_max, scan_first, codes, scales, zeros, group_err);
+    };
+    using One = std::integral_constant<int, 1>;
+    using Two = std::integral_constant<int, 2>;
+    using Four = std::integral_constant<int, 4>;
+    // Lanes a group: a wavefront for every one of the 1024 SIMDs, if 32 weights or more stay with a lane.  Beyond that the
+    // thresholds and the solution, which every lane of a group makes, cost what the shorter pass saves, except at one and two
+    // planes.  us, one lane / two / four: 2048 x 1024 q = 4, G = 64 (512 wavefronts) 76 / 60, G = 128 110 / 75 / 60;  4096 x 1024 q = 4,
+    // G = 64 (1024) 76 / 84, G = 128 (512) 112 / 78, G = 256 - / 112 / 80;  4096 x 4096, G = 128 (2048) q = 1 / 2 / 3 / 4 49.9 / 86.8 / 127 /
+    // 177 by one lane, 47.1 / 85.6 / 134 / 200 by two.
+    const long waves = ((long)dm.N + 63) / 64 * dm.ngroups;   // with one lane a group
+    using G64 = std::integral_constant<int, 64>;
+    using G128 = std::integral_constant<int, 128>;
+    using G256 = std::integral_constant<int, 256>;
     switch (dm.G) {
-    case 32: hlq_quantize_kernel<Q, 32><<<grid, 256, 0, st>>>(W, dm.K, dm.N, t_max, scan_first, codes, scales, zeros, group_err); break;
-    case 64: hlq_quantize_kernel<Q, 64><<<grid, 256, 0, st>>>(W, dm.K, dm.N, t_max, scan_first, codes, scales, zeros, group_err); break;
-    case 128: hlq_quantize_kernel<Q, 128><<<grid, 256, 0, st>>>(W, dm.K, dm.N, t_max, scan_first, codes, scales, zeros, group_err); break;
-    default: hlq_quantize_kernel<Q, 256><<<grid, 256, 0, st>>>(W, dm.K, dm.N, t_max, scan_first, codes, scales, zeros, group_err); break;
+    case 32: launch(std::integral_constant<int, 32>{}, One{}); break;
+    case 64:
+        if (waves > 512) launch(G64{}, One{});
+        else launch(G64{}, Two{});
+        break;
+    case 128:
+        if (waves > (Q <= 2 ? 2048 : 512)) launch(G128{}, One{});
+        else if (waves > 256) launch(G128{}, Two{});
+        else launch(G128{}, Four{});
+        break;
+    default:
+        if (waves > 256) launch(G256{}, Two{});
+        else launch(G256{}, Four{});
+        break;
     }
 }
 
