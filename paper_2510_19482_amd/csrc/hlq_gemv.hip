@@ -509,6 +509,88 @@ void plan_mx_problem(const HlqDims &dm, int W, int cpw, GemvProb &p)
     p.nslices = (dm.nchunks + p.cps - 1) / p.cps;
 }
 
+// Which of several run lengths a launch of several rows gets, by an estimate in chunks.  The chip holds two wavefronts on a SIMD,
+// 2048; a launch is so many rounds of them (one that leaves half the places free counts less), and a round takes its
+// longest run and the start and end of a workgroup.  Places that come free early take what is left, so part of the
+// estimate is the work over the places instead.  K slices cost an exchange at the end, a chunk.  Another candidate than the
+// usual one has to be as much better as the estimate may be wrong.  Candidates whose K slices the counter block or the kernels'
+// reciprocals cannot hold (short runs on the widest and deepest matrices) are passed over.
+struct RunShape {
+    int W, cpw;
+};
+struct RunCosts {
+    double fixed;    // start and end of a workgroup
+    double half;     // a round of at most 1024 wavefronts, in rounds
+    double spread;   // part of the estimate that is work over places
+    double margin;   // of the usual candidate's estimate, what another has to stay below
+};
+
+// estimate for one candidate; below zero: passed over
+double run_estimate(int count, const HlqGemvItem *items, RunShape c, const RunCosts &k)
+{
+    long waves = 0, counters = 0;
+    double work = 0;
+    int longest = 0;
+    for (int i = 0; i < count; ++i) {
+        GemvProb p;
+        plan_mx_problem(items[i].dm, c.W, c.cpw, p);
+        if ((unsigned long long)p.ntg * p.nslices * p.nslices >= 0x100000000ULL) return -1;
+        if (p.nslices > 1) counters += items[i].dm.ntiles;
+        const int run = (p.cps + p.kw - 1) / p.kw;
+        const long w = (long)p.ntg * p.nslices * c.W;
+        waves += w;
+        work += (double)w * (run + k.fixed);
+        longest = run > longest ? run : longest;
+    }
+    if (counters > HLQ_WS_ARRIVAL_COUNTERS) return -1;
+    // runs beyond 16 pay where they make one round of a launch: with several, a start hides behind the others' runs
+    // (many rows, 8192 x 128256, q = 1, 4 rows: 47.7 us with runs of 16, 49.4 with 32)
+    if (c.cpw > 16 && waves > 2048) return -1;
+    const long rest = waves % 2048;
+    const double rounds = (double)(waves / 2048) + (rest == 0 ? 0.0 : rest <= 1024 ? k.half : 1.0), one = longest + k.fixed;
+    const double spread = work / 2048 > one ? work / 2048 : one;
+    return (1 - k.spread) * one * rounds + k.spread * spread + (counters > 0 ? 1 : 0);
+}
+
+template <int NC>
+RunShape plan_runs(int count, const HlqGemvItem *items, RunShape usual, const RunShape (&cand)[NC], const RunCosts &k)
+{
+    RunShape best = usual;
+    const double known = run_estimate(count, items, usual, k);
+    double least = known < 0 ? 1e300 : known * k.margin;
+    for (const RunShape &c : cand) {
+        const double e = run_estimate(count, items, c, k);
+        if (e >= 0 && e < least) {
+            least = e;
+            best = c;
+        }
+    }
+    return best;
+}
+
+// Many-rows kernel: runs of 4 below 12000 chunk-tiles and of 16 above unless the estimate falls by 9 %.  Over 240 launches (2400
+// to 128256 chunk-tiles, single matrices and layers, q = 1 to 4, 4 to 16 rows) 6 % faster than the usual one on average
+// and 2 % slower at most; us:  q = 4, 16 rows  4096 x 14336 21.4 -> 18.8, 14336 x 4096 22.4 -> 20.2, 11008 x 9000 33.8 -> 28.3, 5120 x 13824
+// 27.0 -> 20.9, layer of hidden 3072 / ffn 8192 31.6 -> 25.0, hidden 3840 / ffn 9984 43.6 -> 36.1, 8192 x 57344 81.5 -> 78.5;  q = 2, 8 rows
+// 11008 x 9000 22.4 -> 18.7, 8192 x 57344 40.9 -> 36.3.  (Without the margin 7 % on average, but the layer of hidden 2560 / ffn 9984 28.4 -> 30.2.)
+RunShape plan_many_rows(int count, const HlqGemvItem *items, long units)
+{
+    static const RunShape cand[] = {{4, 24}, {4, 16}, {4, 12}, {4, 10}, {4, 8}, {4, 6}, {4, 4}};
+    return plan_runs(count, items, {4, units < 12000 ? 4 : 16}, cand, {8, 0.6, 0.2, 0.91});
+}
+
+// Few-rows instantiation of the 64-column kernel, from 4096 chunk-tiles on: eight wavefronts with runs of 4 below 12000 chunk-tiles
+// and of 6 above, or what the estimate prefers.  Runs beyond eight chunks are slow whatever the rounds (the activations are
+// cut into terms by every wavefront; hidden 3584 / ffn 10240, q = 4, 4 rows: 23 us with runs of 6, 43 with 16).  Over 379
+// launches 5 % faster on average and 1 % slower at most; us:  q = 4, 4 rows  layer of hidden 3072 / ffn 8192 27.5 -> 18.0, hidden
+// 2816 / ffn 8192 25.9 -> 20.4, 11008 x 9000 31.4 -> 22.3, 8192 x 10240 25.8 -> 20.2;  q = 2, 2 rows  hidden 3072 12.3 -> 10.6,
+// 28672 x 8192 22.1 -> 18.1;  G = 64, q = 4, 2 rows  hidden 3072 22.4 -> 15.8
+RunShape plan_few_rows(int count, const HlqGemvItem *items, long units)
+{
+    static const RunShape cand[] = {{8, 4}, {8, 6}, {8, 8}, {4, 4}, {4, 6}, {4, 8}};
+    return plan_runs(count, items, {8, units < 12000 ? 4 : 6}, cand, {2, 0.5, 0.6, 1});
+}
+
 // Work split of a launch of the one-row matrix-core kernel (hlq_gemv_cols.hip).  A step is 16 columns x 4 chunks of one
 // wavefront.
 struct ColsSplit {
@@ -732,20 +814,19 @@ static hlq_status plan_gemv_batch(int count, const HlqGemvItem *items, hlq_out_d
         (hlq_gemm_rows_all() || hlq_gemm_rows_wins_few(units, items[0].dm.q, rows)))
         rowsk = true;
     if (rowsk) {
-        pl.W = 4;
-        // chunks per K slice: long enough that the partial sums (rows x columns x slices) stay a small part of the
-        // traffic, short enough that the launch has several workgroups per compute unit
-        pl.cpw = units < 12000 ? 4 : 16;   // measured on the 8B layer at q = 4: 16 beats 8 (one round of workgroups instead of two)
+        const RunShape r = plan_many_rows(count, items, units);
+        pl.W = r.W;
+        pl.cpw = r.cpw;
         if (const int v = g_plan_cpw.load(std::memory_order_relaxed)) pl.cpw = v < 4 ? 4 : v;
     } else if (cols) {
         pl.W = pl.forced_w;   // 0: plan_cols chooses
         pl.cpw = pl.forced_cpw;
         if (pl.W < 0 || pl.cpw < 0) return HLQ_ERR_UNSUPPORTED;   // (of the environment)
     } else if (rows > 1) {
-        // measured (8B shapes, q = 4, M = 2..8): short runs on few wavefronts per workgroup for narrow
-        // launches, longer runs and eight wavefronts once there are enough tiles
-        pl.W = units < 4096 ? 4 : 8;
-        pl.cpw = units < 4096 ? 2 : units < 12000 ? 4 : 6;
+        // narrow launches: short runs on few wavefronts per workgroup (measured on 8B shapes, q = 4, 2..8 rows)
+        const RunShape r = units < 4096 ? RunShape{4, 2} : plan_few_rows(count, items, units);
+        pl.W = r.W;
+        pl.cpw = r.cpw;
         if (const int v = g_plan_w.load(std::memory_order_relaxed)) pl.W = v;
         if (const int v = g_plan_cpw.load(std::memory_order_relaxed)) pl.cpw = v;
     }

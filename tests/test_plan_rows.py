@@ -1,0 +1,33 @@
+"""Work split of launches of several rows, on the host: the run length is chosen per launch, and neither the choice nor the
+limits of the counter block and of the block arithmetic may refuse what a fixed run length was accepted for."""
+import pytest
+
+from paper_2510_19482_amd import binding as B
+
+from test_plan_host import check_plan
+
+
+# K and N at both ends of their range, ragged tiles, odd numbers of chunks; short runs on K = 2^21 with eight thousand columns or
+# N = 2^20 take more slices than the block arithmetic or the counter block has room for
+@pytest.mark.parametrize("K,N", [(512, 512), (128 * 67, 5000), (4096, 14336), (14336, 4096), (128 * 33, 128256), (8192, 131072),
+                                 (1 << 21, 8), (1 << 21, 8192), (256, 1 << 20), (4096, 1 << 20)])
+@pytest.mark.parametrize("G,M", [(32, 2), (64, 2), (64, 4), (128, 2), (128, 4), (128, 8), (256, 16)])
+@pytest.mark.parametrize("count", [1, 3, 8])
+def test_runs_of_every_launch_fit(K, N, G, M, count):
+    if K % G:
+        pytest.skip("K is no multiple of the group")
+    for q in (1, 4):
+        infos = B.gemv_plan_query([B.make_desc(K, N, q, G)] * count, M)
+        at = 0
+        for info in infos:
+            check_plan(info, K // 128, (K, N, q, G, M, count))
+            assert info.first_block == at
+            at += info.blocks
+
+
+def test_run_follows_the_rounds_of_the_launch():
+    # 24 and 64 chunks: one round of 512 workgroups with six chunks a wavefront, not two of four
+    layer = [(3072, 3072)] * 2 + [(3072, 512)] * 2 + [(3072, 8192)] * 2 + [(8192, 3072)]
+    infos = B.gemv_plan_query([B.make_desc(K, N, 4, 128) for K, N in layer], 8)
+    assert sum(i.blocks for i in infos) == 512
+    assert max(-(-i.chunks_per_slice // i.waves_per_tile) for i in infos) == 6
