@@ -801,7 +801,7 @@ static hlq_status plan_gemv_batch(int count, const HlqGemvItem *items, hlq_out_d
     const int rows = items[0].M;
     for (int i = 1; i < count; ++i)
         if (items[i].M != rows) return HLQ_ERR_UNSUPPORTED;
-    if (rows < 1 || (rows > HLQ_COLS_ROWS && rows > hlq_gemm_mx_rows_per_pass(items[0].dm.G))) return HLQ_ERR_UNSUPPORTED;
+    if (rows < 1 || (rows > hlq_gemm_mx_rows_per_pass(items[0].dm.G) && !few_rows_win(count, items, rows))) return HLQ_ERR_UNSUPPORTED;
     const bool mx = use_mx() || rows > 1;   // several activation rows exist in the matrix-core kernels only
     const bool cols = mx && (rows == 1 ? cols_wins(units, items[0].dm.q, items[0].dm.G) : few_rows_win(count, items, rows));
     // more rows than one operand of the GEMV kernel holds: the many-rows kernel (terms chained through the

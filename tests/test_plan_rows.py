@@ -31,3 +31,15 @@ def test_run_follows_the_rounds_of_the_launch():
     infos = B.gemv_plan_query([B.make_desc(K, N, 4, 128) for K, N in layer], 8)
     assert sum(i.blocks for i in infos) == 512
     assert max(-(-i.chunks_per_slice // i.waves_per_tile) for i in infos) == 6
+
+
+def test_rows_beyond_the_kernels_have_no_plan():
+    # three rows at G = 32 exceed the two row sets of the 64-column kernel: only the launches that the 16-column kernel takes
+    # (256 to 4096 chunk-tiles of at most 64 chunks, or 14000 and more) have a plan
+    for K, N, planned in [(512, 512, False), (4096, 4096, True), (4096, 14336, False), (8192, 16384, True)]:
+        descs = [B.make_desc(K, N, 2, 32)]
+        if planned:
+            assert B.gemv_plan_query(descs, 3)[0].blocks > 0
+        else:
+            with pytest.raises(B.HlqError):
+                B.gemv_plan_query(descs, 3)
