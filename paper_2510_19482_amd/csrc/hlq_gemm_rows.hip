@@ -15,7 +15,13 @@
 // neighbours.  Four such terms are half the time of four exact bf8 terms and closer to the exact product: relative error of fp32 results,
 // 4096 x 4096, q = 4, M = 16: 3.0e-6 -> 3.0e-7, with 1 % of the channels times 20 1.2e-5 -> 2.5e-6.
 // Three terms are short of it where outliers share a block with the rest (2.5e-4 of a row's largest result, 1 % of K = 1024
-// times 20).
+// times 20), and so are four beside a massive activation, in the columns whose weights are zero there: one channel in 32 a
+// thousand times the rest, relative error 5e-4 (bf8 terms: the fp32 sums' own).  Blocks in which all activations of an
+// expansion register are 2^-8 or less of the largest, as weighted, are wide: their chunk has a second record with four terms of
+// what the first four leave, scaled by itself (down to 2^-36 of the block's largest; 3e-7), and the main kernel goes
+// through such chunks once more at its end.  In the others what is left of an activation is at most 2^-11 of the largest of its
+// register.  With 1 % of the channels times 20 one block in 80000 is wide.  The test and the look at the flags cost 0.1 to 0.5 us
+// a call (8B layer, q = 4, M = 16 41.9 -> 42.2, 4096 x 14336 18.7 -> 19.1).
 //
 // The terms lie along the ACCUMULATION: operand o holds terms [o TPO, (o + 1) TPO) of 16 / TPO activation
 // rows, the NT = 4 / TPO matrix-core instructions of an item (plane j, block of 16 columns) chain
@@ -82,10 +88,20 @@ constexpr int rows_chunk_bytes(int NT) { return rows_quads(NT) * 1024 + (rows_wo
 constexpr int rows_operands(int rows) { return rows <= 4 ? 1 : rows <= 8 ? 2 : 4; }
 constexpr int rows_carried(int NT) { return 4 * NT; }
 
+// A block is wide if all activations of an expansion register (that are not all zero) are this many binary places below the
+// largest, as weighted.
+constexpr int ROWS_WIDE = 8;
+
+// the workspace of a problem: records of all chunks, records of what they leave (of the chunks that have it), a flag for each
+// chunk that has
+__device__ __forceinline__ int *rows_flags(const GemvProb &P, int nt) { return (int *)(P.xt + (size_t)P.nchunks * 2 * rows_chunk_bytes(nt)); }
+// plane codes are worth 1/2, 1, 2, 2 by expansion register: the activations' weights 1/2, 1/4, 1/8, 1/8 make every product a quarter
+__device__ __forceinline__ constexpr int rows_weight(int rr) { return rr < 3 ? rr + 1 : 3; }
+__device__ __forceinline__ float power_of_two(int e) { return __builtin_bit_cast(float, (uint32_t)(127 + e) << 23); }
+
 // Workgroup = one wavefront = 16 / RPO chunks of all rows; problem blockIdx.y.  A lane takes 32 consecutive k of one row.
 // Position 8 rr + 4 hh + n of a k block holds its activation 8 n + 2 rr + hh: weight k0 = 2 p + hh is plane bit p = 4 n + rr,
-// which the plane expansion puts into nibble n + 4 hh of register rr.  Plane codes are worth 1/2, 1, 2, 2 by rr:
-// weights 1/2, 1/4, 1/8, 1/8 make every product bit x activation / 4, and the 4 goes into the scale.
+// which the plane expansion puts into nibble n + 4 hh of register rr.  The 4 of rows_weight goes into the scale.
 template <int NT>
 __global__ void __launch_bounds__(64) hlq_rows_split_kernel(const GemvProbs probs)
 {
@@ -102,21 +118,24 @@ __global__ void __launch_bounds__(64) hlq_rows_split_kernel(const GemvProbs prob
         x[n][0] = v.x; x[n][1] = v.y; x[n][2] = v.z; x[n][3] = v.w;
     }
     // biased exponent ew of the largest weighted magnitude: all of them are below 2^(ew - 14), brought below 16
-    int ew = -2, eall = 0;
+    int ew = -2, eall = 0, own[4];
 #pragma unroll
     for (int rr = 0; rr < 4; ++rr) {
         ushort2_t mx = {0, 0};
 #pragma unroll
         for (int n = 0; n < 4; ++n) mx = __builtin_elementwise_max(mx, __builtin_bit_cast(ushort2_t, x[n][rr] & 0x7fff7fffu));
-        const int e = max((int)mx.x, (int)mx.y) >> 10;
-        ew = max(ew, max(e, 1) - (rr < 3 ? rr + 1 : 3));
+        const int largest = max((int)mx.x, (int)mx.y), e = largest >> 10;
+        own[rr] = largest ? max(e, 1) - rows_weight(rr) : 99;
+        ew = max(ew, max(e, 1) - rows_weight(rr));
         eall = max(eall, e);
     }
+    const bool real = have && eall < 31;   // a row that the call has, and neither an infinity nor a NaN in the block
+    const uint64_t wide = __ballot(real && ew - min(min(own[0], own[1]), min(own[2], own[3])) > ROWS_WIDE);
     const int s = 18 - ew;
     half32_t v;
 #pragma unroll
     for (int rr = 0; rr < 4; ++rr) {
-        const int sr = s - (rr < 3 ? rr + 1 : 3), k1 = sr / 2, k2 = sr - k1;   // two factors: 2^sr need not be an fp16 number
+        const int sr = s - rows_weight(rr), k1 = sr / 2, k2 = sr - k1;   // two factors: 2^sr need not be an fp16 number
         const _Float16 f1 = __builtin_bit_cast(_Float16, (uint16_t)((15 + k1) << 10)), f2 = __builtin_bit_cast(_Float16, (uint16_t)((15 + k2) << 10));
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh)
@@ -129,32 +148,59 @@ __global__ void __launch_bounds__(64) hlq_rows_split_kernel(const GemvProbs prob
     }
     // a row the call does not have: zeros.  An infinity or a NaN: no such codes, but such a scale, and the row's results are NaN
     uint6v term[4];
+    auto cut = [&](bool some) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            term[t] = __builtin_amdgcn_cvt_scalef32_pk32_bf6_f16(v, 1.0f);
+            if (t < 3) v = (v - __builtin_amdgcn_cvt_scalef32_pk32_f16_bf6(term[t], 1.0f)) * (_Float16)16.0f;   // exact
+            if (!some) term[t] = (uint6v){0u, 0u, 0u, 0u, 0u, 0u};
+        }
+    };
+    // lane `row` of k block g: its words; `scale`: the scale byte of term 0
+    auto emit = [&](char *dst, uint32_t scale, uint32_t per_term) {
+#pragma unroll
+        for (int h = 0; h < TPO; ++h) {   // operand rows h RPO + m
+            const int row = h * RPO + m;
+            uint32_t w[4 * QUADS + 1] = {};
+#pragma unroll
+            for (int o = 0; o < NT; ++o) {
+                const int t = o * TPO + h;
+#pragma unroll
+                for (int i = 0; i < 6; ++i) w[6 * o + i] = term[t][i];
+                w[6 * NT] |= (scale - per_term * t) << 8 * o;
+            }
+#pragma unroll
+            for (int i = 0; i < QUADS; ++i) ((uint4 *)dst)[64 * i + 16 * g + row] = make_uint4(w[4 * i], w[4 * i + 1], w[4 * i + 2], w[4 * i + 3]);
+            if (rows_words(NT) % 4 == 1) ((uint32_t *)(dst + 1024 * QUADS))[16 * g + row] = w[4 * QUADS];
+        }
+    };
+    cut(have);
+    char *const record = P.xt + (size_t)ch * rows_chunk_bytes(NT);
+    emit(record, real ? (uint32_t)(127 + 2 - s) : have ? 255u : 127u, real ? 4u : 0u);
+    if (lane % (4 * RPO) == 0) rows_flags(P, NT)[ch] = (wide >> lane & (~0ull >> (64 - 4 * RPO))) != 0;
+    if (__builtin_expect(wide == 0, 1)) return;
+
+    // What the four terms leave, in four more.  It is no more than the activation's own bits, so exact in fp32 and, brought
+    // to where the block's largest remainder lies in [8, 16), in fp16 down to 2^-28 of that.
+    float left[32], most = 0.f;
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-        term[t] = __builtin_amdgcn_cvt_scalef32_pk32_bf6_f16(v, 1.0f);
-        if (t < 3) v = (v - __builtin_amdgcn_cvt_scalef32_pk32_f16_bf6(term[t], 1.0f)) * (_Float16)16.0f;   // exact
-        if (!have) term[t] = (uint6v){0u, 0u, 0u, 0u, 0u, 0u};
-    }
-    auto scale_byte = [&](int t) -> uint32_t { return !have ? 127u : eall == 31 ? 255u : (uint32_t)(127 + 2 - s - 4 * t); };
-    char *dst = P.xt + (size_t)ch * rows_chunk_bytes(NT);
-    // lane `row` of k block g: its words
-    auto emit = [&](int row, const uint32_t (&w)[4 * QUADS + 1]) {
+        const half32_t held = __builtin_amdgcn_cvt_scalef32_pk32_f16_bf6(term[t], 1.0f);
 #pragma unroll
-        for (int i = 0; i < QUADS; ++i) ((uint4 *)dst)[64 * i + 16 * g + row] = make_uint4(w[4 * i], w[4 * i + 1], w[4 * i + 2], w[4 * i + 3]);
-        if (rows_words(NT) % 4 == 1) ((uint32_t *)(dst + 1024 * QUADS))[16 * g + row] = w[4 * QUADS];
-    };
-#pragma unroll
-    for (int h = 0; h < TPO; ++h) {   // operand rows h RPO + m
-        uint32_t w[4 * QUADS + 1] = {};
-#pragma unroll
-        for (int o = 0; o < NT; ++o) {
-            const int t = o * TPO + h;
-#pragma unroll
-            for (int i = 0; i < 6; ++i) w[6 * o + i] = term[t][i];
-            w[6 * NT] |= scale_byte(t) << 8 * o;
+        for (int i = 0; i < 32; ++i) {
+            const int rr = i >> 3, hh = i >> 2 & 1, n = i & 3;
+            if (t == 0) left[i] = (float)__builtin_bit_cast(_Float16, (uint16_t)(x[n][rr] >> (16 * hh))) * power_of_two(s - rows_weight(rr));
+            left[i] -= (float)held[i] * (1.0f / (float)(1 << 4 * t));
+            if (t == 3) most = fmaxf(most, fabsf(left[i]));
         }
-        emit(h * RPO + m, w);
     }
+    const bool some = real && most > 0.f;
+    const int up = some ? 3 + 127 - (int)(__builtin_bit_cast(uint32_t, most) >> 23) : 0;
+    const float factor = power_of_two(up);
+#pragma unroll
+    for (int i = 0; i < 32; ++i) v[i] = (_Float16)(left[i] * factor);
+    cut(some);
+    emit(record + (size_t)P.nchunks * rows_chunk_bytes(NT), some ? (uint32_t)(127 + 2 - s - up) : 127u, some ? 4u : 0u);
 }
 
 template <int Q>
@@ -229,9 +275,7 @@ hlq_gemm_rows_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32_fla
         int8v A[NT];   // of which the instruction reads six registers
         int scale;     // byte o: operand o
     };
-    auto load_ops = [&](int ch, Ops &o) {
-        const int chx = max(min(ch, cend - 1), sbeg);   // stays inside K also past the end of the run
-        const char *src = P.xt + (size_t)chx * rows_chunk_bytes(NT);
+    auto load_record = [&](const char *src, Ops &o) {
         int w[4 * rows_quads(NT) + 1];
 #pragma unroll
         for (int i = 0; i < rows_quads(NT); ++i) {
@@ -242,6 +286,10 @@ hlq_gemm_rows_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32_fla
 #pragma unroll
         for (int t = 0; t < NT; ++t) o.A[t] = (int8v){w[6 * t], w[6 * t + 1], w[6 * t + 2], w[6 * t + 3], w[6 * t + 4], w[6 * t + 5], 0, 0};
         o.scale = w[6 * NT];
+    };
+    auto load_ops = [&](int ch, Ops &o) {
+        const int chx = max(min(ch, cend - 1), sbeg);   // stays inside K also past the end of the run
+        load_record(P.xt + (size_t)chx * rows_chunk_bytes(NT), o);
     };
     // scales: lane <-> column to LDS, read back per column block (this lane's column 16 cb + c)
     struct Sc {
@@ -276,28 +324,31 @@ hlq_gemm_rows_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32_fla
 #pragma unroll
         for (int cb = 0; cb < 4; ++cb) acc[sl][cb] = 0.f;
 
-    // One chunk: the items (plane j, column block cb) as a software pipeline -- matrix-core chain of item n |
-    // expansion of the word of item n + 1, scales applied to the result of item n - 1.  R's planes are reloaded
-    // (chunk two ahead) right after their last item; past the end of the slice the range check answers with zeros.
-    auto step = [&](Regs &R, const Ops &o, const Sc &s, int ch_reload) {
-        constexpr int NI = 4 * Q;
-        auto apply = [&](const float4v &d, int cb, int which) {
-            const float sc = scale_of(s.m[cb], which);
+    auto transpose = [&](const Regs &R, uint32_t (&wt)[Q][4]) {   // 4 x 4 over (16-lane group, word)
 #pragma unroll
-            for (int sl = 0; sl < 4; ++sl) acc[sl][cb] += sc * d[sl];
-        };
-        const int8v ones = {0x11111111, 0x22222222, 0x44444444, 0x44444444, 0, 0, 0, 0};
-        float4v xs = zero4;   // the chunk's activation sums per row, for the zero points
-        unrolled<NT>([&](auto t) { xs = mfma(t, o, ones, xs); });
-        uint32_t wt[Q][4];
-#pragma unroll
-        for (int j = 0; j < Q; ++j) {        // 4 x 4 transpose over (16-lane group, word)
+        for (int j = 0; j < Q; ++j) {
             const uint2v s01 = __builtin_amdgcn_permlane16_swap(R.w[j][0], R.w[j][1], false, false);
             const uint2v s23 = __builtin_amdgcn_permlane16_swap(R.w[j][2], R.w[j][3], false, false);
             const uint2v t02 = __builtin_amdgcn_permlane32_swap(s01.x, s23.x, false, false);
             const uint2v t13 = __builtin_amdgcn_permlane32_swap(s01.y, s23.y, false, false);
             wt[j][0] = t02.x; wt[j][2] = t02.y; wt[j][1] = t13.x; wt[j][3] = t13.y;
         }
+    };
+    auto apply = [&](const Sc &s, const float4v &d, int cb, int which) {
+        const float sc = scale_of(s.m[cb], which);
+#pragma unroll
+        for (int sl = 0; sl < 4; ++sl) acc[sl][cb] += sc * d[sl];
+    };
+    const int8v ones = {0x11111111, 0x22222222, 0x44444444, 0x44444444, 0, 0, 0, 0};
+    // One chunk: the items (plane j, column block cb) as a software pipeline -- matrix-core chain of item n |
+    // expansion of the word of item n + 1, scales applied to the result of item n - 1.  R's planes are reloaded
+    // (chunk two ahead) right after their last item; past the end of the slice the range check answers with zeros.
+    auto step = [&](Regs &R, const Ops &o, const Sc &s, int ch_reload) {
+        constexpr int NI = 4 * Q;
+        float4v xs = zero4;   // the chunk's activation sums per row, for the zero points
+        unrolled<NT>([&](auto t) { xs = mfma(t, o, ones, xs); });
+        uint32_t wt[Q][4];
+        transpose(R, wt);
         load_meta(ch_reload, R);             // its scales were staged one chunk ahead
         // Items go through the matrix core two at a time: the chains of a pair are independent, so the second
         // instruction of one never waits for the first of the same chain, and the vector work of the stage (expansion
@@ -322,8 +373,8 @@ hlq_gemm_rows_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32_fla
             }
             if (n1 % 4 == 3) load_plane(ch_reload, R, n1 / 4);   // the plane's last item is in this pair
             if (pr >= 1) {
-                apply(pA, (n0 - 2) % 4, (n0 - 2) / 4);
-                apply(pB, (n1 - 2) % 4, (n1 - 2) / 4);
+                apply(s, pA, (n0 - 2) % 4, (n0 - 2) / 4);
+                apply(s, pB, (n1 - 2) % 4, (n1 - 2) / 4);
             }
             // 2 NT matrix-core instructions, each followed by its share of the stage's vector instructions
 #pragma unroll
@@ -334,13 +385,18 @@ hlq_gemm_rows_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32_fla
             __builtin_amdgcn_sched_barrier(0);
             pA = dA; pB = dB; B0 = nB0; B1 = nB1;
         }
-        apply(pA, (NI - 2) % 4, (NI - 2) / 4);
-        apply(pB, (NI - 1) % 4, (NI - 1) / 4);
+        apply(s, pA, (NI - 2) % 4, (NI - 2) / 4);
+        apply(s, pB, (NI - 1) % 4, (NI - 1) / 4);
 #pragma unroll
-        for (int cb = 0; cb < 4; ++cb) apply(xs, cb, Q);
+        for (int cb = 0; cb < 4; ++cb) apply(s, xs, cb, Q);
     };
 
     // ---- chunk loop: no barrier; weights two chunks ahead, activation operands and staged scales one chunk ahead -----
+    // which of the run's chunks have a second record: lane l looks at chunk base + l.  Requested ahead of the first operands and
+    // made use of in the loop, in name: what is waited for the operands has it arrive, and nothing waits for it behind the loop
+    // (4096 x 14336, q = 4, M = 16: 0.9 us)
+    auto flag = [&](int base) -> int { return rows_flags(P, NT)[min(base + lane, P.nchunks - 1)]; };
+    int first_flags = flag(cbeg);
     Ops oA, oB;
     load_ops(cbeg, oA);
     Sc sc0, sc1;
@@ -349,11 +405,41 @@ hlq_gemm_rows_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32_fla
         load_ops(ch + 1, oB);
         stage_scales(R[1], sc1);
         step(R[0], oA, sc0, ch + 2);
+        asm volatile("" : "+v"(first_flags));
         if (ch + 1 < cend) {
             load_ops(ch + 2, oA);
             stage_scales(R[0], sc0);
             step(R[1], oB, sc1, ch + 3);
         }
+    }
+
+    // ---- what the four terms of wide blocks leave: the same products with the second record of the chunks that have one.  Rare, so
+    // nothing is arranged for speed.
+    auto remainder = [&](int ch) {
+        Regs Rw;
+#pragma unroll
+        for (int j = 0; j < Q; ++j) load_plane(ch, Rw, j);
+        load_meta(ch, Rw);
+        Ops o;
+        load_record(P.xt + (size_t)(P.nchunks + ch) * rows_chunk_bytes(NT), o);
+        Sc s;
+        stage_scales(Rw, s);
+        uint32_t wt[Q][4];
+        transpose(Rw, wt);
+        auto chain = [&](const int8v &B) {
+            float4v d = zero4;
+            unrolled<NT>([&](auto t) { d = mfma(t, o, B, d); });
+            return d;
+        };
+#pragma unroll
+        for (int j = 0; j <= Q; ++j)
+#pragma unroll
+            for (int cb = 0; cb < 4; ++cb) apply(s, chain(j < Q ? expand(wt[j < Q ? j : 0][cb]) : ones), cb, j);
+    };
+    uint64_t wide = __ballot(first_flags != 0 && cbeg + lane < cend);
+    for (int base = cbeg; base < cend; base += 64) {
+        if (base > cbeg) wide = __ballot(flag(base) != 0 && base + lane < cend);
+        for (; wide != 0; wide &= wide - 1) remainder(base + __builtin_ctzll(wide));
     }
 
     // ---- add the terms that lie in different lanes and the tile's KW runs, store --------------------
@@ -491,7 +577,8 @@ hlq_status launch_q(int G, const GemvBatch &b, unsigned nblocks, int W, int rows
 size_t hlq_gemm_rows_xt_bytes(const HlqDims &dm, int64_t M)
 {
     if (M < 1 || M > hlq_gemm_rows_max(dm.G)) return 0;
-    return (size_t)dm.nchunks * rows_chunk_bytes(rows_operands((int)M)) + 256;   // kept 256-byte aligned
+    const size_t flags = ((size_t)dm.nchunks * sizeof(int) + 255) & ~(size_t)255;
+    return (size_t)dm.nchunks * 2 * rows_chunk_bytes(rows_operands((int)M)) + flags + 256;   // kept 256-byte aligned
 }
 
 // rows this kernel carries for group size G (0: no instantiation)
