@@ -250,7 +250,14 @@ HLQ_API hlq_status hlq_set_gemv_path(int path);
  *     on the few-rows GEMV kernel).
  * Other values: HLQ_ERR_UNSUPPORTED.  The fp16-rebuild kernels represent scales up to |s_j| < 512 (and
  * zeros of that size); they check what they load, and what depends on weights that lie outside is computed again
- * in fp32 (slow, but right for every finite fp16 parameter). */
+ * in fp32 (slow, but right for every finite fp16 parameter).
+ * Precision of the kernels that keep scales in fp32: hlq_lut_gemv's, and the 64-column kernel for several rows, hold an
+ * activation exactly (see hlq_set_gemv_path).  The 16-column kernel with two to four rows and the many-rows kernel hold it as
+ * four 6-bit floats that share a power of two among 32 consecutive k: with each activation taken times 1/2, 1/4, 1/8, 1/8 for
+ * (k mod 8) / 2 = 0, 1, 2, 3, what is left of it is at most 2^-20 of the largest of its 32; where the eight activations
+ * of one value of (k mod 8) / 2 are all 2^-8 or less of that (and not all zero) there are four floats more, which leave at most
+ * 2^-36.  So what is left of an activation is at most 2^-11 of the largest of its eight, whatever stands beside them; sums are
+ * exact to 2^-24 of the largest product of 32 and fp32 beyond.  A row with an infinity or a NaN is NaN as a whole. */
 HLQ_API hlq_status hlq_set_gemm_path(int path);
 
 /* Y[M, N] = X[M, K] @ W^  (same procedure with one table set per row, the decoded

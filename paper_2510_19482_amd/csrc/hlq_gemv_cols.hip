@@ -35,7 +35,9 @@
 // plane words.  They are bf6 terms as in hlq_gemm_rows.hip -- 24 registers a row and not 32, 16 clocks an instruction and not
 // 32 -- with the matrix core's own scale per word, so the window's largest magnitude is not needed; made of the same
 // eight activations per lane, through the packed conversions (at one row their latency, 72 clocks a conversion, is longer than
-// what bf8 terms take).  Relative error of fp32 results at 4096 x 4096, q = 4, 4 rows, 1 % outliers: 1.6e-5 -> 4e-6.
+// what bf8 terms take).  Relative error of fp32 results at 4096 x 4096, q = 4, 4 rows, 1 % outliers: 1.6e-5 -> 4e-6.  What four
+// terms leave in wide words (as in hlq_gemm_rows.hip) is added in a second pass of the wavefront over its windows that have one;
+// whether one has costs four instructions a row (a count of the small activations instead: 0.3 to 0.6 us of 5 to 9).
 //
 // Work split.  A workgroup of W wavefronts owns adjacent column blocks and one K slice; the windows of the slice are
 // dealt out to the wavefronts, whose results meet in LDS.  K slices of different workgroups meet in the workspace: two
@@ -98,6 +100,7 @@ struct ColsRegs {
 // LDS per wavefront: activation codes [term][chunk][word][32], the terms 16 bytes apart from a multiple of the bank
 // count -- the same bytes hold a step's scales while no operands are being made -- then 128 zero bytes
 // (two and four rows: [row][term][chunk][word][24 bytes], and behind the zeros the scales [row][chunk][word])
+constexpr uint32_t COLS_WIDE = 8;   // see ROWS_WIDE in hlq_gemm_rows.hip
 constexpr int COLS_TERM = 4 * 128 + 16, COLS_CODES = 96;
 template <int Q, int G, int NR>
 constexpr int cols_zero_at()
@@ -273,11 +276,19 @@ hlq_gemv_cols_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32, co
             });
     };
     // Several rows: the terms of the many-rows kernel (hlq_gemm_rows.hip), four bf6 codes per activation with one power of two
-    // per 32 activations, i.e. per word; a lane makes the eight codes of one expansion register for every row.
-    auto make_rows = [&]() {
+    // per 32 activations, i.e. per word; a lane makes the eight codes of one expansion register for every row.  LEFT: the same
+    // terms of what these four leave.  Returns whether a word is wide
+    // (as there): a lane that has activations has only such as are 2^-8 of the word's largest, as weighted.
+    auto make_rows = [&](auto left_c) -> bool {
+        constexpr bool LEFT = decltype(left_c)::value;
         half32_t v;
         const int weight = xr < 3 ? xr + 1 : 3;
         char *scales = xt + ZERO_AT + 128;
+        int s[NR];
+        bool odd_row[NR], wide = false;   // an infinity or a NaN
+        auto pair = [&](int row, int n) -> half2_t {   // codes 2 n, 2 n + 1: the even activations of the dwords, then the odd ones
+            return __builtin_bit_cast(half2_t, __builtin_amdgcn_perm(xw[row][2 * (n & 1) + 1], xw[row][2 * (n & 1)], n < 2 ? 0x05040100u : 0x07060302u));
+        };
 #pragma unroll
         for (int row = 0; row < NR; ++row) {
             uint32_t mx = 0;
@@ -286,15 +297,18 @@ hlq_gemv_cols_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32, co
                 mx = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(ushort2_t, mx), __builtin_bit_cast(ushort2_t, xw[row][m] & 0x7fff7fffu)));
             const uint32_t e = max(mx & 0xffffu, mx >> 16) >> 10;
             // biased exponent of the word's largest weighted magnitude, plus four; an infinity or a NaN beyond all of them
-            uint32_t ew = max(e, 1u) - (uint32_t)weight + 4u + (e == 31u ? 256u : 0u);
+            const uint32_t own = max(e, 1u) - (uint32_t)weight + 4u;
+            uint32_t ew = own + (e == 31u ? 256u : 0u);
             ew = max_dpp<0xB1>(ew);          // quad_perm [1,0,3,2]
             ew = max_dpp<0x4E>(ew);          // quad_perm [2,3,0,1]
-            const int s = 18 + 4 - (int)(ew & 0xffu), sr = s - weight, k1 = sr / 2, k2 = sr - k1;
+            odd_row[row] = ew >= 256u;
+            wide = wide || (mx != 0u && ew - own - (COLS_WIDE + 1u) < 64u);
+            s[row] = 18 + 4 - (int)(ew & 0xffu);
+            const int sr = s[row] - weight, k1 = sr / 2, k2 = sr - k1;
             const _Float16 f1 = __builtin_bit_cast(_Float16, (uint16_t)((15 + k1) << 10)), f2 = __builtin_bit_cast(_Float16, (uint16_t)((15 + k2) << 10));
 #pragma unroll
-            for (int n = 0; n < 4; ++n) {   // codes 2 n, 2 n + 1: the even activations of the dwords, then the odd ones
-                const uint32_t a = xw[row][2 * (n & 1)], b = xw[row][2 * (n & 1) + 1];
-                const half2_t p = __builtin_bit_cast(half2_t, __builtin_amdgcn_perm(b, a, n < 2 ? 0x05040100u : 0x07060302u)) * (half2_t){f1, f1} * (half2_t){f2, f2};
+            for (int n = 0; n < 4; ++n) {
+                const half2_t p = pair(row, n) * (half2_t){f1, f1} * (half2_t){f2, f2};
                 v[8 * row + 2 * n] = p.x;
                 v[8 * row + 2 * n + 1] = p.y;
                 if constexpr (NR == 2) {   // the conversions take 32
@@ -302,7 +316,46 @@ hlq_gemv_cols_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32, co
                     v[16 + 8 * row + 2 * n + 1] = (_Float16)0.0f;
                 }
             }
-            if (xr == 0) ((uint8_t *)scales)[(row * 4 + g) * 4 + xi] = (uint8_t)(ew >= 256u ? 255 : 127 + 2 - s);
+        }
+        if constexpr (LEFT) {
+            // at most the activation's own bits, so exact in fp32, and in fp16 down to 2^-28 of the largest
+            float rest[8 * NR];
+#pragma unroll
+            for (int row = 0; row < NR; ++row)
+#pragma unroll
+                for (int n = 0; n < 4; ++n) {
+                    const half2_t p = pair(row, n);
+                    const float f = __builtin_bit_cast(float, (uint32_t)(127 + s[row] - weight) << 23);
+                    rest[8 * row + 2 * n] = (float)p.x * f;
+                    rest[8 * row + 2 * n + 1] = (float)p.y * f;
+                }
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const half32_t held = __builtin_amdgcn_cvt_scalef32_pk32_f16_bf6(__builtin_amdgcn_cvt_scalef32_pk32_bf6_f16(v, 1.0f), 1.0f);
+                if (t < 3) v = (v - held) * (_Float16)16.0f;
+#pragma unroll
+                for (int i = 0; i < 8 * NR; ++i) rest[i] -= (float)held[i] * (1.0f / (float)(1 << 4 * t));
+            }
+#pragma unroll
+            for (int row = 0; row < NR; ++row) {
+                float most = 0.f;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) most = fmaxf(most, fabsf(rest[8 * row + i]));
+                uint32_t b = __builtin_bit_cast(uint32_t, most);
+                b = max_dpp<0xB1>(b);
+                b = max_dpp<0x4E>(b);
+                const bool some = b != 0u && !odd_row[row];
+                const int up = some ? 3 + 127 - (int)(b >> 23) : 0;
+                const float f = __builtin_bit_cast(float, (uint32_t)(127 + up) << 23);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[8 * row + i] = some ? (_Float16)(rest[8 * row + i] * f) : (_Float16)0.0f;
+                s[row] = some ? s[row] + up : 2;
+                odd_row[row] = false;
+            }
+        }
+        if (xr == 0) {
+#pragma unroll
+            for (int row = 0; row < NR; ++row) ((uint8_t *)scales)[(row * 4 + g) * 4 + xi] = (uint8_t)(odd_row[row] ? 255 : 127 + 2 - s[row]);
         }
         // 48 bits a row and term at byte 6 xr of the word's 24: a 32-bit and a 16-bit store, in this order or the other
         const bool odd = xr & 1;
@@ -336,6 +389,7 @@ hlq_gemv_cols_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32, co
             ascale[row] = g == a_sg ? (int)(((const u32_alias *)scales)[row * 4 + a_sg] - 0x04040404u * a_t) : 0x7f7f7f7f;
         }
         sum_groups();
+        return __any(wide);
     };
     auto make_operands = [&]() {
         // largest magnitude of the window -> power-of-two scale (biased fp16 exponent e: |x| < 2^(e-14), scaled by 2^(29-e)
@@ -386,10 +440,13 @@ hlq_gemv_cols_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32, co
     // ---- steps ---------------------------------------------------------------------------------------------------
     auto scale = [](uint16_t h) -> float { return (float)__builtin_bit_cast(_Float16, h); };
     int win = wbeg, cb = s0;
-    auto step = [&]() {
-        if (cb == s0) {
+    bool any_wide = false;   // several rows
+    // AHEAD: the next step's loads are requested on the way
+    auto step = [&](auto ahead_c, bool more) {
+        constexpr bool AHEAD = decltype(ahead_c)::value;
+        if (cb == s0 && !more) {
             if constexpr (NR == 1) make_operands();
-            else make_rows();
+            else any_wide = make_rows(std::false_type{}) || any_wide;
             if (win + 1 < wend) load_x(win + 1);
         }
         __builtin_amdgcn_sched_barrier(0);   // the operands are made before anything waits for the weights
@@ -399,7 +456,7 @@ hlq_gemv_cols_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32, co
         uint16_t mt[SEG][Q + 1];
 #pragma unroll
         for (int i = 0; i < Regs::NM; ++i) ((int4a *)xt)[64 * i + lane] = R.mt[i];
-        if (!ONE) load_meta(R);
+        if (AHEAD) load_meta(R);
 #pragma unroll
         for (int sg = 0; sg < SEG; ++sg) {
 #pragma unroll
@@ -429,7 +486,7 @@ hlq_gemv_cols_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32, co
                 asm volatile("" : "+v"(w));   // expanded here and not earlier, where it would hold four more registers
                 B = expand(w);
             }
-            if (!ONE && n % 4 == 2) load_plane(R, n / 4);   // the plane's last word has been expanded: the next step's
+            if (AHEAD && n % 4 == 2) load_plane(R, n / 4);   // the plane's last word has been expanded: the next step's
             if (n >= CHAIN && n % CHAIN == (CHAIN > 1 ? 1 : 0)) apply(chain - 1);
             __builtin_amdgcn_sched_barrier(0);
         });
@@ -458,18 +515,36 @@ hlq_gemv_cols_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32, co
             if constexpr (NR == 4) v = g & 2 ? (g & 1 ? y[3] : y[2]) : v;
             float *slot = red + (((cb - cb0) * KW + part) * NR + (g & (NR - 1))) * 16 + c;
             if (g < NR) {
-                if (win > wbeg) v += *slot;
+                if (win > wbeg || more) v += *slot;
                 *slot = v;
             }
         }
-        if (!ONE) advance();
+        if (AHEAD) advance();
         if (++cb == s1) {
             cb = s0;
             ++win;
         }
     };
     if (steps > 0) {
-        for (int s = 0; s < (ONE ? 1 : steps); ++s) step();
+        for (int s = 0; s < (ONE ? 1 : steps); ++s) step(std::integral_constant<bool, !ONE>{}, false);
+        // once more through the windows with wide words, with what the terms leave of them
+        if constexpr (NR > 1) {
+            if (__builtin_expect(any_wide, 0))
+                for (int w = wbeg; w < wend; ++w) {
+                    load_x(w);
+                    if (!make_rows(std::true_type{})) continue;
+                    win = w;
+                    for (cb = s0; win == w;) {
+                        l_win = w;
+                        l_cb = cb;
+                        locate();
+                        load_meta(R);
+#pragma unroll
+                        for (int j = 0; j < Q; ++j) load_plane(R, j);
+                        step(std::false_type{}, true);
+                    }
+                }
+        }
     } else if (wend == wbeg) {   // no window: nothing to add
         for (int i = lane; i < (s1 - s0) * 16 * NR; i += 64) red[((s0 - cb0 + i / (16 * NR)) * KW + part) * 16 * NR + i % (16 * NR)] = 0.f;
     }
