@@ -585,10 +585,11 @@ RunShape plan_many_rows(int count, const HlqGemvItem *items, long units)
 // launches 5 % faster on average and 1 % slower at most; us:  q = 4, 4 rows  layer of hidden 3072 / ffn 8192 27.5 -> 18.0, hidden
 // 2816 / ffn 8192 25.9 -> 20.4, 11008 x 9000 31.4 -> 22.3, 8192 x 10240 25.8 -> 20.2;  q = 2, 2 rows  hidden 3072 12.3 -> 10.6,
 // 28672 x 8192 22.1 -> 18.1;  G = 64, q = 4, 2 rows  hidden 3072 22.4 -> 15.8
-RunShape plan_few_rows(int count, const HlqGemvItem *items, long units)
+RunShape plan_few_rows(int count, const HlqGemvItem *items, long units, bool forced)
 {
     static const RunShape cand[] = {{8, 4}, {8, 6}, {8, 8}, {4, 4}, {4, 6}, {4, 8}};
-    return plan_runs(count, items, {8, units < 12000 ? 4 : 6}, cand, {2, 0.5, 0.6, 1});
+    const RunShape usual = {8, units < 12000 ? 4 : 6};
+    return forced ? usual : plan_runs(count, items, usual, cand, {2, 0.5, 0.6, 1});   // (four wavefronts double the slices of a forced run)
 }
 
 // Work split of a launch of the one-row matrix-core kernel (hlq_gemv_cols.hip).  A step is 16 columns x 4 chunks of one
@@ -695,6 +696,19 @@ int plan_cols(int count, const HlqDims *dms, int rows, int forced_w, int cpw, Co
         out[i].ntg = (int)(ntg < 1 ? 1 : ntg);
     }
     return W;
+}
+
+// Whether arrival counters (one per workgroup column where K is split) and the block arithmetic hold such a split.
+bool cols_fit(int count, const HlqDims *dms, const ColsSplit *sp)
+{
+    long counters = 0, blocks = 0;
+    for (int i = 0; i < count; ++i) {
+        const unsigned long long slices = (unsigned long long)(dms[i].nchunks + sp[i].cps - 1) / sp[i].cps;
+        if (sp[i].ntg * slices * slices >= 0x100000000ULL) return false;
+        if (slices > 1) counters += sp[i].ntg;
+        blocks += (long)(sp[i].ntg * slices);
+    }
+    return counters <= HLQ_WS_ARRIVAL_COUNTERS && blocks <= 0x7fffffffL;
 }
 
 void plan_cols_problem(const HlqDims &dm, const ColsSplit &sp, GemvProb &p)
@@ -824,11 +838,10 @@ static hlq_status plan_gemv_batch(int count, const HlqGemvItem *items, hlq_out_d
         if (pl.W < 0 || pl.cpw < 0) return HLQ_ERR_UNSUPPORTED;   // (of the environment)
     } else if (rows > 1) {
         // narrow launches: short runs on few wavefronts per workgroup (measured on 8B shapes, q = 4, 2..8 rows)
-        const RunShape r = units < 4096 ? RunShape{4, 2} : plan_few_rows(count, items, units);
-        pl.W = r.W;
-        pl.cpw = r.cpw;
-        if (const int v = g_plan_w.load(std::memory_order_relaxed)) pl.W = v;
-        if (const int v = g_plan_cpw.load(std::memory_order_relaxed)) pl.cpw = v;
+        const int w = g_plan_w.load(std::memory_order_relaxed), cpw = g_plan_cpw.load(std::memory_order_relaxed);
+        const RunShape r = units < 4096 ? RunShape{4, 2} : plan_few_rows(count, items, units, w || cpw);
+        pl.W = w ? w : r.W;
+        pl.cpw = cpw ? cpw : r.cpw;
     }
     {
         const int q0 = items[0].dm.q, G0 = items[0].dm.G;
@@ -853,6 +866,9 @@ static hlq_status plan_gemv_batch(int count, const HlqGemvItem *items, hlq_out_d
         HlqDims dms[HLQ_MAX_BATCH];
         for (int i = 0; i < count; ++i) dms[i] = items[i].dm;
         pl.W = plan_cols(count, dms, rows, pl.W, pl.cpw, split);
+        // several rows: a forced plan with more slices than there is room for is not followed (it is no reason to refuse the
+        // call: the 64-column kernel counts arrivals per tile and would have had room, the built-in plan always has)
+        if (rows > 1 && !cols_fit(count, dms, split)) pl.W = plan_cols(count, dms, rows, 0, 0, split);
     }
 
     b.count = count;

@@ -43,3 +43,35 @@ def test_rows_beyond_the_kernels_have_no_plan():
         else:
             with pytest.raises(B.HlqError):
                 B.gemv_plan_query(descs, 3)
+
+
+# a forced plan changes how K is cut and nothing else: two to four rows that go to the 16-column kernel, whose workgroups own
+# fewer columns than a tile has, are planned whatever is forced
+@pytest.mark.parametrize("W,cpw", [(0, 1), (1, 1), (1, 2), (1, 100), (2, 1), (4, 2), (8, 1), (8, 100), (16, 3), (0, 5000)])
+@pytest.mark.parametrize("K,N,G,M,count", [(640, 557248, 32, 2, 4), (14080, 845040, 64, 4, 1), (1 << 17, 8192, 32, 3, 8), (1 << 20, 131072, 64, 3, 1),
+                                           (1 << 21, 16384, 32, 4, 1), (512, 1 << 20, 64, 3, 8), (128, 1 << 20, 32, 2, 1), (4096, 4096, 128, 4, 1)])
+def test_forced_plans_refuse_nothing(K, N, G, M, count, W, cpw):
+    descs = [B.make_desc(K, N, 1, G)] * count
+    B.set_gemv_plan(0, W, cpw)
+    try:
+        infos = B.gemv_plan_query(descs, M)
+    finally:
+        B.set_gemv_plan(0, 0, 0)
+    for info in infos:
+        check_plan(info, K // 128, (K, N, G, M, count, W, cpw))
+    # partial results of a workgroup: 64 bytes per row of four (two) and column block and wavefront on it, beside its operands
+    blocks = -(-(-(-N // 16)) // infos[0].tile_groups)
+    rows = 2 if M == 2 else 4
+    assert blocks * infos[0].waves_per_tile * 64 * rows + infos[0].waves_per_workgroup * 6400 <= 160 * 1024
+
+
+# the same of the few-rows kernel, whose own choice of four wavefronts a workgroup would double the slices of a forced run
+@pytest.mark.parametrize("K,N,G,count,cpw", [(128 * 9921, 922440, 128, 1, 3), (1174528, 76184, 128, 4, 1), (992256, 100424, 256, 1, 1)])
+def test_forced_runs_of_the_few_rows_kernel(K, N, G, count, cpw):
+    B.set_gemv_plan(0, 0, cpw)
+    try:
+        infos = B.gemv_plan_query([B.make_desc(K, N, 3, G)] * count, 2)
+    finally:
+        B.set_gemv_plan(0, 0, 0)
+    for info in infos:
+        check_plan(info, K // 128, (K, N, G, count, cpw))
