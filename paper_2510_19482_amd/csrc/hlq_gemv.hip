@@ -833,8 +833,9 @@ static hlq_status plan_gemv_batch(int count, const HlqGemvItem *items, hlq_out_d
         pl.cpw = r.cpw;
         if (const int v = g_plan_cpw.load(std::memory_order_relaxed)) pl.cpw = v < 4 ? 4 : v;
     } else if (cols) {
-        pl.W = pl.forced_w;   // 0: plan_cols chooses
-        pl.cpw = pl.forced_cpw;
+        // 0: plan_cols chooses.  The environment is for one row, as for the other kernels
+        pl.W = rows == 1 ? pl.forced_w : g_plan_w.load(std::memory_order_relaxed);
+        pl.cpw = rows == 1 ? pl.forced_cpw : g_plan_cpw.load(std::memory_order_relaxed);
         if (pl.W < 0 || pl.cpw < 0) return HLQ_ERR_UNSUPPORTED;   // (of the environment)
     } else if (rows > 1) {
         // narrow launches: short runs on few wavefronts per workgroup (measured on 8B shapes, q = 4, 2..8 rows)

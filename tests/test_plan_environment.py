@@ -44,3 +44,11 @@ def test_environment_is_the_knob(W, cpw):
 
 def test_values_out_of_range_are_refused():
     assert plans(HLQ_GEMV_W="-3")[0::2] == [(3,)] * 3
+
+
+@pytest.mark.parametrize("M", [2, 4])
+def test_several_rows_do_not_look_at_it(M):
+    query = QUERY.replace("], 1)[0]", f"], {M})[0]")
+    out = [subprocess.run([sys.executable, "-c", query], cwd=ROOT, env=dict(os.environ, **env), capture_output=True, text=True, check=True).stdout
+           for env in ({}, {"HLQ_GEMV_W": "2", "HLQ_GEMV_CPW": "5"}, {"HLQ_GEMV_W": "-3", "HLQ_GEMV_CPW": "-1"})]
+    assert out[0] == out[1] == out[2]
