@@ -103,7 +103,8 @@ HLQ_API hlq_status hlq_workspace_init(void *ws, size_t ws_bytes, void *stream);
  * consecutive k of a column) into the tensors hlq_pack consumes.  Start: uniform grid over the
  * group's [min, max]; then t_max times (the paper uses 10): per weight the nearest of the 2^q
  * values sum_j s_j bit_j(c) + z (ties: smallest code), then (s, z) by least squares given the
- * bits.  fp64 arithmetic.  If the least-squares system of a group is rank deficient (a plane
+ * bits.  fp64 arithmetic, in which the sums over a group are exact (weights that lie below 2^-21 of their group's largest
+ * are rounded to 2^-43 of it or finer first; G >= 64), so a group's results depend on its weights alone, not on K, N or where it lies.  If the least-squares system of a group is rank deficient (a plane
  * constant over the group, equal or complementary planes, all weights equal), columns are taken in
  * the order 1, b_0, b_1, ... and a column that depends on the earlier ones keeps its previous
  * parameter.  Plane j of the codes belongs to scale j (initially 2^j * Delta).

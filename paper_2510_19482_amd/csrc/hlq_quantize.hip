@@ -66,10 +66,11 @@ __device__ __forceinline__ void sort_keys(uint32_t (&key)[NC])
                     }
 }
 
-// wavefronts on a SIMD that the registers have to leave room for (a lane keeps G weights)
-constexpr int quantize_waves(int q, int G)
+// wavefronts on a SIMD that the registers have to leave room for (a lane keeps G weights; launches with several lanes a group
+// have four at most)
+constexpr int quantize_waves(int q, int G, int L)
 {
-    return G == 32 ? (q == 1 ? 7 : q == 2 ? 5 : q == 3 ? 4 : 3) : G == 128 ? (q == 1 ? 3 : 2) : q <= 2 ? 4 : 3;
+    return G == 32 ? (q == 1 ? (L > 1 ? 6 : 7) : q == 2 ? 5 : q == 3 ? 4 : 3) : G == 128 ? (q == 1 ? 3 : 2) : q <= 2 ? 4 : 3;
 }
 
 // Bit-pattern selection.  The codes are the argmin over 2^q candidate distances, computed in fp64, first minimum in
@@ -102,7 +103,7 @@ constexpr int quantize_waves(int q, int G)
 //   G = 32   fp32 normals         73 / 142 / 270 / 491 -> 50 / 106 / 163 / 272;  -1, 0, 1: 67 / 142 / 268 / 481 -> 58 / 149 / 233 / 435
 //   G = 256                      166 / 686 / 829 / 949 -> 49 / 87 / 124 / 175 (by one lane a group, from the L2 every round, 127 / 155 / 201 / 255)
 template <int Q, int G, int L>
-__global__ void __launch_bounds__(256, quantize_waves(Q, G / L))
+__global__ void __launch_bounds__(256, quantize_waves(Q, G / L, L))
 hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, int scan_first, uint8_t *__restrict__ codes,
                     uint16_t *__restrict__ scales, uint16_t *__restrict__ zeros, float *__restrict__ group_err)
 {
@@ -139,16 +140,16 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, int sc
 
     float wv[GL];
     float lof, hif;   // Alg. 1 steps 2-3 (min / max are exact in fp32)
-    double rw = 0.0;  // sum of the weights, in order
+    double rw = 0.0;  // sum of the weights
     load_rows(wv, 0, N);
     lof = hif = wv[0];
+    float least = fabsf(wv[0]);
 #pragma unroll
     for (int i = 1; i < GL; ++i) {
         lof = wv[i] < lof ? wv[i] : lof;
         hif = wv[i] > hif ? wv[i] : hif;
+        least = fminf(least, fabsf(wv[i]));
     }
-#pragma unroll
-    for (int i = 0; i < GL; ++i) rw += (double)wv[i];
     // the lanes of a group are neighbours: l apart is a permutation of four
     auto across = [](uint32_t v, auto l) -> uint32_t { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(l)::value == 1 ? 0xB1 : 0x4E, 0xf, 0xf, false); };
     auto add_parts = [&](double v) -> double {
@@ -165,9 +166,37 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, int sc
             const float lo2 = __builtin_bit_cast(float, across(__builtin_bit_cast(uint32_t, lof), l)), hi2 = __builtin_bit_cast(float, across(__builtin_bit_cast(uint32_t, hif), l));
             lof = lo2 < lof ? lo2 : lof;
             hif = hi2 > hif ? hi2 : hif;
+            least = fminf(least, __builtin_bit_cast(float, across(__builtin_bit_cast(uint32_t, least), l)));
         });
-        rw = add_parts(rw);
     }
+    const float largest = fmaxf(fabsf(lof), fabsf(hif));
+    // The number of lanes of a group depends on the size of the launch; its results do not, since its sums are exact in fp64 and
+    // so the same in any order.  fp32 weights down to 2^-21 of the largest are so as they are.  Where some (not zero) are
+    // smaller, all are rounded to multiples of 2^-52 of a power of two that no sum of magnitudes exceeds: a change, by less
+    // than fp64 sums are rounded by, in weights below 2^-21 of the largest.  (One number in ten million of a normal distribution.)
+    double unit = 0.0;   // adding and subtracting it rounds
+    auto in_units = [&](float w) -> float { return (float)(((double)w + unit) - unit); };
+    if constexpr (G > 32) {
+        if (__builtin_expect(__any(least < largest * 0x1p-21f), 0)) {
+            least = __builtin_inff();
+#pragma unroll
+            for (int i = 0; i < GL; ++i) least = wv[i] != 0.f ? fminf(least, fabsf(wv[i])) : least;
+            if constexpr (L > 1) unrolled<(L == 4 ? 2 : 1)>([&](auto k) { least = fminf(least, __builtin_bit_cast(float, across(__builtin_bit_cast(uint32_t, least), std::integral_constant<int, 1 + decltype(k)::value>{}))); });
+            constexpr int LOG_G = G == 64 ? 6 : G == 128 ? 7 : 8;
+            const int above = (int)(__builtin_bit_cast(uint32_t, largest) >> 23) - 126 + LOG_G;
+            if (least < largest * 0x1p-21f && largest < __builtin_inff()) unit = __builtin_bit_cast(double, (uint64_t)(1023 + above) << 52 | 1ull << 51);
+            if (__any(unit != 0.0)) {
+#pragma unroll
+                for (int i = 0; i < GL; ++i) {
+                    asm volatile("" : "+v"(wv[i]));
+                    wv[i] = in_units(wv[i]);
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < GL; ++i) rw += (double)wv[i];
+    rw = add_parts(rw);
     auto weight = [&](int i) -> float {
         // opaque to the optimiser, so the fp64 copies are made per use instead of being kept
         // for the whole kernel (which would double the registers held)
@@ -177,7 +206,6 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, int sc
     const double lo = (double)lof, hi = (double)hif;
     const double delta = (hi - lo) / (double)(NC - 1);
     const bool constant = lof == hif && rw - rw == 0.0;   // all weights equal (and no NaN among them)
-    const float largest = fmaxf(fabsf(lof), fabsf(hif));
     double theta[P];   // theta[0] = z, theta[1 + j] = s_j
     theta[0] = lo;
 #pragma unroll
@@ -559,7 +587,7 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, int sc
                     __builtin_amdgcn_sched_barrier(0);   // the loads go out first
 #pragma unroll
                     for (int u = 0; u < AHEAD; ++u) {
-                        take(i + u, cur[u]);
+                        take(i + u, in_units(cur[u]));
                         if ((u & 3) == 3) __builtin_amdgcn_sched_barrier(0);   // not many weights converted ahead (registers)
                     }
                 }
@@ -726,18 +754,26 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, int sc
         for (int j = 0; j < Q; ++j) scales[((size_t)j * ngroups + gi) * N + n] = __builtin_bit_cast(uint16_t, (_Float16)theta[1 + j]);
     }
     if (group_err) {
+        // not exact: the lanes of a group one after the other, each from where the one before it stopped
         double e = 0.0;
+#pragma unroll 1
+        for (unsigned turn = 0; turn < (unsigned)L; ++turn) {
+            const uint64_t b = __builtin_bit_cast(uint64_t, e);
+            constexpr int BEFORE = L == 4 ? 0x90 : 0xA0;   // quad_perm [0,0,1,2], [0,0,2,2]
+            const uint32_t lo32 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, BEFORE, 0xf, 0xf, false), hi32 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(b >> 32), BEFORE, 0xf, 0xf, false);
+            if (turn != part) continue;
+            if (turn > 0) e = __builtin_bit_cast(double, (uint64_t)hi32 << 32 | lo32);
 #pragma unroll
-        for (int i = 0; i < GL; ++i) {
-            const int c = __builtin_amdgcn_raw_buffer_load_b8(c_rows, (int)n + first_row, i * N, 0);
-            double v = theta[0];
+            for (int i = 0; i < GL; ++i) {
+                const int c = __builtin_amdgcn_raw_buffer_load_b8(c_rows, (int)n + first_row, i * N, 0);
+                double v = theta[0];
 #pragma unroll
-            for (int j = 0; j < Q; ++j) v += theta[1 + j] * (double)((c >> j) & 1);
-            const double dlt = (double)weight(i) - v;
-            e += dlt * dlt;
+                for (int j = 0; j < Q; ++j) v += theta[1 + j] * (double)((c >> j) & 1);
+                const double dlt = (double)weight(i) - v;
+                e += dlt * dlt;
+            }
         }
-        e = add_parts(e);
-        if (part == 0) group_err[(size_t)gi * N + n] = (float)e;
+        if (part == L - 1) group_err[(size_t)gi * N + n] = (float)e;
     }
 }
 

@@ -31,3 +31,33 @@ def test_columns(K, N, G, q):
         assert (np.abs(got.astype(np.float64) - want) <= 2.0 ** -10 * np.abs(want) + 2.0 ** -24).all()
     err_ref = ((QO.reconstruct(ref, S_ref, Z_ref, q, G) - W[:, cols].astype(np.float64)) ** 2).reshape(K // G, G, -1).sum(axis=1)
     assert np.allclose(err.cpu().numpy()[:, cols], err_ref, rtol=1e-5, atol=1e-12)
+
+
+@pytest.mark.parametrize("q", [1, 2, 3, 4])
+@pytest.mark.parametrize("G", [64, 128, 256])
+def test_columns_do_not_depend_on_the_launch(q, G):
+    """The same columns in launches of one, two and four lanes a group (two and four at G = 256), also where weights are so far
+    apart that their fp64 sums are rounded: 2^-60 to 1 in a column, and sums that decide between two codes."""
+    K = 1024
+    rng = np.random.default_rng(q + G)
+    W = (rng.standard_normal((K, 64)) * 0.02).astype(np.float32)
+    W[:, 8:32] = rng.uniform(1.0, 2.0, (K, 24)) * np.exp2(rng.integers(-60, 1, (K, 24))) * np.where(rng.random((K, 24)) < 0.5, -1, 1)
+    W[:, 30] *= np.float32(2.0 ** -100)                                    # to where fp32 numbers are subnormal
+    W[:, 31] *= np.float32(2.0 ** 120)
+    W[:, 32:40] = np.where(rng.random((K, 8)) < 0.5, 0, W[:, 32:40])         # zeros are not far apart
+    # two clusters with means 0 and 2 and a weight midway (equally near: code 0), unless the sum of the rest, -2^-50 each and
+    # rounded away beside the others, is kept
+    W[:, 40:48] = -2.0 ** -50
+    W[:, 40:48].reshape(K // G, G, 8)[:, :11] = np.array([4, -1, 1] + 8 * [1.75], dtype=np.float32)[:, None]
+    results = []
+    for N in ((64, 2056) if G == 256 else (64, 2056, 16456)):
+        wide = np.full((K, N), 0.01, dtype=np.float32)
+        wide[:, :64], wide[:, -64:] = W, W
+        codes, S, Z, err = (t.cpu().numpy() for t in B.hlq_quantize(B.make_desc(K, N, q, G), dev(wide), 3, with_err=True))
+        for cols in (slice(0, 64), slice(N - 64, N)):
+            results.append((codes[:, cols], S[:, :, cols].view(np.uint16), Z[:, cols].view(np.uint16), err[:, cols].view(np.uint32)))
+    for other in results[1:]:
+        assert all(np.array_equal(a, b) for a, b in zip(results[0], other))
+    if q == 1:
+        codes = results[0][0][:, 40:48].reshape(K // G, G, 8)
+        assert (codes[:, 2] == 0).all() and (codes[:, [0, 3]] == 1).all()
