@@ -13,7 +13,7 @@ from gpu_util import dev, pack_on_gpu
 pytestmark = pytest.mark.gpu
 
 
-def product(K, N, q, G, X, pad=0, key="few"):
+def product(K, N, q, G, X, pad=0, key="few", cols=slice(None)):
     """fp32 result, reference, and a bound: what the terms leave of an activation is at most 2^-18 of the largest of its word
     (32 k), the sums are fp32 over the planes one by one (2^-20 of the sum of magnitudes is ample for K <= 8192)."""
     codes, S, Z = synth.make_weight(K, N, q, G, "few", key)
@@ -28,9 +28,10 @@ def product(K, N, q, G, X, pad=0, key="few"):
     Y = ybuf.cpu().numpy().astype(np.float64)
     assert (Y[:, N:] == 7.0).all() and int(ws[:131072].view(torch.int32).abs().sum()) == 0
     x = np.abs(X.astype(np.float64))
+    codes, S, Z = codes[:, cols], S[:, :, cols], Z[:, cols]
     planes = np.repeat(S.astype(np.float64).sum(0) + np.abs(Z.astype(np.float64)), G, 0)
     largest = np.repeat(x.reshape(M, K // 32, 32).max(2), 32, 1)
-    return Y[:, :N], O.gemm_dequant(X, codes, S, Z, q, G), 2.0 ** -18 * largest @ planes + 2.0 ** -20 * x @ planes
+    return Y[:, :N][:, cols], O.gemm_dequant(X, codes, S, Z, q, G), 2.0 ** -18 * largest @ planes + 2.0 ** -20 * x @ planes
 
 
 @pytest.mark.parametrize("M", [2, 3, 4])
@@ -42,11 +43,23 @@ def test_formats(q, G, M):
     assert (np.abs(Y - ref) <= bound).all()
 
 
-@pytest.mark.parametrize("K,N", [(8192, 264), (8064, 520), (512, 4104), (256, 16392), (4096, 4096), (4096, 8200)])
+@pytest.mark.parametrize("K,N", [(8192, 264), (8064, 520), (512, 4104), (256, 16392), (4096, 4096), (4096, 8136)])
 def test_one_step_and_several(K, N):
     for M in (2, 4):
         Y, ref, bound = product(K, N, 2, 128, synth.make_x(M, K, "few"))
         assert (np.abs(Y - ref) <= bound).all()
+
+
+# a wavefront walks over several column blocks, within a tile, into the next one and into a narrow last one: the largest launches of
+# up to 4096 chunk-tiles, and the smallest from 14000 on (groups of 32 and 64).  Results of the first and last tiles and some between
+@pytest.mark.parametrize("K,N,q,G,M", [(4096, 8136, 2, 128, 4), (4096, 8072, 4, 256, 3), (2048, 16328, 1, 64, 4), (1024, 112072, 2, 64, 4), (1024, 112072, 4, 64, 3),
+                                       (1024, 112072, 2, 32, 2), (128, 896136, 1, 32, 3), (8192, 14216, 3, 32, 4)])
+def test_several_column_blocks(K, N, q, G, M):
+    info = B.gemv_plan_query([B.make_desc(K, N, q, G)], M)[0]
+    assert info.tile_groups * (info.waves_per_workgroup // info.waves_per_tile) < -(-N // 16)
+    cols = np.unique(np.concatenate([np.arange(0, 200), np.arange(N - 200, N), np.random.default_rng(N).integers(0, N, 400)]))
+    Y, ref, bound = product(K, N, q, G, synth.make_x(M, K, "few"), cols=cols)
+    assert (np.abs(Y - ref) <= bound).all()
 
 
 @pytest.mark.parametrize("W,cpw", [(8, 1), (4, 2), (2, 3)])

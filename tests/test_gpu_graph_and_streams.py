@@ -33,7 +33,9 @@ CASES = [
     ("gemv, K split", 14336, 512, 2, 128, 1),
     ("gemv lookups, K split", 14336, 512, 2, 128, 1),
     ("few rows on the GEMV kernel", 8192, 264, 4, 128, 3),
-    ("tiled kernel, K split + reduce kernel", 14336, 256, 2, 128, 16),
+    ("many-rows kernel, K split", 4096, 5128, 4, 128, 16),
+    ("short-M kernel, K split + reduce kernel", 14336, 256, 2, 128, 16),
+    ("tiled kernel, K split + reduce kernel", 14336, 256, 2, 128, 40),
     ("tiled kernel, several row blocks", 2048, 520, 3, 64, 200),
 ]
 
