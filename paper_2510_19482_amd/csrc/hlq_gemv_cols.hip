@@ -249,8 +249,6 @@ hlq_gemv_cols_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32, co
     const char *a_zero = xt + ZERO_AT, *a_data = xt + a_t * COLS_TERM + a_sg * 128 + 16 * (g & 1);
     const char *a_lo = a_on && a_sg < 2 ? a_data : a_zero, *a_hi = a_on && a_sg >= 2 ? a_data : a_zero;
     if (lane < 8) ((int4a *)(xt + ZERO_AT))[lane] = (int4a){0, 0, 0, 0};
-    // several rows: row (lane & 15) = 4 sg + t holds the codes of chunk sg, which are k block sg: in lane group g == sg
-    const char *r_data = g == a_sg ? xt + (a_t * 4 + a_sg) * COLS_CODES : xt + ZERO_AT;
     auto expand = [](uint32_t w) -> int8v {   // plane word -> 32 fp4 codes (bit 4p+r -> nibble p of register r)
         return (int8v){(int)(w & 0x11111111u), (int)(w & 0x22222222u), (int)(w & 0x44444444u),
                        (int)((w >> 1) & 0x44444444u), 0, 0, 0, 0};
@@ -281,6 +279,11 @@ hlq_gemv_cols_kernel(const int4v bb_lo, const int4v bb_hi, const int out_f32, co
     // (as there): a lane that has activations has only such as are 2^-8 of the word's largest, as weighted.
     auto make_rows = [&](auto left_c) -> bool {
         constexpr bool LEFT = decltype(left_c)::value;
+        int mine = lane;
+        if constexpr (Q == 4 && G == 32 && NR == 4) asm volatile("" : "+v"(mine));   // what follows from it is made again: no registers are left to keep it in
+        const int g = mine >> 4, xi = (mine >> 2) & 3, xr = mine & 3, a_sg = (mine & 15) >> 2, a_t = mine & 3;
+        // row (lane & 15) = 4 sg + t holds the codes of chunk sg, which are k block sg: in lane group g == sg
+        const char *r_data = g == a_sg ? xt + (a_t * 4 + a_sg) * COLS_CODES : xt + ZERO_AT;
         half32_t v;
         const int weight = xr < 3 ? xr + 1 : 3;
         char *scales = xt + ZERO_AT + 128;

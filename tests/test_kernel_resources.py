@@ -20,7 +20,8 @@ def kernels():
     return found
 
 
-@pytest.mark.parametrize("part", ["hlq_quantize_kernel", "hlq_gemm_mfma_group_reduce_kernel", "hlq_gemm_safe_kernel"])
+@pytest.mark.parametrize("part", ["hlq_quantize_kernel", "hlq_gemm_mfma_group_reduce_kernel", "hlq_gemm_safe_kernel", "hlq_gemv_cols_kernel",
+                                  "hlq_rows_split_kernel", "hlq_gemm_rows_kernel", "hlq_gemm_short_kernel"])
 def test_no_scratch_memory(part):
     # scratch is memory that the runtime sets aside per wavefront, and a spilled register is a trip to it in the inner loop
     mine = {n: k for n, k in kernels().items() if part in n}
