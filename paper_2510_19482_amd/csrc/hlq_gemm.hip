@@ -298,9 +298,10 @@ hlq_status hlq_launch_gemm(const HlqDims &dm, const void *packed, const uint16_t
 {
     if (use_mfma(M)) {
         // up to one row set of the matrix-core GEMV kernel (several activation rows per operand): measured
-        // faster than the tiled kernel there; from the second row set on the tiled kernel, whose time
-        // hardly depends on M up to 32 rows, is as fast or faster for a single call
-        if (!hlq_gemm_tiled_only() && (M <= hlq_gemv_mx_rows_per_set(dm.G) || hlq_gemm_few_wins(1, &dm, M)))
+        // faster than rebuilding weights there; from the second row set on the short-M kernel, whose time
+        // hardly depends on M up to 32 rows, is as fast or faster for a single call, except for up to four rows where
+        // hlq_gemm_few_rows says so
+        if (!hlq_gemm_tiled_only() && (M <= hlq_gemv_mx_rows_per_set(dm.G) || hlq_gemm_few_rows(1, &dm, M)))
             return hlq_launch_gemm_mx_rows(dm, packed, X, M, ldx, Y, ldy, out, ws, st);
         // 5..16 rows on a large matrix: the many-rows kernel (same rule as for grouped launches)
         if (g_gemm_path.load(std::memory_order_relaxed) != 3 && M <= hlq_gemm_rows_max(dm.G) &&

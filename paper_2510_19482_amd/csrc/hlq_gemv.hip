@@ -698,19 +698,6 @@ int plan_cols(int count, const HlqDims *dms, int rows, int forced_w, int cpw, Co
     return W;
 }
 
-// Whether arrival counters (one per workgroup column where K is split) and the block arithmetic hold such a split.
-bool cols_fit(int count, const HlqDims *dms, const ColsSplit *sp)
-{
-    long counters = 0, blocks = 0;
-    for (int i = 0; i < count; ++i) {
-        const unsigned long long slices = (unsigned long long)(dms[i].nchunks + sp[i].cps - 1) / sp[i].cps;
-        if (sp[i].ntg * slices * slices >= 0x100000000ULL) return false;
-        if (slices > 1) counters += sp[i].ntg;
-        blocks += (long)(sp[i].ntg * slices);
-    }
-    return counters <= HLQ_WS_ARRIVAL_COUNTERS && blocks <= 0x7fffffffL;
-}
-
 void plan_cols_problem(const HlqDims &dm, const ColsSplit &sp, GemvProb &p)
 {
     p.kw = sp.kw;
@@ -805,7 +792,21 @@ static bool few_rows_win(int count, const HlqGemvItem *items, int64_t rows)
     return hlq_gemm_few_wins(count, dms, rows);
 }
 
-static hlq_status plan_gemv_batch(int count, const HlqGemvItem *items, hlq_out_dtype out, void *ws, GemvBatch &b,
+static bool few_rows(int count, const HlqGemvItem *items, int64_t rows)
+{
+    HlqDims dms[HLQ_MAX_BATCH];
+    for (int i = 0; i < count; ++i) dms[i] = items[i].dm;
+    return hlq_gemm_few_rows(count, dms, rows);
+}
+
+// What a launch of several rows is planned with; where that does not fit, the next.
+enum PlanBy {
+    PLAN_KNOBS,   // the choice of kernel, and hlq_set_gemv_plan
+    PLAN_OWN,     // the choice of kernel, no knobs
+    PLAN_COLS,    // the 16-column kernel, no knobs
+};
+
+static hlq_status plan_gemv_batch(int count, const HlqGemvItem *items, hlq_out_dtype out, void *ws, PlanBy by, GemvBatch &b,
                                   GemvLaunchShape &ls)
 {
     if (count < 1 || count > HLQ_MAX_BATCH) return HLQ_ERR_UNSUPPORTED;
@@ -817,7 +818,7 @@ static hlq_status plan_gemv_batch(int count, const HlqGemvItem *items, hlq_out_d
         if (items[i].M != rows) return HLQ_ERR_UNSUPPORTED;
     if (rows < 1 || (rows > hlq_gemm_mx_rows_per_pass(items[0].dm.G) && !few_rows_win(count, items, rows))) return HLQ_ERR_UNSUPPORTED;
     const bool mx = use_mx() || rows > 1;   // several activation rows exist in the matrix-core kernels only
-    const bool cols = mx && (rows == 1 ? cols_wins(units, items[0].dm.q, items[0].dm.G) : few_rows_win(count, items, rows));
+    const bool cols = mx && (rows == 1 ? cols_wins(units, items[0].dm.q, items[0].dm.G) : by == PLAN_COLS ? few_rows(count, items, rows) : few_rows_win(count, items, rows));
     // more rows than one operand of the GEMV kernel holds: the many-rows kernel (terms chained through the
     // accumulator, activations converted once per workgroup), where it exists for this group size
     bool rowsk = !cols && rows > hlq_gemv_mx_rows_per_set(items[0].dm.G) && rows <= hlq_gemm_rows_max(items[0].dm.G) &&
@@ -827,22 +828,22 @@ static hlq_status plan_gemv_batch(int count, const HlqGemvItem *items, hlq_out_d
     if (!cols && !rowsk && rows >= 3 && rows <= hlq_gemm_rows_max(items[0].dm.G) &&
         (hlq_gemm_rows_all() || hlq_gemm_rows_wins_few(units, items[0].dm.q, rows)))
         rowsk = true;
+    // several rows: the knobs only, the environment is for one row
+    const int knob_w = by == PLAN_KNOBS ? g_plan_w.load(std::memory_order_relaxed) : 0, knob_cpw = by == PLAN_KNOBS ? g_plan_cpw.load(std::memory_order_relaxed) : 0;
     if (rowsk) {
         const RunShape r = plan_many_rows(count, items, units);
         pl.W = r.W;
         pl.cpw = r.cpw;
-        if (const int v = g_plan_cpw.load(std::memory_order_relaxed)) pl.cpw = v < 4 ? 4 : v;
+        if (knob_cpw) pl.cpw = knob_cpw < 4 ? 4 : knob_cpw;
     } else if (cols) {
-        // 0: plan_cols chooses.  The environment is for one row, as for the other kernels
-        pl.W = rows == 1 ? pl.forced_w : g_plan_w.load(std::memory_order_relaxed);
-        pl.cpw = rows == 1 ? pl.forced_cpw : g_plan_cpw.load(std::memory_order_relaxed);
+        pl.W = rows == 1 ? pl.forced_w : knob_w;   // 0: plan_cols chooses
+        pl.cpw = rows == 1 ? pl.forced_cpw : knob_cpw;
         if (pl.W < 0 || pl.cpw < 0) return HLQ_ERR_UNSUPPORTED;   // (of the environment)
     } else if (rows > 1) {
         // narrow launches: short runs on few wavefronts per workgroup (measured on 8B shapes, q = 4, 2..8 rows)
-        const int w = g_plan_w.load(std::memory_order_relaxed), cpw = g_plan_cpw.load(std::memory_order_relaxed);
-        const RunShape r = units < 4096 ? RunShape{4, 2} : plan_few_rows(count, items, units, w || cpw);
-        pl.W = w ? w : r.W;
-        pl.cpw = cpw ? cpw : r.cpw;
+        const RunShape r = units < 4096 ? RunShape{4, 2} : plan_few_rows(count, items, units, knob_w || knob_cpw);
+        pl.W = knob_w ? knob_w : r.W;
+        pl.cpw = knob_cpw ? knob_cpw : r.cpw;
     }
     {
         const int q0 = items[0].dm.q, G0 = items[0].dm.G;
@@ -852,7 +853,7 @@ static hlq_status plan_gemv_batch(int count, const HlqGemvItem *items, hlq_out_d
         if (!mx && table_variant() >= 0 && pl.W > 8) pl.W = 8;   // the plain variant kernels: up to 512 lanes
         if (rowsk) {
             pl.W = 4;
-            if (const int v = g_plan_w.load(std::memory_order_relaxed)) pl.W = v >= 8 ? 8 : v >= 4 ? 4 : 2;
+            if (knob_w) pl.W = knob_w >= 8 ? 8 : knob_w >= 4 ? 4 : 2;
         }
         if (mx)   // a power of two
             while (pl.W & (pl.W - 1)) pl.W &= pl.W - 1;
@@ -867,9 +868,6 @@ static hlq_status plan_gemv_batch(int count, const HlqGemvItem *items, hlq_out_d
         HlqDims dms[HLQ_MAX_BATCH];
         for (int i = 0; i < count; ++i) dms[i] = items[i].dm;
         pl.W = plan_cols(count, dms, rows, pl.W, pl.cpw, split);
-        // several rows: a forced plan with more slices than there is room for is not followed (it is no reason to refuse the
-        // call: the 64-column kernel counts arrivals per tile and would have had room, the built-in plan always has)
-        if (rows > 1 && !cols_fit(count, dms, split)) pl.W = plan_cols(count, dms, rows, 0, 0, split);
     }
 
     b.count = count;
@@ -971,13 +969,25 @@ static hlq_status plan_gemv_batch(int count, const HlqGemvItem *items, hlq_out_d
     return HLQ_OK;
 }
 
+// The plan of a launch.  With several rows a forced plan of more K slices than the counter block or the block arithmetic has room
+// for is not followed (it is no reason to refuse the call), and where the built-in plan of the 64-column kernel has too many, on
+// the widest and deepest matrices, the 16-column kernel, which seldom cuts K, takes the calls that it can.
+static hlq_status plan_launch(int count, const HlqGemvItem *items, hlq_out_dtype out, void *ws, GemvBatch &b, GemvLaunchShape &ls)
+{
+    hlq_status s = plan_gemv_batch(count, items, out, ws, PLAN_KNOBS, b, ls);
+    if (s != HLQ_ERR_UNSUPPORTED || items[0].M < 2) return s;
+    s = plan_gemv_batch(count, items, out, ws, PLAN_OWN, b, ls);
+    if (s != HLQ_ERR_UNSUPPORTED || !few_rows(count, items, items[0].M)) return s;
+    return plan_gemv_batch(count, items, out, ws, PLAN_COLS, b, ls);
+}
+
 hlq_status hlq_launch_gemv_batch(int count, const HlqGemvItem *items, hlq_out_dtype out, void *ws,
                                  hipStream_t st, size_t ws_cap)
 {
     hlq_clear_stale_error();
     GemvBatch b;
     GemvLaunchShape ls;
-    hlq_status s = plan_gemv_batch(count, items, out, ws, b, ls);
+    hlq_status s = plan_launch(count, items, out, ws, b, ls);
     if (s != HLQ_OK) return s;
     if (ws_cap && ls.ws_used > ws_cap) return HLQ_ERR_BUFFER_TOO_SMALL;   // checked on the plan that is launched
     const int q = items[0].dm.q, G = items[0].dm.G;
@@ -1025,7 +1035,7 @@ hlq_status hlq_gemv_ws_used(const HlqDims &dm, size_t *bytes)
     it.y = nullptr;
     GemvBatch b;
     GemvLaunchShape ls;
-    const hlq_status s = plan_gemv_batch(1, &it, HLQ_OUT_F16, nullptr, b, ls);
+    const hlq_status s = plan_launch(1, &it, HLQ_OUT_F16, nullptr, b, ls);
     if (s == HLQ_OK) *bytes = ls.ws_used;
     return s;
 }
@@ -1047,7 +1057,7 @@ hlq_status hlq_gemv_plan_describe(int count, const HlqDims *dms, int M, hlq_gemv
     }
     GemvBatch b;
     GemvLaunchShape ls;
-    const hlq_status s = plan_gemv_batch(count, items, HLQ_OUT_F16, nullptr, b, ls);
+    const hlq_status s = plan_launch(count, items, HLQ_OUT_F16, nullptr, b, ls);
     if (s != HLQ_OK) return s;
     bool taken[HLQ_MAX_BATCH] = {};
     for (int i = 0; i < count; ++i) {
@@ -1078,27 +1088,53 @@ int hlq_gemm_mx_rows_per_pass(int G)
     return many > two_sets ? many : two_sets;
 }
 
-// Two to four rows on the kernel of one row (hlq_gemv_cols.hip) instead of the few-rows instantiation of the 64-column one, the
-// many-rows or the short-M kernel.  Its operands take 24 registers a row, which leaves eight wavefronts on a compute unit: the
-// better one where a launch is one step or two of all its wavefronts, and where the alternative is weights rebuilt in
-// fp16 or two row sets (G <= 64).  us, alternative / this one:
-//   G >= 128, 2 rows:   4096 x 1024 (512 chunk-tiles) q = 2 6.7 / 5.2,  4096 x 4096 7.4 / 5.5, q = 4 8.4 / 6.1,  4096 x 8192 7.5 / 7.5, q = 4
-//                       10.0 / 8.5,  4096 x 14336 7.8 / 11.5
-//             4 rows:   4096 x 1024 q = 4 9.8 / 7.8,  4096 x 4096 q = 2 9.7 / 7.5,  8192 x 4096 13.4 / 11.3,  4096 x 14336, q = 4 13.3 / 13.6
-//   short or deep:      1024 x 512, q = 2, 2 rows 4.3 / 4.7;  14336 x 1024 10.8 / 11.5
-//   G = 64, 4 rows:     8B layer q = 2 33 / 28, q = 4 50 / 43;  8192 x 57344, q = 2 66 / 47;  4096 x 14336, q = 2 10.0 / 11.6
-//   G = 32:             8192 x 57344, q = 4, 2 rows 109 / 79;  8B layer, q = 2, 4 rows 41 / 36
-bool hlq_gemm_few_wins(int count, const HlqDims *dms, int64_t rows)
+static long chunk_tiles(int count, const HlqDims *dms, int &deepest)
 {
-    if (rows < 2 || rows > HLQ_COLS_ROWS || (rows > 2 && hlq_gemm_rows_all())) return false;
     long units = 0;
-    int deepest = 0;
+    deepest = 0;
     for (int i = 0; i < count; ++i) {
         units += (long)dms[i].ntiles * dms[i].nchunks;
         deepest = dms[i].nchunks > deepest ? dms[i].nchunks : deepest;
     }
-    if (rows > hlq_gemv_mx_rows_per_set(dms[0].G) && units >= 14000) return true;
-    return units >= 256 && units <= 4096 && deepest <= 64;
+    return units;
+}
+
+// Calls of two to four rows that a GEMV-shaped kernel takes (this one or the 64-column one, which keep scales in fp32) also
+// where the rows exceed a row set of the latter and a single call would otherwise go to the kernels that rebuild weights in fp16
+bool hlq_gemm_few_rows(int count, const HlqDims *dms, int64_t rows)
+{
+    if (rows < 2 || rows > HLQ_COLS_ROWS || (rows > 2 && hlq_gemm_rows_all())) return false;
+    int deepest;
+    const long units = chunk_tiles(count, dms, deepest);
+    return (rows > hlq_gemv_mx_rows_per_set(dms[0].G) && units >= 14000) || (units >= 256 && units <= 4096 && deepest <= 64);
+}
+
+// Which of those go to the kernel of one row (hlq_gemv_cols.hip) instead of the 64-column one.  It pays for the operands of every
+// window (512 k) of every row, whatever the number of column blocks that a wavefront walks over with them, and eight
+// wavefronts are what a compute unit holds: it loses on short K, where operands are most of a step, and on deep K with few columns,
+// where a wavefront makes many and walks little.  Time over the other kernel's, at q = 1 / 2 / 4:
+//   up to 4096 chunk-tiles   512 x 4096 G = 128 M = 2 1.14 / 1.10 / 1.06, M = 3 1.23 / 1.20 / 1.19;  256 x 65536 1.4 to 1.6;
+//     2048 x 6144 M = 2 .75 / .74 / .76, M = 4 .72 / .72 / .74;  4096 x 1024 .80 / .78 / .79, .82 / .79 / .81;  4096 x 6144 .95 / .94 / .93,
+//     .82 / .86 / .84;  4096 x 8192 M = 2 1.11 / 1.04 / .89, M = 4 .99 / .93 / .84;  6144 x 5120 M = 2 1.20 / 1.17 / 1.15, M = 3 .87 / .94 / .96;
+//     8192 x 256 1.2;  8192 x 2048 M = 3 1.06 / 1.11 / 1.14;  8192 x 4096 M = 2 .99 / .91 / .80, M = 4 .86 / .87 / .83
+//   more rows than a row set  4096 x 28672 (14336) G = 64 M = 4 .88 / .87 / .92, M = 3 .99 / .93 / .97, G = 32 M = 2 1.23 / 1.07 / 1.06;
+//     8192 x 14336 M = 4 1.11 / 1.06 / 1.06, M = 3 1.25 / 1.16 / 1.16, G = 32 M = 2 1.50 / 1.25 / 1.13;  8192 x 18432 (18432) M = 4 .70 / .67 / .68,
+//     M = 3 .98 / .73 / .75, G = 32 M = 2 1.00 / .84 / .79;  8B layer (26624) M = 4 .87 / .85 / .87, M = 3 1.26 / .94 / .95;  16384 x 28672 M = 4 .72 /
+//     .73 / .77, M = 3 1.01 / .83 / .86;  28672 x 24576 M = 4 1.81 / 1.68 / 1.45, M = 3 2.30 / 1.90 / 1.64;  70B layer M = 4 1.11 / 1.13 / 1.08
+bool hlq_gemm_few_wins(int count, const HlqDims *dms, int64_t rows)
+{
+    if (!hlq_gemm_few_rows(count, dms, rows)) return false;
+    const int G = dms[0].G, q = dms[0].q;
+    if (rows > hlq_gemm_mx_rows_per_pass(G)) return true;   // three and four rows at G = 32: more than the other one's two row sets
+    int deepest;
+    const long units = chunk_tiles(count, dms, deepest);
+    if (units > 4096) {
+        const bool one_more = rows == hlq_gemv_mx_rows_per_set(G) + 1;
+        if (deepest <= 32) return units >= (one_more ? 18000 : 14000);
+        return units >= 18000 && deepest <= 160 && !(one_more && q == 1);
+    }
+    if (deepest <= 32) return deepest >= 12 && (units <= 3072 || q > 2 || rows == 4 || G == 32);
+    return units > 3072 && (rows > 2 || deepest > 56);
 }
 
 // Many-rows kernel or, with weights rebuilt in fp16, the short-M kernel (hlq_gemm_short.hip) for 5..16 rows (G >= 128)?  The

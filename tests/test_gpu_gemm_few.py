@@ -13,6 +13,15 @@ from gpu_util import dev, pack_on_gpu
 pytestmark = pytest.mark.gpu
 
 
+def on_the_one_row_kernel(K, N, q, G, M):
+    """Whether the launch is planned for it: wavefronts by windows of four chunks, and workgroups that do not own whole tiles."""
+    info = B.gemv_plan_query([B.make_desc(K, N, q, G)], M)[0]
+    kw = 1
+    while kw * 2 <= 8 and kw < -(-K // 512):
+        kw *= 2
+    return info.waves_per_workgroup == 8 and info.waves_per_tile == kw and info.tile_groups != -(-(-(-N // 64)) // (8 // kw))
+
+
 def product(K, N, q, G, X, pad=0, key="few", cols=slice(None)):
     """fp32 result, reference, and a bound: what the terms leave of an activation is at most 2^-18 of the largest of its word
     (32 k), the sums are fp32 over the planes one by one (2^-20 of the sum of magnitudes is ample for K <= 8192)."""
@@ -39,23 +48,26 @@ def product(K, N, q, G, X, pad=0, key="few", cols=slice(None)):
 @pytest.mark.parametrize("G", [32, 64, 128, 256])
 def test_formats(q, G, M):
     K = 2304 if G < 256 else 2560          # 18 or 20 chunks: five windows, the last one short
+    assert on_the_one_row_kernel(K, 1096, q, G, M)
     Y, ref, bound = product(K, 1096, q, G, synth.make_x(M, K, "few", outliers=True), pad=1)
     assert (np.abs(Y - ref) <= bound).all()
 
 
-@pytest.mark.parametrize("K,N", [(8192, 264), (8064, 520), (512, 4104), (256, 16392), (4096, 4096), (4096, 8136)])
+@pytest.mark.parametrize("K,N", [(8192, 3208), (8064, 3400), (1536, 8200), (4096, 520), (4096, 4096), (2048, 12168)])
 def test_one_step_and_several(K, N):
     for M in (2, 4):
+        assert on_the_one_row_kernel(K, N, 2, 128, M)
         Y, ref, bound = product(K, N, 2, 128, synth.make_x(M, K, "few"))
         assert (np.abs(Y - ref) <= bound).all()
 
 
 # a wavefront walks over several column blocks, within a tile, into the next one and into a narrow last one: the largest launches of
-# up to 4096 chunk-tiles, and the smallest from 14000 on (groups of 32 and 64).  Results of the first and last tiles and some between
-@pytest.mark.parametrize("K,N,q,G,M", [(4096, 8136, 2, 128, 4), (4096, 8072, 4, 256, 3), (2048, 16328, 1, 64, 4), (1024, 112072, 2, 64, 4), (1024, 112072, 4, 64, 3),
-                                       (1024, 112072, 2, 32, 2), (128, 896136, 1, 32, 3), (8192, 14216, 3, 32, 4)])
+# up to 4096 chunk-tiles, and the smallest from 14000 or 18000 on (groups of 32 and 64).  Results of the first and last tiles and some between
+@pytest.mark.parametrize("K,N,q,G,M", [(4096, 8136, 2, 128, 4), (4096, 8072, 4, 256, 3), (2048, 16328, 1, 64, 4), (1024, 112072, 2, 64, 4), (1024, 144072, 4, 64, 3),
+                                       (1024, 144072, 2, 32, 2), (128, 896136, 1, 32, 3), (8192, 14216, 3, 32, 4)])
 def test_several_column_blocks(K, N, q, G, M):
     info = B.gemv_plan_query([B.make_desc(K, N, q, G)], M)[0]
+    assert on_the_one_row_kernel(K, N, q, G, M)
     assert info.tile_groups * (info.waves_per_workgroup // info.waves_per_tile) < -(-N // 16)
     cols = np.unique(np.concatenate([np.arange(0, 200), np.arange(N - 200, N), np.random.default_rng(N).integers(0, N, 400)]))
     Y, ref, bound = product(K, N, q, G, synth.make_x(M, K, "few"), cols=cols)

@@ -64,7 +64,7 @@ def test_many_rows_kernel(q, G, M, ratio):
 
 
 # one step a wavefront, several windows of one column block, several column blocks of one window, both; a narrow last tile
-@pytest.mark.parametrize("K,N,G", [(4096, 1032, 128), (8192, 264, 64), (512, 8200, 32), (2304, 4104, 128), (6144, 5400, 128), (8192, 4040, 256)])
+@pytest.mark.parametrize("K,N,G", [(4096, 1032, 128), (8192, 3208, 64), (2048, 2056, 32), (2304, 4104, 128), (4096, 5400, 128), (8192, 4040, 256)])
 @pytest.mark.parametrize("M", [2, 3, 4])
 @pytest.mark.parametrize("ratio,share", [(1000.0, 1.0), (8000.0, 0.03), (32000.0, 0.3)])
 def test_few_rows_kernel(K, N, G, M, ratio, share):
