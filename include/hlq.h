@@ -241,12 +241,13 @@ HLQ_API hlq_status hlq_set_gemv_path(int path);
  *     launches of 256 .. 4096 chunk-tiles with K <= 8192 and, at G <= 64, from 14000 on) the
  *     GEMV kernels of hlq_set_gemv_path(2) with several activation rows, for 5..16 rows on large
  *     problems (G >= 128) the many-rows kernel, otherwise kernels that rebuild W^ in fp16 registers: up to 32 rows
- *     (below 80000 chunk-tiles) the short-M kernel, which cuts K inside a workgroup, else the tiled kernel
+ *     the short-M kernel, which cuts K inside a workgroup, where the launch is one round of its workgroups (256 tiles of
+ *     64 columns and K slices) or it is estimated to be the faster one (below 80000 chunk-tiles), else the tiled kernel
  *     (hlq_lut_gemm_batch keeps up to twice as many rows on the GEMV kernel at G <= 64),
  * 3 = the tiled kernel always,
  * 4 = as 2, and 3..16 rows (G >= 128) always go to the many-rows kernel (by default only when the call or grouped
  *     launch is large enough for it to win: from 4096 chunk-tiles of 64 columns x 128 k at q >= 3 and 12000 at
- *     q <= 2 for 5..8 rows, from 2400 resp. 14000 for 9..16 rows, smaller ones going to the short-M kernel; 3 and 4
+ *     q <= 2 for 5..8 rows, from 2400 resp. 14000 for 9..16 rows, smaller ones going to the kernels that rebuild W^; 3 and 4
  *     rows from 20000 chunk-tiles at q = 4, 4 rows from 40000 at q = 3 and 60000 at q <= 2, otherwise they stay
  *     on the few-rows GEMV kernel).
  * Other values: HLQ_ERR_UNSUPPORTED.  The fp16-rebuild kernels represent scales up to |s_j| < 512 (and

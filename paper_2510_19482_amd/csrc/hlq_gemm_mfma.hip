@@ -502,6 +502,36 @@ size_t hlq_gemm_mfma_batch_partial_bytes(int count, const HlqDims *dms, int64_t 
     return b;
 }
 
+// What a call takes with this kernel, us, up to 32 rows: for the choice between it and the short-M kernel (hlq_gemm_short_wins).
+// The time of a chunk, by planes; workgroups in rounds as in plan_mfma; the launch that adds slices.  Fitted to 1204 calls of
+// both kinds (single matrices of 64 to 2000 column tiles and 1 to 112 chunks, groups of layers, 16 to 32 rows, q = 1 to 4); error 9 %.
+double hlq_gemm_mfma_estimate(int count, const HlqDims *dms, int64_t M)
+{
+    const double t1 = 0.58 + 0.31 * dms[0].q, t2 = 1.65 * t1;
+    double t, sums = 0;   // partial sums
+    if (count == 1) {
+        const MfmaPlan p = plan_mfma(dms[0], M);
+        const long total = (long)((dms[0].ntiles + 3) / 4) * p.rowblocks * p.nslices, rem = total % 512;
+        t = p.cps * ((double)(total / 512) * t2 + (rem == 0 ? 0.0 : rem <= 256 ? t1 : t2));
+        if (p.nslices > 1) sums = (double)p.nslices * (double)M * dms[0].N;
+    } else {
+        const GroupPlan g = plan_group(count, dms, M);
+        long total = 0;
+        int longest = 0;
+        double work = 0;
+        for (int i = 0; i < count; ++i) {
+            const long n = (long)((dms[i].ntiles + 3) / 4) * g.rowblocks * g.nslices[i];
+            total += n;
+            work += (double)n * g.cps[i];
+            longest = g.cps[i] > longest ? g.cps[i] : longest;
+            if (g.nslices[i] > 1) sums += (double)g.nslices[i] * (double)M * dms[i].N;
+        }
+        const double even = work / 512 * t2, last = total <= 512 ? 0.0 : total % 512 ? 0.5 * longest * t2 : 0.0, one = longest * (total <= 512 ? t1 : t2);
+        t = 3.4 + 0.73 * (one > even + last ? one : even + last);
+    }
+    return 3.8 + t + (sums > 0 ? 1.35 + sums * 1.65e-6 : 0.0);
+}
+
 // One launch for several problems of the same q, G and M.  HLQ_ERR_UNSUPPORTED if the launch cannot be
 // formed (the caller then runs the problems one after the other).
 hlq_status hlq_launch_gemm_mfma_batch(int count, const HlqGemvItem *items, int64_t M, hlq_out_dtype out, void *ws,

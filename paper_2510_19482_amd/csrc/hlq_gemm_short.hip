@@ -311,14 +311,36 @@ size_t hlq_gemm_short_partial_bytes(int count, const HlqDims *dms, int64_t M)
     return b;
 }
 
+// One round of workgroups (256): always (0.44 to 1.05 of the tiled kernel's time).  More of them pay start and end of a workgroup per
+// round, whatever the depth, where the tiled kernel has a quarter as many with four times the columns; which of the two
+// is the longer time is estimated.  us, tiled / this one, M = 32, G = 64: 64 x 2000 tiles of 2 chunks (256 x 127976) q = 1 9.2 / 34.9,
+// 1000 x 8 12.3 / 19.3, 1000 x 32 q = 2 44.6 / 47.9, q = 4 (M = 16) 61.4 / 56.9;  300 x 8 q = 2 12.2 / 10.6;  450 x 24 q = 2 21.5 / 19.8;  600 x 48 q = 1
+// 31.2 / 38.3.  Over the calls the estimate was fitted to, 1 % from the better of the two on average, 23 % at most (this kernel always: 23 % and
+// 4.5 times).  From 80000 chunk-tiles on the tiled kernel: 86016 q = 2, M = 16 99.8 / 98.8, 128256 q = 2, M = 24 141 / 158.
 bool hlq_gemm_short_wins(int count, const HlqDims *dms, int64_t M)
 {
     if (M < 1 || M > HLQ_SHORT_ROWS) return false;
-    // us, tiled kernel / this one: 57344 chunk-tiles q = 2, M = 24 79.4 / 79.1, q = 4, M = 32 117 / 106;  86016  q = 2, M = 16
-    // 99.8 / 98.8, q = 4, M = 24 157 / 159;  128256  q = 2, M = 24 141 / 158
-    long units = 0;
-    for (int i = 0; i < count; ++i) units += (long)dms[i].ntiles * dms[i].nchunks;
-    return units < 80000;
+    const ShortPlan p = plan_short(count, dms, M);
+    const double round = M > 16 ? 2.5 : 2.0, step = M > 16 ? 1.0 + 0.5 * dms[0].q : 0.8 + 0.47 * dms[0].q;   // us: a workgroup, and a chunk of each of its wavefronts
+    long units = 0, blocks = 0;
+    double work = 0, longest = 0, shortest = 1e30;
+    bool sliced = false;
+    for (int i = 0; i < count; ++i) {
+        units += (long)dms[i].ntiles * dms[i].nchunks;
+        const long n = (long)dms[i].ntiles * p.nslices[i];
+        const int chunks = p.cps[i] < dms[i].nchunks ? p.cps[i] : dms[i].nchunks;
+        const double t = round + step * ((chunks + SHORT_WAVES - 1) / SHORT_WAVES);
+        blocks += n;
+        work += (double)n * t;
+        longest = t > longest ? t : longest;
+        shortest = t < shortest ? t : shortest;
+        sliced = sliced || p.nslices[i] > 1;
+    }
+    if (units >= 80000) return false;
+    if (blocks <= 256) return true;
+    double t = count == 1 ? (double)((blocks + 255) / 256) * longest : work / 256 + 0.5 * shortest;
+    t = 1.3 + (t > longest ? t : longest) + (sliced ? 2.9 : 0.0);
+    return hlq_gemm_mfma_estimate(count, dms, M) >= (dms[0].q == 1 ? 1.03 : 0.93) * t;   // (the estimates are good to 9 %)
 }
 
 hlq_status hlq_launch_gemm_short(int count, const HlqGemvItem *items, int64_t M, hlq_out_dtype out, void *ws, hipStream_t st)

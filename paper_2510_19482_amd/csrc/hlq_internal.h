@@ -154,6 +154,7 @@ hlq_status hlq_gemm_path_override(int path);
 bool hlq_gemm_uses_matrix_cores(int64_t M);
 hlq_status hlq_launch_gemm_mfma_batch(int count, const HlqGemvItem *items, int64_t M, hlq_out_dtype out, void *ws,
                                       hipStream_t st);
+double hlq_gemm_mfma_estimate(int count, const HlqDims *dms, int64_t M);
 size_t hlq_gemm_mfma_batch_partial_bytes(int count, const HlqDims *dms, int64_t M);
 hlq_status hlq_launch_gemm_safe(int count, const HlqGemvItem *items, int64_t M, hlq_out_dtype out, void *ws, hipStream_t st);
 // up to 32 rows, K cut inside a workgroup (hlq_gemm_short.hip)

@@ -87,3 +87,31 @@ def test_grouped_launch(M):
         batch.launch()
         for Y, ref, bound in zip(Ys, refs, bounds):
             assert (np.abs(Y.cpu().numpy().astype(np.float64) - ref) <= bound).all()
+
+
+@pytest.mark.parametrize("K,N,M", [(256, 65536, 24), (1024, 65536, 16)])
+def test_wide_and_short_launches_are_not_left_to_it(K, N, M):
+    """Many workgroups of few chunks each pay its start and end per round: 2.7 and 1.5 times the tiled kernel's time, to which
+    they go (1.0 measured)."""
+    desc, packed = pack_on_gpu(*synth.make_weight(K, N, 1, 64, "short-wide"), 1, 64)
+    x, ws = dev(synth.make_x(M, K, "short-wide")), B.alloc_workspace(desc, M)
+    y = torch.empty((M, N), dtype=torch.float16, device="cuda")
+
+    def us(path):
+        B.set_gemm_path(path)
+        try:
+            best = 1e9
+            for _ in range(5):
+                B.hlq_lut_gemm(desc, packed, x, y, ws=ws)
+                a, e = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                a.record()
+                for _ in range(50):
+                    B.hlq_lut_gemm(desc, packed, x, y, ws=ws)
+                e.record()
+                e.synchronize()
+                best = min(best, a.elapsed_time(e) * 20)
+            return best
+        finally:
+            B.set_gemm_path(B.GEMM_AUTO)
+
+    assert us(B.GEMM_AUTO) < 1.25 * us(B.GEMM_MFMA_FP16)

@@ -75,3 +75,13 @@ def test_forced_runs_of_the_few_rows_kernel(K, N, G, count, cpw):
         B.set_gemv_plan(0, 0, 0)
     for info in infos:
         check_plan(info, K // 128, (K, N, G, count, cpw))
+
+
+# two to four rows on the 16-column kernel only where a wavefront walks over enough columns with the operands that it makes
+@pytest.mark.parametrize("K,N,G,M,columns", [(256, 65536, 128, 2, False), (512, 4096, 128, 3, False), (8192, 256, 64, 4, False), (6144, 5120, 256, 2, False),
+                                             (28672, 24576, 64, 3, False), (8192, 14336, 32, 2, False), (2048, 6144, 128, 4, True), (4096, 1024, 64, 2, True),
+                                             (8192, 4096, 128, 4, True), (4096, 28672, 64, 4, True), (8192, 18432, 64, 3, True), (28672, 24576, 32, 4, True)])
+def test_two_to_four_rows_by_columns(K, N, G, M, columns):
+    info = B.gemv_plan_query([B.make_desc(K, N, 2, G)], M)[0]
+    tiles = -(-(-(-N // 64)) // (info.waves_per_workgroup // info.waves_per_tile))   # workgroups that own whole tiles
+    assert (info.tile_groups != tiles) == columns
