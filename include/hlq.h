@@ -173,8 +173,8 @@ HLQ_API hlq_status hlq_lut_gemv_batch(int count, const hlq_desc *descs, const vo
 /* Several independent products Y_i[M, N_i] = X_i[M, K_i] @ W^_i in one launch (the GEMMs of a
  * decoder layer: Sec. 2, batched rows).  All problems share q, G and M; X_i row-major with
  * leading dimension ldx[i] >= K_i (a multiple of 8 for M > 1), Y_i with ldy[i] >= N_i; descs,
- * packed, X, ldx, Y, ldy are host arrays of `count` (1..8) entries.  One launch of the few-rows
- * kernel takes all problems up to 4 rows at G >= 128 (4 at G = 64, 2 at G = 32: two row sets);
+ * packed, X, ldx, Y, ldy are host arrays of `count` (1..8) entries.  One launch of a few-rows
+ * kernel takes all problems up to 4 rows at G >= 64 (2 at G = 32, 3 and 4 in the launches named at hlq_set_gemm_path);
  * 5..16 rows at G >= 128 go to the many-rows kernel (a small pre-pass that writes the activations in
  * matrix-core operand form into the workspace, then one launch) when the launch is large enough
  * for it to win, see hlq_set_gemm_path; everything else to one launch of a matrix-core kernel that
@@ -194,12 +194,14 @@ HLQ_API hlq_status hlq_lut_gemm_batch(int count, const hlq_desc *descs, const vo
  * there is no per-call or per-thread setting): force the launch shape
  * of the GEMV kernel -- column tiles per wavefront (1 or 2), wavefronts per workgroup (1..16),
  * chunks of 128 k per wavefront -- instead of the built-in choice.  0 leaves a value automatic.
- * Results stay within the documented tolerance for every setting; only speed changes.
+ * Results stay within the documented tolerance for every setting; only speed changes.  (Launches of several rows do not
+ * follow a setting that cuts K into more slices than they have counters for.)
  * Values outside the ranges above: HLQ_ERR_UNSUPPORTED. */
 HLQ_API hlq_status hlq_set_gemv_plan(int tiles_per_wave, int waves_per_workgroup, int chunks_per_wave);
 
 /* Host-only: the work split hlq_lut_gemv_batch (M = 1) or the few-rows / many-rows launch of
- * hlq_lut_gemm_batch (2 <= M <= rows one pass carries: 16 at G >= 128, 4 at G = 64, 2 at G = 32) would use for these `count` problems with the knobs as they
+ * hlq_lut_gemm_batch (2 <= M <= rows one pass carries: 16 at G >= 128, 4 at G = 64, 2 at G = 32, there 4 in the
+ * launches that hlq_set_gemm_path names for any G) would use for these `count` problems with the knobs as they
  * are now; nothing is launched and no GPU is needed.  For tests and tools: every K slice of a
  * plan starts inside K, i.e. (slices - 1) * chunks_per_slice < K / 128.
  *   descs host array of `count` (1..8) descriptors sharing q and G; out host array of `count`.
@@ -208,8 +210,8 @@ typedef struct {
     int32_t formulation;          /* 1 = table lookups, 2 = matrix cores                             */
     int32_t waves_per_workgroup;  /* wavefronts of a workgroup                                       */
     int32_t waves_per_tile;       /* of those, the wavefronts that share one column tile's K slice   */
-                                  /* (a tile: 64 columns; 16 in the one-row matrix-core kernel that  */
-                                  /* most launches with M = 1 go to)                                 */
+                                  /* (a tile: 64 columns; 16 in the matrix-core kernel that most     */
+                                  /* launches with M = 1 and many with 2..4 rows go to)              */
     int32_t chunks_per_slice;     /* chunks of 128 k per K slice (a slice = one workgroup's share)   */
     int32_t slices;               /* K slices, i.e. partial sums per output in the workspace (two    */
                                   /* slices of the 16-column kernel may meet in slots instead)       */

@@ -116,7 +116,7 @@ hlq_status hlq_gemm_batch_workspace_bytes(int count, const hlq_desc *descs, int6
         if (s != HLQ_OK) return s;
         b += M <= 1 ? hlq_gemv_partial_bytes(dms[i]) : hlq_gemm_partial_bytes(dms[i], M);
     }
-    // the grouped launch of the tiled kernel splits K on its own terms
+    // the grouped launches of the kernels that rebuild weights split K on their own terms
     const size_t grouped = HLQ_WS_COUNTER_BYTES + batch_partial_bytes(count, dms, M);
     if (grouped > b) b = grouped;
     *bytes = (b + 255u) & ~(size_t)255u;
@@ -272,7 +272,7 @@ hlq_status hlq_lut_gemm_batch(int count, const hlq_desc *descs, const void *cons
     // one launch when the few-rows kernel carries M rows and the lookup formulation is not forced
     if (M == 1 || (hlq_gemm_batch_on_mx(count, items, M) && hlq_gemm_uses_mx_rows(M)))
         return hlq_launch_gemv_batch(count, items, out, ws, (hipStream_t)stream);
-    // more rows on the matrix cores: one launch of the tiled kernel over all problems (and one for the partial
+    // more rows on the matrix cores: one launch of the short-M or the tiled kernel over all problems (and one for the partial
     // sums where K is split)
     if (count > 1 && hlq_gemm_uses_matrix_cores(M)) {
         HlqDims dms[HLQ_MAX_BATCH];

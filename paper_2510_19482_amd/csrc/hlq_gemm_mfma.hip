@@ -328,7 +328,9 @@ struct MfmaPlan {
 // (M = 16 .. 2048, the 8B layer shapes): a chunk costs a workgroup t1 when it has its CU to itself
 // and t2 = 1.65 t1 when two workgroups share the CU (two per CU is the occupancy limit), workgroups
 // run in rounds of 512, and the reduction costs a launch plus reading the partials back (fitted when the sums and the
-// range fallback were two launches, 5 us; they are one now, and the split has not been fitted again).
+// range fallback were two launches, 5 us; they are one now.  The time of a chunk is that of weights rebuilt by FMA, which
+// took 80 / 120 / 160 instructions a word at q = 2 / 3 / 4 where the look-up takes 50 / 66 / 106: up to 32 rows 0.58 + 0.31 q
+// fits it now.  The split has not been fitted again).
 MfmaPlan plan_mfma(const HlqDims &dm, int64_t M)
 {
     MfmaPlan p;

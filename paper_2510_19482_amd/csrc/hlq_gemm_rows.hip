@@ -54,16 +54,6 @@
 
 namespace {
 
-// compile-time loop: body(std::integral_constant<int, 0>), ..., body(std::integral_constant<int, N - 1>)
-template <int N, class F>
-__device__ __forceinline__ void unrolled(F &&body)
-{
-    if constexpr (N > 0) {
-        unrolled<N - 1>(body);
-        body(std::integral_constant<int, N - 1>{});
-    }
-}
-
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 typedef unsigned short ushort2_t __attribute__((ext_vector_type(2)));
 typedef _Float16 half32_t __attribute__((ext_vector_type(32)));

@@ -1,5 +1,6 @@
-// The fp32 recomputation behind the tiled matrix-core GEMM (hlq_gemm_safe.hip says when and why), as a device function: a
-// launch behind the tiled kernel runs it if that kernel raised its flag.
+// The fp32 recomputation behind the matrix-core GEMMs that rebuild weights in fp16 (hlq_gemm_safe.hip says when and why), as
+// device functions: the launch behind the tiled kernel, or behind K slices of either, runs it if the flag was raised; a workgroup of
+// the short-M kernel that has all of K runs it for its own tile.
 #pragma once
 
 #include "hlq_internal.h"

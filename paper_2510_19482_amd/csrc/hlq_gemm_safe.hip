@@ -1,4 +1,4 @@
-// Fallback of the tiled matrix-core GEMM for weights it cannot represent.  That kernel rebuilds
+// Fallback of the tiled matrix-core GEMM (and of the short-M one where it cuts K across workgroups) for weights it cannot represent.  That kernel rebuilds
 // W^ = sum_j s_j b_j + z (Eq. 3) in fp16 registers with pre-scaled scales (s_j * 2^7), which is only
 // finite for |s_j| < 512; any finite fp16 scale is a valid HLQ parameter, though.  The tiled kernel
 // therefore looks at every scale and zero it loads and raises a flag in the workspace if one lies
@@ -22,7 +22,7 @@ hlq_gemm_safe_kernel(const HlqSafeProbs pr, const int M, const int out_f32, int 
 }
 
 // Adds the partial sums of the problems of a launch whose K was split, four outputs per lane (N is a multiple of 8), or,
-// if the tiled kernel met parameters outside its range, computes the call again: one launch behind the tiled kernel instead
+// if the kernel before it met parameters outside its range, computes the call again: one launch behind the tiled kernel instead
 // of two.  A dependent launch costs 1.7 us even when it only looks at the flag; the sums are latency-bound themselves
 // (one 4-byte load per lane and slice and a 64-bit division per output before).
 typedef int int4v __attribute__((ext_vector_type(4)));

@@ -1,5 +1,5 @@
-// hlq_lut_gemm for up to 32 rows (those the many-rows kernel does not take, up to the size at which the tiled kernel
-// catches up): the formulation of the tiled kernel (hlq_gemm_mfma.hip) -- W^ = sum_j s_j b_j + z (Eq. 3) rebuilt in fp16 registers,
+// hlq_lut_gemm for up to 32 rows (those the many-rows kernel does not take, where hlq_gemm_short_wins finds it faster than the
+// tiled kernel): the formulation of the tiled kernel (hlq_gemm_mfma.hip) -- W^ = sum_j s_j b_j + z (Eq. 3) rebuilt in fp16 registers,
 // v_mfma_f32_32x32x16_f16 -- with K cut inside the workgroup instead of across workgroups.
 //
 // Work split.  A workgroup of eight wavefronts owns one tile of 64 columns and one K slice (all of K if there are enough
@@ -260,7 +260,8 @@ hlq_gemm_short_kernel(const int4v bb_lo, const int4v bb_hi, const int M, const i
     }
 }
 
-// K slices: as many as give the launch one workgroup per place, none shorter than a chunk for each wavefront
+// K slices: as many as give the launch one workgroup per place, of a chunk for each wavefront or more (but for the last: slices
+// are even numbers of chunks, what is left may be less)
 struct ShortPlan {
     int cps[HLQ_MAX_BATCH], nslices[HLQ_MAX_BATCH];
 };

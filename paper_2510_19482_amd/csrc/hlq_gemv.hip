@@ -1163,7 +1163,7 @@ bool hlq_gemm_rows_wins(long units, int q, int64_t M)
 }
 
 // Whether a grouped launch of M rows goes to the matrix-core GEMV-shaped kernels (few-rows / many-rows) rather
-// than to the tiled kernel: up to one row set (four rows at G >= 128) and whatever the second row set of the
+// than to the kernels that rebuild weights: up to one row set (four rows at G >= 128) and whatever the second row set of the
 // GEMV kernel carries at G <= 64 always; 5..16 rows at G >= 128 by the rule above; hlq_set_gemm_path(4) sends all of
 // them here.
 bool hlq_gemm_batch_on_mx(int count, const HlqGemvItem *items, int64_t M)

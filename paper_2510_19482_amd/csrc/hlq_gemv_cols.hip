@@ -4,7 +4,7 @@
 //   y[n] = sum_groups ( sum_j s_j[g,n] * <b_j[.,n], x>_g  +  z[g,n] * sum_g(x) )
 //
 // with the bit-plane dot products <b_j, x> on v_mfma_f32_16x16x128_f8f6f4, planes as fp4 codes and activations as an exact
-// sum of four bf8 terms, as hlq_gemv_mx.hip describes them (that kernel serves two rows and more).  What is different
+// sum of four bf8 terms, as hlq_gemv_mx.hip describes them (that kernel serves the launches that the rules in hlq_gemv.hip leave to it).  What is different
 // here is what a wavefront owns: 16 columns x a window of 4 chunks (512 k) instead of 64 columns x 1 chunk.
 //
 //   - Lane c + 16 g loads the 16 bytes of column c in chunk g of the window, so its four words are, as loaded, the plane
@@ -31,7 +31,7 @@
 // four wavefronts at a time instead of one after the other: no gain on long launches; 80 registers (six wavefronts on a
 // SIMD): spills, 10-20 % slower.
 //
-// Two and four rows (small launches, see hlq_gemm_few_wins): every row has four operands of its own, which share the expanded
+// Two and four rows (the launches of hlq_gemm_few_wins): every row has four operands of its own, which share the expanded
 // plane words.  They are bf6 terms as in hlq_gemm_rows.hip -- 24 registers a row and not 32, 16 clocks an instruction and not
 // 32 -- with the matrix core's own scale per word, so the window's largest magnitude is not needed; made of the same
 // eight activations per lane, through the packed conversions (at one row their latency, 72 clocks a conversion, is longer than
@@ -68,16 +68,6 @@ template <int NR>
 struct ColsProbs {
     std::conditional_t<NR == 1, ColsProb, ColsRowsProb> p[HLQ_MAX_BATCH];
 };
-
-// compile-time loop: body(std::integral_constant<int, 0>), ..., body(std::integral_constant<int, N - 1>)
-template <int N, class F>
-__device__ __forceinline__ void unrolled(F &&body)
-{
-    if constexpr (N > 0) {
-        unrolled<N - 1>(body);
-        body(std::integral_constant<int, N - 1>{});
-    }
-}
 
 template <int CTRL, int ROWMASK = 0xf>
 __device__ __forceinline__ uint32_t max_dpp(uint32_t v)

@@ -7,6 +7,8 @@
 #include <stdio.h>
 #include <stdlib.h>
 
+#include <type_traits>
+
 #include "hlq.h"
 
 // ---------------------------------------------------------------------------------------
@@ -84,6 +86,16 @@ __host__ __device__ __forceinline__ size_t hlq_rec_off(size_t col_bytes, int til
            (size_t)w * ((size_t)c * q * 16 + (size_t)hlq_groups_before(c, G) * (q + 1) * 2);
 }
 
+// compile-time loop: body(std::integral_constant<int, 0>), ..., body(std::integral_constant<int, N - 1>)
+template <int N, class F>
+__device__ __forceinline__ void unrolled(F &&body)
+{
+    if constexpr (N > 0) {
+        unrolled<N - 1>(body);
+        body(std::integral_constant<int, N - 1>{});
+    }
+}
+
 hlq_status hlq_check_desc(const hlq_desc *d, HlqDims *out);
 
 hlq_status hlq_launch_pack(const HlqDims &dm, const uint8_t *codes, const uint16_t *scales,
@@ -120,7 +132,8 @@ hlq_status hlq_gemv_path_override(int path);
 // Workspace = [HLQ_WS_COUNTER_BYTES of split-K arrival counters][fp32 partial sums].
 // Counters are zero between calls (hlq_workspace_init zeroes them; kernels re-zero them).
 #define HLQ_WS_COUNTER_BYTES 131072
-// The last two counters are not arrival counters: [0] is raised by the tiled matrix-core GEMM when it meets a
+// The last two counters are not arrival counters: [0] is raised by the kernels that rebuild weights in fp16 (the tiled one, and
+// the short-M one where it cuts K across workgroups) when they meet a
 // scale or zero outside the range its fp16 weight rebuild can represent, [1] counts the fallback kernel's
 // workgroups out (hlq_gemm_safe.hip).  Both are zero between calls, like the arrival counters.
 #define HLQ_WS_ARRIVAL_COUNTERS (HLQ_WS_COUNTER_BYTES / 4 - 2)

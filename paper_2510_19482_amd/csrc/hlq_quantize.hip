@@ -37,16 +37,6 @@
 
 namespace {
 
-// compile-time loop: body(std::integral_constant<int, 0>), ..., body(std::integral_constant<int, N - 1>)
-template <int N, class F>
-__device__ __forceinline__ void unrolled(F &&body)
-{
-    if constexpr (N > 0) {
-        unrolled<N - 1>(body);
-        body(std::integral_constant<int, N - 1>{});
-    }
-}
-
 // ascending odd-even merge sort of NC keys (a power of two), all comparisons at compile-time positions
 template <int NC>
 __device__ __forceinline__ void sort_keys(uint32_t (&key)[NC])
