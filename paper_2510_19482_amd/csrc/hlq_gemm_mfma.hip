@@ -505,7 +505,7 @@ size_t hlq_gemm_mfma_batch_partial_bytes(int count, const HlqDims *dms, int64_t 
 }
 
 // What a call takes with this kernel, us, up to 32 rows: for the choice between it and the short-M kernel (hlq_gemm_short_wins).
-// The time of a chunk, by planes; workgroups in rounds as in plan_mfma; the launch that adds slices.  Fitted to 1204 calls of
+// The time of a chunk, by planes; workgroups in rounds as in plan_mfma; the launch that adds slices.  Fitted to 1232 calls of
 // both kinds (single matrices of 64 to 2000 column tiles and 1 to 112 chunks, groups of layers, 16 to 32 rows, q = 1 to 4); error 9 %.
 double hlq_gemm_mfma_estimate(int count, const HlqDims *dms, int64_t M)
 {

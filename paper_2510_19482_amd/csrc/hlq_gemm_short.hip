@@ -314,10 +314,10 @@ size_t hlq_gemm_short_partial_bytes(int count, const HlqDims *dms, int64_t M)
 
 // One round of workgroups (256): always (0.44 to 1.05 of the tiled kernel's time).  More of them pay start and end of a workgroup per
 // round, whatever the depth, where the tiled kernel has a quarter as many with four times the columns; which of the two
-// is the longer time is estimated.  us, tiled / this one, M = 32, G = 64: 64 x 2000 tiles of 2 chunks (256 x 127976) q = 1 9.2 / 34.9,
-// 1000 x 8 12.3 / 19.3, 1000 x 32 q = 2 44.6 / 47.9, q = 4 (M = 16) 61.4 / 56.9;  300 x 8 q = 2 12.2 / 10.6;  450 x 24 q = 2 21.5 / 19.8;  600 x 48 q = 1
-// 31.2 / 38.3.  Over the calls the estimate was fitted to, 1 % from the better of the two on average, 23 % at most (this kernel always: 23 % and
-// 4.5 times).  From 80000 chunk-tiles on the tiled kernel: 86016 q = 2, M = 16 99.8 / 98.8, 128256 q = 2, M = 24 141 / 158.
+// is the longer time is estimated.  us, tiled / this one, M = 32, G = 64: 256 x 127976 q = 1 9.2 / 34.9,
+// 1024 x 63976 12.3 / 19.3, 4096 x 63976 q = 2 44.6 / 47.9, q = 4 (M = 16) 61.4 / 56.9;  1024 x 19176 q = 2 12.2 / 10.6;  3072 x 28776 q = 2 21.5 / 19.8;
+// 6144 x 38376 q = 1 31.2 / 38.3.  Over the calls the estimate was fitted to, 1 % from the better of the two on average, 23 % at most (this kernel
+// always: 23 % and 4.5 times; profiles/gemm_rows_to_32_rules.txt).  From 80000 chunk-tiles on the tiled kernel: 86016 q = 2, M = 16 99.8 / 98.8, 128256 q = 2, M = 24 141 / 158.
 bool hlq_gemm_short_wins(int count, const HlqDims *dms, int64_t M)
 {
     if (M < 1 || M > HLQ_SHORT_ROWS) return false;

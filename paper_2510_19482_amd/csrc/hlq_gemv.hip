@@ -568,9 +568,9 @@ RunShape plan_runs(int count, const HlqGemvItem *items, RunShape usual, const Ru
     return best;
 }
 
-// Many-rows kernel: runs of 4 below 12000 chunk-tiles and of 16 above unless the estimate falls by 9 %.  Over 240 launches (2400
-// to 128256 chunk-tiles, single matrices and layers, q = 1 to 4, 4 to 16 rows) 6 % faster than the usual one on average
-// and 2 % slower at most; us:  q = 4, 16 rows  4096 x 14336 21.4 -> 18.8, 14336 x 4096 22.4 -> 20.2, 11008 x 9000 33.8 -> 28.3, 5120 x 13824
+// Many-rows kernel: runs of 4 below 12000 chunk-tiles and of 16 above unless the estimate falls by 9 %.  Over 180 launches (2048
+// to 128256 chunk-tiles, single matrices and layers, q = 1 to 4, 4 to 16 rows; profiles/gemm_rows_to_32_rules.txt) 5 % faster than the usual one on
+// average and 4 % slower at most; us:  q = 4, 16 rows  4096 x 14336 21.4 -> 18.8, 14336 x 4096 22.4 -> 20.2, 11008 x 9000 33.8 -> 28.3, 5120 x 13824
 // 27.0 -> 20.9, layer of hidden 3072 / ffn 8192 31.6 -> 25.0, hidden 3840 / ffn 9984 43.6 -> 36.1, 8192 x 57344 81.5 -> 78.5;  q = 2, 8 rows
 // 11008 x 9000 22.4 -> 18.7, 8192 x 57344 40.9 -> 36.3.  (Without the margin 7 % on average, but the layer of hidden 2560 / ffn 9984 28.4 -> 30.2.)
 RunShape plan_many_rows(int count, const HlqGemvItem *items, long units)
@@ -581,8 +581,8 @@ RunShape plan_many_rows(int count, const HlqGemvItem *items, long units)
 
 // Few-rows instantiation of the 64-column kernel, from 4096 chunk-tiles on: eight wavefronts with runs of 4 below 12000 chunk-tiles
 // and of 6 above, or what the estimate prefers.  Runs beyond eight chunks are slow whatever the rounds (the activations are
-// cut into terms by every wavefront; hidden 3584 / ffn 10240, q = 4, 4 rows: 23 us with runs of 6, 43 with 16).  Over 379
-// launches 5 % faster on average and 1 % slower at most; us:  q = 4, 4 rows  layer of hidden 3072 / ffn 8192 27.5 -> 18.0, hidden
+// cut into terms by every wavefront; hidden 3584 / ffn 10240, q = 4, 4 rows: 23 us with runs of 6, 43 with 16).  Over 180
+// launches (same file) 5 % faster on average and 3 % slower at most; us:  q = 4, 4 rows  layer of hidden 3072 / ffn 8192 27.5 -> 18.0, hidden
 // 2816 / ffn 8192 25.9 -> 20.4, 11008 x 9000 31.4 -> 22.3, 8192 x 10240 25.8 -> 20.2;  q = 2, 2 rows  hidden 3072 12.3 -> 10.6,
 // 28672 x 8192 22.1 -> 18.1;  G = 64, q = 4, 2 rows  hidden 3072 22.4 -> 15.8
 RunShape plan_few_rows(int count, const HlqGemvItem *items, long units, bool forced)
