@@ -1,0 +1,76 @@
+"""hlq_quantize where its rounds end or its sorted lists are tested: parameters that stay as they are before the last round,
+weights equal to a midpoint or next to one at zero, weights too far apart for exact sums, infinite weights beside finite ones."""
+import numpy as np
+import pytest
+
+from oracle import hlq_quantize_oracle as QO
+from paper_2510_19482_amd import binding as B
+
+from gpu_util import dev
+
+pytestmark = pytest.mark.gpu
+
+
+def quantize(W, q, G, rounds):
+    return [t.cpu().numpy() for t in B.hlq_quantize(B.make_desc(*W.shape, q, G), dev(W), rounds)]
+
+
+@pytest.mark.parametrize("q", [1, 2, 3, 4])
+@pytest.mark.parametrize("G", [32, 64, 128, 256])
+def test_rounds_after_the_last_change(q, G):
+    # codes of the oracle after 2, 3, .. rounds; the columns of a wavefront come to rest after different numbers of them
+    W = (np.random.default_rng(q * G).standard_normal((256, 136)) * 0.02).astype(np.float32)
+    for rounds in (2, 3, 7, 40):
+        assert np.array_equal(quantize(W, q, G, rounds)[0], QO.quantize(W.astype(np.float64), q, G, t_max=rounds)[0]), rounds
+    # at rest, so the same bytes whatever is left (60 rounds and more suffice for these groups)
+    a, b = quantize(W[:, :8], q, G, 300), quantize(W[:, :8], q, G, 301)
+    assert all(np.array_equal(x.view(np.uint8), y.view(np.uint8)) for x, y in zip(a, b))
+
+
+@pytest.mark.parametrize("q", [1, 2, 3])
+@pytest.mark.parametrize("G", [32, 64, 128])
+def test_weights_at_the_midpoints(q, G):
+    """First round only (the starting parameters are the same numbers on both sides, so are exact ties): a grid of 2^q + 1 steps
+    whose ends make the candidates small integers, and weights at integers and halves, one fp32 step off them, and at zero from
+    both sides."""
+    rng = np.random.default_rng(5)
+    W = np.empty((256, 72), dtype=np.float32)
+    for n in range(72):
+        low = np.float32(rng.integers(-8, 2))
+        vals = low + rng.integers(0, 2 * (2 ** q - 1) + 1, 256) / np.float32(2)
+        near = np.nextafter(vals.astype(np.float32), np.float32(rng.choice([-100, 100])))
+        W[:, n] = np.where(rng.random(256) < 0.4, near, vals)
+        W[::7, n] = rng.choice([0.0, -0.0, 1e-42, -1e-42, 2.0 ** -60, -2.0 ** -60], len(W[::7]))
+        W[:, n] = np.clip(W[:, n], low, low + 2 ** q - 1)
+        W[0::G, n], W[1::G, n] = low, low + 2 ** q - 1
+    if G > 32:   # (far apart: rounded to what the sums hold, which the oracle does not do)
+        W[np.abs(W) < 1e-10] = 0
+    assert np.array_equal(quantize(W, q, G, 1)[0], QO.quantize(W.astype(np.float64), q, G, t_max=1)[0])
+
+
+@pytest.mark.parametrize("q", [1, 2, 3, 4])
+def test_groups_of_32_far_apart(q):
+    # sums of such groups depend on the order: that of the rows, as fp64 sums of the oracle's design matrix have it up to rounding
+    rng = np.random.default_rng(q)
+    W = (rng.standard_normal((256, 136)) * 0.02).astype(np.float32)
+    W[::5] *= np.float32(2.0 ** -30)
+    W[3::32, ::2] = 0
+    codes, S, Z = quantize(W, q, 32, 5)
+    ref, S_ref, Z_ref = QO.quantize(W.astype(np.float64), q, 32, t_max=5)
+    assert np.array_equal(codes, ref)
+    # fp16 parameters: one unit in the last place (2^-10 of the value) and the subnormals' spacing
+    for got, want in ((S, S_ref), (Z, Z_ref)):
+        assert (np.abs(got.astype(np.float64) - want) <= 2.0 ** -10 * np.abs(want) + 2.0 ** -24).all()
+
+
+@pytest.mark.parametrize("G", [32, 128])
+@pytest.mark.parametrize("q", [1, 2, 3, 4])
+def test_infinite_neighbours(q, G):
+    # groups with infinities and NaN share wavefronts with finite ones, which keep their bytes
+    W = (np.random.default_rng(9).standard_normal((256, 72)) * 0.02).astype(np.float32)
+    alone = quantize(W, q, G, 4)
+    W[5, 3], W[200, 40], W[130, 41], W[131, 41] = np.inf, np.nan, np.inf, -np.inf
+    mixed = quantize(W, q, G, 4)
+    keep = [n for n in range(72) if n not in (3, 40, 41)]
+    for a, b in zip(alone, mixed):
+        assert np.array_equal(np.ascontiguousarray(a[..., keep]).view(np.uint8), np.ascontiguousarray(b[..., keep]).view(np.uint8))
