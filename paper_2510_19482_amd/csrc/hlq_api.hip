@@ -119,6 +119,17 @@ hlq_status hlq_gemm_batch_workspace_bytes(int count, const hlq_desc *descs, int6
     // the grouped launches of the kernels that rebuild weights split K on their own terms
     const size_t grouped = HLQ_WS_COUNTER_BYTES + batch_partial_bytes(count, dms, M);
     if (grouped > b) b = grouped;
+    // what a call can do without but is faster with; the plans count the problems of long K first
+    if (M > 1) {
+        for (int i = 1; i < count; ++i)
+            for (int j = i; j > 0 && dms[j].nchunks > dms[j - 1].nchunks; --j) {
+                const HlqDims d = dms[j];
+                dms[j] = dms[j - 1];
+                dms[j - 1] = d;
+            }
+        const size_t with_tail = HLQ_WS_COUNTER_BYTES + hlq_gemm_mfma_batch_partial_bytes(count, dms, M) + hlq_gemm_mfma_tail_bytes(count, dms, M);
+        if (with_tail > b) b = with_tail;
+    }
     *bytes = (b + 255u) & ~(size_t)255u;
     return HLQ_OK;
 }
@@ -281,7 +292,7 @@ hlq_status hlq_lut_gemm_batch(int count, const hlq_desc *descs, const void *cons
             const hlq_status s = hlq_launch_gemm_short(count, items, M, out, ws, (hipStream_t)stream);
             if (s != HLQ_ERR_UNSUPPORTED) return s;
         }
-        const hlq_status s = hlq_launch_gemm_mfma_batch(count, items, M, out, ws, (hipStream_t)stream);
+        const hlq_status s = hlq_launch_gemm_mfma_batch(count, items, M, out, ws, ws_bytes, (hipStream_t)stream);
         if (s != HLQ_ERR_UNSUPPORTED) return s;
     }
     for (int i = 0; i < count; ++i) {

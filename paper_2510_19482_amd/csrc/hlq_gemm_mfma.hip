@@ -472,6 +472,8 @@ struct GroupPlan {
     int MW;
     long rowblocks;
     int cps[HLQ_MAX_BATCH], nslices[HLQ_MAX_BATCH];
+    // the last `tail_groups` column groups of problem `tail` are cut further
+    int tail = -1, tail_groups = 0, tail_cps = 0, tail_nslices = 1;
 };
 
 static GroupPlan plan_group(int count, const HlqDims *dms, int64_t M)
@@ -494,6 +496,119 @@ static GroupPlan plan_group(int count, const HlqDims *dms, int64_t M)
     return g;
 }
 
+// When the last workgroup ends, in chunk steps of two workgroups on a compute unit: workgroups of n kinds (steps, number; longest
+// first) on 512 places in list order; of the two places of a unit the one left alone runs at 1 / 0.6 the speed.
+static double launch_steps(int n, const int *steps, const long *number)
+{
+    constexpr int MOST = 48;
+    int load[MOST], kinds = 1;   // places by what they have been given
+    long places[MOST];
+    load[0] = 0;
+    places[0] = 512;
+    for (int i = 0; i < n; ++i)
+        for (long left = number[i]; left > 0;) {
+            int low = 0;
+            for (int k = 1; k < kinds; ++k)
+                if (load[k] < load[low]) low = k;
+            const long m = left < places[low] ? left : places[low];
+            const int to = load[low] + steps[i];
+            left -= m;
+            places[low] -= m;
+            int at = 0;
+            while (at < kinds && load[at] != to) ++at;
+            if (at < kinds) {
+                places[at] += m;
+            } else if (places[low] == 0) {
+                load[low] = to;
+                places[low] = m;
+            } else {
+                if (kinds == MOST) return 1e9;
+                load[kinds] = to;
+                places[kinds++] = m;
+            }
+            if (places[low] == 0) {
+                load[low] = load[kinds - 1];
+                places[low] = places[--kinds];
+            }
+        }
+    for (int i = 1; i < kinds; ++i)
+        for (int j = i; j > 0 && load[j] < load[j - 1]; --j) {
+            const int l = load[j];
+            const long m = places[j];
+            load[j] = load[j - 1];
+            places[j] = places[j - 1];
+            load[j - 1] = l;
+            places[j - 1] = m;
+        }
+    double end = 0;
+    for (int a = 0, b = kinds - 1; a <= b;) {   // the longest beside the shortest
+        const double t = load[a] + 0.6 * (load[b] - load[a]);
+        if (t > end) end = t;
+        const long m = a == b ? places[a] : places[a] < places[b] ? places[a] : places[b];
+        places[a] -= m;
+        if (a != b) places[b] -= m;
+        if (places[a] == 0) ++a;
+        else --b;
+    }
+    return end;
+}
+
+// The last round of a launch of more than 512 workgroups is rarely even: with 32 chunks a tile and 32 tiles too many for one workgroup
+// a compute unit, 32 units have two of them to the end (8B layer at M = 512: 64 chunk steps, where all units together would be
+// through after 52).  Cutting as many tiles of one problem in two or three along K evens that out at the price of their partial
+// sums: a number of column groups of the widest problem of the shortest K is chosen by the estimate above, where it finds
+// 4 % or more.  Grouped launches, us, without -> with: 8B layer q = 2, M = 300 / 400 / 512 / 640 184 / 236 / 244 / 285 -> 176 / 218 /
+// 223 / 265, q = 4, M = 512 282 -> 262; hidden 3072, ffn 9216, q = 3, M = 500 152 -> 131; hidden 3840, ffn 11008, M = 800 308 -> 294.
+// Below 4 % the estimate is no guide (8B layer at M = 2048, 2.6 %: 809 -> 825), nor
+// is it with fewer than 16 chunks a tile (hidden 1536, M = 1800 154 -> 156).
+static void plan_tail(int count, const HlqDims *dms, GroupPlan &g)
+{
+    if (g.MW < 4 || count >= HLQ_MAX_BATCH) return;
+    int steps[HLQ_MAX_BATCH + 1], order[HLQ_MAX_BATCH], wide = -1, whole = 0;
+    long number[HLQ_MAX_BATCH + 1], total = 0;
+    bool sums = false;
+    for (int i = 0; i < count; ++i) {
+        int at = i;
+        for (; at > 0 && g.cps[order[at - 1]] < g.cps[i]; --at) order[at] = order[at - 1];
+        order[at] = i;
+        total += (long)((dms[i].ntiles + 3) / 4) * g.rowblocks * g.nslices[i];
+        sums = sums || g.nslices[i] > 1;
+        if (g.nslices[i] == 1 && (wide < 0 || dms[i].nchunks < dms[wide].nchunks || (dms[i].nchunks == dms[wide].nchunks && dms[i].ntiles > dms[wide].ntiles))) wide = i;
+    }
+    if (total <= 512 || total > 4096 || wide < 0 || dms[wide].nchunks < 16) return;
+    for (int k = 0; k < count; ++k) {
+        steps[k] = g.cps[order[k]];
+        number[k] = (long)((dms[order[k]].ntiles + 3) / 4) * g.rowblocks * g.nslices[order[k]];
+        if (order[k] == wide) whole = k;
+    }
+    const double step = 3.0 + 0.3 * dms[0].q;   // us
+    const int groups = (dms[wide].ntiles + 3) / 4;
+    double best = launch_steps(count, steps, number) * step * 0.96;
+    for (int c = 1; c < groups && c * g.rowblocks <= 256; c += 1 + groups / 16)
+        for (int ns = 2; ns <= 3; ++ns) {
+            const int cps = ((dms[wide].nchunks + ns - 1) / ns + 1) & ~1;
+            number[whole] = (long)(groups - c) * g.rowblocks;
+            steps[count] = cps;
+            number[count] = (long)c * g.rowblocks * ns;
+            const double t = launch_steps(count + 1, steps, number) * step + (sums ? 0.0 : 5.0) + (double)number[count] * (128 * 256 * 4) / 4.0e6;   // (partial sums at 4 TB/s)
+            if (t < best) {
+                best = t;
+                g.tail = wide;
+                g.tail_groups = c;
+                g.tail_cps = cps;
+                g.tail_nslices = (dms[wide].nchunks + cps - 1) / cps;
+            }
+        }
+}
+
+// partial sums of the tail
+static size_t tail_bytes(const HlqDims *dms, const GroupPlan &g, int64_t M)
+{
+    if (g.tail < 0) return 0;
+    const int first = ((dms[g.tail].ntiles + 3) / 4 - g.tail_groups) * 4 * HLQ_TILE_N;
+    return (size_t)g.tail_nslices * (size_t)M * (size_t)(dms[g.tail].N - first) * sizeof(float);
+}
+
 size_t hlq_gemm_mfma_batch_partial_bytes(int count, const HlqDims *dms, int64_t M)
 {
     if (count < 2 || M < 1) return 0;
@@ -504,7 +619,16 @@ size_t hlq_gemm_mfma_batch_partial_bytes(int count, const HlqDims *dms, int64_t 
     return b;
 }
 
-// What a call takes with this kernel, us, up to 32 rows: for the choice between it and the short-M kernel (hlq_gemm_short_wins).
+// on top of what a call needs: with it the tail of the launch is cut
+size_t hlq_gemm_mfma_tail_bytes(int count, const HlqDims *dms, int64_t M)
+{
+    if (count < 2 || M < 1) return 0;
+    GroupPlan g = plan_group(count, dms, M);
+    plan_tail(count, dms, g);
+    return tail_bytes(dms, g, M);
+}
+
+// What a call takes with this kernel, us, up to 32 rows (where no tail is cut): for the choice between it and the short-M kernel (hlq_gemm_short_wins).
 // The time of a chunk, by planes; workgroups in rounds as in plan_mfma; the launch that adds slices.  Fitted to 1232 calls of
 // both kinds (single matrices of 64 to 2000 column tiles and 1 to 112 chunks, groups of layers, 16 to 32 rows, q = 1 to 4); error 9 %.
 double hlq_gemm_mfma_estimate(int count, const HlqDims *dms, int64_t M)
@@ -537,7 +661,7 @@ double hlq_gemm_mfma_estimate(int count, const HlqDims *dms, int64_t M)
 // One launch for several problems of the same q, G and M.  HLQ_ERR_UNSUPPORTED if the launch cannot be
 // formed (the caller then runs the problems one after the other).
 hlq_status hlq_launch_gemm_mfma_batch(int count, const HlqGemvItem *items, int64_t M, hlq_out_dtype out, void *ws,
-                                      hipStream_t st)
+                                      size_t ws_bytes, hipStream_t st)
 {
     static_assert(HLQ_MAX_BATCH == 8, "the grouped kernels take the first blocks of eight problems");
     hlq_clear_stale_error();
@@ -553,45 +677,54 @@ hlq_status hlq_launch_gemm_mfma_batch(int count, const HlqGemvItem *items, int64
         }
     HlqDims dms[HLQ_MAX_BATCH];
     for (int i = 0; i < count; ++i) dms[i] = items[order[i]].dm;
-    const GroupPlan g = plan_group(count, dms, M);
+    const GroupPlan whole = plan_group(count, dms, M);
+    GroupPlan g = whole;
+    plan_tail(count, dms, g);
+    if (HLQ_WS_COUNTER_BYTES + hlq_gemm_mfma_batch_partial_bytes(count, dms, M) + tail_bytes(dms, g, M) > ws_bytes) g = whole;
     GemmProbs pr;
     HlqReduce red(M, out == HLQ_OUT_F32);
     int begin[HLQ_MAX_BATCH];
     long blk = 0;
     float *part = (float *)((char *)ws + HLQ_WS_COUNTER_BYTES);
     auto magic = [](int d) { return d > 1 ? (unsigned)((0x100000000ULL + (unsigned)d - 1) / (unsigned)d) : 0u; };
-    for (int i = 0; i < count; ++i) {
+    // a problem each, and the part of one that is cut further
+    const int entries = count + (g.tail >= 0 ? 1 : 0);
+    for (int e = 0; e < entries; ++e) {
+        const bool tail = e == count;
+        const int i = tail ? g.tail : e;
         const HlqGemvItem &it = items[order[i]];
         if (it.dm.q != items[0].dm.q || it.dm.G != items[0].dm.G) return HLQ_ERR_UNSUPPORTED;
-        GemmProb &p = pr.p[i];
-        p.packed = (const char *)it.packed;
+        const int groups = (it.dm.ntiles + 3) / 4, first = tail ? groups - g.tail_groups : 0;   // column groups
+        GemmProb &p = pr.p[e];
+        p.colgroups = (i == g.tail && !tail ? groups - g.tail_groups : groups) - first;
+        const int n0 = first * 4 * HLQ_TILE_N;
+        p.packed = (const char *)it.packed + (size_t)n0 * it.dm.col_bytes;
         p.col_bytes = it.dm.col_bytes;
         p.X = it.x;
         p.ldx = it.ldx;
-        p.Y = it.y;
+        p.Y = (char *)it.y + (size_t)n0 * (out == HLQ_OUT_F32 ? 4 : 2);
         p.ldy = it.ldy;
         p.part = part;
-        p.N = it.dm.N;
-        p.ntiles = it.dm.ntiles;
+        p.N = i == g.tail && !tail ? p.colgroups * 4 * HLQ_TILE_N : it.dm.N - n0;
+        p.ntiles = (p.N + HLQ_TILE_N - 1) / HLQ_TILE_N;
         p.nchunks = it.dm.nchunks;
-        p.colgroups = (it.dm.ntiles + 3) / 4;
-        p.cps = g.cps[i];
-        p.nslices = g.nslices[i];
+        p.cps = tail ? g.tail_cps : g.cps[i];
+        p.nslices = tail ? g.tail_nslices : g.nslices[i];
         p.cg_magic = magic(p.colgroups);
         p.ns_magic = magic(p.nslices);
         const unsigned long long blocks = (unsigned long long)p.colgroups * p.nslices * g.rowblocks;
         // the reciprocals are exact while (largest dividend) * divisor < 2^32
         if (blocks * p.colgroups >= 0x100000000ULL || blocks * p.nslices >= 0x100000000ULL) return HLQ_ERR_UNSUPPORTED;
         p.blk_begin = (int)blk;
-        begin[i] = (int)blk;
+        begin[e] = (int)blk;
         blk += (long)blocks;
         if (blk > 0x7fffffffL) return HLQ_ERR_UNSUPPORTED;
         if (p.nslices > 1) {
-            if (!red.add(part, it.y, it.ldy, it.dm.N, p.nslices)) return HLQ_ERR_UNSUPPORTED;
-            part += (size_t)p.nslices * (size_t)M * (size_t)it.dm.N;
+            if (!red.add(part, p.Y, it.ldy, p.N, p.nslices)) return HLQ_ERR_UNSUPPORTED;
+            part += (size_t)p.nslices * (size_t)M * (size_t)p.N;
         }
     }
-    for (int i = count; i < HLQ_MAX_BATCH; ++i) {
+    for (int i = entries; i < HLQ_MAX_BATCH; ++i) {
         pr.p[i] = pr.p[0];
         begin[i] = 0x7fffffff;
     }

@@ -165,8 +165,10 @@ hlq_status hlq_launch_gemm_mfma(const HlqDims &dm, const void *packed, const uin
                                 int64_t ldx, void *Y, int64_t ldy, hlq_out_dtype out, void *ws, hipStream_t st);
 hlq_status hlq_gemm_path_override(int path);
 bool hlq_gemm_uses_matrix_cores(int64_t M);
+// (ws_bytes: of the workspace, which decides whether the tail of a launch is cut)
 hlq_status hlq_launch_gemm_mfma_batch(int count, const HlqGemvItem *items, int64_t M, hlq_out_dtype out, void *ws,
-                                      hipStream_t st);
+                                      size_t ws_bytes, hipStream_t st);
+size_t hlq_gemm_mfma_tail_bytes(int count, const HlqDims *dms, int64_t M);
 double hlq_gemm_mfma_estimate(int count, const HlqDims *dms, int64_t M);
 size_t hlq_gemm_mfma_batch_partial_bytes(int count, const HlqDims *dms, int64_t M);
 hlq_status hlq_launch_gemm_safe(int count, const HlqGemvItem *items, int64_t M, hlq_out_dtype out, void *ws, hipStream_t st);
