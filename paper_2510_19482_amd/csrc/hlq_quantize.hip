@@ -892,8 +892,10 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
 // and only those near an fp32 number looked at again one by one, a division is saved for all but the last unknown, and columns
 // are not asked for independence where the codes show it: 4096 x 1024, G = 64 80 -> 75 us, 4096 x 4096, G = 32 / 64 / 128 / 256
 // 282 / 215 / 190 / 185 -> 230 / 196 / 182 / 175.
+// Groups of 64, one lane each: groups that are at rest leave their lanes to the others of their wavefront (below), 4096 x 1024 75 -> 67 us,
+// 4096 x 4096 196 -> 182, bf16 weights 103 -> 79 and 237 -> 213, -1, 0, 1 130 -> 81 and 399 -> 240; two wavefronts on a SIMD instead of three for it.
 template <int G, int L>
-__global__ void __launch_bounds__(256, G / L == 128 ? 2 : 3)
+__global__ void __launch_bounds__(256, G / L == 128 || (G == 64 && L == 1) ? 2 : 3)
 hlq_quantize_kernel_4(const float *__restrict__ W, int K, int N, int t_max, uint8_t *__restrict__ codes,
                     uint16_t *__restrict__ scales, uint16_t *__restrict__ zeros, float *__restrict__ group_err)
 {
@@ -939,8 +941,9 @@ hlq_quantize_kernel_4(const float *__restrict__ W, int K, int N, int t_max, uint
     }
     // the lanes of a group are neighbours: l apart is a permutation of four
     auto across = [](uint32_t v, auto l) -> uint32_t { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(l)::value == 1 ? 0xB1 : 0x4E, 0xf, 0xf, false); };
-    auto add_parts = [&](double v) -> double {
-        unrolled<(L == 4 ? 2 : L == 2 ? 1 : 0)>([&](auto k) {
+    using Lanes = std::integral_constant<int, L>;
+    auto add_parts = [&](double v, auto lanes) -> double {
+        unrolled<(decltype(lanes)::value == 4 ? 2 : decltype(lanes)::value == 2 ? 1 : 0)>([&](auto k) {
             const std::integral_constant<int, 1 + decltype(k)::value> l;
             const uint64_t b = __builtin_bit_cast(uint64_t, v);
             v += __builtin_bit_cast(double, (uint64_t)across((uint32_t)(b >> 32), l) << 32 | across((uint32_t)b, l));
@@ -956,7 +959,7 @@ hlq_quantize_kernel_4(const float *__restrict__ W, int K, int N, int t_max, uint
             least = fminf(least, __builtin_bit_cast(float, across(__builtin_bit_cast(uint32_t, least), l)));
         });
     }
-    const float largest = fmaxf(fabsf(lof), fabsf(hif));
+    float largest = fmaxf(fabsf(lof), fabsf(hif));
     // The number of lanes of a group depends on the size of the launch; its results do not, since its sums are exact in fp64 and
     // so the same in any order.  fp32 weights down to 2^-21 of the largest are so as they are.  Where some (not zero) are
     // smaller, all are rounded to multiples of 2^-52 of a power of two that no sum of magnitudes exceeds: a change, by less
@@ -983,7 +986,7 @@ hlq_quantize_kernel_4(const float *__restrict__ W, int K, int N, int t_max, uint
     }
 #pragma unroll
     for (int i = 0; i < GL; ++i) rw += (double)wv[i];
-    rw = add_parts(rw);
+    rw = add_parts(rw, Lanes{});
     auto weight = [&](int i) -> float {
         // opaque to the optimiser, so the fp64 copies are made per use instead of being kept
         // for the whole kernel (which would double the registers held)
@@ -992,7 +995,7 @@ hlq_quantize_kernel_4(const float *__restrict__ W, int K, int N, int t_max, uint
     };
     const double lo = (double)lof, hi = (double)hif;
     const double delta = (hi - lo) / (double)(NC - 1);
-    const bool constant = lof == hif && rw - rw == 0.0;   // all weights equal (and no NaN among them)
+    bool constant = lof == hif && rw - rw == 0.0;   // all weights equal (and no NaN among them)
     double theta[P];   // theta[0] = z, theta[1 + j] = s_j
     theta[0] = lo;
 #pragma unroll
@@ -1003,9 +1006,11 @@ hlq_quantize_kernel_4(const float *__restrict__ W, int K, int N, int t_max, uint
     // be a coincidence, candidates closer than the keys' 19 bits tell apart.
     constexpr int STAY = 2;
     int scans = 0;
-    // one iteration of Alg. 1; the last one also stores the codes (a separate instantiation: a test per weight costs more)
-    auto iteration = [&](auto last_c) -> bool {
+    // one iteration of Alg. 1 for groups of which `lanes` lanes have the weights src each; the last one also stores the codes (a
+    // separate instantiation: a test per weight costs more).  Returns whether the lane's next round can differ.
+    auto iteration = [&](auto last_c, auto &src, auto lanes) -> bool {
         constexpr bool last = decltype(last_c)::value;
+        constexpr int LEN = sizeof(src) / sizeof(src[0]), PARTS = decltype(lanes)::value;
         int stride = N;   // of rows; an opaque copy: the multiples of N that the first loads took are not kept for later
         asm volatile("" : "+s"(stride));
         const double z = theta[0];
@@ -1171,16 +1176,14 @@ hlq_quantize_kernel_4(const float *__restrict__ W, int K, int N, int t_max, uint
             // previous eight between the levels: an LDS read is used some thirty instructions after it was issued
             // (with the weights in registers there are two to five wavefronts on a SIMD to cover for each other).
             constexpr int B = 8;
-            // LEN weights from src, the group's weights i0, i0 + 1, ..
-            auto pass = [&](auto &src, auto len_c, int i0) {
-                constexpr int LEN = decltype(len_c)::value;
+            {
                 uint32_t word[2][B];
                 uint32_t *at[B];
                 // an opaque copy of the weight, made at its use: otherwise the optimiser converts every weight to fp64 once
                 // and keeps both
                 auto sum_up = [&](int i, uint32_t w) {
                     asm volatile("" : "+v"(src[i]));
-                    fold(i0 + i, src[i], w);
+                    fold(i, src[i], w);
                 };
 #pragma unroll
                 for (int i = 0; i < LEN; i += B) {
@@ -1242,8 +1245,7 @@ hlq_quantize_kernel_4(const float *__restrict__ W, int K, int N, int t_max, uint
                 }
 #pragma unroll
                 for (int u = 0; u < B; ++u) sum_up(LEN - B + u, word[(LEN / B - 1) & 1][u]);
-            };
-            pass(wv, std::integral_constant<int, GL>{}, 0);
+            }
         } else {
             // the scan of all candidates
             double V[NC];
@@ -1270,11 +1272,11 @@ hlq_quantize_kernel_4(const float *__restrict__ W, int K, int N, int t_max, uint
             };
             // from the registers; at q = 4, G = 128 that would be 9000 instructions a round, and the weights come from memory,
             // requested eight ahead
-            if constexpr (GL * NC <= 1024) {
+            if constexpr (LEN * NC <= 1024) {
 #pragma unroll
-                for (int i = 0; i < GL; ++i) {
+                for (int i = 0; i < LEN; ++i) {
                     float w;   // a copy: the register itself is the same one whichever way the round went
-                    asm volatile("" : "=v"(w) : "0"(wv[i]));
+                    asm volatile("" : "=v"(w) : "0"(src[i]));
                     take(i, w);
                     if ((i & 3) == 3) __builtin_amdgcn_sched_barrier(0);   // not many weights converted ahead (registers)
                 }
@@ -1298,7 +1300,7 @@ hlq_quantize_kernel_4(const float *__restrict__ W, int K, int N, int t_max, uint
             }
         }
 #pragma unroll
-        for (int j = 0; j < Q; ++j) rb[j] = add_parts(rb[j] * 0x1p15);
+        for (int j = 0; j < Q; ++j) rb[j] = add_parts(rb[j] * 0x1p15, lanes);
 
         // counts by code, from counts by sorted position
         {
@@ -1311,16 +1313,93 @@ hlq_quantize_kernel_4(const float *__restrict__ W, int K, int N, int t_max, uint
                 for (int i = 0; i < NC; ++i) cnt[i] = (int)plane[i * 64];
             }
         }
-        if constexpr (L > 1) {
+        if constexpr (PARTS > 1) {
 #pragma unroll
             for (int c = 0; c < NC; ++c)
-                unrolled<(L == 4 ? 2 : 1)>([&](auto k) { cnt[c] += (int)across((uint32_t)cnt[c], std::integral_constant<int, 1 + decltype(k)::value>{}); });
+                unrolled<(PARTS == 4 ? 2 : 1)>([&](auto k) { cnt[c] += (int)across((uint32_t)cnt[c], std::integral_constant<int, 1 + decltype(k)::value>{}); });
         }
-        return __any(reconstruct<Q, G>(cnt, rb, rw, theta));   // whether the next round can differ
+        return reconstruct<Q, G>(cnt, rb, rw, theta);
     };
-    for (int t = 0; t + 1 < t_max && iteration(std::false_type{}); ++t) {
+    int left = t_max - 1;   // rounds before the last
+    // Rounds for the groups of the lanes in `changing` only, at most 64 / PARTS of them, with PARTS lanes and a part of the weights each, until
+    // no more than `enough` of them change; returns which do.
+    auto share_out = [&](auto parts_c, uint64_t changing, int enough) -> uint64_t {
+        constexpr int PARTS = decltype(parts_c)::value, SLOTS = 64 / PARTS, LEN = GL / PARTS;
+        const int lane = (int)(threadIdx.x & 63), slot = lane / PARTS, mine_of = lane % PARTS;
+        const bool mine = changing >> lane & 1, used = slot < __popcll(changing);
+        const int to = __popcll(changing & ((1ull << lane) - 1));
+        uint32_t *const all = lds + (threadIdx.x >> 6) * (3 * NC * 64);   // of the wavefront; word i of all slots together
+        auto put = [&](int word, double v, int at) {
+            const uint64_t b = __builtin_bit_cast(uint64_t, v);
+            all[word * SLOTS + at] = (uint32_t)b;
+            all[(word + 1) * SLOTS + at] = (uint32_t)(b >> 32);
+        };
+        auto get = [&](int word, int at) -> double { return __builtin_bit_cast(double, (uint64_t)all[(word + 1) * SLOTS + at] << 32 | all[word * SLOTS + at]); };
+        auto handed_over = [] { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); };   // (one wavefront: LDS accesses are in order)
+        double own[P];
+        const double own_rw = rw;
+        const float own_largest = largest;
+        const bool own_constant = constant;
+#pragma unroll
+        for (int k = 0; k < P; ++k) own[k] = theta[k];
+        handed_over();
+        if (mine) {
+#pragma unroll
+            for (int i = 0; i < GL; ++i) all[i * SLOTS + to] = __builtin_bit_cast(uint32_t, wv[i]);
+        }
+        handed_over();
+        float few[LEN];   // (a slot without a group: equal weights)
+#pragma unroll
+        for (int i = 0; i < LEN; ++i) few[i] = used ? __builtin_bit_cast(float, all[(mine_of * LEN + i) * SLOTS + slot]) : 0.f;
+        handed_over();
+        if (mine) {
+#pragma unroll
+            for (int k = 0; k < P; ++k) put(2 * k, theta[k], to);
+            put(2 * P, rw, to);
+            all[(2 * P + 2) * SLOTS + to] = __builtin_bit_cast(uint32_t, largest);
+            all[(2 * P + 3) * SLOTS + to] = constant ? 1u : 0u;
+        }
+        handed_over();
+#pragma unroll
+        for (int k = 0; k < P; ++k) theta[k] = used ? get(2 * k, slot) : 0.0;
+        rw = used ? get(2 * P, slot) : 0.0;
+        largest = used ? __builtin_bit_cast(float, all[(2 * P + 2) * SLOTS + slot]) : 0.f;
+        constant = used ? all[(2 * P + 3) * SLOTS + slot] != 0u : true;
+        handed_over();
+        uint64_t still = changing;
+        while (left > 0) {
+            --left;
+            still = __ballot(iteration(std::false_type{}, few, parts_c) && mine_of == 0);
+            if (__popcll(still) <= enough) break;
+        }
+        handed_over();
+        if (used && mine_of == 0) {
+#pragma unroll
+            for (int k = 0; k < P; ++k) put(2 * k, theta[k], slot);
+        }
+        handed_over();
+#pragma unroll
+        for (int k = 0; k < P; ++k) theta[k] = mine ? get(2 * k, to) : own[k];
+        rw = own_rw;
+        largest = own_largest;
+        constant = own_constant;
+        return __ballot(mine && (still >> (to * PARTS) & 1));
+    };
+    while (left > 0) {
+        --left;
+        uint64_t changing = __ballot(iteration(std::false_type{}, wv, Lanes{}));
+        // A group of 64 is at rest after three or four rounds on average, the last of 64 groups after ten.  When half of them are left they
+        // get two lanes each, then four.  (Their sums are exact, so the same.)
+        if constexpr (L == 1 && G == 64) {
+            if (__popcll(changing) <= 32 && left > 2 && __ballot(true) == ~0ull) {
+                if (__popcll(changing) > 16) changing = share_out(std::integral_constant<int, 2>{}, changing, 16);
+                if (changing != 0) changing = share_out(std::integral_constant<int, 4>{}, changing, 0);
+                break;
+            }
+        }
+        if (changing == 0) break;
     }
-    iteration(std::true_type{});
+    iteration(std::true_type{}, wv, Lanes{});
 
     // ---- outputs: parameters rounded to fp16 (nearest even); error with the unrounded ones ---------------
     if (part == 0) {

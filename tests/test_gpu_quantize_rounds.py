@@ -74,3 +74,24 @@ def test_infinite_neighbours(q, G):
     keep = [n for n in range(72) if n not in (3, 40, 41)]
     for a, b in zip(alone, mixed):
         assert np.array_equal(np.ascontiguousarray(a[..., keep]).view(np.uint8), np.ascontiguousarray(b[..., keep]).view(np.uint8))
+
+
+@pytest.mark.parametrize("rounds", [4, 5, 10, 30])
+def test_lanes_of_groups_at_rest(rounds):
+    """Four planes, groups of 64, enough columns for one lane a group: whole wavefronts, in which the last groups to change get two
+    and four lanes, and an incomplete one (the last), in which they do not; with columns that are at rest at once, that scan, that have
+    sums to be rounded."""
+    K, N = 4096, 1032
+    rng = np.random.default_rng(3)
+    W = (rng.standard_normal((K, N)) * 0.02).astype(np.float32)
+    W[:, 64:120] = 0.013
+    W[:, 130] = (rng.integers(-1, 2, K) * 0.03).astype(np.float32)
+    W[::3, 200] *= np.float32(2.0 ** -12)
+    codes, S, Z = quantize(W, 4, 64, rounds)
+    # (not the two with ties that are decided by how the parameters are rounded)
+    cols = np.concatenate([np.arange(0, 64, 5), np.arange(118, 130), [131, 199, 201, 1023], np.arange(1024, 1032)])
+    ref, S_ref, Z_ref = QO.quantize(W[:, cols].astype(np.float64), 4, 64, t_max=rounds)
+    assert np.array_equal(codes[:, cols], ref)
+    # fp16 parameters: one unit in the last place (2^-10 of the value) and the subnormals' spacing
+    for got, want in ((S[:, :, cols], S_ref), (Z[:, cols], Z_ref)):
+        assert (np.abs(got.astype(np.float64) - want) <= 2.0 ** -10 * np.abs(want) + 2.0 ** -24).all()
