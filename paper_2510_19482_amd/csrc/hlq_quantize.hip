@@ -921,8 +921,7 @@ hlq_quantize_kernel_4(const float *__restrict__ W, int K, int N, int t_max, uint
             offset += stride * 4;
         }
     };
-    // this lane's columns, one word every 64: thresholds in order | plane words by sorted position | counts.  The
-    // second and third also hold the candidate values (fp64, by code) while the thresholds are made.
+    // this lane's columns, one word every 64: thresholds in order | plane words by sorted position | counts
     uint32_t *const tree = lds + (threadIdx.x >> 6) * (3 * NC * 64) + (threadIdx.x & 63);
     uint32_t *const plane = tree + NC * 64;
     uint32_t *const count = plane + NC * 64;
@@ -1002,8 +1001,7 @@ hlq_quantize_kernel_4(const float *__restrict__ W, int K, int N, int t_max, uint
     for (int j = 0; j < Q; ++j) theta[1 + j] = delta * (double)(1 << j);
 
     // Rounds in a row that needed the scan: a wavefront stays with it after STAY of them (data of few distinct values needs
-    // it in every round: without this -1, 0, 1 at q = 2, G = 32 takes 226 us and not 149).  At q = 4 a single one can
-    // be a coincidence, candidates closer than the keys' 19 bits tell apart.
+    // it in every round).  Two here: the scan takes four times what a search does, and one in a row can be a coincidence.
     constexpr int STAY = 2;
     int scans = 0;
     // one iteration of Alg. 1 for groups of which `lanes` lanes have the weights src each; the last one also stores the codes (a
@@ -1022,7 +1020,7 @@ hlq_quantize_kernel_4(const float *__restrict__ W, int K, int N, int t_max, uint
         const double zt = constant ? (double)__builtin_inff() : z;
 
         uint32_t key[NC];
-        float top[3];   // the thresholds at the quarters (q = 1: the only one); the others are in LDS
+        float top[3];   // the thresholds at the quarters; the others are in LDS
         // through readfirstlane, here and below: the optimiser takes the choice for a scalar one (otherwise it keeps the
         // registers of both ways at once) and makes no copy of the round for each value
         scans = __builtin_amdgcn_readfirstlane(scans);
@@ -1190,9 +1188,8 @@ hlq_quantize_kernel_4(const float *__restrict__ W, int K, int N, int t_max, uint
                     const int par = (i / B) & 1;
                     {
                         // All comparisons of a level before what they choose: a comparison's outcome can be read two
-                        // instructions later, and the compiler would wait those out eight times a level (4096 x 1024, G = 64,
-                        // q = 4 80.5 -> 75.7 us, q = 3 54.5 -> 50.7).  Two planes in registers have other work to fill that with
-                        // and lose the shorter encoding (4096 x 1024, G = 128 56 -> 59).
+                        // instructions later, and the compiler would wait those out eight times a level (4096 x 1024, G = 64
+                        // 80.5 -> 75.7 us).
                         auto apart = [] {
                             __builtin_amdgcn_sched_barrier(0);
                         };
