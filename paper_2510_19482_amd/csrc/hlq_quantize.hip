@@ -1318,8 +1318,9 @@ hlq_quantize_kernel_4(const float *__restrict__ W, int K, int N, int t_max, uint
         return reconstruct<Q, G>(cnt, rb, rw, theta);
     };
     int left = t_max - 1;   // rounds before the last
-    // Rounds for the groups of the lanes in `changing` only, at most 64 / PARTS of them, with PARTS lanes and a part of the weights each, until
-    // no more than `enough` of them change; returns which do.
+    // Rounds for the groups of the lanes in `changing` only, with PARTS lanes and a part of the weights each, until
+    // no more than `enough` of them change; returns which do (as many as before where no round is left).  At most
+    // 64 / PARTS groups: one more and its numbers would be handed over in the words of another one.
     auto share_out = [&](auto parts_c, uint64_t changing, int enough) -> uint64_t {
         constexpr int PARTS = decltype(parts_c)::value, SLOTS = 64 / PARTS, LEN = GL / PARTS;
         const int lane = (int)(threadIdx.x & 63), slot = lane / PARTS, mine_of = lane % PARTS;
@@ -1390,7 +1391,7 @@ hlq_quantize_kernel_4(const float *__restrict__ W, int K, int N, int t_max, uint
         if constexpr (L == 1 && G == 64) {
             if (__popcll(changing) <= 32 && left > 2 && __ballot(true) == ~0ull) {
                 if (__popcll(changing) > 16) changing = share_out(std::integral_constant<int, 2>{}, changing, 16);
-                if (changing != 0) changing = share_out(std::integral_constant<int, 4>{}, changing, 0);
+                if (changing != 0 && left > 0) changing = share_out(std::integral_constant<int, 4>{}, changing, 0);   // (rounds left: 16 or fewer change)
                 break;
             }
         }

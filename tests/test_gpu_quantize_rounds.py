@@ -1,5 +1,7 @@
 """hlq_quantize where its rounds end or its sorted lists are tested: parameters that stay as they are before the last round,
 weights equal to a midpoint or next to one at zero, weights too far apart for exact sums, infinite weights beside finite ones."""
+import functools
+
 import numpy as np
 import pytest
 
@@ -95,3 +97,49 @@ def test_lanes_of_groups_at_rest(rounds):
     # fp16 parameters: one unit in the last place (2^-10 of the value) and the subnormals' spacing
     for got, want in ((S[:, :, cols], S_ref), (Z[:, cols], Z_ref)):
         assert (np.abs(got.astype(np.float64) - want) <= 2.0 ** -10 * np.abs(want) + 2.0 ** -24).all()
+
+
+# columns of a wavefront that are not constant: as many as two lanes each suffice for, and fewer
+LIVE = (32, 32, 30, 28, 24, 17)
+LIVE_COLUMNS = np.concatenate([64 * b + np.arange(n) for b, n in enumerate(LIVE)])
+
+
+@functools.lru_cache(maxsize=None)
+def heavy_tailed():
+    """Weights of six wavefronts by 16 groups of rows, and the oracle's codes and parameters of the live columns after every round."""
+    K, q, G = 1024, 4, 64
+    rng = np.random.default_rng(0)
+    W = (rng.standard_normal((K, 64 * len(LIVE))) * 0.02).astype(np.float32)
+    W[rng.random(W.shape) < 0.05] *= np.float32(20)
+    Wg = QO.to_groups(W[:, LIVE_COLUMNS].astype(np.float64), G)
+    s, z = QO.init_params(Wg, q)
+    rounds = []
+    for _ in range(9):
+        codes = QO.select_bits(Wg, s, z, q)
+        s, z = QO.lse(Wg, codes, s, z, q)
+        rounds.append((codes, s, z))
+    dead = np.setdiff1d(np.arange(W.shape[1]), LIVE_COLUMNS)
+    W[:, dead] = 0.013
+    return W, rounds
+
+
+@pytest.mark.parametrize("rounds", [5, 6, 7, 8, 9])
+def test_rounds_run_out_with_many_groups_changing(rounds):
+    """The same kernel where the rounds end before it has come to 16 groups or fewer that change."""
+    W, by_round = heavy_tailed()
+    K, N = W.shape
+    codes, S, Z = by_round[rounds - 1]
+    # a group changes its parameters in a round where it has other codes than in the one before
+    changing = (by_round[rounds - 2][0] != by_round[rounds - 3][0]).any(axis=1).reshape(K // 64, -1)
+    start = np.concatenate([[0], np.cumsum(LIVE)])
+    most = max(changing[:, a:b].sum(axis=1).max() for a, b in zip(start, start[1:]))
+    assert most > 16 or rounds > 7, most
+    wide = np.concatenate([W] + [W[:, :64]] * 28, axis=1)   # enough columns for one lane a group
+    got = quantize(wide, 4, 64, rounds)
+    assert np.array_equal(got[0][:, LIVE_COLUMNS], QO.from_groups_codes(codes, K, len(LIVE_COLUMNS), 64))
+    # fp16 parameters: one unit in the last place (2^-10 of the value) and the subnormals' spacing
+    for have, want in ((got[1], S.reshape(K // 64, -1, 4).transpose(2, 0, 1)), (got[2], Z.reshape(K // 64, -1))):
+        assert (np.abs(have[..., LIVE_COLUMNS].astype(np.float64) - want) <= 2.0 ** -10 * np.abs(want) + 2.0 ** -24).all()
+    # and every byte as by the launch of six wavefronts a group of rows, which has two lanes a group throughout
+    for have, want in zip(got, quantize(W, 4, 64, rounds)):
+        assert np.array_equal(np.ascontiguousarray(have[..., :N]).view(np.uint8), np.ascontiguousarray(want).view(np.uint8))
