@@ -264,7 +264,7 @@ constexpr int quantize_waves(int gl) { return gl == 32 ? 3 : 2; }
 //     not so the lane's weights around the threshold are asked one after the other.
 // A group whose weights are all equal (padded or pruned columns) has equal candidates in every round; it takes code 0.
 // A lane that meets none of this (candidates that coincide up to rounding: groups of few distinct values) sends its
-// wavefront through the scan for that round, once for every distinct weight, and for the rounds after it.
+// wavefront through the scan for that round and for the rounds after it.
 // Bound: vector instructions and their latency at two wavefronts per SIMD, as many as LDS takes (20 KiB for 64 weights a
 // lane; blocks of four, 24 KiB and six wavefronts a compute unit, 71 us where blocks of eight take 60).  Per round and group (two lanes)
 // at q = 2 some 800 instructions, where going through the weights took 2050; sorting is 1200 a lane.  4096 x 4096, ten rounds,
@@ -470,6 +470,12 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
             rank[u] = r;
         }
     };
+
+    // Runs of equal weights in the list, a bit where one starts: found when the scan first asks for them.  (In row order every weight is one.)
+    using Bits = std::conditional_t<GL == 64, uint64_t, uint32_t>;
+    Bits starts = ~(Bits)0;
+    constexpr int MANY = (Q == 3 ? 7 : 6) * GL / 16;
+    int runs_known = in_order;
 
     // Rounds in a row that needed the scan: a wavefront stays with it after STAY of them (data of few distinct values needs
     // it in every round).
@@ -769,7 +775,11 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             }
         } else {
-            // The scan of all candidates, once for every run of equal weights.
+            // The scan of all candidates: one run of equal weights after the other where no lane has more than MANY, and otherwise
+            // weight by weight, eight side by side (the lane that needs the scan may be one in 64, and the weights of the others all
+            // different).  4096 x 4096, us, runs / weights, by the values of a column: G = 128, q = 2 10 59 / 89, 18 82 / 106, 32 121 / 125, 48
+            // 155 / 134, all different 252 / 132;  q = 3 105 / 192, 133 / 209, 181 / 231, 225 / 240, 363 / 238;  1024 x 1024, G = 64 (32 weights
+            // a lane) q = 2 17 / 19, 25 / 22, 35 / 26, 43 / 27, 49 / 27.
             double V[NC];
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
@@ -790,31 +800,44 @@ hlq_quantize_kernel(const float *__restrict__ W, int K, int N, int t_max, uint8_
                 }
                 return best;
             };
-            uint64_t starts = 0u;   // of runs
-            if (in_order) {
-                starts = ~0ull >> (64 - GL);
-            } else {
+            if (runs_known == 0) {
+                starts = 0u;
                 float before = __builtin_nanf("");
 #pragma unroll
                 for (int i = 0; i < GL; ++i) {
                     const float v = __builtin_bit_cast(float, list[i * 64]);
-                    starts |= v != before ? 1ull << i : 0ull;
+                    starts |= v != before ? (Bits)1 << i : (Bits)0;
                     before = v;
                 }
+                runs_known = 1;
             }
-            uint64_t counted = 0u;   // by code, eight bits each
-#pragma unroll 1
-            while (__any(starts != 0u)) {
-                if (starts != 0u) {
-                    const int i = __builtin_ctzll(starts);
-                    starts &= starts - 1;
-                    const int many = (starts ? __builtin_ctzll(starts) : GL) - i;
-                    const float w = __builtin_bit_cast(float, list[i * 64]);
-                    const uint32_t best = choose(w);
-                    const double all = (double)many * (double)w;   // exact
+            std::conditional_t<SMALL, uint32_t, uint64_t> counted = 0u;   // by code, eight bits each
+            auto fold = [&](float w, uint32_t code, int number) {
+                const double all = (double)number * (double)w;   // exact
 #pragma unroll
-                    for (int j = 0; j < Q; ++j) rb[j] = __builtin_fma((double)(best >> j & 1u), all, rb[j]);
-                    counted += (uint64_t)many << 8 * best;
+                for (int j = 0; j < Q; ++j) rb[j] = __builtin_fma((double)(code >> j & 1u), all, rb[j]);
+                counted += (decltype(counted))number << 8 * code;
+            };
+            if (__any(__popcll(starts) > MANY)) {
+#pragma unroll 1
+                for (int i = 0; i < GL; i += 8) {
+                    float w[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) w[u] = __builtin_bit_cast(float, list[(i + u) * 64]);
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) fold(w[u], choose(w[u]), 1);
+                }
+            } else {
+                Bits left = starts;
+#pragma unroll 1
+                while (__any(left != 0u)) {
+                    if (left != 0u) {
+                        const int i = __builtin_ctzll(left);
+                        left &= left - 1;
+                        const int number = (left ? __builtin_ctzll(left) : GL) - i;
+                        const float w = __builtin_bit_cast(float, list[i * 64]);
+                        fold(w, choose(w), number);
+                    }
                 }
             }
 #pragma unroll
