@@ -497,7 +497,8 @@ static GroupPlan plan_group(int count, const HlqDims *dms, int64_t M)
 }
 
 // When the last workgroup ends, in chunk steps of two workgroups on a compute unit: workgroups of n kinds (steps, number; longest
-// first) on 512 places in list order; of the two places of a unit the one left alone runs at 1 / 0.6 the speed.
+// first) on 512 places in list order; of the two places of a unit the one left alone runs at 1 / 0.6 the speed.  -1: more
+// different loads than there is room for.
 static double launch_steps(int n, const int *steps, const long *number)
 {
     constexpr int MOST = 48;
@@ -522,7 +523,7 @@ static double launch_steps(int n, const int *steps, const long *number)
                 load[low] = to;
                 places[low] = m;
             } else {
-                if (kinds == MOST) return 1e9;
+                if (kinds == MOST) return -1.0;
                 load[kinds] = to;
                 places[kinds++] = m;
             }
@@ -544,11 +545,12 @@ static double launch_steps(int n, const int *steps, const long *number)
     for (int a = 0, b = kinds - 1; a <= b;) {   // the longest beside the shortest
         const double t = load[a] + 0.6 * (load[b] - load[a]);
         if (t > end) end = t;
-        const long m = a == b ? places[a] : places[a] < places[b] ? places[a] : places[b];
+        if (a == b) break;
+        const long m = places[a] < places[b] ? places[a] : places[b];
         places[a] -= m;
-        if (a != b) places[b] -= m;
+        places[b] -= m;
         if (places[a] == 0) ++a;
-        else --b;
+        if (places[b] == 0) --b;
     }
     return end;
 }
@@ -583,14 +585,18 @@ static void plan_tail(int count, const HlqDims *dms, GroupPlan &g)
     }
     const double step = 3.0 + 0.3 * dms[0].q;   // us
     const int groups = (dms[wide].ntiles + 3) / 4;
-    double best = launch_steps(count, steps, number) * step * 0.96;
+    const double whole_steps = launch_steps(count, steps, number);
+    if (whole_steps < 0.0) return;
+    double best = whole_steps * step * 0.96;
     for (int c = 1; c < groups && c * g.rowblocks <= 256; c += 1 + groups / 16)
         for (int ns = 2; ns <= 3; ++ns) {
             const int cps = ((dms[wide].nchunks + ns - 1) / ns + 1) & ~1;
             number[whole] = (long)(groups - c) * g.rowblocks;
             steps[count] = cps;
             number[count] = (long)c * g.rowblocks * ns;
-            const double t = launch_steps(count + 1, steps, number) * step + (sums ? 0.0 : 5.0) + (double)number[count] * (128 * 256 * 4) / 4.0e6;   // (partial sums at 4 TB/s)
+            const double cut_steps = launch_steps(count + 1, steps, number);
+            if (cut_steps < 0.0) continue;
+            const double t = cut_steps * step + (sums ? 0.0 : 5.0) + (double)number[count] * (128 * 256 * 4) / 4.0e6;   // (partial sums at 4 TB/s)
             if (t < best) {
                 best = t;
                 g.tail = wide;
