@@ -182,7 +182,10 @@ HLQ_API hlq_status hlq_lut_gemv_batch(int count, const hlq_desc *descs, const vo
  * the partial sums when K is cut: the seven GEMMs of an 8B layer run 1.3x faster than as seven calls at M = 2048).  If the
  * lookup formulation is forced the problems run one after the other on the stream.  M = 0 is a
  * no-op.
- *   ws / ws_bytes: workspace of at least hlq_gemm_batch_workspace_bytes(count, descs, M). */
+ *   ws / ws_bytes: hlq_gemm_batch_workspace_bytes(count, descs, M) bytes.  For some calls of more than 64 rows that
+ *   is more than the least a call accepts: with the room the workgroups that would end last are cut along K, which is
+ *   faster, and without it they stay whole.  The two differ in the order of fp32 sums of the columns concerned, so by
+ *   their rounding: results that are to be the same in every bit take workspaces of the same size. */
 HLQ_API hlq_status hlq_gemm_batch_workspace_bytes(int count, const hlq_desc *descs, int64_t M, size_t *bytes);
 HLQ_API hlq_status hlq_lut_gemm_batch(int count, const hlq_desc *descs, const void *const *packed,
                                       const uint16_t *const *X, int64_t M, const int64_t *ldx, void *const *Y,

@@ -558,11 +558,15 @@ static double launch_steps(int n, const int *steps, const long *number)
 // The last round of a launch of more than 512 workgroups is rarely even: with 32 chunks a tile and 32 tiles too many for one workgroup
 // a compute unit, 32 units have two of them to the end (8B layer at M = 512: 64 chunk steps, where all units together would be
 // through after 52).  Cutting as many tiles of one problem in two or three along K evens that out at the price of their partial
-// sums: a number of column groups of the widest problem of the shortest K is chosen by the estimate above, where it finds
-// 4 % or more.  Grouped launches, us, without -> with: 8B layer q = 2, M = 300 / 400 / 512 / 640 184 / 236 / 244 / 285 -> 176 / 218 /
-// 223 / 265, q = 4, M = 512 282 -> 262; hidden 3072, ffn 9216, q = 3, M = 500 152 -> 131; hidden 3840, ffn 11008, M = 800 308 -> 294.
-// Below 4 % the estimate is no guide (8B layer at M = 2048, 2.6 %: 809 -> 825), nor
-// is it with fewer than 16 chunks a tile (hidden 1536, M = 1800 154 -> 156).
+// sums: a number of column groups of the widest problem of the shortest K that is not in slices already is chosen by the estimate above,
+// where it finds 4 % or more.  Looked at are up to 16 numbers of column groups, of 256 tiles together at most and never all of the problem.
+// Grouped launches, us, timed in turn without -> with: 8B layer q = 2, M = 300 / 400 / 512 / 640 190 / 239 / 237 / 276 -> 176 / 219 /
+// 220 / 260, q = 4, M = 512 279 -> 251; hidden 3072, ffn 9216, q = 3, M = 500 148 -> 123; hidden 3840, ffn 11008, M = 800 298 -> 277.
+// 490 launches that are cut (layers and groups of two to four matrices, all q, G = 32 to 128, 100 to 2048 rows): 6 % faster on average, 63
+// slower by more than 1 %, 17 by more than 3 %, 10 % at most (K = 7808 and 6144, N = 5656 and 18648, q = 1, G = 32,
+// M = 729 238 -> 263).  From 6 % on it would be 5 of the 17, but 190 launches would stay whole that gain 4 % on average.
+// Below 4 % the estimate is no guide (8B layer at M = 2048, 2.6 %: 809 -> 825), nor is it with fewer than 16 chunks a tile (hidden
+// 1536, M = 1800 154 -> 156).
 static void plan_tail(int count, const HlqDims *dms, GroupPlan &g)
 {
     if (g.MW < 4 || count >= HLQ_MAX_BATCH) return;

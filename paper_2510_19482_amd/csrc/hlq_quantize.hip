@@ -20,7 +20,7 @@
 //
 // A round is a function of the parameters alone, so a wavefront whose parameters all stay as they are (in every bit) goes on with
 // the last round: groups of 32 normal weights are there after 2 to 3 rounds on average, 64 of them together after 6 to 8
-// (4096 x 4096, G = 32, q = 3 138 -> 130 us, q = 4 247 -> 223; weights on a coarse grid up to a half).
+// (4096 x 4096, G = 32, when it was brought in: q = 3 138 -> 130 us, q = 4 247 -> 223; weights on a coarse grid up to a half).
 //
 // Rank-deficient systems (a plane constant over the group, equal or complementary planes, all
 // weights equal): columns are taken in the order 1, b_0, b_1, ...; a column that depends linearly on
@@ -268,8 +268,8 @@ constexpr int quantize_waves(int gl) { return gl == 32 ? 3 : 2; }
 // Bound: vector instructions and their latency at two wavefronts per SIMD, as many as LDS takes (20 KiB for 64 weights a
 // lane; blocks of four, 24 KiB and six wavefronts a compute unit, 71 us where blocks of eight take 60).  Per round and group (two lanes)
 // at q = 2 some 800 instructions, where going through the weights took 2050; sorting is 1200 a lane.  4096 x 4096, ten rounds,
-// us, search per weight and round -> this: G = 128 q = 1 / 2 / 3 51 / 94 / 138 -> 40 / 60 / 102;  G = 64 50 / 93 / 144 -> 37 / 58 / 104;
-// G = 32 53 / 115 / 177 -> 43 / 75 / 130;  G = 256 53 / 96 / 134 -> 41 / 60 / 102;  4096 x 1024, G = 128 19 / 36 / 55 -> 17 / 23 / 40.  With four
+// us, search per weight and round -> this: G = 128 q = 1 / 2 / 3 47 / 85 / 128 -> 37 / 54 / 92;  G = 64 46 / 84 / 134 -> 35 / 53 / 91;
+// G = 32 55 / 106 / 165 -> 39 / 65 / 115;  G = 256 49 / 88 / 125 -> 38 / 56 / 93;  4096 x 1024, G = 128 18 / 34 / 50 -> 16 / 21 / 36.  With four
 // planes the fifteen searches cost more than they save (G = 128 190 -> 203 us).
 template <int Q, int G, int L>
 __global__ void __launch_bounds__(quantize_threads(L), quantize_waves(G / L))
@@ -1146,15 +1146,13 @@ hlq_quantize_kernel_4(const float *__restrict__ W, int K, int N, int t_max, uint
                     else if (near[i]) tree[i * 64] = __builtin_bit_cast(uint32_t, T);
                 });
             }
-            {
-                if (__builtin_expect(__any(hard != 0u), 0)) {
-                    const uint32_t at = hard & 0xffu, code_below = hard >> 8 & 0xffu, code_above = hard >> 16;
-                    const double below = exact_value(code_below), above = exact_value(code_above);
-                    const float T = bisect(below, above, code_above < code_below, hard != 0u);
+            if (__builtin_expect(__any(hard != 0u), 0)) {
+                const uint32_t at = hard & 0xffu, code_below = hard >> 8 & 0xffu, code_above = hard >> 16;
+                const double below = exact_value(code_below), above = exact_value(code_above);
+                const float T = bisect(below, above, code_above < code_below, hard != 0u);
 #pragma unroll
-                    for (int k = 0; k < 3; ++k) top[k] = at == (uint32_t)((k + 1) * QUARTER) ? T : top[k];
-                    if (at) tree[at * 64] = __builtin_bit_cast(uint32_t, T);
-                }
+                for (int k = 0; k < 3; ++k) top[k] = at == (uint32_t)((k + 1) * QUARTER) ? T : top[k];
+                if (at) tree[at * 64] = __builtin_bit_cast(uint32_t, T);
             }
             chosen = __any(!good) ? 1 : 0;
         } else {
@@ -1234,7 +1232,7 @@ hlq_quantize_kernel_4(const float *__restrict__ W, int K, int N, int t_max, uint
 #pragma unroll
                         for (int u = 0; u < B; ++u) at[u] = tree + half[u] + (quarter[u] ? NC / 4 * 64u : 0u);
                     }
-                    constexpr int levels = Q > 2 ? Q - 1 : 1;             // LDS reads in a row
+                    constexpr int levels = Q - 1;                         // LDS reads in a row
                     constexpr int per = (B + levels - 1) / levels;        // previous weights summed up behind each
 #pragma unroll
                     for (int lv = 0; lv < levels; ++lv) {

@@ -5,6 +5,8 @@ import torch
 
 from paper_2510_19482_amd import binding as B
 
+from test_plan_tail import plan
+
 pytestmark = pytest.mark.gpu
 COUNTERS = 131072   # bytes ahead of the partial sums
 
@@ -52,6 +54,45 @@ def test_cut_tail(q, G, M, shapes, f32):
         # the two launches differ in the order of fp32 sums, and by that in the rounding of fp16 results
         assert ((a.double() - b.double()).abs() / top).max() <= (2e-6 if f32 else 1e-3)
         assert (a[:, :256] == b[:, :256]).all()   # never in the tail
+
+
+# activations and results in wider matrices, results at addresses and strides of no more than their element's alignment; in the
+# second set a problem that is in slices already beside the one whose tail is cut
+@pytest.mark.parametrize("q,M,shapes,sliced", [(2, 1100, [(2048, 5000), (2048, 5000), (2048, 5064)], False),
+                                               (3, 520, [(8192, 2056), (2048, 9224), (2048, 9736)], True)])
+@pytest.mark.parametrize("f32", [False, True])
+@pytest.mark.parametrize("big", [False, True])
+def test_strides_slices_and_range(q, M, shapes, sliced, f32, big):
+    """big: scales of 700 and 3000 in the last column that is cut and in the first problem, for which the call is computed again."""
+    cut, slices = plan(shapes, q, M)
+    assert cut is not None and (max(slices) > 1) == sliced
+    mats = []
+    for i, (K, N) in enumerate(shapes):
+        codes, scales, zeros, w = matrix(K, N, q, 128, 11 * i + q)
+        if big and i in (0, cut[0]):
+            at = scales[0, 1, N - 1].clone()
+            scales[0, 1, N - 1] = 3000.0 if i else 700.0
+            w[128:256, N - 1] += (scales[0, 1, N - 1].double() - at.double()) * (codes[128:256, N - 1] & 1)
+        mats.append((codes, scales, zeros, w))
+    descs = [B.make_desc(K, N, q, 128) for K, N in shapes]
+    packed = [B.hlq_pack(d, *m[:3]) for d, m in zip(descs, mats)]
+    X = [torch.randn((M, K + 24), device="cuda", generator=torch.Generator(device="cuda").manual_seed(K + i)).half()[:, 16:16 + K] for i, (K, _) in enumerate(shapes)]
+    wide = [torch.full((M, N + 7), 7.0, dtype=torch.float32 if f32 else torch.float16, device="cuda") for _, N in shapes]
+    Y = [w[:, 3:3 + N] for w, (_, N) in zip(wide, shapes)]
+    batch = B.GemmBatch(descs, packed, X, Y, out_f32=f32)
+    for _ in range(2):
+        batch.launch()
+        torch.cuda.synchronize()
+        assert not batch.ws[:COUNTERS].any()
+    for (K, N), m, x, y, w in zip(shapes, mats, X, Y, wide):
+        assert (w[:, :3] == 7).all() and (w[:, 3 + N:] == 7).all()
+        ref = x.double() @ m[3]
+        # as above; where the call is computed again its weights are exact, and fp16 results that are too large are infinite
+        finite = y.isfinite()
+        assert finite.all() or (big and not f32 and (ref.abs()[~finite] > 65500).all())
+        for part in (slice(0, N - 1), slice(N - 1, N)):   # (the last column may be the one with the large scale)
+            err = torch.where(finite, (y.double() - ref).abs(), 0.0)[:, part]
+            assert err.max() <= 1e-3 * ref[:, part].abs().max()
 
 
 def test_replays():
